@@ -452,7 +452,8 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         CSAT_TRY(transpose_pack<T>(K, (T*)w.KT, w.ldn, BH, d.n, d.d, st));
-        if (!vt_ready) CSAT_TRY(transpose_pack<T>(V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
+        // (vt_ready says what the caller needs afterwards; the V product below reads the transposed copy either way)
+        if (!vt_ready || want_v) CSAT_TRY(transpose_pack<T>(V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
         if (VcT) CSAT_TRY(fill_zero(VcT, (size_t)BH * d.d * w.ldm * sizeof(T), st));
     }
     if (separate) {

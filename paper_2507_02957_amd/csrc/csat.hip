@@ -7,6 +7,7 @@
 #include "csat_fwht.h"
 #include "csat_gemm_big.h"
 #include "csat_attention.h"
+#include "csat_attention_z.h"
 #include "csat_measure.h"
 #include "csat_launch.h"
 #include "csat_peaks.h"
@@ -374,6 +375,17 @@ csat_status prepare_phi(const csat_dims& d, const Workspace& w, const T* Phi, bo
     return CSAT_OK;
 }
 
+// CUs of the current device (persistent grids and work-distribution heuristics)
+int cu_count() {
+    static const int n = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 256;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
+        return v;
+    }();
+    return n;
+}
+
 // Whether the measurement runs as the one kernel that reads K and V as they are (csat_measure.h): bf16, d of
 // one or two 64-wide tiles, one matrix for both products.
 template <typename T>
@@ -435,14 +447,17 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
             const dim3 grid((unsigned)(8 * ((BH + 7) / 8) * a.blocks_per_head));
             // 64 rows of K and V per step; two steps in flight, four for long contractions (measured on the five
             // workloads: 26 us either way at n = 1600, 221 against 247 us at n = 4096, 238 against 285 at n = 16384)
-#define MD(DT, PD)                                                                                      \
-    do {                                                                                                \
-        if (want_v) hipLaunchKernelGGL((measure_direct_kernel<DT, 64, PD, true>), grid, dim3(256), 0, st, a);  \
-        else hipLaunchKernelGGL((measure_direct_kernel<DT, 64, PD, false>), grid, dim3(256), 0, st, a); \
+#define MD(DT, KS, PD, KG)                                                                                            \
+    do {                                                                                                              \
+        if (want_v) hipLaunchKernelGGL((measure_direct_kernel<DT, KS, PD, true, KG>), grid, dim3(256 * KG), 0, st, a);  \
+        else hipLaunchKernelGGL((measure_direct_kernel<DT, KS, PD, false, KG>), grid, dim3(256 * KG), 0, st, a);        \
     } while (0)
             const bool deep = d.n >= 4096;
-            if (d.d == 64) { if (deep) MD(2, 4); else MD(2, 2); }
-            else { if (deep) MD(4, 4); else MD(4, 2); }
+            // No more workgroups than CUs: two groups of wavefronts split the contraction (csat_measure.h), once it is long
+            // enough to pay for the meeting of the sums.
+            const bool two = (long long)BH * a.blocks_per_head <= cu_count() && d.n >= 512;
+            if (d.d == 64) { if (two) MD(2, 64, 4, 2); else if (deep) MD(2, 64, 4, 1); else MD(2, 64, 2, 1); }
+            else { if (two) MD(4, 32, 4, 2); else if (deep) MD(4, 64, 4, 1); else MD(4, 64, 2, 1); }
 #undef MD
             HIP_TRY(hipGetLastError());
             if (kc_packed) *kc_packed = a.KcPack != nullptr;
@@ -478,17 +493,6 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
     EpiStore<T> ev{Vc, d.d, (long long)d.m * d.d, VcT, w.ldm, (long long)d.d * w.ldm, 1.f, d.m, d.d};
     CSAT_TRY((gemm<T>(g, d.d, BH, ev, st)));
     return CSAT_OK;
-}
-
-// CUs of the current device (persistent grids and work-distribution heuristics)
-int cu_count() {
-    static const int n = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
-        return v;
-    }();
-    return n;
 }
 
 // Whether the one-kernel attention keeps all of a head's K~ fragments (ns per tile of m, mt tiles) in LDS and all
@@ -587,6 +591,58 @@ bool attention_is_fused(const csat_dims& d, const Workspace& w, bool split_k) {
     const bool short_side = (d.n_q + 31) / 32 < 8 &&
                             (long long)w.MT * (sizeof(T) == 2 && split_k ? 2 : 1) * ((d.d + frag_depth - 1) / frag_depth) > 32;
     return d.d <= 128 && attn_opt != 1 && (attn_opt == 2 || !short_side);
+}
+
+// Whether a call that wants Z but not A~ takes the kernel that never stores A~ (csat_attention_z.h): bf16, d a multiple
+// of 32 up to 128, every m and n_q.
+template <typename T>
+bool attention_z_applies(const csat_dims& d) {
+    return sizeof(T) == 2 && d.d % 32 == 0 && d.d <= 128 && (*tl_opt)[CSAT_OPT_ATTENTION] == 0;
+}
+// Z and / or ZT (see run_attention) without A~.  Ksrc: K~ rows [BH][m][kparts * d]; Vc: V~ rows.  kc_packed / v_packed: their
+// fragments are in w.KcPack / w.VcT already.
+template <typename T>
+csat_status run_attention_z(const csat_dims& d, const Workspace& w, const T* Q, const T* Ksrc, int kparts, bool kc_packed,
+                            const T* Vc, bool v_packed, T* Z, T* ZT, hipStream_t st) {
+    const int BH = d.B * d.H;
+    AttentionZArgs a{};
+    a.Q = (const bf16_t*)Q;
+    a.Kf = w.KcPack;
+    a.Vf = (const uint4*)w.VcT;
+    a.Z = (bf16_t*)Z; a.ZT = (bf16_t*)ZT;
+    a.ldT = 2 * w.ldn; a.strideT = (long long)d.d * a.ldT;
+    a.n_q = d.n_q; a.m = d.m; a.MT = w.MT;
+    a.scale_log2e = 1.4426950408889634f / sqrtf((float)d.d);
+    a.tiles_per_head = (d.n_q + 31) / 32;
+    if (!kc_packed || !v_packed) {
+        Timed tm(w, CSAT_K_LAYOUT, st);
+        const long long nk = kc_packed ? 0 : (long long)BH * w.MT * kparts * (d.d / 16) * 64;
+        const long long nv = v_packed ? 0 : (long long)BH * w.MT * (d.d / 16) * 64;
+        hipLaunchKernelGGL(pack_kv_fragments_kernel, dim3((unsigned)((nk + nv + 255) / 256)), dim3(256), 0, st, (const bf16_t*)Ksrc,
+                           (const bf16_t*)Vc, d.m, d.d, kparts, w.MT, w.KcPack, (uint4*)w.VcT, nk, nv);
+        HIP_TRY(hipGetLastError());
+    }
+    // All of a head's fragments in LDS where they fit; a workgroup then works through several rounds of one row tile
+    // per wavefront, as many as need the fewest passes of the grid over the chip (a round's time per tile of m: a
+    // quarter of the staging's; ties: fewer rounds).  Else two tiles of m at a time, one round.
+    const int slot = attention_z_slot_bytes(d.d, kparts), slots = (w.MT + kAttnZTiles - 1) / kAttnZTiles;
+    const bool resident = (long long)slot * slots <= (long long)kLdsPerWorkgroup;
+    const size_t lds_bytes = (size_t)slot * (resident ? slots : 2);
+    const int per_cu = d.d <= 64 && 2 * lds_bytes <= kLdsPerWorkgroup ? 2 : 1;
+    a.rounds = 1;
+    if (resident) {
+        const long long slots_on_chip = (long long)cu_count() * per_cu;
+        long long best = -1;
+        for (int r = 1; r <= 8; ++r) {
+            const long long wgs = (long long)BH * ((a.tiles_per_head + kAttnZWaves * r - 1) / (kAttnZWaves * r));
+            const long long cost = (wgs + slots_on_chip - 1) / slots_on_chip * (4 * r + 1);
+            if (best < 0 || cost < best) { best = cost; a.rounds = r; }
+        }
+    }
+    a.wg_per_head = (a.tiles_per_head + kAttnZWaves * a.rounds - 1) / (kAttnZWaves * a.rounds);
+    Timed tm(w, CSAT_K_SOFTMAX, st);
+    HIP_TRY(attention_z_launch(d.d, kparts, resident, a, (unsigned)(BH * a.wg_per_head), lds_bytes, st));
+    return CSAT_OK;
 }
 
 // A = softmax(Q Kc^T / sqrt(d)) (float, [rows, m]); P = operand copy [rows, ldm];
@@ -874,6 +930,8 @@ template <typename T>
 csat_status attention_t(const csat_dims& d, const Workspace& w, const void* Q, const void* Kc, const void* Vc,
                         float* A, void* Z, hipStream_t st) {
     const int BH = d.B * d.H;
+    if (!A && attention_z_applies<T>(d))
+        return run_attention_z<T>(d, w, (const T*)Q, (const T*)Kc, 1, false, (const T*)Vc, false, (T*)Z, (T*)nullptr, st);
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         CSAT_TRY(transpose_pack<T>((const T*)Vc, (T*)w.VcT, w.ldm, BH, d.m, d.d, st));
@@ -913,13 +971,21 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
     const bool need_z = Z || iters == 0;
     T* zdst = (iters == 0) ? (T*)C : (T*)Z;
     bool kc_packed = false, v_packed = false;
+    const bool direct = measure_is_direct<T>(d, separate);
+    // no decoder: A~ is not wanted
+    const bool z_only = iters == 0 && attention_z_applies<T>(d);
     // (then nothing reads V^T: the one-kernel measurement takes V as it is)
-    const bool syn = iters > 0 && synthesis_in_decoder(d, w) && measure_is_direct<T>(d, separate);
-    CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, need_z ? (T*)w.VcT : nullptr, syn || synthesis_is_direct<T>(d), true, st,
-                            (const T*)PhiK, (const T*)Phi, need_z, &kc_packed,
+    const bool syn = iters > 0 && synthesis_in_decoder(d, w) && direct;
+    CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, need_z && (direct || !z_only) ? (T*)w.VcT : nullptr,
+                            syn || synthesis_is_direct<T>(d), true, st, (const T*)PhiK, (const T*)Phi, need_z, &kc_packed,
                             // (the two-sweep form of the kernel leaves Z to a product GEMM: with the product's registers
                             // on top it spills; long_video 4.0 ms against 1.2)
-                            attention_is_fused<T>(d, w, true) && attention_packed_v_fits(w.MT, d.d) ? &v_packed : nullptr));
+                            z_only || (attention_is_fused<T>(d, w, true) && attention_packed_v_fits(w.MT, d.d)) ? &v_packed : nullptr));
+    if (z_only) {
+        CSAT_TRY(run_attention_z<T>(d, w, (const T*)Q, (const T*)w.KcHL, 2, kc_packed, (const T*)w.Vc, v_packed, zdst, (T*)nullptr, st));
+        if (Z) HIP_TRY(hipMemcpyAsync(Z, C, (size_t)d.B * d.H * d.n_q * d.d * sizeof(T), hipMemcpyDeviceToDevice, st));
+        return CSAT_OK;
+    }
     // the operand copy of A~ feeds the Z product as a GEMM and the GEMM-pair decoder; the fused decoder reads A~ itself
     T* pcopy = ((need_z && !v_packed) || !w.fused) ? (T*)w.R : nullptr;
     // A~ in accumulator tiles between the attention kernel and the two-chunk decoder: both then move whole 1 KB pieces
@@ -967,17 +1033,23 @@ csat_status forward_rd_t(const csat_dims& d, const Workspace& w, const Workspace
     const long long rows = (long long)BH * d.d;          // decoder problems
     const csat_dims dr = rd_dims(d);
     CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, true, false, st));
-    CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, (T*)w.VcT,
-                            measure_is_direct<T>(d, PhiK && PhiK != Phi), true, st, (const T*)PhiK, (const T*)Phi));
+    const bool direct = measure_is_direct<T>(d, PhiK && PhiK != Phi), z_only = attention_z_applies<T>(d);
+    bool kc_packed = false, v_packed = false;
+    CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, direct || !z_only ? (T*)w.VcT : nullptr,
+                            direct, true, st, (const T*)PhiK, (const T*)Phi, true, z_only ? &kc_packed : nullptr, z_only ? &v_packed : nullptr));
+    // the compressed block's output (and its transpose ZT): nothing here reads A~
+    auto attention = [&](T* Zdst, T* ZTdst) -> csat_status {
+        if (z_only) return run_attention_z<T>(d, w, (const T*)Q, (const T*)w.KcHL, 2, kc_packed, (const T*)w.Vc, v_packed, Zdst, ZTdst, st);
+        return run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, (T*)w.R, Zdst, true, st, ZTdst);
+    };
     if (iters == 0) {
-        CSAT_TRY(run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, (T*)w.R, (T*)C, true, st));
+        CSAT_TRY(attention((T*)C, (T*)nullptr));
         if (Z) HIP_TRY(hipMemcpyAsync(Z, C, (size_t)BH * d.n * d.d * sizeof(T), hipMemcpyDeviceToDevice, st));
         return CSAT_OK;
     }
     const long long ldzt = kBf16 ? 2 * w.ldn : w.ldn;
     CSAT_TRY(fill_zero(x.ZT, (size_t)rows * ldzt * sizeof(T), st));
-    CSAT_TRY(run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, (T*)w.R, (T*)Z, true, st,
-                              (T*)x.ZT));
+    CSAT_TRY(attention((T*)Z, (T*)x.ZT));
     {   // Y^T [m, rows] = Phi Z^T per column, stored transposed as the decoder's measurement rows
         CSAT_TRY(fill_zero(wr.A, (size_t)rows * wr.ldy * 4, st));
         GemmArgs g{w.PhiP, w.ldn, 0, x.ZT, ldzt, 0, d.m, (int)rows, kBf16 ? (int)(2 * w.ldn) : d.n, kBf16 ? (int)(w.ldn / 8) : 0};
@@ -1285,12 +1357,16 @@ csat_status forward_hadamard_t(const csat_dims& d, const Workspace& w, const voi
     CSAT_TRY(measure_hadamard_t<T>(d, rows_of_h, signs, K, V, w.Kc, w.Vc, w.prof, st, kBf16 ? w.KcHL : nullptr));
     const bool need_z = Z || iters == 0;
     T* zdst = (iters == 0) ? (T*)C : (T*)Z;
-    if (need_z) {
-        Timed tm(w, CSAT_K_LAYOUT, st);
-        CSAT_TRY(transpose_pack<T>((const T*)w.Vc, (T*)w.VcT, w.ldm, BH, d.m, d.d, st));
+    if (iters == 0 && attention_z_applies<T>(d)) {
+        CSAT_TRY(run_attention_z<T>(d, w, (const T*)Q, (const T*)w.KcHL, 2, false, (const T*)w.Vc, false, zdst, (T*)nullptr, st));
+    } else {
+        if (need_z) {
+            Timed tm(w, CSAT_K_LAYOUT, st);
+            CSAT_TRY(transpose_pack<T>((const T*)w.Vc, (T*)w.VcT, w.ldm, BH, d.m, d.d, st));
+        }
+        CSAT_TRY(run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, need_z ? (T*)w.R : nullptr,
+                                  need_z ? zdst : nullptr, true, st));
     }
-    CSAT_TRY(run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, need_z ? (T*)w.R : nullptr,
-                              need_z ? zdst : nullptr, true, st));
     if (iters == 0) {
         if (Z) HIP_TRY(hipMemcpyAsync(Z, C, (size_t)BH * d.n_q * d.d * sizeof(T), hipMemcpyDeviceToDevice, st));
         return CSAT_OK;
@@ -1310,19 +1386,23 @@ csat_status forward_rd_hadamard_t(const csat_dims& d, const Workspace& w, const 
     const long long rows = (long long)BH * d.d;          // decoder problems
     const csat_dims dr = rd_dims(d);
     CSAT_TRY(measure_hadamard_t<T>(d, rows_of_h, signs, K, V, w.Kc, w.Vc, w.prof, st, kBf16 ? w.KcHL : nullptr));
-    {
-        Timed tm(w, CSAT_K_LAYOUT, st);
-        CSAT_TRY(transpose_pack<T>((const T*)w.Vc, (T*)w.VcT, w.ldm, BH, d.m, d.d, st));
-    }
+    auto attention = [&](T* Zdst, T* ZTdst) -> csat_status {      // (nothing here reads A~)
+        if (attention_z_applies<T>(d))
+            return run_attention_z<T>(d, w, (const T*)Q, (const T*)w.KcHL, 2, false, (const T*)w.Vc, false, Zdst, ZTdst, st);
+        {
+            Timed tm(w, CSAT_K_LAYOUT, st);
+            CSAT_TRY(transpose_pack<T>((const T*)w.Vc, (T*)w.VcT, w.ldm, BH, d.m, d.d, st));
+        }
+        return run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, (T*)w.R, Zdst, true, st, ZTdst);
+    };
     if (iters == 0) {
-        CSAT_TRY(run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, (T*)w.R, (T*)C, true, st));
+        CSAT_TRY(attention((T*)C, (T*)nullptr));
         if (Z) HIP_TRY(hipMemcpyAsync(Z, C, (size_t)BH * d.n * d.d * sizeof(T), hipMemcpyDeviceToDevice, st));
         return CSAT_OK;
     }
     const long long ldzt = kBf16 ? 2 * w.ldn : w.ldn;
     CSAT_TRY(fill_zero(x.ZT, (size_t)rows * ldzt * sizeof(T), st));
-    CSAT_TRY(run_attention<T>(d, w, (const T*)Q, (const T*)w.Kc, (const T*)w.VcT, w.A, w.ldy, (T*)w.R, (T*)Z, true, st,
-                              (T*)x.ZT));
+    CSAT_TRY(attention((T*)Z, (T*)x.ZT));
     int N = 1, logN = 0;
     while (N < d.n) { N *= 2; ++logN; }
     float scale = 1.f / sqrtf((float)d.m);

@@ -8,6 +8,7 @@ namespace csat {
 
 struct IstaFusedArgs;
 struct AttentionArgs;
+struct AttentionZArgs;
 
 // Fused ISTA decoder for MT tiles of m (csat_ista_fused.h, csat_ista_fused2.h).  variant: 0 dense state, 1 sparse
 // state, 2 one 32-row tile per workgroup (thin); 3 and 4: dense and sparse state on the two-chunk schedule.  One function per MT, defined by csat_tu_ista_fused.hip
@@ -30,5 +31,9 @@ hipError_t attention_fused_launch_bf16_z1(int mt_total, bool single, const Atten
 // ... with the output product from V~ as packed fragments (a.Vf), d = 64 (z2) or 128 (z3)
 hipError_t attention_fused_launch_bf16_z2(int mt_total, bool single, const AttentionArgs& a, unsigned grid, size_t lds_bytes, hipStream_t st);
 hipError_t attention_fused_launch_bf16_z3(int mt_total, bool single, const AttentionArgs& a, unsigned grid, size_t lds_bytes, hipStream_t st);
+
+// Compressed attention without A~ (csat_attention_z.h): bf16, d a multiple of 32 up to 128; parts: 2 where K~ comes as
+// its (hi | lo) pair; resident: all of a head's fragments in LDS.
+hipError_t attention_z_launch(int d, int parts, bool resident, const AttentionZArgs& a, unsigned grid, size_t lds_bytes, hipStream_t st);
 
 }  // namespace csat

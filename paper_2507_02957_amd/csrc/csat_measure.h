@@ -46,8 +46,13 @@ struct MeasureDirectArgs {
 };
 
 // DT = d / 32; KS: rows of K and V per step; PD: steps in flight; WANT_V: V~ too (a.Vc != nullptr)
-template <int DT, int KS, int PD, bool WANT_V>
-__global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a) {
+// KG: groups of four wavefronts that share the workgroup's tiles and split the contraction between them (group g takes the
+// steps g, g + KG, ...; their sums meet in LDS at the end).  With one wavefront per SIMD a step is its own chain of
+// global loads, LDS stores, fragment reads and a barrier (1150 cycles against 256 of MFMA time); where the launch has no
+// more workgroups than the chip has CUs a second group fills those waits: 48 heads, n = 8192, m = 256, d = 64 (192
+// workgroups) 70 -> 60 us (what is left is the L2: 24 KB a step for 64 rows of Phi, about 25 B per clock and CU).
+template <int DT, int KS, int PD, bool WANT_V, int KG = 1>
+__global__ __launch_bounds__(256 * KG) void measure_direct_kernel(MeasureDirectArgs a) {
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
@@ -62,14 +67,17 @@ __global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a
     // 16 consecutive rows then cover all banks once)
     constexpr int MROWS = WANT_V ? 64 : 128;
     constexpr int PA = KS * 2 + 16, PRA = KS / 8, PPA = MROWS * PRA / 256;
-    constexpr int STAGE = 2 * TILE + MROWS * PA;
+    constexpr int OFF_A = (WANT_V ? 2 : 1) * TILE;
+    constexpr int STAGE = OFF_A + MROWS * PA;
     static_assert(DT == 2 || DT == 4, "d = 64 or 128");
-    __shared__ __attribute__((aligned(16))) char lds[2 * STAGE];      // [stage][K | V | Phi]
+    __shared__ __attribute__((aligned(16))) char lds_all[KG * 2 * STAGE];      // [group][stage][K | V (if wanted) | Phi]
+    const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0, tid = threadIdx.x & 255;
+    char* const lds = lds_all + kg * 2 * STAGE;
     // workgroup id -> (head, block of tiles): XCD x = id % 8 takes heads x, x + 8, ...
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
     const int z = (slot / a.blocks_per_head) * 8 + xcd, mb = slot % a.blocks_per_head;
     if (z >= a.heads) return;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = tid & 63, wave = tid >> 6;
     const int kh = lane >> 5, li = lane & 31;
     constexpr bool want_v = WANT_V;
     const int mt = want_v ? mb * 2 + (wave >> 1) : mb * 4 + wave;
@@ -88,7 +96,7 @@ __global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a
     // use.  So every step loads (addresses beyond the data fall back to row 0 / column 0, the staged rows from n on
     // are replaced by zeros, and what Phi contributes there is multiplied by those zeros), wavefronts without a
     // tile multiply like the others and skip the epilogue, and the step count is rounded up to a multiple of PD.
-    const int steps = ((a.n + KS - 1) / KS + PD - 1) / PD * PD;
+    const int steps = ((a.n + KG * KS - 1) / (KG * KS) + PD - 1) / PD * PD;      // per group
     // (a native vector type: arrays of the HIP uint4 struct end up in scratch memory here)
     typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
     u32x4 gK[PD][PPT], gV[PD][PPT];
@@ -96,8 +104,8 @@ __global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a
     auto gload = [&](int s, u32x4 (&k)[PPT], u32x4 (&v)[PPT]) {
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
-            const int p = threadIdx.x + 256 * q, r = p / PR, c = p % PR;
-            long long row = (long long)s * KS + r;
+            const int p = tid + 256 * q, r = p / PR, c = p % PR;
+            long long row = (long long)(s * KG + kg) * KS + r;
             row = row < a.n ? row : 0;
             k[q] = *(const u32x4*)(Kz + row * D + c * 8);
             if constexpr (WANT_V) v[q] = *(const u32x4*)(Vz + row * D + c * 8);
@@ -106,8 +114,8 @@ __global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a
     auto lstore = [&](char* stage, int s, const u32x4 (&k)[PPT], const u32x4 (&v)[PPT]) {
 #pragma unroll
         for (int q = 0; q < PPT; ++q) {
-            const int p = threadIdx.x + 256 * q, r = p / PR, c = p % PR;
-            const unsigned keep = (long long)s * KS + r < a.n ? ~0u : 0u;
+            const int p = tid + 256 * q, r = p / PR, c = p % PR;
+            const unsigned keep = (long long)(s * KG + kg) * KS + r < a.n ? ~0u : 0u;
             *(u32x4*)(stage + r * PITCH + c * 16) = k[q] & keep;
             if constexpr (WANT_V) *(u32x4*)(stage + TILE + r * PITCH + c * 16) = v[q] & keep;
         }
@@ -115,23 +123,23 @@ __global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a
     auto aload = [&](int s, u32x4 (&f)[PPA]) {
 #pragma unroll
         for (int q = 0; q < PPA; ++q) {
-            const int p = threadIdx.x + 256 * q, r = p / PRA, c = p % PRA;
+            const int p = tid + 256 * q, r = p / PRA, c = p % PRA;
             long long row = (long long)mb * MROWS + r;
             row = row < a.m ? row : a.m - 1;
-            const int col = s * KS + c * 8;
+            const int col = (s * KG + kg) * KS + c * 8;
             f[q] = *(const u32x4*)(Az + row * a.ldp + (col + 8 <= a.ncols ? col : 0));
         }
     };
     auto astore = [&](char* stage, const u32x4 (&f)[PPA]) {
 #pragma unroll
         for (int q = 0; q < PPA; ++q) {
-            const int p = threadIdx.x + 256 * q, r = p / PRA, c = p % PRA;
-            *(u32x4*)(stage + 2 * TILE + r * PA + c * 16) = f[q];
+            const int p = tid + 256 * q, r = p / PRA, c = p % PRA;
+            *(u32x4*)(stage + OFF_A + r * PA + c * 16) = f[q];
         }
     };
     // this lane's corner of the 4 x 16 blocks it helps to read: row 8 kh + e, column 16 jg + 4 q
     const int tr_off = (8 * kh + ((lane & 15) >> 2)) * PITCH + (16 * ((lane >> 4) & 1) + 4 * (lane & 3)) * 2;
-    const int fa_off = 2 * TILE + (wtile * 32 + li) * PA + 16 * kh;
+    const int fa_off = OFF_A + (wtile * 32 + li) * PA + 16 * kh;
     auto product = [&](const char* stage) {
         const char* tile = stage + (for_v ? TILE : 0);
         bf16x8 f[KS / 16];
@@ -177,13 +185,32 @@ __global__ __launch_bounds__(256) void measure_direct_kernel(MeasureDirectArgs a
             __syncthreads();
         }
     }
+    if constexpr (KG == 2) {      // the second group's sums, through the staging LDS (free after the last step's barrier)
+        float* ex = (float*)lds_all + wave * (DT * 16 * 64) + lane;
+        if (kg == 1) {
+#pragma unroll
+            for (int t = 0; t < DT; ++t)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) ex[(t * 16 + v) * 64] = acc[t][v];
+        }
+        __syncthreads();
+        if (kg == 1) return;
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][v] += ex[(t * 16 + v) * 64];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        static_assert(4 * DT * 16 * 64 * 4 <= 4 * STAGE, "the sums fit the stages");
+    }
     if (!live) return;
     // Epilogue.  The accumulators hold columns (lane = column, 16 rows each); rows of the outputs are contiguous in
     // memory, so a tile goes through this wavefront's piece of the staging LDS (free after the last step's barrier)
     // and leaves as 16-byte pieces of rows.  The transpose of V~ wants four consecutive rows of a column: that is
     // what a lane holds, and it is stored from the registers.
     constexpr int PE = D * 2 + 16;                     // row pitch of the tile in LDS
-    char* ep = lds + wave * (32 * PE);
+    // (KG = 2: each wavefront's piece lies inside the piece of sums it has read itself)
+    char* ep = lds_all + wave * (KG == 2 ? DT * 16 * 64 * 4 : 32 * PE);
+    static_assert(32 * PE <= DT * 16 * 64 * 4, "");
     const long long zm = (long long)z * a.m;
     const int ng = D / 16;
     // which: 0 the value in the element type, 1 what is left of it (the lo half of the pair); rows beyond m as zero

@@ -36,3 +36,71 @@ def test_separate_matrices_read_only_what_the_call_wrote(d, iters):
     torch.cuda.synchronize()
     assert_close("Z", to_np(Z), ref["Z"], TOL[w.dtype])
     assert_close("C", to_np(C), ref["C"] if iters else ref["Z"], TOL[w.dtype])
+
+
+# n_q around a wavefront's 32 rows and a workgroup's 256; m around a tile, around the last pair of tiles and on both
+# sides of what fits LDS (d = 64: 20 tiles; d = 128: 10)
+Z_ONLY_CASES = [(1, 5, 5, 32), (33, 31, 31, 32), (32, 33, 33, 64), (257, 96, 64, 64), (70, 640, 640, 64), (70, 641, 641, 64),
+                (300, 1100, 1055, 64), (65, 200, 97, 96), (40, 320, 320, 128), (290, 330, 321, 128), (1, 400, 353, 128)]
+
+
+@pytest.mark.parametrize("n_q,n,m,d", Z_ONLY_CASES)
+def test_compressed_attention_without_the_attention_matrix(n_q, n, m, d, options):
+    """Z when A~ is not asked for (a kernel of its own in bf16) against the oracle and against the call that asks for it."""
+    w = _small("z_only", B=1, H=3, n_q=n_q, n=n, d=d, m=m, dtype="bf16")
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    p = _problem(w, Q, K, V, Phi)
+    Kc, Vc = p.measure()
+    A, Z = orc.compressed_attention(Q, to_np(Kc), to_np(Vc))
+    Zg = p.empty(p.BH, n_q, d)
+    p.ws.fill_(0xFF)
+    csat.csat_compressed_attention(p.dims, p.Q, Kc, Vc, None, Zg, p.ws)
+    torch.cuda.synchronize()
+    assert_close("Z", to_np(Zg), Z, TOL["bf16"])
+    _, Zf = p.attention(Kc, Vc)
+    assert_close("Z against the call with A~", to_np(Zg), to_np(Zf), TOL["bf16"])
+    # the block without iterations: the (hi | lo) pair of K~ through the same kernel
+    mu = _mu(Phi)
+    ref = orc.forward(Q, K, V, Phi, w.lam, mu, 0)
+    C, Z0, _ = p.forward(w.lam, mu, 0, want_x=False)
+    assert_close("C (no iterations)", to_np(C), ref["Z"], TOL["bf16"])
+    assert torch.equal(C, Z0)
+
+
+def test_compressed_attention_moves_its_reference_score():
+    """Scores that grow along m by far more than 2^8 from one pair of tiles to the next (the kernel without A~ rescales its
+    output then), and by less than that (it does not)."""
+    d, m, n_q = 64, 224, 64
+    w = _small("z_growing", B=1, H=2, n_q=n_q, n=256, d=d, m=m, dtype="bf16")
+    rng = np.random.default_rng(3)
+    Q = gen.quantize(rng.standard_normal((2, n_q, d)).astype(np.float32), "bf16")
+    ramp = np.stack([np.linspace(0.0, 12.0, m), np.linspace(0.0, 0.6, m)])
+    Kc = gen.quantize((Q[:, :1] * ramp[:, :, None] + 0.1 * rng.standard_normal((2, m, d))).astype(np.float32), "bf16")
+    Vc = gen.quantize(rng.standard_normal((2, m, d)).astype(np.float32), "bf16")
+    p = _problem(w, Q, Q[:, :1].repeat(256, 1), Q[:, :1].repeat(256, 1), gen.make_workload_phi(w))
+    _, Z = orc.compressed_attention(Q, Kc, Vc)
+    Zg = p.empty(2, n_q, d)
+    csat.csat_compressed_attention(p.dims, p.Q, to_dev(Kc, "bf16"), to_dev(Vc, "bf16"), None, Zg, p.ws)
+    torch.cuda.synchronize()
+    assert_close("Z", to_np(Zg), Z, TOL["bf16"])
+
+
+# few workgroups and a long contraction: two groups of wavefronts split it (n = 512 is where that begins; 511 stays with one)
+@pytest.mark.parametrize("n,m,d,zero_iters", [(511, 40, 64, True), (512, 40, 64, True), (700, 97, 128, True), (1025, 64, 128, False),
+                                              (1500, 33, 64, False), (4097, 65, 64, True)])
+def test_measurement_with_a_split_contraction(n, m, d, zero_iters, options):
+    w = _small("split", B=1, H=3, n_q=40, n=n, d=d, m=m, dtype="bf16", iters=0 if zero_iters else 2, lam=0.02)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    ref = orc.forward(Q, K, V, Phi, w.lam, mu, w.iters)
+    p = _problem(w, Q, K, V, Phi)
+    Kc, Vc = p.measure()
+    assert_close("Kc", to_np(Kc), ref["Kc"], TOL["bf16"])
+    assert_close("Vc", to_np(Vc), ref["Vc"], TOL["bf16"])
+    p.ws.fill_(0xFF)
+    C, Z, _ = p.forward(w.lam, mu, w.iters, want_x=False)              # K~ as a pair and as fragments
+    assert_close("Z", to_np(Z), ref["Z"], TOL["bf16"])
+    C2, _, _ = p.forward(w.lam, mu, w.iters, want_z=False, want_x=False)   # K~ only
+    assert_close("C", to_np(C2), to_np(C), TOL["bf16"])

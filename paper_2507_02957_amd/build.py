@@ -29,6 +29,9 @@ UNITS = [("csat", "csat.hip", [])]
 UNITS += [(f"ista_fused_mt{mt}", "csat_tu_ista_fused.hip", [f"-DCSAT_TU_MT={mt}"]) for mt in range(1, 17)]
 UNITS += [(f"attention_{'bf16' if b else 'f32'}_z{z}", "csat_tu_attention.hip", [f"-DCSAT_TU_BF16={b}", f"-DCSAT_TU_Z={z}"])
           for b in (1, 0) for z in ((0, 1, 2, 3) if b else (0, 1))]
+# (largest first: they compile longest)
+UNITS = [(f"ista_resident_{mt}_{c}", "csat_tu_ista_resident.hip", [f"-DCSAT_TU_MT={mt}", f"-DCSAT_TU_NCT={c}"])
+         for c in (16, 12, 9, 7, 5, 3) for mt in range(8, 0, -1) if c * mt <= 80] + UNITS
 UNITS += [("attention_z", "csat_tu_attention_z.hip", [])]
 SOURCES = sorted({os.path.join(CSRC, src) for _, src, _ in UNITS})
 

@@ -3,6 +3,7 @@
 #include "csat.h"
 #include "csat_kernels.h"
 #include "csat_ista_fused.h"
+#include "csat_ista_resident.h"
 #include "csat_omp.h"
 #include "csat_fwht.h"
 #include "csat_gemm_big.h"
@@ -253,6 +254,16 @@ Workspace carve(const csat_dims& d, char* base) {
         csat_status s_ = (expr);        \
         if (s_ != CSAT_OK) return s_;   \
     } while (0)
+
+// Whether the ISTA decoder keeps Phi in LDS and the iterate in registers (csat_ista_resident.h).  Any option that asks
+// for another decoder, or for a property of one, is honoured.
+bool decoder_is_resident(const Workspace& w) {
+    const Options& o = *tl_opt;
+    if (o[CSAT_OPT_DECODER] || o[CSAT_OPT_STATE] || o[CSAT_OPT_FUSED_SEGMENTS] || o[CSAT_OPT_FUSED_THIN] || o[CSAT_OPT_FUSED_SPIN_LIMIT] ||
+        o[CSAT_OPT_INJECT_DECODER_ERROR] || o[CSAT_OPT_FUSED_SCHEDULE])
+        return false;
+    return w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
+}
 
 struct Timed {   // brackets the launches issued during its lifetime
     Profiler* p; hipStream_t st;
@@ -750,9 +761,23 @@ int fused_variant(int MT, long long rows_pad, int nct) {
 // The synthesis C = X V inside the two-chunk decoder's last iteration (csat_ista_fused2.h): bf16, d = 64, whole
 // 32-row tiles per head, and V's fragments must fit the buffer of V^T they replace.
 bool synthesis_in_decoder(const csat_dims& d, const Workspace& w) {
-    if (!w.fused || d.dtype != CSAT_BF16 || d.d != 64 || d.n_q % 32 != 0 || (*tl_opt)[CSAT_OPT_SYNTHESIS] >= 1) return false;
+    if (!w.fused || decoder_is_resident(w) || d.dtype != CSAT_BF16 || d.d != 64 || d.n_q % 32 != 0 || (*tl_opt)[CSAT_OPT_SYNTHESIS] >= 1) return false;
     if (fused_variant(w.MT, w.rows_pad, w.nct) < 3) return false;
     return (long long)((w.nct + 1) / 2 * 2) * 32 <= w.ldn;
+}
+
+csat_status launch_ista_resident(const csat_dims& d, const Workspace& w, IstaResidentArgs a, hipStream_t st) {
+    const long long tiles = (a.rows + 31) / 32;
+    const int cus = cu_count();
+    a.tiles_per_wg = tiles <= cus ? 1 : tiles <= 2ll * cus ? 2 : 4;
+    const unsigned grid = (unsigned)((tiles + a.tiles_per_wg - 1) / a.tiles_per_wg);
+    *tl_decoder_kernel = 5;
+    switch (w.MT * 100 + ista_resident_chunks(w.MT, w.nct)) {
+#define CSAT_RESIDENT_CASE(MT_, NCT_) case MT_ * 100 + NCT_: HIP_TRY(ista_resident_launch_##MT_##_##NCT_(a, grid, st)); return CSAT_OK;
+        CSAT_RESIDENT_INSTANCES(CSAT_RESIDENT_CASE)
+#undef CSAT_RESIDENT_CASE
+    }
+    return CSAT_ERR_SHAPE;
 }
 
 csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipStream_t st) {
@@ -802,6 +827,12 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const float* Y, lon
     constexpr bool kBf16 = sizeof(T) == 2;
     const long long rows = (long long)d.B * d.H * d.n_q;
     const float theta = mu * lambda;
+    if constexpr (kBf16) {
+        if (decoder_is_resident(w)) {
+            Timed tm(w, CSAT_K_UPDATE, st);
+            return launch_ista_resident(d, w, IstaResidentArgs{w.PhiPack, Y, w.Xb, Xout, w.Status, rows, d.n, w.nct, (int)ldY, (int)w.ldn, iters, 1, mu, theta}, st);
+        }
+    }
     // word 0 of the status block: set by the fused decoder when its bounded wait gives up
     // (and, in the same launch, the fused decoder's unit counter and progress words: 2 + one per group of 32 rows at most)
     const long long sync_words = w.fused ? 2 + w.rows_pad / 32 : 0;
@@ -993,7 +1024,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
     // kernels that support it (single sweep with the scores kept in the accumulator file; the two-chunk decoder).
     bool y_tiled = false;
     if constexpr (sizeof(T) == 2) {
-        y_tiled = iters > 0 && w.fused && d.n_q % 32 == 0 && (*tl_opt)[CSAT_OPT_Y_LAYOUT] != 1 &&
+        y_tiled = iters > 0 && w.fused && !decoder_is_resident(w) && d.n_q % 32 == 0 && (*tl_opt)[CSAT_OPT_Y_LAYOUT] != 1 &&
                   fused_variant(w.MT, w.rows_pad, w.nct) >= 3 && attention_is_fused<T>(d, w, true) &&
                   attention_single_sweep(w.MT, 2 * ((d.d + 15) / 16)) &&
                   (v_packed || (!need_z && attention_mtp(w.MT, true) == 13));

@@ -1,0 +1,229 @@
+// ISTA decoder for problems so small that the whole packed Phi fits the LDS of a compute unit and a 32-row tile's
+// whole iterate fits the registers of one wavefront (bf16): one launch runs every iteration, and between the load of
+// Phi at the start and the stores of the result at the end a wavefront touches neither barrier nor memory, except for
+// the rows of y that each iteration's residual starts from.
+//
+// The arithmetic is the fused decoder's (csat_ista_fused.h), product by product in the same order, so the results are
+// the same bits: per 32-column chunk U^T = Phi_chunk^T r^T (fragments read from LDS with the transposing load),
+// x <- eta_theta(x + mu U) in registers, racc -= Phi_chunk x^T (the same fragments read plainly).
+//
+// What bounded these shapes on the streaming kernels was the chain of chunk steps: at three tiles of m a step has 12
+// MFMAs (384 cycles) but took about 2000, for the barrier, the wait for the staged chunk, the memory round trip of the
+// old iterate and the requests of the next step.  Here a step is the MFMAs, their LDS reads (1 KB each: four
+// wavefronts at the full MFMA rate need the whole LDS bandwidth, the bound that is left) and the threshold.
+// Measured, whole forward before -> after: image_text (26 304 rows, n = 274, m = 96, 20 iterations) 221 -> 103 us;
+// 76 800 rows, n = 300, m = 128: 675 -> 386; 131 072 rows, n = 512, m = 32: 1778 -> 383; 1096 rows of image_text's
+// kind: 150 -> 88; n = 500, m = 150 (the largest Phi that fits), 128 000 rows: 1028 -> 511.
+#pragma once
+#include "csat_ista_fused.h"
+
+namespace csat {
+
+struct IstaResidentArgs {
+    const uint4* PhiPack;   // [nct][ista_fused_set_frags(MT)][64], as the fused decoder's
+    const float* Y;         // [rows, ldy], ldy = 32 * MT, columns >= m zero
+    bf16_t* Xb;             // [rows, ldxb] bf16 copy of the final iterate, zero beyond n, or null
+    float* Xout;            // [rows, n] or null
+    int* status;            // set to 0: this decoder cannot give up
+    long long rows;
+    int n, nct, ldy, ldxb, iters;
+    int tiles_per_wg;       // wavefronts of a workgroup that own a tile (1, 2 or 4)
+    float mu, theta;
+};
+
+constexpr size_t ista_resident_lds_bytes(int MT, int nct) { return (size_t)nct * 2 * MT * 1024; }
+// Chunk count of the instance that takes nct chunks at MT tiles of m, 0 if there is none: Phi has to fit the 160 KB of
+// LDS, the iterate and the residual the 512 registers.  (The instances are straight-line code over their chunks: with
+// a count that is only known at run time the branches made the compiler spill hundreds of registers.  Chunks between
+// the row's and the instance's multiply zeros.)
+constexpr int ista_resident_chunks(int MT, int nct) {
+    const int c = nct <= 3 ? 3 : nct <= 5 ? 5 : nct <= 7 ? 7 : nct <= 9 ? 9 : nct <= 12 ? 12 : nct <= 16 ? 16 : 0;
+    return MT <= 8 && c * MT <= 80 ? c : 0;
+}
+
+// NCT: chunks of the instance (nct <= NCT)
+template <int MT, int NCT>
+__global__ __launch_bounds__(256, 1) void ista_resident_kernel(IstaResidentArgs a) {
+    extern __shared__ uint4 lds[];
+    constexpr int NF = 2 * MT, SETF = ista_fused_set_frags(MT), CHUNK = NF * 1024;
+    constexpr int G = 2;                        // fragments per LDS wait
+    const int lane = threadIdx.x & 63, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nct = a.nct;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *a.status = 0;
+
+    for (int f = wave; f < nct * NF; f += 4)    // all of Phi, 1 KB per request
+        __builtin_amdgcn_global_load_lds((glb_ptr_t)(a.PhiPack + ((long long)(f / NF) * SETF + f % NF) * 64 + lane),
+                                         (lds_ptr_t)((char*)lds + f * 1024), 16, 0, 0);
+    for (int f = nct * NF + wave; f < NCT * NF; f += 4) lds[f * 64 + lane] = uint4{0u, 0u, 0u, 0u};
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (wave >= a.tiles_per_wg) return;         // (no barrier below)
+    const long long rt = (long long)blockIdx.x * a.tiles_per_wg + wave;
+    if (rt * 32 >= a.rows) return;
+    const long long row = rt * 32 + (lane & 31);
+    const bool row_ok = row < a.rows;
+    const float* yrow = a.Y + (row_ok ? row : a.rows - 1) * a.ldy + 4 * lh;      // rows past the end compute on a valid row
+    const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)lds;
+    const uint32_t nat16 = lds0 + frag_slot(lane & 31, lh) * 16;                 // see ista_fused_kernel
+    const uint32_t tr8 = lds0 + ((lane >> 4) & 1) * (MT * 1024) + frag_slot(4 * lh + ((lane & 15) >> 2), lane & 1) * 16 +
+                         ((lane >> 1) & 1) * 8;
+
+    f32x16 x[NCT], racc[MT], u;
+    bf16x8 rb[NF], xb[2];
+#pragma unroll
+    for (int i = 0; i < NCT; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[i][v] = 0.f;
+    auto load_y = [&]() {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 y4 = *(const f32x4*)(yrow + 32 * mt + 8 * g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) racc[mt][4 * g + e] = y4[e];
+            }
+    };
+    auto boundary = [&]() {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            rb[2 * mt] = cvt8<0>(racc[mt], 1.f);
+            rb[2 * mt + 1] = cvt8<8>(racc[mt], 1.f);
+        }
+    };
+
+    // One step: GEMM-U of chunk `cu` (DO_U) with the threshold of chunk I (DO_T) between its MFMAs, then GEMM-R of
+    // chunk I (DO_R).
+    auto step = [&](auto do_u, auto do_t, auto do_r, auto ic, int cu) {
+        constexpr bool DO_U = decltype(do_u)::value, DO_T = decltype(do_t)::value, DO_R = decltype(do_r)::value;
+        constexpr int I = decltype(ic)::value;
+        constexpr int NU = DO_U ? NF : 0, NR = DO_R ? NF : 0, NA = NU + NR, NG = (NA + G - 1) / G;
+        constexpr int NTG = NU / G, EPG = NTG > 0 ? (16 + NTG - 1) / NTG : 16;
+        const uint32_t baseA = tr8 + cu * CHUNK, baseB = nat16 + I * CHUNK;
+        auto ops = [](int k) constexpr {
+            int c = 0;
+            for (int i = 0; i < G; ++i) c += (k * G + i < NU) ? 2 : (k * G + i < NA) ? 1 : 0;
+            return c;
+        };
+        u32x4 fr[2][G];
+        u32x2 ft[2][G][2];
+        f32x16 un;
+        auto fetch = [&](auto kc, auto jc) {
+            constexpr int k = decltype(kc)::value, i = decltype(jc)::value, f = k * G + i;
+            if constexpr (f < NU) {
+                lds_read8_tr<(f >> 1) * 1024 + (f & 1) * 256>(ft[k & 1][i][0], baseA);
+                lds_read8_tr<(f >> 1) * 1024 + (f & 1) * 256 + 128>(ft[k & 1][i][1], baseA);
+            } else if constexpr (f < NA) lds_read16<(f - NU) * 1024>(fr[k & 1][i], baseB);
+        };
+        auto fetch_group = [&](auto self, auto kc, auto jc) {
+            constexpr int i = decltype(jc)::value;
+            if constexpr (i < G) {
+                fetch(kc, jc);
+                self(self, kc, std::integral_constant<int, i + 1>{});
+            }
+        };
+        auto threshold = [&](int v) {
+            float xv = soft_threshold(x[I][v] + a.mu * u[v], a.theta);
+            asm volatile("" : "+v"(xv));           // keeps the arithmetic between the MFMAs it is written next to
+            x[I][v] = xv;
+        };
+        auto operand = [&]() {
+            if constexpr (DO_R) {
+                xb[0] = cvt8<0>(x[I], -1.f);
+                xb[1] = cvt8<8>(x[I], -1.f);
+            }
+        };
+#pragma unroll
+        for (int v = 0; v < 16; ++v) un[v] = 0.f;
+        using Z_ = std::integral_constant<int, 0>;
+        if constexpr (NG > 0) fetch_group(fetch_group, Z_{}, Z_{});
+        if constexpr (DO_T && NTG == 0) {
+#pragma unroll
+            for (int v = 0; v < 16; ++v) threshold(v);
+            operand();
+        }
+        auto group = [&](auto kc) {
+            constexpr int k = decltype(kc)::value;
+            constexpr int NEXT = (k + 1 < NG) ? ops(k + 1) : 0;
+            if constexpr (k + 1 < NG) fetch_group(fetch_group, std::integral_constant<int, k + 1>{}, Z_{});
+            lds_wait_n<NEXT>();
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                if (k * G + i < NU) lds_pin(ft[k & 1][i][0], ft[k & 1][i][1]);
+                else if (k * G + i < NA) lds_pin(fr[k & 1][i]);
+            }
+            if constexpr (DO_T && NTG > 0 && k == NTG) operand();
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const int f = k * G + i;
+                if (f < NU) {
+                    const u32x4 fa = __builtin_shufflevector(ft[k & 1][i][0], ft[k & 1][i][1], 0, 1, 2, 3);
+                    un = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa), rb[f], un, 0, 0, 0);
+                } else if (f < NA) {
+                    const int r = f - NU;
+                    racc[r % MT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[k & 1][i]),
+                                                                           xb[r / MT], racc[r % MT], 0, 0, 0);
+                }
+            }
+            if constexpr (DO_T && NTG > 0 && k < NTG) {
+#pragma unroll
+                for (int e = 0; e < EPG; ++e)
+                    if (k * EPG + e < 16) threshold(k * EPG + e);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        auto run = [&](auto self, auto kc) {
+            constexpr int k = decltype(kc)::value;
+            if constexpr (k < NG) {
+                group(kc);
+                self(self, std::integral_constant<int, k + 1>{});
+            }
+        };
+        run(run, Z_{});
+        if constexpr (DO_U) u = un;
+    };
+
+    using T_ = std::true_type;
+    using F_ = std::false_type;
+    auto chunks = [&](auto self, auto ic, auto do_r) {
+        constexpr int I = decltype(ic)::value;
+        if constexpr (I + 1 < NCT) {
+            step(T_{}, T_{}, do_r, ic, I + 1);
+            self(self, std::integral_constant<int, I + 1>{}, do_r);
+        } else {
+            step(F_{}, T_{}, do_r, ic, 0);
+        }
+    };
+    using I0 = std::integral_constant<int, 0>;
+    load_y();
+    boundary();
+    for (int t = 0; t + 1 < a.iters; ++t) {
+        load_y();
+        step(T_{}, F_{}, F_{}, I0{}, 0);
+        chunks(chunks, I0{}, T_{});
+        boundary();
+    }
+    step(T_{}, F_{}, F_{}, I0{}, 0);
+    chunks(chunks, I0{}, F_{});
+    if (!row_ok) return;
+#pragma unroll
+    for (int i = 0; i < NCT; ++i)
+        {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int col = 32 * i + 8 * g + 4 * lh;
+                if (a.Xb && col < a.ldxb)      // (zero beyond n)
+                    *(uint2*)(a.Xb + row * a.ldxb + col) = uint2{f2bf_pk(x[i][4 * g], x[i][4 * g + 1]), f2bf_pk(x[i][4 * g + 2], x[i][4 * g + 3])};
+                if (a.Xout) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < a.n) a.Xout[row * (long long)a.n + col + e] = x[i][4 * g + e];
+                }
+            }
+        }
+    if (a.Xb)                                   // operand columns beyond the instance's chunks
+        for (int col = 32 * NCT + 4 * lh; col < a.ldxb; col += 8) *(uint2*)(a.Xb + row * a.ldxb + col) = uint2{0u, 0u};
+}
+
+}  // namespace csat

@@ -7,6 +7,7 @@
 namespace csat {
 
 struct IstaFusedArgs;
+struct IstaResidentArgs;
 struct AttentionArgs;
 struct AttentionZArgs;
 
@@ -20,6 +21,16 @@ CSAT_DECLARE_FUSED(6) CSAT_DECLARE_FUSED(7) CSAT_DECLARE_FUSED(8) CSAT_DECLARE_F
 CSAT_DECLARE_FUSED(11) CSAT_DECLARE_FUSED(12) CSAT_DECLARE_FUSED(13) CSAT_DECLARE_FUSED(14) CSAT_DECLARE_FUSED(15)
 CSAT_DECLARE_FUSED(16)
 #undef CSAT_DECLARE_FUSED
+
+// ISTA decoder with Phi in LDS and the iterate in registers (csat_ista_resident.h): one function per instance
+// (tiles of m, chunks of n), defined by csat_tu_ista_resident.hip.
+#define CSAT_RESIDENT_INSTANCES(F)                                                                                       \
+    F(1, 3) F(2, 3) F(3, 3) F(4, 3) F(5, 3) F(6, 3) F(7, 3) F(8, 3) F(1, 5) F(2, 5) F(3, 5) F(4, 5) F(5, 5) F(6, 5) F(7, 5) \
+    F(8, 5) F(1, 7) F(2, 7) F(3, 7) F(4, 7) F(5, 7) F(6, 7) F(7, 7) F(8, 7) F(1, 9) F(2, 9) F(3, 9) F(4, 9) F(5, 9) F(6, 9) \
+    F(7, 9) F(8, 9) F(1, 12) F(2, 12) F(3, 12) F(4, 12) F(5, 12) F(6, 12) F(1, 16) F(2, 16) F(3, 16) F(4, 16) F(5, 16)
+#define CSAT_DECLARE_RESIDENT(MT_, NCT_) hipError_t ista_resident_launch_##MT_##_##NCT_(const IstaResidentArgs& a, unsigned grid, hipStream_t st);
+CSAT_RESIDENT_INSTANCES(CSAT_DECLARE_RESIDENT)
+#undef CSAT_DECLARE_RESIDENT
 
 // Compressed attention in one kernel (csat_attention.h) for mt_total tiles of m; `single`: all of K~ is kept in
 // registers and LDS at once.  One function per element type and per "with the output product", defined by

@@ -104,3 +104,34 @@ def test_measurement_with_a_split_contraction(n, m, d, zero_iters, options):
     assert_close("Z", to_np(Z), ref["Z"], TOL["bf16"])
     C2, _, _ = p.forward(w.lam, mu, w.iters, want_z=False, want_x=False)   # K~ only
     assert_close("C", to_np(C2), to_np(C), TOL["bf16"])
+
+
+# (n_q, n, m, iterations, decoder kernel): chunk counts on both sides of every instance's, one tile of m and eight, the
+# largest Phi that fits LDS (80 chunk-tiles) and the first that does not, a ragged last row tile, one iteration
+RESIDENT_CASES = [(33, 65, 8, 3, 5), (31, 96, 33, 4, 5), (70, 97, 96, 3, 5), (64, 160, 129, 2, 5), (40, 161, 160, 3, 5),
+                  (97, 224, 224, 2, 5), (50, 225, 200, 3, 5), (129, 288, 256, 1, 5), (33, 289, 192, 3, 5), (32, 384, 161, 2, 5),
+                  (20, 385, 160, 3, 5), (65, 512, 32, 3, 5), (40, 513, 32, 2, 2), (40, 385, 161, 2, 2), (64, 200, 200, 1, 5)]
+
+
+@pytest.mark.parametrize("n_q,n,m,iters,kernel", RESIDENT_CASES)
+def test_decoder_with_phi_in_lds(n_q, n, m, iters, kernel, options):
+    """Small problems keep Phi in LDS and the iterate in registers: the bits of the decoder that streams both, and the
+    oracle.  lambda small enough for a dense iterate in every chunk."""
+    w = _small("resident", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, lam=0.002)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    C, _, X = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() == kernel
+    assert csat.csat_decoder_status(p.ws) == 0
+    ref = orc.forward(Q, K, V, Phi, w.lam, mu, iters)
+    assert_close("X", to_np(X), ref["X"], TOL["bf16"])
+    assert_close("C", to_np(C), ref["C"], TOL["bf16"])
+    options("fused_thin", 1)
+    options("synthesis", 1)       # (that decoder can also form C itself, in another summation order)
+    p.ws.fill_(0xFF)
+    C1, _, X1 = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() != 5
+    same = torch.equal(X, X1) and torch.equal(C, C1)
+    assert same

@@ -7,6 +7,7 @@
 #include "csat_omp.h"
 #include "csat_fwht.h"
 #include "csat_gemm_big.h"
+#include "csat_gemm_f32.h"
 #include "csat_attention.h"
 #include "csat_attention_z.h"
 #include "csat_measure.h"
@@ -265,6 +266,17 @@ bool decoder_is_resident(const Workspace& w) {
     return w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
 }
 
+// CUs of the current device (persistent grids and work-distribution heuristics)
+int cu_count() {
+    static const int n = [] {
+        int dev = 0, v = 0;
+        if (hipGetDevice(&dev) != hipSuccess) return 256;
+        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
+        return v;
+    }();
+    return n;
+}
+
 struct Timed {   // brackets the launches issued during its lifetime
     Profiler* p; hipStream_t st;
     Timed(const Workspace& w, int kid, hipStream_t s) : p(w.prof), st(s) { p->begin(kid, st); }
@@ -321,6 +333,16 @@ bool use_big_gemm(const GemmArgs& g, long long n_cover) {
     return Kp <= g.lda && Kp <= g.ldb && g.a_kwrap == 0 && g.M >= 256 && n_cover >= 128 && gemm_choice() != 1;
 }
 
+// float products (csat_gemm_f32.h)
+template <typename Epi>
+csat_status launch_gemm_f32(GemmArgs g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
+    g.raster = (int)((n_cover + kF32TileN - 1) / kF32TileN);      // column tiles; row tiles in whole groups of eight
+    const dim3 grid((unsigned)((g.M + 8 * kF32TileM - 1) / (8 * kF32TileM) * 8 * g.raster), 1, (unsigned)batch);
+    hipLaunchKernelGGL((gemm_nt_f32_split_kernel<Epi>), grid, dim3(256), 0, st, g, epi);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+
 template <typename T, typename Epi>
 csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     if constexpr (sizeof(T) == 2) {
@@ -330,6 +352,9 @@ csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi
             gb.K = (int)Kp;
             return launch_gemm_big<Epi>(gb, n_cover, batch, epi, st);
         }
+    }
+    if constexpr (sizeof(T) == 4) {
+        if (gemm_choice() != 1) return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
     }
     if (n_cover <= 64) return launch_gemm<T, 128, 64, 2, 2, Epi>(g, n_cover, batch, epi, st);
     return launch_gemm<T, 128, 128, 2, 2, Epi>(g, n_cover, batch, epi, st);
@@ -384,17 +409,6 @@ csat_status prepare_phi(const csat_dims& d, const Workspace& w, const T* Phi, bo
         }
     }
     return CSAT_OK;
-}
-
-// CUs of the current device (persistent grids and work-distribution heuristics)
-int cu_count() {
-    static const int n = [] {
-        int dev = 0, v = 0;
-        if (hipGetDevice(&dev) != hipSuccess) return 256;
-        if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v <= 0) return 256;
-        return v;
-    }();
-    return n;
 }
 
 // Whether the measurement runs as the one kernel that reads K and V as they are (csat_measure.h): bf16, d of

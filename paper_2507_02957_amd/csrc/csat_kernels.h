@@ -97,6 +97,9 @@ __device__ __forceinline__ void mfma_group<float>(const uint4& a, const uint4& b
     for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], bv[s], acc, 0, 0, 0);
 }
 
+template <typename E, typename = void> struct has_rows_epilogue : std::false_type {};
+template <typename E> struct has_rows_epilogue<E, std::enable_if_t<E::kRows>> : std::true_type {};
+
 template <typename T, int BM, int BN, int WM, int WN, typename Epi>
 __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g, Epi epi) {
     static_assert(WM * WN == 4, "four wavefronts per workgroup");
@@ -193,6 +196,10 @@ __global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g, Epi epi) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             long long c = col0 + (wn * TN + j) * 32 + li;
+            if constexpr (has_rows_epilogue<Epi>::value) {
+                epi.rows(row0 + (wm * TM + i) * 32 + 4 * lh, c, acc[i][j]);
+                continue;
+            }
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 long long r = row0 + (wm * TM + i) * 32 + 8 * (v / 4) + 4 * lh + (v % 4);
@@ -275,6 +282,23 @@ struct EpiResidual {
         float out = (c < N) ? Y[r * ldY + c] - v : 0.f;
         Elem<TO>::store(R + r * ldR + c, out);
     }
+    // one lane's 16 accumulators of a tile (rows r0 + 8 (v / 4) + v % 4): all reads before the first store, which the
+    // compiler cannot tell from them
+    static constexpr bool kRows = true;
+    __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {
+        if (c >= ldR) return;
+        float y[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long long r = r0 + 8 * (v / 4) + (v % 4);
+            y[v] = r < M && c < N ? Y[r * ldY + c] : 0.f;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long long r = r0 + 8 * (v / 4) + (v % 4);
+            if (r < M) Elem<TO>::store(R + r * ldR + c, c < N ? y[v] - acc[v] : 0.f);
+        }
+    }
 };
 
 // ISTA update: u = x + mu * acc (acc = (Phi^T r)[c]); x <- sign(u) max(|u| - theta, 0).
@@ -298,6 +322,28 @@ struct EpiIstaUpdate {
         }
         Xs[r * ldS + c] = x;
         if (Xb) Xb[r * ldS + c] = f2bf(x);
+    }
+    static constexpr bool kRows = true;       // as EpiResidual::rows
+    __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {
+        if (c >= ldS) return;
+        float old[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long long r = r0 + 8 * (v / 4) + (v % 4);
+            old[v] = !first && r < M && c < N ? Xs[r * ldS + c] : 0.f;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long long r = r0 + 8 * (v / 4) + (v % 4);
+            if (r >= M) continue;
+            float u = mu * acc[v];
+            if (!first) u += old[v];
+            const float a = fabsf(u) - theta;
+            const float x = c < N && a > 0.f ? copysignf(a, u) : 0.f;
+            if (Xo && c < N) Xo[r * (long long)N + c] = x;
+            Xs[r * ldS + c] = x;
+            if (Xb) Xb[r * ldS + c] = f2bf(x);
+        }
     }
 };
 
@@ -323,6 +369,31 @@ struct EpiListaUpdate {
         }
         Xnew[r * ldS + c] = x;
         if (Xb) Xb[r * ldS + c] = f2bf(x);
+    }
+    static constexpr bool kRows = true;       // as EpiResidual::rows
+    __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {
+        if (c >= ldS) return;
+        float old[16], w[16];
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long long r = r0 + 8 * (v / 4) + (v % 4);
+            const bool in = r < M && c < N;
+            old[v] = in ? Xold[r * ldS + c] : 0.f;
+            w[v] = in ? W[r * ldS + c] : 0.f;
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const long long r = r0 + 8 * (v / 4) + (v % 4);
+            if (r >= M) continue;
+            float x = 0.f;
+            if (c < N) {
+                const float u = old[v] + acc[v] + w[v];
+                x = u - __builtin_amdgcn_fmed3f(u, -theta, theta);
+                if (Xo) Xo[r * (long long)N + c] = x;
+            }
+            Xnew[r * ldS + c] = x;
+            if (Xb) Xb[r * ldS + c] = f2bf(x);
+        }
     }
 };
 

@@ -135,3 +135,32 @@ def test_decoder_with_phi_in_lds(n_q, n, m, iters, kernel, options):
     assert csat.csat_profile_decoder_kernel() != 5
     same = torch.equal(X, X1) and torch.equal(C, C1)
     assert same
+
+
+# (m, n, d): rows around the 128-row tile, columns around the 64-wide one, contractions around a step of 32 and shorter
+FLOAT_PRODUCTS = [(127, 130, 64), (128, 160, 72), (129, 131, 8), (5, 6, 8), (257, 1056, 128), (33, 33, 136), (1, 31, 64), (200, 4099, 40)]
+
+
+@pytest.mark.parametrize("m,n,d", FLOAT_PRODUCTS)
+def test_float_products_keep_float_precision(m, n, d, options):
+    """Float products run as six bf16 ones over the operands' three parts.  Bound per element: parts and dropped products
+    2^-25 of sum |a b|, one rounding (2^-24) of a partial sum per 16 of K and one per workgroup end."""
+    w = _small("f32_products", B=1, H=3, n_q=4, n=n, d=d, m=m, dtype="f32")
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    p = _problem(w, Q, K, V, Phi)
+    Kc, Vc = (to_np(t).astype(np.float64) for t in p.measure())
+    P = Phi.astype(np.float64)
+    for got, X in ((Kc, K), (Vc, V)):
+        X = X.reshape(-1, n, d).astype(np.float64)
+        bound = (2.0 ** -25 + 2.0 ** -24 * (n / 16 + 3)) * (np.abs(P) @ np.abs(X))
+        assert (np.abs(got.reshape(-1, m, d) - P @ X) <= bound).all()
+    # infinities, NaN and the largest floats come out as the float MFMA has them
+    Kx = K.copy().reshape(-1, n, d)
+    Kx[0, n // 2, 1], Kx[0, 0, 3], Kx[1, n - 1, 2], Kx[2, n // 3, 0], Kx[2, 0, 7] = np.inf, -np.inf, np.nan, 3.4e38, 1.0
+    p = _problem(w, Q, Kx.reshape(K.shape), V, Phi)
+    Kc = p.measure()[0].clone()
+    options("gemm", 1)
+    Ko = p.measure()[0]
+    assert torch.equal(Kc.isnan(), Ko.isnan()) and torch.equal(Kc.isposinf(), Ko.isposinf()) and torch.equal(Kc.isneginf(), Ko.isneginf())
+    assert Ko.isinf().any() and Ko.isnan().any()

@@ -32,6 +32,7 @@ UNITS += [(f"attention_{'bf16' if b else 'f32'}_z{z}", "csat_tu_attention.hip", 
 # (largest first: they compile longest)
 UNITS = [(f"ista_resident_{mt}_{c}", "csat_tu_ista_resident.hip", [f"-DCSAT_TU_MT={mt}", f"-DCSAT_TU_NCT={c}"])
          for c in (16, 12, 9, 7, 5, 3) for mt in range(8, 0, -1) if c * mt <= 80] + UNITS
+UNITS += [("ista_resident_f32", "csat_tu_ista_resident_f32.hip", [])]
 UNITS += [("attention_z", "csat_tu_attention_z.hip", [])]
 SOURCES = sorted({os.path.join(CSRC, src) for _, src, _ in UNITS})
 

@@ -258,12 +258,18 @@ Workspace carve(const csat_dims& d, char* base) {
 
 // Whether the ISTA decoder keeps Phi in LDS and the iterate in registers (csat_ista_resident.h).  Any option that asks
 // for another decoder, or for a property of one, is honoured.
-bool decoder_is_resident(const Workspace& w) {
+bool decoder_options_free() {
     const Options& o = *tl_opt;
-    if (o[CSAT_OPT_DECODER] || o[CSAT_OPT_STATE] || o[CSAT_OPT_FUSED_SEGMENTS] || o[CSAT_OPT_FUSED_THIN] || o[CSAT_OPT_FUSED_SPIN_LIMIT] ||
-        o[CSAT_OPT_INJECT_DECODER_ERROR] || o[CSAT_OPT_FUSED_SCHEDULE])
-        return false;
-    return w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
+    return !(o[CSAT_OPT_DECODER] || o[CSAT_OPT_STATE] || o[CSAT_OPT_FUSED_SEGMENTS] || o[CSAT_OPT_FUSED_THIN] ||
+             o[CSAT_OPT_FUSED_SPIN_LIMIT] || o[CSAT_OPT_INJECT_DECODER_ERROR] || o[CSAT_OPT_FUSED_SCHEDULE]);
+}
+bool decoder_is_resident(const Workspace& w) {
+    return decoder_options_free() && w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
+}
+// ... and its float form.  (A row with an infinite y: all NaN from the second iteration on, whichever decoder runs; after
+// a single iteration the parts would give NaN where float products give infinities, so that goes to those.)
+bool decoder_is_resident_f32(const csat_dims& d, const Workspace& w, int iters) {
+    return d.dtype == CSAT_F32 && iters >= 2 && decoder_options_free() && gemm_choice() != 1 && ista_resident_f32_chunks(w.MT, w.nct) != 0;
 }
 
 // CUs of the current device (persistent grids and work-distribution heuristics)
@@ -393,8 +399,9 @@ csat_status fill_zero(void* p, size_t bytes, hipStream_t st) {   // bytes multip
 // Operand copies of Phi: row-major padded (measurement GEMM; generic decoder's residual GEMM),
 // transposed (generic decoder's update GEMM) or MFMA fragments (fused decoder).
 template <typename T>
-csat_status prepare_phi(const csat_dims& d, const Workspace& w, const T* Phi, bool for_measure, bool for_decoder,
+csat_status prepare_phi(const csat_dims& d, const Workspace& w, const T* Phi, bool for_measure, int decoder_iters,
                         hipStream_t st) {
+    const bool for_decoder = decoder_iters > 0 && !decoder_is_resident_f32(d, w, decoder_iters);
     Timed tm(w, CSAT_K_LAYOUT, st);
     const bool generic = for_decoder && !w.fused;
     if (for_measure || generic) CSAT_TRY((pack_rows<T, T>(Phi, d.n, (T*)w.PhiP, w.ldn, d.m, d.n, st)));
@@ -836,7 +843,7 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
 // or w.Xb (bf16 mode).  Fused decoder (bf16, m <= 512): Y must be w.A-style rows with
 // ldY == w.ldy and zero pads; the final iterate is left in w.Xb.
 template <typename T>
-csat_status run_ista(const csat_dims& d, const Workspace& w, const float* Y, long long ldY, float lambda, float mu,
+csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const float* Y, long long ldY, float lambda, float mu,
                      int iters, float* Xout, hipStream_t st, const T* Vsyn = nullptr, T* Csyn = nullptr, bool y_tiled = false) {
     constexpr bool kBf16 = sizeof(T) == 2;
     const long long rows = (long long)d.B * d.H * d.n_q;
@@ -845,6 +852,15 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const float* Y, lon
         if (decoder_is_resident(w)) {
             Timed tm(w, CSAT_K_UPDATE, st);
             return launch_ista_resident(d, w, IstaResidentArgs{w.PhiPack, Y, w.Xb, Xout, w.Status, rows, d.n, w.nct, (int)ldY, (int)w.ldn, iters, 1, mu, theta}, st);
+        }
+    }
+    if constexpr (!kBf16) {
+        if (decoder_is_resident_f32(d, w, iters)) {
+            *tl_decoder_kernel = 5;
+            Timed tm(w, CSAT_K_UPDATE, st);
+            HIP_TRY(ista_resident_f32_launch(w.MT, IstaResidentF32Args{Phi, Y, ldY, w.Xs, w.ldn, Xout, w.Status, rows, d.m, d.n, w.nct, iters, mu, theta},
+                                             (unsigned)((rows + 31) / 32), st));
+            return CSAT_OK;
         }
     }
     // word 0 of the status block: set by the fused decoder when its bounded wait gives up
@@ -966,7 +982,7 @@ template <typename T>
 csat_status measure_t(const csat_dims& d, const Workspace& w, const void* PhiK, const void* Phi, const void* K,
                       const void* V, void* Kc, void* Vc, hipStream_t st) {
     const bool separate = PhiK && PhiK != Phi;
-    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !measure_reads_raw_phi<T>(d, separate), false, st));
+    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !measure_reads_raw_phi<T>(d, separate), 0, st));
     return run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)Kc, (T*)Vc, nullptr, measure_is_direct<T>(d, separate), false, st, (const T*)PhiK,
                           (const T*)Phi);
 }
@@ -995,14 +1011,14 @@ csat_status recover_t(const csat_dims& d, const Workspace& w, const float* Y, co
         if (want_c) CSAT_TRY(fill_zero(C, (size_t)rows * d.d * sizeof(T), st));
         return CSAT_OK;
     }
-    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, false, true, st));
+    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, false, iters, st));
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         if (w.fused) CSAT_TRY((pack_rows<float, float>(Y, d.m, w.A, w.ldy, rows, d.m, st)));
-        else CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));
+        else if (!decoder_is_resident_f32(d, w, iters)) CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));
         if (want_c && !synthesis_is_direct<T>(d)) CSAT_TRY(transpose_pack<T>((const T*)V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
     }
-    CSAT_TRY(run_ista<T>(d, w, w.fused ? w.A : Y, w.fused ? w.ldy : (long long)d.m, lambda, mu, iters, X, st));
+    CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, w.fused ? w.A : Y, w.fused ? w.ldy : (long long)d.m, lambda, mu, iters, X, st));
     if (want_c) CSAT_TRY(run_synthesis<T>(d, w, (T*)C, st, (const T*)V));
     return CSAT_OK;
 }
@@ -1012,7 +1028,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
                       const void* PhiK, const void* Phi, float lambda, float mu, int iters, void* C, void* Z,
                       float* X, hipStream_t st) {
     const bool separate = PhiK && PhiK != Phi;
-    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !measure_reads_raw_phi<T>(d, separate), iters > 0, st));
+    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !measure_reads_raw_phi<T>(d, separate), iters, st));
     const bool need_z = Z || iters == 0;
     T* zdst = (iters == 0) ? (T*)C : (T*)Z;
     bool kc_packed = false, v_packed = false;
@@ -1032,7 +1048,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
         return CSAT_OK;
     }
     // the operand copy of A~ feeds the Z product as a GEMM and the GEMM-pair decoder; the fused decoder reads A~ itself
-    T* pcopy = ((need_z && !v_packed) || !w.fused) ? (T*)w.R : nullptr;
+    T* pcopy = ((need_z && !v_packed) || !(w.fused || decoder_is_resident_f32(d, w, iters))) ? (T*)w.R : nullptr;
     // A~ in accumulator tiles between the attention kernel and the two-chunk decoder: both then move whole 1 KB pieces
     // per instruction instead of 16-byte pieces of 32 rows.  Needs whole 32-row tiles per head and the forms of the two
     // kernels that support it (single sweep with the scores kept in the accumulator file; the two-chunk decoder).
@@ -1049,8 +1065,8 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
         if (Z) HIP_TRY(hipMemcpyAsync(Z, C, (size_t)d.B * d.H * d.n_q * d.d * sizeof(T), hipMemcpyDeviceToDevice, st));
         return CSAT_OK;
     }
-    if (syn) return run_ista<T>(d, w, w.A, w.ldy, lambda, mu, iters, X, st, (const T*)V, (T*)C, y_tiled);
-    CSAT_TRY(run_ista<T>(d, w, w.A, w.ldy, lambda, mu, iters, X, st, nullptr, nullptr, y_tiled));
+    if (syn) return run_ista<T>(d, w, (const T*)Phi, w.A, w.ldy, lambda, mu, iters, X, st, (const T*)V, (T*)C, y_tiled);
+    CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, w.A, w.ldy, lambda, mu, iters, X, st, nullptr, nullptr, y_tiled));
     return run_synthesis<T>(d, w, (T*)C, st, (const T*)V);
 }
 
@@ -1077,7 +1093,7 @@ csat_status forward_rd_t(const csat_dims& d, const Workspace& w, const Workspace
     const int BH = d.B * d.H;
     const long long rows = (long long)BH * d.d;          // decoder problems
     const csat_dims dr = rd_dims(d);
-    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, true, false, st));
+    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, true, 0, st));
     const bool direct = measure_is_direct<T>(d, PhiK && PhiK != Phi), z_only = attention_z_applies<T>(d);
     bool kc_packed = false, v_packed = false;
     CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, direct || !z_only ? (T*)w.VcT : nullptr,
@@ -1102,12 +1118,12 @@ csat_status forward_rd_t(const csat_dims& d, const Workspace& w, const Workspace
         Timed tm(w, CSAT_K_MEASURE, st);
         CSAT_TRY((gemm<T>(g, rows, 1, ey, st)));
     }
-    CSAT_TRY(prepare_phi<T>(dr, wr, (const T*)Phi, false, true, st));
-    if (!wr.fused) {
+    CSAT_TRY(prepare_phi<T>(dr, wr, (const T*)Phi, false, iters, st));
+    if (!wr.fused && !decoder_is_resident_f32(dr, wr, iters)) {
         Timed tm(w, CSAT_K_LAYOUT, st);
         CSAT_TRY((pack_rows<float, T>(wr.A, wr.ldy, (T*)wr.R, wr.ldm, rows, d.m, st)));
     }
-    CSAT_TRY(run_ista<T>(dr, wr, wr.A, wr.ldy, lambda, mu, iters, x.Xout, st));
+    CSAT_TRY(run_ista<T>(dr, wr, (const T*)Phi, wr.A, wr.ldy, lambda, mu, iters, x.Xout, st));
     {   // C[b,h,j,k] = decoded column k at token j
         Timed tm(w, CSAT_K_SYNTHESIS, st);
         dim3 grid((unsigned)((d.d + 31) / 32), (unsigned)((d.n + 31) / 32), (unsigned)BH);

@@ -15,6 +15,7 @@
 // 76 800 rows, n = 300, m = 128: 675 -> 386; 131 072 rows, n = 512, m = 32: 1778 -> 383; 1096 rows of image_text's
 // kind: 150 -> 88; n = 500, m = 150 (the largest Phi that fits), 128 000 rows: 1028 -> 511.
 #pragma once
+#include "csat_gemm_f32.h"
 #include "csat_ista_fused.h"
 
 namespace csat {
@@ -224,6 +225,215 @@ __global__ __launch_bounds__(256, 1) void ista_resident_kernel(IstaResidentArgs 
         }
     if (a.Xb)                                   // operand columns beyond the instance's chunks
         for (int col = 32 * NCT + 4 * lh; col < a.ldxb; col += 8) *(uint2*)(a.Xb + row * a.ldxb + col) = uint2{0u, 0u};
+}
+
+
+// ----------------------------------------------------------------------------------------
+// The same for float problems, with Phi, the residual and the iterate as three bf16 parts each and six part products
+// per product (csat_gemm_f32.h).  A workgroup of 4 wavefronts owns one 32-row tile: the wavefronts split the chunks of
+// n (wavefront w takes chunks w, w + 4, ...), and once per iteration their partial sums of Phi x meet in LDS, one tile
+// of m at a time, where every thread forms two elements of y - Phi x and writes their parts as the next operands.
+// Splitting a tile over the four SIMDs matters because these launches have few tiles: 256 x 256 with m = 64 (8 tiles)
+// took 20 products of two or eight workgroups each, 445 us a forward with the launches between them; now 139 us, 41 of
+// them this kernel.  Errors against float64 are at most those of the float MFMA's products (the residual's sums meet in a
+// fixed order).
+// ----------------------------------------------------------------------------------------
+struct IstaResidentF32Args {
+    const float* Phi;       // [m, n]
+    const float* Y; long long ldY;      // [rows, ldY]
+    float* Xs; long long ldS;           // [rows, ldS] final iterate, zero beyond n, or null
+    float* Xout;                        // [rows, n] or null
+    int* status;
+    long long rows;
+    int m, n, nct, iters;
+    float mu, theta;
+};
+
+constexpr size_t ista_resident_f32_lds_bytes(int MT, int nct) { return ((size_t)nct * 6 * MT + 16 + 6 * MT) * 1024; }
+constexpr int kResidentF32MaxMT = 4;
+// Chunks per wavefront of the instance that takes nct chunks at MT tiles of m (whose Phi must fit LDS), 0: none
+constexpr int ista_resident_f32_chunks(int MT, int nct) {
+    if (MT > kResidentF32MaxMT || ista_resident_f32_lds_bytes(MT, nct) > 160 * 1024) return 0;
+    const int c = (nct + 3) / 4;
+    return MT == 1 ? (c <= 3 ? 3 : 6) : MT == 2 ? 3 : 2;
+}
+
+template <int MT, int CPW>
+__global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF32Args a) {
+    extern __shared__ uint4 lds[];
+    constexpr int NF = 2 * MT, PLANE = NF * 1024, CHUNK = 3 * PLANE;     // bytes of one part of a chunk, of a chunk
+    const int tid = threadIdx.x, lane = tid & 63, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int nct = a.nct;
+    const long long row0 = (long long)blockIdx.x * 32, row = row0 + (lane & 31);
+    const bool row_ok = row < a.rows;
+    float* red = (float*)((char*)lds + nct * CHUNK);                     // [wavefront][group][lane] float4 of one tile of m
+    uint4* op = (uint4*)((char*)red + 16 * 1024);                        // [part][fragment][lane]: the residual's operands
+    if (blockIdx.x == 0 && tid == 0) *a.status = 0;
+
+    // Phi's parts as fragments (pack_phi_fragments_kernel's order)
+    for (int p = tid; p < nct * NF * 64; p += 256) {
+        const int slot = p & 63, f = (p >> 6) % NF, ct = (p >> 6) / NF;
+        const int h = slot >> 5, l = 32 * (f % MT) + ((slot & 31) ^ (4 * h)), j0 = 32 * ct + 16 * (f / MT) + 4 * h;
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int j = j0 + 8 * (q >> 2) + (q & 3);
+            v[q] = l < a.m && j < a.n ? a.Phi[(long long)l * a.n + j] : 0.f;
+        }
+        uint32_t w[3][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) split3(v[2 * q], v[2 * q + 1], w[0][q], w[1][q], w[2][q]);
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+            lds[(ct * CHUNK + s * PLANE) / 16 + f * 64 + slot] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};
+    }
+
+    // This thread's share of the residual: elements 2 half, 2 half + 1 of group g of lane `el`, for every tile of m
+    const int half = tid & 1, el = (tid >> 1) & 31, eh = (tid >> 6) & 1, g0 = tid >> 7;      // groups g0, g0 + 2
+    const long long erow = row0 + el < a.rows ? row0 + el : a.rows - 1;
+    float y[MT][2][2];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const int l = 32 * mt + 8 * (g0 + 2 * k) + 4 * eh + 2 * half + e;
+                y[mt][k][e] = l < a.m ? a.Y[erow * a.ldY + l] : 0.f;
+            }
+    const uint32_t nat16 = frag_slot(lane & 31, lh) * 16;
+    const uint32_t tr8 = ((lane >> 4) & 1) * (MT * 1024) + frag_slot(4 * lh + ((lane & 15) >> 2), lane & 1) * 16 + ((lane >> 1) & 1) * 8;
+
+    f32x16 x[CPW], racc[MT], rcorr[MT];
+    bf16x8 rb[3][NF];
+#pragma unroll
+    for (int i = 0; i < CPW; ++i)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[i][v] = 0.f;
+
+    // residual operands from the partial sums (first: Phi x = 0)
+    auto residual = [&](bool first) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            if (!first) {
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    f32x4 s;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s[e] = racc[mt][4 * g + e] + rcorr[mt][4 * g + e];
+                    *(f32x4*)(red + ((wave * 4 + g) * 64 + lane) * 4) = s;
+                }
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int g = g0 + 2 * k, ln = el + 32 * eh;
+                float r0 = y[mt][k][0], r1 = y[mt][k][1];
+                if (!first) {
+                    float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const float2 p = *(const float2*)(red + ((w * 4 + g) * 64 + ln) * 4 + 2 * half);
+                        s0 += p.x; s1 += p.y;
+                    }
+                    r0 -= s0; r1 -= s1;
+                }
+                uint32_t w[3];
+                split3(r0, r1, w[0], w[1], w[2]);
+#pragma unroll
+                for (int s = 0; s < 3; ++s) ((uint32_t*)(op + (s * NF + 2 * mt + (g >> 1)) * 64 + ln))[(g & 1) * 2 + half] = w[s];
+            }
+            __syncthreads();
+        }
+#pragma unroll
+        for (int s = 0; s < 3; ++s)
+#pragma unroll
+            for (int f = 0; f < NF; ++f) rb[s][f] = __builtin_bit_cast(bf16x8, op[(s * NF + f) * 64 + lane]);
+    };
+
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+    typedef __attribute__((address_space(3))) const char* lds_bytes_t;
+    const lds_bytes_t base = (lds_bytes_t)(lds_ptr_t)lds;
+    auto read_t = [&](uint32_t off) {      // a fragment of Phi^T
+        const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(base + off));
+        const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(base + off + 128));
+        return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+    // one product: five smaller ones into `corr`, the large one into `acc`
+    auto product = [](const bf16x8 (&p)[3], const bf16x8& q0, const bf16x8& q1, const bf16x8& q2, f32x16& acc, f32x16& corr) {
+        corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[2], q0, corr, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[0], q0, acc, 0, 0, 0);
+        corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[0], q2, corr, 0, 0, 0);
+        corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[1], q1, corr, 0, 0, 0);
+        corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[1], q0, corr, 0, 0, 0);
+        corr = __builtin_amdgcn_mfma_f32_32x32x16_bf16(p[0], q1, corr, 0, 0, 0);
+    };
+    residual(true);
+    for (int t = 0; t < a.iters; ++t) {
+        const bool last = t + 1 == a.iters;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) racc[mt][v] = rcorr[mt][v] = 0.f;
+#pragma unroll
+        for (int i = 0; i < CPW; ++i) {
+            const int ct = wave + 4 * i;
+            if (ct >= nct) continue;             // uniform
+            const uint32_t chunk = ct * CHUNK;
+            f32x16 u, uc;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) u[v] = uc[v] = 0.f;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                bf16x8 p[3];
+#pragma unroll
+                for (int s = 0; s < 3; ++s) p[s] = read_t(chunk + tr8 + s * PLANE + (f >> 1) * 1024 + (f & 1) * 256);
+                product(p, rb[0][f], rb[1][f], rb[2][f], u, uc);
+            }
+            bf16x8 xp[3][2];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) x[i][v] = soft_threshold(x[i][v] + a.mu * (u[v] + uc[v]), a.theta);
+            if (last) continue;
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                uint32_t w[3][4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) split3(x[i][8 * q + 2 * k], x[i][8 * q + 2 * k + 1], w[0][k], w[1][k], w[2][k]);
+#pragma unroll
+                for (int s = 0; s < 3; ++s) xp[s][q] = __builtin_bit_cast(bf16x8, uint4{w[s][0], w[s][1], w[s][2], w[s][3]});
+            }
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    bf16x8 p[3];
+#pragma unroll
+                    for (int s = 0; s < 3; ++s)
+                        p[s] = __builtin_bit_cast(bf16x8, lds[(chunk + nat16 + s * PLANE + (q * MT + mt) * 1024) / 16]);
+                    product(p, xp[0][q], xp[1][q], xp[2][q], racc[mt], rcorr[mt]);
+                }
+        }
+        if (!last) residual(false);
+    }
+    if (!row_ok) return;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        const int ct = wave + 4 * i;
+        if (ct >= nct) continue;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int col = 32 * ct + 8 * g + 4 * lh;
+            if (a.Xs && col < a.ldS)             // (ldS is a multiple of 8, less than 32 beyond n)
+                *(f32x4*)(a.Xs + row * a.ldS + col) = f32x4{x[i][4 * g], x[i][4 * g + 1], x[i][4 * g + 2], x[i][4 * g + 3]};
+            if (a.Xout) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (col + e < a.n) a.Xout[row * (long long)a.n + col + e] = x[i][4 * g + e];
+            }
+        }
+    }
 }
 
 }  // namespace csat

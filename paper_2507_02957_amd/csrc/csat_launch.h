@@ -8,6 +8,7 @@ namespace csat {
 
 struct IstaFusedArgs;
 struct IstaResidentArgs;
+struct IstaResidentF32Args;
 struct AttentionArgs;
 struct AttentionZArgs;
 
@@ -31,6 +32,7 @@ CSAT_DECLARE_FUSED(16)
 #define CSAT_DECLARE_RESIDENT(MT_, NCT_) hipError_t ista_resident_launch_##MT_##_##NCT_(const IstaResidentArgs& a, unsigned grid, hipStream_t st);
 CSAT_RESIDENT_INSTANCES(CSAT_DECLARE_RESIDENT)
 #undef CSAT_DECLARE_RESIDENT
+hipError_t ista_resident_f32_launch(int MT, const IstaResidentF32Args& a, unsigned grid, hipStream_t st);
 
 // Compressed attention in one kernel (csat_attention.h) for mt_total tiles of m; `single`: all of K~ is kept in
 // registers and LDS at once.  One function per element type and per "with the output product", defined by

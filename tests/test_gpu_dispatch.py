@@ -164,3 +164,34 @@ def test_float_products_keep_float_precision(m, n, d, options):
     Ko = p.measure()[0]
     assert torch.equal(Kc.isnan(), Ko.isnan()) and torch.equal(Kc.isposinf(), Ko.isposinf()) and torch.equal(Kc.isneginf(), Ko.isneginf())
     assert Ko.isinf().any() and Ko.isnan().any()
+
+
+# (n_q, n, m, iterations, in LDS): chunks per wavefront below, at and beyond one, idle wavefronts, one to four tiles of m,
+# the largest Phi that fits and the first that does not, ragged rows, unaligned n
+FLOAT_RESIDENT_CASES = [(33, 40, 8, 2, True), (32, 128, 32, 5, True), (50, 131, 64, 4, True), (64, 160, 128, 3, True), (7, 161, 128, 3, False),
+                        (40, 224, 96, 3, True), (31, 225, 96, 2, False), (70, 350, 64, 3, True), (20, 353, 64, 3, False), (33, 736, 32, 3, True),
+                        (20, 737, 32, 2, False), (96, 97, 97, 6, True), (40, 128, 64, 1, False), (1, 20, 20, 3, True)]
+
+
+@pytest.mark.parametrize("n_q,n,m,iters,resident", FLOAT_RESIDENT_CASES)
+def test_float_decoder_with_phi_in_lds(n_q, n, m, iters, resident):
+    """Small float problems in one launch: codes, support and context against the oracle, forward and stage call."""
+    w = _small("f32_resident", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="f32", iters=iters, lam=0.01)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    C, _, X = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() == (5 if resident else -1)
+    assert csat.csat_decoder_status(p.ws) == 0
+    ref = orc.forward(Q, K, V, Phi, w.lam, mu, iters)
+    assert_close("X", to_np(X), ref["X"], TOL["f32"])
+    assert_close("C", to_np(C), ref["C"], TOL["f32"])
+    _support_check(w.name, to_np(X), ref, mu * w.lam)
+    Y = to_dev(ref["A"].astype(np.float32), "f32")
+    Xr, Cr = p.empty(p.BH, n_q, n, dtype=torch.float32), p.empty(p.BH, n_q, w.d)
+    p.ws.fill_(0xFF)
+    csat.csat_recover(p.dims, Y, p.Phi, w.lam, mu, iters, Xr, p.V, Cr, p.ws)
+    torch.cuda.synchronize()
+    assert_close("X (stage call)", to_np(Xr), ref["X"], TOL["f32"])
+    assert_close("C (stage call)", to_np(Cr), ref["C"], TOL["f32"])

@@ -266,8 +266,7 @@ bool decoder_options_free() {
 bool decoder_is_resident(const Workspace& w) {
     return decoder_options_free() && w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
 }
-// ... and its float form.  (A row with an infinite y: all NaN from the second iteration on, whichever decoder runs; after
-// a single iteration the parts would give NaN where float products give infinities, so that goes to those.)
+// ... and its float form.  (One iteration is one product: nothing to keep in LDS.)
 bool decoder_is_resident_f32(const csat_dims& d, const Workspace& w, int iters) {
     return d.dtype == CSAT_F32 && iters >= 2 && decoder_options_free() && gemm_choice() != 1 && ista_resident_f32_chunks(w.MT, w.nct) != 0;
 }
@@ -359,11 +358,20 @@ csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi
             return launch_gemm_big<Epi>(gb, n_cover, batch, epi, st);
         }
     }
+    if (n_cover <= 64) return launch_gemm<T, 128, 64, 2, 2, Epi>(g, n_cover, batch, epi, st);
+    return launch_gemm<T, 128, 128, 2, 2, Epi>(g, n_cover, batch, epi, st);
+}
+
+// The ISTA decoder's products and its synthesis: in float, on the bf16 matrix cores (csat_gemm_f32.h).  The measurement,
+// the output product, the unrolled decoder's layers and matching pursuit's correlations stay on the float MFMA: no
+// case spends its time on the first two, and what the last two amplify (a layer's S is not a contraction; a pick is a
+// comparison) would move their outputs further than two correct float implementations are allowed to differ.
+template <typename T, typename Epi>
+csat_status decoder_gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
         if (gemm_choice() != 1) return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
     }
-    if (n_cover <= 64) return launch_gemm<T, 128, 64, 2, 2, Epi>(g, n_cover, batch, epi, st);
-    return launch_gemm<T, 128, 128, 2, 2, Epi>(g, n_cover, batch, epi, st);
+    return gemm<T>(g, n_cover, batch, epi, st);
 }
 
 template <typename TI, typename TO>
@@ -923,7 +931,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
                 CSAT_TRY(launch_gemm_big(g, w.ldm, 1, er, st));
             } else {
                 EpiResidual<T> er{Y, ldY, (T*)w.R, w.ldm, rows, d.m};
-                CSAT_TRY((gemm<T>(g, w.ldm, 1, er, st)));
+                CSAT_TRY((decoder_gemm<T>(g, w.ldm, 1, er, st)));
             }
         }
         GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
@@ -937,7 +945,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         }
         EpiIstaUpdate eu{w.Xs, kBf16 ? w.Xb : nullptr, w.ldn, (t == iters - 1) ? Xout : nullptr,
                          mu, theta, rows, d.n, t == 0};
-        CSAT_TRY((gemm<T>(g, w.ldn, 1, eu, st)));
+        CSAT_TRY((decoder_gemm<T>(g, w.ldn, 1, eu, st)));
     }
     return CSAT_OK;
 }
@@ -975,7 +983,7 @@ csat_status run_synthesis(const csat_dims& d, const Workspace& w, T* C, hipStrea
                w.VT, w.ldn, (long long)d.d * w.ldn, d.n_q, d.d, d.n, 0};
     EpiStore<T> ec{C, d.d, (long long)d.n_q * d.d, nullptr, 0, 0, 1.f, d.n_q, d.d};
     Timed tm(w, CSAT_K_SYNTHESIS, st);
-    return gemm<T>(g, d.d, BH, ec, st);
+    return decoder_gemm<T>(g, d.d, BH, ec, st);
 }
 
 template <typename T>

@@ -258,6 +258,39 @@ constexpr int ista_resident_f32_chunks(int MT, int nct) {
     return MT == 1 ? (c <= 3 ? 3 : 6) : MT == 2 ? 3 : 2;
 }
 
+// One tile in plain float arithmetic: infinities and NaN then come out as the float products give them (EpiIstaUpdate's
+// threshold turns a NaN into 0).  The residuals are in LDS (32 x m floats), the iterate where the result goes.
+static __device__ __noinline__ void resident_f32_plain(const IstaResidentF32Args& a, long long row0, float* r, int tid) {
+    const int rows = a.rows - row0 < 32 ? (int)(a.rows - row0) : 32;
+    float* X = a.Xs ? a.Xs + row0 * a.ldS : a.Xout + row0 * a.n;
+    const long long ld = a.Xs ? a.ldS : a.n;
+    for (int i = tid; i < rows * a.n; i += 256) X[(i / a.n) * ld + i % a.n] = 0.f;
+    for (int i = tid; i < rows * (int)(ld - a.n); i += 256) X[(i / (ld - a.n)) * ld + a.n + i % (ld - a.n)] = 0.f;
+    for (int t = 0; t < a.iters; ++t) {
+        __syncthreads();
+        for (int i = tid; i < rows * a.m; i += 256) {
+            const int q = i / a.m, l = i % a.m;
+            float s = 0.f;
+            if (t > 0)
+                for (int j = 0; j < a.n; ++j) s += a.Phi[(long long)l * a.n + j] * X[q * ld + j];
+            r[i] = a.Y[(row0 + q) * a.ldY + l] - s;
+        }
+        __syncthreads();
+        for (int i = tid; i < rows * a.n; i += 256) {
+            const int q = i / a.n, j = i % a.n;
+            float s = 0.f;
+            for (int l = 0; l < a.m; ++l) s += a.Phi[(long long)l * a.n + j] * r[q * a.m + l];
+            float u = a.mu * s;
+            if (t > 0) u += X[q * ld + j];
+            const float b = fabsf(u) - a.theta;
+            X[q * ld + j] = b > 0.f ? copysignf(b, u) : 0.f;
+        }
+    }
+    __syncthreads();
+    if (a.Xs && a.Xout)
+        for (int i = tid; i < rows * a.n; i += 256) a.Xout[row0 * a.n + i] = X[(i / a.n) * ld + i % a.n];
+}
+
 template <int MT, int CPW>
 __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF32Args a) {
     extern __shared__ uint4 lds[];
@@ -271,6 +304,7 @@ __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF
     uint4* op = (uint4*)((char*)red + 16 * 1024);                        // [part][fragment][lane]: the residual's operands
     if (blockIdx.x == 0 && tid == 0) *a.status = 0;
 
+    bool special = false;          // an input that is not finite, or so large that its parts or sums may not be
     // Phi's parts as fragments (pack_phi_fragments_kernel's order)
     for (int p = tid; p < nct * NF * 64; p += 256) {
         const int slot = p & 63, f = (p >> 6) % NF, ct = (p >> 6) / NF;
@@ -280,6 +314,7 @@ __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF
         for (int q = 0; q < 8; ++q) {
             const int j = j0 + 8 * (q >> 2) + (q & 3);
             v[q] = l < a.m && j < a.n ? a.Phi[(long long)l * a.n + j] : 0.f;
+            special |= !(fabsf(v[q]) <= 1e18f);
         }
         uint32_t w[3][4];
 #pragma unroll
@@ -301,7 +336,19 @@ __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF
             for (int e = 0; e < 2; ++e) {
                 const int l = 32 * mt + 8 * (g0 + 2 * k) + 4 * eh + 2 * half + e;
                 y[mt][k][e] = l < a.m ? a.Y[erow * a.ldY + l] : 0.f;
+                special |= !(fabsf(y[mt][k][e]) <= 1e18f);
             }
+    // (the vote goes through `red`: the compiler's own would need LDS beyond the 160 KB that the largest instance fills)
+    if (tid == 0) *(volatile int*)red = 0;
+    __syncthreads();
+    if (special) *(volatile int*)red = 1;
+    __syncthreads();
+    const bool plain = *(volatile int*)red != 0;
+    __syncthreads();
+    if (plain) {
+        resident_f32_plain(a, row0, (float*)lds, tid);
+        return;
+    }
     const uint32_t nat16 = frag_slot(lane & 31, lh) * 16;
     const uint32_t tr8 = ((lane >> 4) & 1) * (MT * 1024) + frag_slot(4 * lh + ((lane & 15) >> 2), lane & 1) * 16 + ((lane >> 1) & 1) * 8;
 

@@ -137,33 +137,45 @@ def test_decoder_with_phi_in_lds(n_q, n, m, iters, kernel, options):
     assert same
 
 
-# (m, n, d): rows around the 128-row tile, columns around the 64-wide one, contractions around a step of 32 and shorter
-FLOAT_PRODUCTS = [(127, 130, 64), (128, 160, 72), (129, 131, 8), (5, 6, 8), (257, 1056, 128), (33, 33, 136), (1, 31, 64), (200, 4099, 40)]
+# (rows, n, m): rows around the 128-row tile, columns around the 64-wide one, contractions around a step of 32 and shorter
+FLOAT_PRODUCTS = [(127, 130, 96), (128, 64, 64), (129, 65, 33), (5, 9, 8), (257, 1056, 130), (33, 33, 31), (1, 31, 1), (1025, 1099, 1000)]
 
 
-@pytest.mark.parametrize("m,n,d", FLOAT_PRODUCTS)
-def test_float_products_keep_float_precision(m, n, d, options):
-    """Float products run as six bf16 ones over the operands' three parts.  Bound per element: parts and dropped products
-    2^-25 of sum |a b|, one rounding (2^-24) of a partial sum per 16 of K and one per workgroup end."""
-    w = _small("f32_products", B=1, H=3, n_q=4, n=n, d=d, m=m, dtype="f32")
+@pytest.mark.parametrize("rows,n,m", FLOAT_PRODUCTS)
+def test_float_products_keep_float_precision(rows, n, m, options):
+    """The float decoder's products run as six bf16 ones over the operands' three parts.  One iteration without a
+    threshold is X = mu Phi^T y, and C = X V.  Bound per element: parts and dropped products 2^-25 of sum |a b|, one
+    rounding (2^-24) of a partial sum per 16 of the contraction and three at the end; 2^-23 for the iterate itself."""
+    w = _small("f32_products", B=1, H=1, n_q=rows, n=n, d=64, m=m, dtype="f32", iters=1)
     Q, K, V = gen.make_qkv(w)
     Phi = gen.make_workload_phi(w)
     p = _problem(w, Q, K, V, Phi)
-    Kc, Vc = (to_np(t).astype(np.float64) for t in p.measure())
-    P = Phi.astype(np.float64)
-    for got, X in ((Kc, K), (Vc, V)):
-        X = X.reshape(-1, n, d).astype(np.float64)
-        bound = (2.0 ** -25 + 2.0 ** -24 * (n / 16 + 3)) * (np.abs(P) @ np.abs(X))
-        assert (np.abs(got.reshape(-1, m, d) - P @ X) <= bound).all()
+    Y = np.random.default_rng(rows).standard_normal((rows, m)).astype(np.float32)
+    X, C = p.empty(1, rows, n, dtype=torch.float32), p.empty(1, rows, w.d)
+
+    def decode(y):
+        p.ws.fill_(0xFF)
+        csat.csat_recover(p.dims, to_dev(y, "f32"), p.Phi, 0.0, 0.5, 1, X, p.V, C, p.ws)
+        return X.clone(), C.clone()
+
+    def bound(k):
+        return 2.0 ** -25 + 2.0 ** -24 * (k / 16 + 3)
+
+    Xg, Cg = (to_np(t)[0].astype(np.float64) for t in decode(Y))
+    P, V64 = Phi.astype(np.float64), V.reshape(n, w.d).astype(np.float64)
+    want = 0.5 * (Y.astype(np.float64) @ P)
+    slack = (bound(m) + 2.0 ** -23) * 0.5 * (np.abs(Y) @ np.abs(P))
+    assert (np.abs(Xg - want) <= slack).all()
+    assert (np.abs(Cg - Xg @ V64) <= bound(n) * (np.abs(Xg) @ np.abs(V64))).all()
     # infinities, NaN and the largest floats come out as the float MFMA has them
-    Kx = K.copy().reshape(-1, n, d)
-    Kx[0, n // 2, 1], Kx[0, 0, 3], Kx[1, n - 1, 2], Kx[2, n // 3, 0], Kx[2, 0, 7] = np.inf, -np.inf, np.nan, 3.4e38, 1.0
-    p = _problem(w, Q, Kx.reshape(K.shape), V, Phi)
-    Kc = p.measure()[0].clone()
+    Y[0, 0], Y[rows // 2, m - 1], Y[rows // 3, m // 2], Y[rows - 1, 0] = np.inf, -np.inf, 3.4e38, np.nan
+    Xg, Cg = decode(Y)
     options("gemm", 1)
-    Ko = p.measure()[0]
-    assert torch.equal(Kc.isnan(), Ko.isnan()) and torch.equal(Kc.isposinf(), Ko.isposinf()) and torch.equal(Kc.isneginf(), Ko.isneginf())
-    assert Ko.isinf().any() and Ko.isnan().any()
+    Xo, Co = decode(Y)
+    for got, old in ((Xg, Xo), (Cg, Co)):
+        same = torch.equal(got.isnan(), old.isnan()) and torch.equal(got.isposinf(), old.isposinf()) and torch.equal(got.isneginf(), old.isneginf())
+        assert same
+    assert rows == 1 or Xo.isinf().any()
 
 
 # (n_q, n, m, iterations, in LDS): chunks per wavefront below, at and beyond one, idle wavefronts, one to four tiles of m,
@@ -174,7 +186,7 @@ FLOAT_RESIDENT_CASES = [(33, 40, 8, 2, True), (32, 128, 32, 5, True), (50, 131, 
 
 
 @pytest.mark.parametrize("n_q,n,m,iters,resident", FLOAT_RESIDENT_CASES)
-def test_float_decoder_with_phi_in_lds(n_q, n, m, iters, resident):
+def test_float_decoder_with_phi_in_lds(n_q, n, m, iters, resident, options):
     """Small float problems in one launch: codes, support and context against the oracle, forward and stage call."""
     w = _small("f32_resident", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="f32", iters=iters, lam=0.01)
     Q, K, V = gen.make_qkv(w)
@@ -195,3 +207,17 @@ def test_float_decoder_with_phi_in_lds(n_q, n, m, iters, resident):
     torch.cuda.synchronize()
     assert_close("X (stage call)", to_np(Xr), ref["X"], TOL["f32"])
     assert_close("C (stage call)", to_np(Cr), ref["C"], TOL["f32"])
+    # a NaN, infinities and a huge value in y: what the float products make of them
+    Y[0, 0, 0], Y[1, n_q // 2, m - 1], Y[2, n_q - 1, m // 2], Y[3, 0, 0] = float("inf"), float("-inf"), float("nan"), 1e30
+    out = []
+    for gemm in (0, 1):
+        options("gemm", gemm)
+        csat.csat_recover(p.dims, Y, p.Phi, w.lam, mu, iters, Xr, p.V, Cr, p.ws)
+        torch.cuda.synchronize()
+        out.append((Xr.clone(), Cr.clone()))
+    for got, old in zip(*out):
+        same = torch.equal(got.isnan(), old.isnan()) and torch.equal(got.isinf(), old.isinf())
+        assert same
+        fine = old.isfinite()
+        rows_ok = fine.all(-1) & (old.abs().amax(-1) < 1e20)
+        assert_close("finite rows", to_np(got[rows_ok]), to_np(old[rows_ok]), TOL["f32"])

@@ -261,7 +261,7 @@ csat_status csat_profile_read(void* ctx, int kernel_id, double* total_ms, int* l
 /* Which kernel the last ISTA decoder call on this context launched (for the benchmark's kernel names):
  * -1 not the fused decoder (or no decoder call yet); fused decoder, one chunk per step: 0 dense state, 1 sparse
  * state, 2 one 32-row tile per workgroup; two chunks per step: 3 dense state, 4 sparse state; 5 the decoder for
- * small problems, Phi in LDS and the iterate in registers. */
+ * small problems, Phi in LDS and the iterate in registers; 6 one 32-row tile shared by eight wavefronts. */
 csat_status csat_profile_decoder_kernel(void* ctx, int* kernel);
 
 /* Measurement (section 3, K~ = Phi K, V~ = Phi V) for the same structured Phi, by transforms: one Walsh-Hadamard

@@ -3,6 +3,7 @@
 #include "csat.h"
 #include "csat_kernels.h"
 #include "csat_ista_fused.h"
+#include "csat_ista_coop.h"
 #include "csat_ista_resident.h"
 #include "csat_omp.h"
 #include "csat_fwht.h"
@@ -777,6 +778,13 @@ int fused_segments(long long groups, int iters, int cus, double overhead) {
 int fused_variant(int MT, long long rows_pad, int nct) {
     const int cus = cu_count();
     // few rows: one 32-row tile per workgroup, so that every tile has a CU of its own
+    // Few rows: eight wavefronts share a tile, one tile per CU at a time (csat_ista_coop.h).  A CU's 128-row group takes
+    // about as long as two such tiles at thirteen tiles of m (0.59 against 1.08 us a chunk) and as three at three (0.24
+    // against 0.7), so the line is at one tile per CU, two up to four tiles of m.  Measured, forward of 10 iterations:
+    // m = 392, 300 tiles 682 against 631 us on groups; m = 192, 256 tiles 190 against 202 (with a single wavefront per
+    // tile), 512 tiles 334 against 329; m = 90, 384 tiles 195 against 285, 512 tiles 234 against 312; m = 40, 304 tiles
+    // 114 against 182, 608 tiles 207 against 190.
+    if (decoder_options_free() && MT <= kCoopMaxMT && rows_pad / 32 <= (MT <= 4 ? 2 : 1) * cus) return 6;
     const bool thin = rows_pad / 32 <= cus && (*tl_opt)[CSAT_OPT_FUSED_THIN] != 1;      // (14 tiles of m and more: only when forced)
     int variant = thin ? 2 : (sparse_state((size_t)rows_pad * nct * 32 * 4) ? 1 : 0);
     // 128-row workgroups on rows of at least five chunks and three tiles of m: two chunks per step (the schedule
@@ -791,7 +799,8 @@ int fused_variant(int MT, long long rows_pad, int nct) {
 // 32-row tiles per head, and V's fragments must fit the buffer of V^T they replace.
 bool synthesis_in_decoder(const csat_dims& d, const Workspace& w) {
     if (!w.fused || decoder_is_resident(w) || d.dtype != CSAT_BF16 || d.d != 64 || d.n_q % 32 != 0 || (*tl_opt)[CSAT_OPT_SYNTHESIS] >= 1) return false;
-    if (fused_variant(w.MT, w.rows_pad, w.nct) < 3) return false;
+    const int v = fused_variant(w.MT, w.rows_pad, w.nct);
+    if (v != 3 && v != 4) return false;
     return (long long)((w.nct + 1) / 2 * 2) * 32 <= w.ldn;
 }
 
@@ -813,9 +822,9 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     const int cus = cu_count();
     const int variant = fused_variant(MT, rows_pad, a.nct);
     const bool thin = variant == 2;
-    a.groups = (int)(rows_pad / (thin ? 32 : 128));
+    a.groups = variant == 6 ? (int)((a.rows + 31) / 32) : (int)(rows_pad / (thin ? 32 : 128));
     const int nct_real = a.nct;
-    if (variant >= 3) a.nct = (a.nct + 1) / 2 * 2;
+    if (variant >= 3 && variant != 6) a.nct = (a.nct + 1) / 2 * 2;
     // A dense-ish iterate larger than the Infinity Cache streams through once per iteration: its accesses carry the
     // non-temporal hint on the one-chunk schedule (cross_modal: 7.97 -> 7.30 ms per launch; nothing to gain where the
     // iterate is sparse or cache-resident).  CSAT_OPT_STATE + 4 / + 8: always / never.
@@ -827,13 +836,13 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     // The two-chunk kernel cuts the group-iterations of the launch into one equal share per CU instead (each group cut
     // at most once; see the kernel), unless a segment count is asked for.
     a.tape = 0;
-    if (variant >= 3 && a.groups > cus) a.tape = cus;
+    if (variant >= 3 && variant != 6 && a.groups > cus) a.tape = cus;
     if (const int v = (*tl_opt)[CSAT_OPT_FUSED_SEGMENTS]; v >= 1 && v <= a.iters) { a.segs = v; a.tape = 0; }
     else if (v < 0 && variant >= 3) a.tape = -v < a.groups ? -v : a.groups;       // (tests: shares on small launches)
     if ((*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] != 0) a.spin_limit = (*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] < 0 ? 0 : (*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT];
     // (a.sync was cleared together with the status word: run_ista)
     const long long units = a.tape > 0 ? a.tape : (long long)a.groups * a.segs;
-    const unsigned grid = (unsigned)(units < cus ? units : cus);
+    const unsigned grid = (unsigned)(variant == 6 ? a.groups : units < cus ? units : cus);
     *tl_decoder_kernel = variant;
     switch (MT) {
 #define CSAT_FUSED_CASE(N) case N: HIP_TRY(ista_fused_launch_mt##N(variant, a, grid, st)); return CSAT_OK;
@@ -1063,7 +1072,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
     bool y_tiled = false;
     if constexpr (sizeof(T) == 2) {
         y_tiled = iters > 0 && w.fused && !decoder_is_resident(w) && d.n_q % 32 == 0 && (*tl_opt)[CSAT_OPT_Y_LAYOUT] != 1 &&
-                  fused_variant(w.MT, w.rows_pad, w.nct) >= 3 && attention_is_fused<T>(d, w, true) &&
+                  (fused_variant(w.MT, w.rows_pad, w.nct) == 3 || fused_variant(w.MT, w.rows_pad, w.nct) == 4) && attention_is_fused<T>(d, w, true) &&
                   attention_single_sweep(w.MT, 2 * ((d.d + 15) / 16)) &&
                   (v_packed || (!need_z && attention_mtp(w.MT, true) == 13));
     }

@@ -1,0 +1,267 @@
+// Fused ISTA decoder (bf16, m <= 416) for launches with few rows: the eight wavefronts of a workgroup share one 32-row
+// tile.  The arithmetic is ista_fused_kernel's, product by product in the same order (same bits); what is shared out:
+//   wavefronts 0, 1   GEMM-U and the threshold of the even and the odd chunks (a chunk's U is one accumulator chain, so
+//                     it stays with one wavefront and takes two steps; consecutive chunks overlap by one)
+//   wavefronts 2, 3   GEMM-R of every chunk, each for its half of the tiles of m (independent accumulators)
+//   wavefronts 4 - 7  stage the packed chunks, global -> LDS (a wavefront is held while its requests drain)
+// A step is one chunk: U's first part of chunk c, U's second part and threshold of chunk c - 1, R of chunk c - 2, while
+// chunk c + 2 is being requested; five ring slots.  The iterate goes from the U to the R wavefronts as bf16 operands
+// through LDS (2 KB per chunk), the next residual back once per iteration through a ring slot that is free then.
+//
+// Why: on the one-tile form of ista_fused_kernel a single wavefront did all the products, 52 MFMAs per chunk at
+// m = 392 (1664 cycles; with the threshold and the waits 1.08 us a chunk), on one of the CU's four matrix pipes.  Here
+// a chunk takes 0.13 + 0.035 us per tile of m: what grows with m is the 2 KB per tile that the CU pulls from L2 (about
+// 32 bytes a clock) and the 6 KB it moves in LDS; the rest is the step's barrier, the ramp of the fragment reads and
+// the threshold.  Column-wise short_video (96 tiles, m = 392, 20 iterations): 1106 -> 600 us a launch, 1260 -> 750 us a
+// call; 3330 rows of n = 1571, m = 197: 800 -> 520 us a call.  (U's first part as a half or five sixths: equal, 4 % slower.)
+#pragma once
+#include "csat_ista_fused.h"
+
+namespace csat {
+
+constexpr int kCoopSlots = 5;
+constexpr int kCoopMaxMT = 13;
+constexpr size_t ista_coop_lds_bytes(int MT) { return (size_t)kCoopSlots * ista_fused_set_frags(MT) * 1024 + 4096; }
+
+template <int MT>
+__global__ __launch_bounds__(512, 1) void ista_coop_kernel(IstaFusedArgs a) {
+    extern __shared__ uint4 lds[];
+    constexpr int NF = 2 * MT, SETF = ista_fused_set_frags(MT), FW = SETF / 4, SLOT = SETF * 1024;
+    constexpr int G = 2, D = 2;                        // fragments per LDS wait, groups of them on the way (3, 4: up to 5 % slower)
+    constexpr int OFF_X = kCoopSlots * SLOT;           // two buffers of x operands, 2 KB each
+    constexpr int RT = (MT + 1) / 2;                   // tiles of m per R wavefront (tile 2 j + its index)
+    // fragments of U's first part: about as long as the rest with the threshold behind it
+    constexpr int H = MT <= 3 ? NF : (NF * 2 / 3 + 1) / 2 * 2;
+    const int lane = threadIdx.x & 63, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nct = a.nct, iters = a.iters;
+    const long long rt = blockIdx.x, row = rt * 32 + (lane & 31);
+    const bool row_ok = row < a.rows;
+    const float* yrow = a.Y + (row_ok ? row : a.rows - 1) * a.ldy + 4 * lh;
+    const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)lds;
+    auto barrier = [&]() {       // LDS writes of this wavefront done; loads from memory stay in flight
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    auto next = [](int s, int by) { s += by; return s >= kCoopSlots ? s - kCoopSlots : s; };
+    // Every wavefront walks the same steps: iterations 0 .. iters - 2 have nct + 2 of them, the last one nct + 1.
+    // k: ring slot of the iteration's chunk 0.
+
+    if (wave >= 4) {             // ---- staging ----
+        auto issue = [&](int c, int slot) {
+            const uint4* src = a.PhiPack + ((long long)c * SETF + (wave - 4) * FW) * 64 + lane;
+            char* dst = (char*)lds + slot * SLOT + (wave - 4) * FW * 1024;
+#pragma unroll
+            for (int i = 0; i < FW; ++i) __builtin_amdgcn_global_load_lds((glb_ptr_t)(src + i * 64), (lds_ptr_t)(dst + i * 1024), 16, 0, 0);
+        };
+        issue(0, 0);
+        issue(1, 1);
+        asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FW) : "memory");
+        barrier();
+        int k = 0;
+        for (int t = 0; t < iters; ++t) {
+            const bool last = t + 1 == iters;
+            int s = next(k, 2);                                   // slot of chunk c + 2
+            for (int c = 0; c < nct + (last ? 1 : 2); ++c) {
+                const int cn = c + 2 < nct ? c + 2 : c + 2 - nct; // (beyond the end: the next iteration's first two)
+                const bool want = c + 2 < nct || (!last && c < nct);
+                if (want) issue(cn, s);
+                s = next(s, 1);
+                if (want) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(FW) : "memory");     // chunk c + 1 has landed
+                else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                barrier();
+            }
+            k = (k + nct) % kCoopSlots;
+        }
+        return;
+    }
+
+    if (wave >= 2) {             // ---- GEMM-R ----
+        const int rw = wave - 2;
+        const uint32_t nat16 = lds0 + rw * 1024 + frag_slot(lane & 31, lh) * 16;
+        f32x16 racc[RT];
+        barrier();
+        int k = 0;
+        for (int t = 0; t + 1 < iters; ++t) {
+#pragma unroll
+            for (int j = 0; j < RT; ++j) {
+                const int mt = 2 * j + rw < MT ? 2 * j + rw : 0;  // (an odd count's missing tile: computed on, never used)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const f32x4 y4 = *(const f32x4*)(yrow + 32 * mt + 8 * g);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) racc[j][4 * g + e] = y4[e];
+                }
+            }
+            barrier();
+            barrier();
+            int s = k;
+            for (int c = 0; c < nct; ++c) {                       // step c + 2
+                const uint32_t base = nat16 + s * SLOT, xa = lds0 + OFF_X + (c & 1) * 2048 + lane * 16;
+                u32x4 x0, x1, fr[D][G];
+                lds_read16<0>(x0, xa);
+                lds_read16<1024>(x1, xa);
+                constexpr int NR = 2 * RT, NG = NR / G;
+                auto fetch_group = [&](auto kc) {
+                    constexpr int q = decltype(kc)::value, f = q * G;
+                    if constexpr (f < NR) {
+                        lds_read16<((f / RT) * MT + 2 * (f % RT)) * 1024>(fr[q % D][0], base);
+                        lds_read16<(((f + 1) / RT) * MT + 2 * ((f + 1) % RT)) * 1024>(fr[q % D][1], base);
+                    }
+                };
+                auto run = [&](auto self, auto kc) {
+                    constexpr int q = decltype(kc)::value;
+                    if constexpr (q < NG) {
+                        fetch_group(std::integral_constant<int, q + D - 1>{});
+                        lds_wait_n<G * (NG - 1 - q < D - 1 ? NG - 1 - q : D - 1)>();
+                        if constexpr (q == 0) { lds_pin(x0); lds_pin(x1); }
+#pragma unroll
+                        for (int i = 0; i < G; ++i) lds_pin(fr[q % D][i]);
+#pragma unroll
+                        for (int i = 0; i < G; ++i) {
+                            const int f = q * G + i;
+                            racc[f % RT] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[q % D][i]),
+                                                                                   __builtin_bit_cast(bf16x8, f < RT ? x0 : x1), racc[f % RT], 0, 0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                        self(self, std::integral_constant<int, q + 1>{});
+                    }
+                };
+                fetch_group(std::integral_constant<int, 0>{});
+                run(run, std::integral_constant<int, 0>{});
+                if (c + 1 == nct) {                               // the residual's operands, for the U wavefronts
+                    uint4* op = lds + (next(next(k, nct % kCoopSlots), 3) * SLOT) / 16 + lane;
+#pragma unroll
+                    for (int j = 0; j < RT; ++j)
+                        if (2 * j + rw < MT) {
+                            op[(2 * (2 * j + rw)) * 64] = __builtin_bit_cast(uint4, cvt8<0>(racc[j], 1.f));
+                            op[(2 * (2 * j + rw) + 1) * 64] = __builtin_bit_cast(uint4, cvt8<8>(racc[j], 1.f));
+                        }
+                }
+                s = next(s, 1);
+                barrier();
+            }
+            k = (k + nct) % kCoopSlots;
+        }
+        for (int c = 0; c < nct + 1; ++c) barrier();              // last iteration: no residual
+        return;
+    }
+
+    // ---- GEMM-U and threshold ----
+    const uint32_t tr8 = lds0 + ((lane >> 4) & 1) * (MT * 1024) + frag_slot(4 * lh + ((lane & 15) >> 2), lane & 1) * 16 +
+                         ((lane >> 1) & 1) * 8;
+    f32x4* st = (f32x4*)a.state + rt * nct * 256 + lane;
+    bf16x8 rb[NF];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {                             // x = 0: r = y
+        f32x16 r;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f32x4 y4 = *(const f32x4*)(yrow + 32 * mt + 8 * g);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[4 * g + e] = y4[e];
+        }
+        rb[2 * mt] = cvt8<0>(r, 1.f);
+        rb[2 * mt + 1] = cvt8<8>(r, 1.f);
+    }
+    barrier();
+    f32x16 u;
+    f32x4 old[4];
+    // fragments [F0, F1) of the chunk in `slot` into u
+    auto part = [&](auto f0c, auto f1c, int slot) {
+        constexpr int F0 = decltype(f0c)::value, F1 = decltype(f1c)::value, NG = (F1 - F0 + G - 1) / G;
+        const uint32_t base = tr8 + slot * SLOT;
+        u32x2 ft[D][G][2];
+        auto fetch_group = [&](auto kc) {
+            constexpr int q = decltype(kc)::value, f = F0 + q * G;
+            if constexpr (f < F1) {
+                lds_read8_tr<(f >> 1) * 1024 + (f & 1) * 256>(ft[q % D][0][0], base);
+                lds_read8_tr<(f >> 1) * 1024 + (f & 1) * 256 + 128>(ft[q % D][0][1], base);
+                lds_read8_tr<((f + 1) >> 1) * 1024 + ((f + 1) & 1) * 256>(ft[q % D][1][0], base);
+                lds_read8_tr<((f + 1) >> 1) * 1024 + ((f + 1) & 1) * 256 + 128>(ft[q % D][1][1], base);
+            }
+        };
+        auto run = [&](auto self, auto kc) {
+            constexpr int q = decltype(kc)::value;
+            if constexpr (q < NG) {
+                fetch_group(std::integral_constant<int, q + D - 1>{});
+                lds_wait_n<2 * G * (NG - 1 - q < D - 1 ? NG - 1 - q : D - 1)>();
+                lds_pin(ft[q % D][0][0], ft[q % D][0][1]);
+                lds_pin(ft[q % D][1][0], ft[q % D][1][1]);
+#pragma unroll
+                for (int i = 0; i < G; ++i) {
+                    const u32x4 fa = __builtin_shufflevector(ft[q % D][i][0], ft[q % D][i][1], 0, 1, 2, 3);
+                    u = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa), rb[F0 + q * G + i], u, 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                self(self, std::integral_constant<int, q + 1>{});
+            }
+        };
+        static_assert((F1 - F0) % G == 0, "whole groups");
+        if constexpr (NG > 0) {
+            fetch_group(std::integral_constant<int, 0>{});
+            run(run, std::integral_constant<int, 0>{});
+        }
+    };
+    auto first_part = [&](int c, int slot, bool first) {
+        if (!first) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) old[g] = st[(long long)(c * 4 + g) * 64];
+        } else {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) old[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) u[v] = 0.f;
+        part(std::integral_constant<int, 0>{}, std::integral_constant<int, H>{}, slot);
+    };
+    auto second_part = [&](int c, int slot, bool last) {
+        part(std::integral_constant<int, H>{}, std::integral_constant<int, NF>{}, slot);
+        f32x16 x;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) x[v] = soft_threshold(old[v >> 2][v & 3] + a.mu * u[v], a.theta);
+        if (!last) {
+            uint4* xo = lds + (OFF_X + (c & 1) * 2048) / 16 + lane;
+            xo[0] = __builtin_bit_cast(uint4, cvt8<0>(x, -1.f));
+            xo[64] = __builtin_bit_cast(uint4, cvt8<8>(x, -1.f));
+#pragma unroll
+            for (int g = 0; g < 4; ++g) st[(long long)(c * 4 + g) * 64] = f32x4{x[4 * g], x[4 * g + 1], x[4 * g + 2], x[4 * g + 3]};
+        } else if (row_ok) {
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int col = 32 * c + 8 * g + 4 * lh;
+                if (a.Xb && col < a.ldxb)
+                    *(uint2*)(a.Xb + row * a.ldxb + col) = uint2{f2bf_pk(x[4 * g], x[4 * g + 1]), f2bf_pk(x[4 * g + 2], x[4 * g + 3])};
+                if (a.Xout) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < a.n) a.Xout[row * (long long)a.n + col + e] = x[4 * g + e];
+                }
+            }
+        }
+    };
+    int k = 0;
+    for (int t = 0; t < iters; ++t) {
+        const bool last = t + 1 == iters;
+        if (t > 0) {
+            const uint4* op = lds + (next(k, 3) * SLOT) / 16 + lane;
+#pragma unroll
+            for (int f = 0; f < NF; ++f) rb[f] = __builtin_bit_cast(bf16x8, op[f * 64]);
+        }
+        int s = k;
+        const int steps = nct + (last ? 1 : 2);
+        for (int c = 0; c < steps; ++c) {
+            if ((c & 1) == wave) {
+                if (c < nct) first_part(c, s, t == 0);
+            } else if (c > 0 && c <= nct) {
+                second_part(c - 1, next(s, kCoopSlots - 1), last);
+            }
+            s = next(s, 1);
+            barrier();
+        }
+        k = (k + nct) % kCoopSlots;
+    }
+}
+
+}  // namespace csat

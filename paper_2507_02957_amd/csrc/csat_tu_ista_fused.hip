@@ -1,6 +1,7 @@
 // Translation unit of the fused ISTA decoder for one value of MT (tiles of m): compile with -DCSAT_TU_MT=<1..16>.
 #include "csat_ista_fused.h"
 #include "csat_ista_fused2.h"
+#include "csat_ista_coop.h"
 #include "csat_launch.h"
 
 #ifndef CSAT_TU_MT
@@ -20,6 +21,16 @@ hipError_t CSAT_CAT(ista_fused_launch_mt, CSAT_TU_MT)(int variant, const IstaFus
         hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), lds_bytes, st, a);
         return hipGetLastError();
     };
+    if (variant == 6) {
+        if constexpr (MT <= kCoopMaxMT) {
+            const auto kernel = ista_coop_kernel<MT>;
+            const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)ista_coop_lds_bytes(MT));
+            if (e != hipSuccess) return e;
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(512), ista_coop_lds_bytes(MT), st, a);
+            return hipGetLastError();
+        }
+        return hipErrorInvalidValue;
+    }
     if constexpr (MT >= 3 && MT <= 13) {      // (the two-chunk schedule: three to thirteen tiles of m)
         if (variant == 4) return launch(ista_fused2_kernel<MT, true>);
         if (variant == 3) return launch(ista_fused2_kernel<MT, false>);

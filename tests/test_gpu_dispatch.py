@@ -110,7 +110,7 @@ def test_measurement_with_a_split_contraction(n, m, d, zero_iters, options):
 # largest Phi that fits LDS (80 chunk-tiles) and the first that does not, a ragged last row tile, one iteration
 RESIDENT_CASES = [(33, 65, 8, 3, 5), (31, 96, 33, 4, 5), (70, 97, 96, 3, 5), (64, 160, 129, 2, 5), (40, 161, 160, 3, 5),
                   (97, 224, 224, 2, 5), (50, 225, 200, 3, 5), (129, 288, 256, 1, 5), (33, 289, 192, 3, 5), (32, 384, 161, 2, 5),
-                  (20, 385, 160, 3, 5), (65, 512, 32, 3, 5), (40, 513, 32, 2, 2), (40, 385, 161, 2, 2), (64, 200, 200, 1, 5)]
+                  (20, 385, 160, 3, 5), (65, 512, 32, 3, 5), (40, 513, 32, 2, 6), (40, 385, 161, 2, 6), (64, 200, 200, 1, 5)]
 
 
 @pytest.mark.parametrize("n_q,n,m,iters,kernel", RESIDENT_CASES)
@@ -221,3 +221,32 @@ def test_float_decoder_with_phi_in_lds(n_q, n, m, iters, resident, options):
         fine = old.isfinite()
         rows_ok = fine.all(-1) & (old.abs().amax(-1) < 1e20)
         assert_close("finite rows", to_np(got[rows_ok]), to_np(old[rows_ok]), TOL["f32"])
+
+
+# (n_q, n, m, iterations): the fewest chunks this decoder gets, one to thirteen tiles of m (odd and even), odd and even
+# chunk counts modulo its ring of five, a ragged last chunk and row tile, one and two iterations
+SHARED_TILE_CASES = [(33, 513, 20, 4), (40, 544, 64, 3), (64, 577, 90, 1), (31, 700, 128, 2), (70, 609, 160, 5), (32, 416, 416, 3), (5, 500, 390, 4),
+                     (97, 900, 217, 3), (160, 1600, 392, 2), (33, 353, 300, 6), (20, 330, 330, 2), (45, 1333, 352, 3)]
+
+
+@pytest.mark.parametrize("n_q,n,m,iters", SHARED_TILE_CASES)
+def test_decoder_with_a_tile_shared_by_eight_wavefronts(n_q, n, m, iters, options):
+    """Launches with few rows and a Phi too large for LDS: the bits of the 128-row decoder, and the oracle."""
+    w = _small("shared_tile", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, lam=0.002)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    C, _, X = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() == 6
+    assert csat.csat_decoder_status(p.ws) == 0
+    ref = orc.forward(Q, K, V, Phi, w.lam, mu, iters)
+    assert_close("X", to_np(X), ref["X"], TOL["bf16"])
+    assert_close("C", to_np(C), ref["C"], TOL["bf16"])
+    options("fused_thin", 1)
+    options("synthesis", 1)
+    p.ws.fill_(0xFF)
+    C1, _, X1 = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() in (0, 1, 3, 4)
+    same = torch.equal(X, X1) and torch.equal(C, C1)
+    assert same

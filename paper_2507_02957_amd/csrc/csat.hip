@@ -377,9 +377,9 @@ csat_status decoder_gemm(const GemmArgs& g, long long n_cover, int batch, const 
 
 template <typename TI, typename TO>
 csat_status pack_rows(const TI* src, long long lds_, TO* dst, long long ldd, long long rows, int cols, hipStream_t st) {
-    long long total = rows * ldd;
-    hipLaunchKernelGGL((pack_rows_kernel<TI, TO>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       src, lds_, dst, ldd, rows, cols);
+    const int vec = lds_ % 4 == 0 && ldd % 4 == 0 && reinterpret_cast<uintptr_t>(src) % (4 * sizeof(TI)) == 0 &&
+                    reinterpret_cast<uintptr_t>(dst) % (4 * sizeof(TO)) == 0;
+    hipLaunchKernelGGL((pack_rows_kernel<TI, TO>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, src, lds_, dst, ldd, rows, cols, vec);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
@@ -1297,17 +1297,28 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
         CSAT_TRY((pack_rows<float, float>(Y, d.m, x.Rf, x.mq, rows, d.m, st)));
     }
     for (int it = 0; it < k; ++it) {
-        {   // correlations of every residual with every column
-            GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
-            EpiStoreStream ec{x.Cm, w.ldn, (int)rows, d.n};
+        // correlations of every residual with every column, and each row's largest: in the product's epilogue where the
+        // large-tile kernel runs (EpiOmpBest; the same picks)
+        GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
+        const bool in_product = use_big_gemm<T>(g, d.n);
+        OmpCand* cand = in_product ? (OmpCand*)x.Cm : nullptr;
+        const int nseg = (d.n + 127) / 128;
+        {
             Timed tm(w, CSAT_K_UPDATE, st);
-            CSAT_TRY((gemm<T>(g, d.n, 1, ec, st)));
+            if (in_product) {
+                g.K = (int)round_up(g.K, 64);
+                CSAT_TRY(launch_gemm_big(g, d.n, 1, EpiOmpBest{cand, nseg, x.picks, k, it, rows, d.n}, st));
+            } else {
+                EpiStoreStream ec{x.Cm, w.ldn, (int)rows, d.n};
+                CSAT_TRY((gemm<T>(g, d.n, 1, ec, st)));
+            }
         }
         Timed tm(w, CSAT_K_RESIDUAL, st);
-        hipLaunchKernelGGL(omp_pick_kernel, dim3(row_blocks), dim3(256), 0, st, x.Cm, w.ldn, rows, d.n, x.picks, k, it);
+        if (!in_product)
+            hipLaunchKernelGGL(omp_pick_kernel, dim3(row_blocks), dim3(256), 0, st, x.Cm, w.ldn, rows, d.n, x.picks, k, it);
 #define CSAT_OMP_UPDATE(MQ_)                                                                                              \
-    hipLaunchKernelGGL((omp_update_kernel<T, MQ_>), dim3(row_blocks), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m, x.picks, \
-                       k, it, x.Qb, x.Tri, x.Z, x.Rf, x.mq, (T*)w.R, w.ldm, rows)
+    hipLaunchKernelGGL((omp_update_kernel<T, MQ_>), dim3(row_blocks), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m, cand, nseg, \
+                       x.picks, k, it, x.Qb, x.Tri, x.Z, x.Rf, x.mq, (T*)w.R, w.ldm, rows)
         if (x.mq <= 256) CSAT_OMP_UPDATE(4);
         else if (x.mq <= 512) CSAT_OMP_UPDATE(8);
         else CSAT_OMP_UPDATE(16);

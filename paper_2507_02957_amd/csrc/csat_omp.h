@@ -55,19 +55,107 @@ static __global__ __launch_bounds__(256) void omp_pick_kernel(const float* Cm, l
     if (lane == 0) pk[it] = bi < n ? bi : 0;      // only reachable when every correlation is NaN
 }
 
+// Epilogue of the correlation product on the large-tile GEMM: instead of the correlations, the best column of each row
+// within the wavefront's 128 (largest |c|, lowest index on a tie, earlier picks left out).  The update kernel takes the
+// best of those.  The correlations (491 MB at 76 800 x 1600, m = 392) are neither written nor read back: a pick took
+// 182 us of product and 92 us of search and takes 187 us; what bounds it now is the short contraction, whose seven steps
+// per tile do not cover the tile's start and epilogue.
+struct OmpCand { float val; int idx; };
+struct EpiOmpBest {
+    static constexpr bool kTile = true, kWhole = true;
+    static constexpr int kPitch = 33 * 8;                       // 32 candidates and a pad against bank conflicts
+    static constexpr int kStageBytes = 64 * kPitch + 64 * 16;
+    struct Pre { uint4 ex; };                                   // columns of this block that row r0w + lane may not pick
+    OmpCand* cand; int nseg;                                    // [M][nseg], one per 128 columns
+    const int* picks; int k, it;                                // [M][k], `it` made so far
+    long long M; int N;
+    // (before the main loop: the reads of the earlier picks hide behind the first operands', eight at a time)
+    __device__ __forceinline__ Pre begin(long long r0w, long long c0w, int lane) const {
+        uint32_t ex[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const long long left = N - c0w - 32 * j;
+            ex[j] = left >= 32 ? 0u : left <= 0 ? 0xffffffffu : 0xffffffffu << left;
+        }
+        const long long row = r0w + lane < M ? r0w + lane : M - 1;
+        for (int s0 = 0; s0 < it; s0 += 8) {
+            int p[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) p[s] = picks[row * k + (s0 + s < it ? s0 + s : 0)];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const int q = p[s] - (int)c0w;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ex[j] |= (q >> 5) == j ? 1u << (q & 31) : 0u;
+            }
+        }
+        return Pre{uint4{ex[0], ex[1], ex[2], ex[3]}};
+    }
+    __device__ __forceinline__ void whole(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][4], char* stage,
+                                          const Pre& pre) const {
+        if (r0w >= M || c0w >= N) return;                       // (uniform)
+        const int li = lane & 31, lh = lane >> 5;
+        const long long row = r0w + lane;
+        uint4* mask = (uint4*)(stage + 64 * kPitch);
+        mask[lane] = pre.ex;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int rr = 32 * i + 8 * (v / 4) + 4 * lh + (v % 4);
+                const uint4 e = mask[rr];
+                const uint32_t w[4] = {e.x, e.y, e.z, e.w};
+                OmpCand b{-1.f, 0x7fffffff};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int c = (int)c0w + 32 * j + li;
+                    const float a = (w[j] >> li) & 1u ? -2.f : fabsf(acc[i][j][v]);
+                    if (a > b.val) b = OmpCand{a, c};
+                }
+                *(OmpCand*)(stage + rr * kPitch + li * 8) = b;
+            }
+        OmpCand b{-1.f, 0x7fffffff};
+#pragma unroll
+        for (int q = 0; q < 32; ++q) {
+            const OmpCand o = *(const OmpCand*)(stage + lane * kPitch + q * 8);
+            if (o.val > b.val || (o.val == b.val && o.idx < b.idx)) b = o;
+        }
+        if (row < M) cand[row * nseg + (c0w >> 7)] = b;
+    }
+    __device__ __forceinline__ void flush(long long, long long, int, const char*) const {}
+};
+
 // Adds the picked column to the row's factorisation and updates its residual.
 //   PhiT [n, ldp]   columns of Phi as rows (element type T)
 //   Qb [rows, k, mq]  orthonormal vectors, Tri [rows, k, k] the triangular factor (column `it` written here),
 //   Z [rows, k]  q^T y,  Rf [rows, mq] fp32 residual (in/out),  Rop [rows, ldr] operand copy of it (pads zero)
+// cand [rows, nseg]: the pick is the best of these (EpiOmpBest) and is written to picks here; null: picks holds it.
 // MQ: values of an m-vector per lane, ceil(m / 64) rounded up to 4, 8 or 16.
 template <typename T, int MQ>
-__global__ __launch_bounds__(256) void omp_update_kernel(const T* PhiT, long long ldp, int m, const int* picks, int k, int it,
-                                                         float* Qb, float* Tri, float* Z, float* Rf, int mq, T* Rop,
+__global__ __launch_bounds__(256) void omp_update_kernel(const T* PhiT, long long ldp, int m, const OmpCand* cand, int nseg,
+                                                         int* picks, int k, int it, float* Qb, float* Tri, float* Z, float* Rf, int mq, T* Rop,
                                                          long long ldr, long long rows) {
     const int lane = threadIdx.x & 63;
     const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (r >= rows) return;
-    const int j = picks[r * k + it];
+    int j;
+    if (cand) {
+        OmpCand b{-1.f, 0x7fffffff};
+        for (int q = lane; q < nseg; q += 64) {
+            const OmpCand o = cand[r * nseg + q];
+            if (o.val > b.val) b = o;                   // ascending index per lane
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const float ob = __shfl_xor(b.val, o, 64);
+            const int oi = __shfl_xor(b.idx, o, 64);
+            if (ob > b.val || (ob == b.val && oi < b.idx)) b = OmpCand{ob, oi};
+        }
+        j = b.val >= 0.f ? b.idx : 0;                   // (0: every correlation is NaN)
+        if (lane == 0) picks[r * k + it] = j;
+    } else {
+        j = picks[r * k + it];
+    }
     const T* col = PhiT + (long long)j * ldp;
     float* qrow = Qb + r * (long long)k * mq;
     float v[MQ];
@@ -130,36 +218,38 @@ __global__ __launch_bounds__(256) void omp_finish_kernel(const float* Tri, const
     if (r >= rows) return;
     const float* tri = Tri + r * (long long)k * k;
     const int* pk = picks + r * k;
+    // Lane s holds row s of the factor and the unknown x_s; from the last unknown on, each is broadcast and subtracted.
+    // (With every lane running the whole substitution its k^2 / 2 loads came one after the other: 216 us on 76 800 rows of
+    // eight picks.)
+    const int row = lane < k ? lane : 0;
+    float t[kOmpMaxPicks];
+#pragma unroll
+    for (int s = 0; s < kOmpMaxPicks; ++s) t[s] = s < k ? tri[row * k + (s >= row ? s : row)] : 0.f;
+    float acc = lane < k ? Z[r * k + row] : 0.f, mine = 0.f;
     float x[kOmpMaxPicks];
 #pragma unroll
-    for (int s = 0; s < kOmpMaxPicks; ++s) x[s] = 0.f;
-    // every lane runs the same k^2/2 operations (k <= 32): no communication needed
-#pragma unroll
     for (int s = kOmpMaxPicks - 1; s >= 0; --s) {
+        x[s] = 0.f;
         if (s < k) {
-            float acc = Z[r * k + s];
-#pragma unroll
-            for (int t = 0; t < kOmpMaxPicks; ++t)
-                if (t > s && t < k) acc -= tri[s * k + t] * x[t];
-            const float dg = tri[s * k + s];
-            x[s] = dg > 0.f ? acc / dg : 0.f;
+            const float xs = t[s] > 0.f ? acc / t[s] : 0.f;          // (lane s: t[s] is the diagonal)
+            x[s] = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(xs), s));
+            if (lane == s) mine = x[s];
+            acc -= t[s] * x[s];
         }
     }
-#pragma unroll
-    for (int s = 0; s < kOmpMaxPicks; ++s) {
-        if (s < k && lane == 0) {
-            if (X) X[r * (long long)n + pk[s]] = x[s];
-            if (picks_out) picks_out[r * k + s] = pk[s];
-        }
+    const int my_pick = lane < k ? pk[lane] : 0;
+    if (lane < k) {
+        if (X) X[r * (long long)n + my_pick] = mine;
+        if (picks_out) picks_out[r * k + lane] = my_pick;
     }
     if (C) {
         const T* v = V + (r / n_q) * (long long)n * d;
         for (int c = lane; c < d; c += 64) {
-            float acc = 0.f;
+            float sum = 0.f;
 #pragma unroll
             for (int s = 0; s < kOmpMaxPicks; ++s)
-                if (s < k) acc += x[s] * Elem<T>::load(v + (long long)pk[s] * d + c);
-            Elem<T>::store(C + r * (long long)d + c, acc);
+                if (s < k) sum += x[s] * Elem<T>::load(v + (long long)__builtin_amdgcn_readlane(my_pick, s) * d + c);
+            Elem<T>::store(C + r * (long long)d + c, sum);
         }
     }
 }

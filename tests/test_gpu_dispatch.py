@@ -250,3 +250,37 @@ def test_decoder_with_a_tile_shared_by_eight_wavefronts(n_q, n, m, iters, option
     assert csat.csat_profile_decoder_kernel() in (0, 1, 3, 4)
     same = torch.equal(X, X1) and torch.equal(C, C1)
     assert same
+
+
+# (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
+# picked in the end (m = n = picks), several column tiles
+PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20)]
+
+
+@pytest.mark.parametrize("n_q,n,m,picks", PICK_CASES)
+def test_matching_pursuit_picks_in_the_product(n_q, n, m, picks, options):
+    """The largest correlation is found in the product's epilogue where the large-tile kernel runs: the picks of the
+    search over stored correlations (the same product, forced onto the other kernel, differs in summation order only, so
+    rows whose picks agree are compared in full and few may not), no column twice, coefficients consistent."""
+    w = _small("omp_picks", B=1, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16")
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    p = _problem(w, Q, K, V, Phi)
+    rng = np.random.default_rng(n)
+    Y = to_dev(rng.standard_normal((3, n_q, m)).astype(np.float32), "f32")
+    ws = torch.empty(csat.csat_omp_workspace_bytes(p.dims, picks), dtype=torch.uint8, device=DEV)
+    out = []
+    for gemm in (0, 1):
+        options("gemm", gemm)
+        ws.fill_(0xFF)
+        X, S, C = p.empty(3, n_q, n, dtype=torch.float32), p.empty(3, n_q, picks, dtype=torch.int32), p.empty(3, n_q, w.d)
+        csat.csat_recover_omp(p.dims, Y, p.Phi, picks, X, S, p.V, C, ws)
+        torch.cuda.synchronize()
+        out.append([to_np(t) for t in (X, S, C)])
+    (X, S, C), (X1, S1, C1) = out
+    assert (S >= 0).all() and (S < n).all() and (np.diff(np.sort(S, -1), axis=-1) > 0).all()
+    agree = (S == S1).all(-1)
+    assert agree.mean() > 0.9
+    assert_close("X", X[agree], X1[agree], TOL["f32"])
+    assert_close("C", C[agree], C1[agree], TOL["bf16"])
+    assert_close("C = X V", C, X.astype(np.float64) @ V.reshape(3, n, w.d).astype(np.float64), TOL["bf16"])

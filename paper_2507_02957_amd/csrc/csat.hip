@@ -1353,7 +1353,8 @@ csat_status hadamard_t(const csat_dims& d, const Workspace& w, const float* Y, l
                    d.n, d.m, N, logN, iters, mu, mu * lambda, scale};
     const bool in_regs = N >= 512 && hadamard_choice() != 1;      // the iterate in registers (two values per thread at least)
     const size_t lds_bytes = ista_hadamard_lds_bytes(N, d.m), reg_lds = (size_t)(fwht_pad(N) + 1 + 2 * d.m) * 4;
-    if ((in_regs ? reg_lds : lds_bytes) > kLdsPerWorkgroup) return CSAT_ERR_SHAPE;     // the row's buffers must fit LDS
+    if ((in_regs ? reg_lds : lds_bytes) > kLdsPerWorkgroup) return CSAT_ERR_SHAPE;     // the documented limit
+    const size_t row_lds = (size_t)(fwht_pad(N) + 1) * 4;                              // (what the kernel with the iterate in registers uses of it)
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         if (want_c && !synthesis_is_direct<T>(d)) CSAT_TRY(transpose_pack<T>((const T*)V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
@@ -1371,8 +1372,8 @@ csat_status hadamard_t(const csat_dims& d, const Workspace& w, const float* Y, l
 #define CSAT_HADAMARD_REG_LAUNCH(NT_, VPT_)                                                                              \
     do {                                                                                                              \
         HIP_TRY(hipFuncSetAttribute((const void*)ista_hadamard_reg_kernel<T, NT_, VPT_>,                              \
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)reg_lds));                       \
-        hipLaunchKernelGGL((ista_hadamard_reg_kernel<T, NT_, VPT_>), grid, dim3(NT_), reg_lds, st, a, inv);           \
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)row_lds));                       \
+        hipLaunchKernelGGL((ista_hadamard_reg_kernel<T, NT_, VPT_>), grid, dim3(NT_), row_lds, st, a, inv);           \
     } while (0)
         if (in_regs) {
             int* inv = (int*)w.PhiT;                   // N ints; the stored-matrix operands are not used on this path

@@ -210,72 +210,90 @@ static __global__ void hadamard_inverse_scatter_kernel(const int* rows_of_h, int
     inv[v < 0 ? 0 : (v >= N ? N - 1 : v)] = l;
 }
 
-// The same decoder for long transforms (N = NT * VPT >= 4096).  The iterate, the column signs and the
-// inverse of the row selection live in registers (thread tid owns indices tid + NT*j), so LDS holds only
-// the transform buffer: two workgroups fit a CU at N = 16384 and fill each other's barrier waits, the
-// zero-fill-then-scatter of the residual becomes one gather through the inverse map, and the iterate
-// makes no LDS round trip.
+// The same decoder with the iterate in registers (N = NT * VPT).  Thread tid owns indices tid + NT*j of the iterate, so
+// the stages of (up to four of) the top index bits are butterflies among its own registers; and it owns the 2^LB
+// consecutive indices of each of its low groups, so the last stages of the first transform, the residual
+// y - Phi x at the selected rows (zero elsewhere), and the first stages of the second transform all happen in
+// registers too, between one LDS read and the write to the same words.  What is left in LDS are the stages between:
+// per iteration two writes and two reads of the row in all plus one pass over the middle bits per transform, four
+// barriers (N <= 4096).  The iterate is kept with the column signs applied (the threshold is odd), so the signs
+// only matter when it is written out.
+// Bound by the vector units: 22 adds per index and iteration, 6 other instructions; short_video (N = 2048, 76 800 rows,
+// 20 iterations) 3921 us a launch with the residual gathered through LDS, 2350 now; N = 1024 1240 -> 650 us a forward
+// (64 000 rows, 10 iterations), N = 4096 1710 -> 1260, N = 16 384 2820 -> 2220.
 template <typename T, int NT, int VPT>
 __global__ __launch_bounds__(NT, 4) void ista_hadamard_reg_kernel(HadamardArgs a, const int* __restrict__ inv) {
     extern __shared__ float hl[];
     float* Wl = hl;                               // [pad(N)+1] transform buffer
-    float* Yl = Wl + fwht_pad(a.N) + 1;           // [m]      measurements of this row
-    float* Rl = Yl + a.m;                         // [m]      residual
     const int tid = threadIdx.x;
     const float cs = a.mu * a.scale;
-    auto hrow = [&](int l) { const int v = a.rows_of_h[l]; return v < 0 ? 0 : (v >= a.N ? a.N - 1 : v); };
     // index tid + NT*j sits at word fwht_pad(tid) + j * (NT + NT/32): one base, constant offsets
     float* Wt = Wl + fwht_pad(tid);
     constexpr int WS = NT + NT / 32;
-    // The values a thread owns differ in the top log2 VPT bits of the index, so the stages of (up to four
-    // of) those bits are butterflies among its own registers: on the way into LDS for the first transform
-    // of an iteration (its result is read at the selected rows, from LDS), on the way out for the second
-    // (its result meets the iterate in registers).  LDS passes cover the bits below.
-    constexpr int LOGV = VPT == 2 ? 1 : VPT == 4 ? 2 : VPT == 8 ? 3 : VPT == 16 ? 4 : 5;
-    constexpr int RB = LOGV < 4 ? LOGV : 4, G = VPT >> RB;
+    constexpr int LOGV = VPT == 8 ? 3 : VPT == 16 ? 4 : 5;
+    constexpr int RB = LOGV < 4 ? LOGV : 4, G = VPT >> RB;                  // top bits in registers, groups of them
     constexpr int LOGN = LOGV + (NT == 64 ? 6 : NT == 128 ? 7 : NT == 256 ? 8 : 9), TOP = LOGN - RB;
-    // residual entry that lands on index tid + NT*j, 16 bits each (m <= 16384), 0xffff = none
+    constexpr int LB = RB, E = 1 << LB;                                     // low bits; a thread's groups tid + NT*p, p < G
+    // y's entry for low-group element (p, e), 16 bits each (m <= 16384), 0xffff = the row is not selected
     uint32_t src[VPT / 2];
-    uint32_t neg = 0;                             // bit j: the column sign of index tid + NT*j is -1
+    uint32_t neg = 0, sel = 0;                    // bit j: the column sign of index tid + NT*j is -1; element j is selected
+    float sc[VPT <= 16 ? VPT : 1];                // (kept as factors where registers allow)
 #pragma unroll
     for (int j = 0; j < VPT; ++j) {
-        const int i = tid + NT * j;
-        const uint32_t v = (uint32_t)inv[i] & 0xffffu;
+        const uint32_t v = (uint32_t)inv[(tid + NT * (j / E)) * E + j % E] & 0xffffu;
         src[j / 2] = (j & 1) ? (src[j / 2] | (v << 16)) : v;
-        neg |= (a.signs[i] < 0 ? 1u : 0u) << j;
+        sel |= (v != 0xffffu ? 1u : 0u) << j;
+        if (VPT <= 16) sc[j % (VPT <= 16 ? VPT : 1)] = v != 0xffffu ? -a.scale : 0.f;
+        neg |= (a.signs[tid + NT * j] < 0 ? 1u : 0u) << j;
     }
+    const int full = a.n / NT;                    // j < full: every thread's index is below n; j > full: none
     for (long long r = blockIdx.x; r < a.rows; r += gridDim.x) {
-        float x[VPT];
+        float x[VPT], y[VPT];
 #pragma unroll
-        for (int j = 0; j < VPT; ++j) x[j] = 0.f;
-        for (int l = tid; l < a.m; l += NT) Yl[l] = a.Y[r * a.ldy + l];
-        __syncthreads();
+        for (int j = 0; j < VPT; ++j) {
+            const uint32_t l = (src[j / 2] >> (16 * (j & 1))) & 0xffffu;
+            x[j] = 0.f;
+            y[j] = l != 0xffffu ? a.Y[r * a.ldy + l] : 0.f;
+        }
+        __syncthreads();                          // the previous row's last reads
         for (int t = 0; t < a.iters; ++t) {
-            if (t > 0) {      // r = y - Phi x   (x is zero beyond n)
+            if (t > 0) {      // Phi x, but for the low stages   (x is zero beyond n)
 #pragma unroll
                 for (int p = 0; p < G; ++p) {
                     float v[1 << RB];
 #pragma unroll
-                    for (int q = 0; q < (1 << RB); ++q) v[q] = ((neg >> (p + G * q)) & 1) ? -x[p + G * q] : x[p + G * q];
+                    for (int q = 0; q < (1 << RB); ++q) v[q] = x[p + G * q];
                     fwht_regs<RB>(v);
 #pragma unroll
                     for (int q = 0; q < (1 << RB); ++q) Wt[(p + G * q) * WS] = v[q];
                 }
                 __syncthreads();
-                fwht_lds_static<NT, LOGN, TOP>(Wl, tid);
-                for (int l = tid; l < a.m; l += NT) Rl[l] = Yl[l] - a.scale * Wl[fwht_pad(hrow(l))];
-            } else {
-                for (int l = tid; l < a.m; l += NT) Rl[l] = Yl[l];
+                fwht_lds_static<NT, LOGN, TOP, LB>(Wl, tid);
             }
-            __syncthreads();
 #pragma unroll
-            for (int j = 0; j < VPT; ++j) {      // Phi^T r: the residual gathered to its rows of H
-                const uint32_t l = (src[j / 2] >> (16 * (j & 1))) & 0xffffu;
-                Wt[j * WS] = l != 0xffffu ? Rl[l] : 0.f;
-                if (j % 8 == 7) asm volatile("" ::: "memory");      // eight gathers in flight, not VPT: registers
+            for (int p = 0; p < G; ++p) {         // r = y - Phi x at the selected rows, and the low stages of Phi^T r
+                float* Wb = Wl + fwht_pad((tid + NT * p) * E);
+                float v[E];
+                if (t > 0) {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) v[e] = Wb[e];
+                    fwht_regs<LB>(v);
+#pragma unroll
+                    for (int e = 0; e < E; ++e) {
+                        const int j = p * E + e;
+                        if (VPT <= 16) v[e] = fmaf(sc[j % (VPT <= 16 ? VPT : 1)], v[e], y[j]);
+                        else v[e] = ((sel >> j) & 1) ? fmaf(-a.scale, v[e], y[j]) : 0.f;
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < E; ++e) v[e] = y[p * E + e];
+                }
+                fwht_regs<LB>(v);
+#pragma unroll
+                for (int e = 0; e < E; ++e) Wb[e] = v[e];
             }
             __syncthreads();
-            fwht_lds_static<NT, LOGN, TOP>(Wl, tid);
+            fwht_lds_static<NT, LOGN, TOP, LB>(Wl, tid);
 #pragma unroll
             for (int p = 0; p < G; ++p) {
                 float v[1 << RB];
@@ -285,21 +303,22 @@ __global__ __launch_bounds__(NT, 4) void ista_hadamard_reg_kernel(HadamardArgs a
 #pragma unroll
                 for (int q = 0; q < (1 << RB); ++q) {
                     const int j = p + G * q;
-                    if (tid + NT * j < a.n) {
-                        const float u = x[j] + cs * (((neg >> j) & 1) ? -v[q] : v[q]);
+                    if (j < full || (j == full && tid + NT * j < a.n)) {
+                        const float u = x[j] + cs * v[q];
                         x[j] = u - __builtin_amdgcn_fmed3f(u, -a.theta, a.theta);
                     }
                 }
             }
-            __syncthreads();
+            // (the next iteration's first writes go to the words this thread has just read)
         }
         float* xo = a.X ? a.X + r * (long long)a.n + tid : nullptr;
         T* xp = a.Xop ? (T*)a.Xop + r * a.ldx + tid : nullptr;
 #pragma unroll
         for (int j = 0; j < VPT; ++j) {
             const int i = tid + NT * j;
-            if (xo && i < a.n) xo[NT * j] = x[j];
-            if (xp && i < a.ldx) Elem<T>::store(xp + NT * j, x[j]);
+            const float out = ((neg >> j) & 1) ? 0.f - x[j] : x[j];
+            if (xo && i < a.n) xo[NT * j] = out;
+            if (xp && i < a.ldx) Elem<T>::store(xp + NT * j, out);
             asm volatile("" ::: "memory");      // one address pair at a time (registers)
         }
     }

@@ -284,3 +284,54 @@ def test_matching_pursuit_picks_in_the_product(n_q, n, m, picks, options):
     assert_close("X", X[agree], X1[agree], TOL["f32"])
     assert_close("C", C[agree], C1[agree], TOL["bf16"])
     assert_close("C = X V", C, X.astype(np.float64) @ V.reshape(3, n, w.d).astype(np.float64), TOL["bf16"])
+
+
+# (n, m, iterations): every length of the register-resident transforms, n at and off multiples of the thread count, just
+# above half the length and equal to it, one and two iterations
+HADAMARD_CASES = [(257, 30, 3), (512, 512, 2), (513, 100, 1), (1000, 64, 4), (1088, 200, 3), (2048, 300, 2), (2049, 90, 3), (4100, 1000, 2), (8200, 40, 2)]
+
+
+@pytest.mark.parametrize("n,m,iters", HADAMARD_CASES)
+def test_transform_decoder_lengths(n, m, iters, options):
+    """The transform-based decoder with the iterate in registers against the one in LDS (same transforms, another order
+    of their stages) and, where the explicit matrix is small, the oracle."""
+    w = _small("hadamard_lengths", B=1, H=2, n_q=9, n=n, d=64, m=m, dtype="f32", iters=iters, lam=0.002)
+    Q, K, V = gen.make_qkv(w)
+    rows, signs = _selection(m, n)
+    p = _problem(w, Q, K, V, np.zeros((m, n), np.float32))
+    Y = np.random.default_rng(m).standard_normal((2, 9, m)).astype(np.float32) * 0.1
+    N = len(signs)
+    mu = m / N
+    out = []
+    for choice in (0, 1):
+        options("hadamard", choice)
+        p.ws.fill_(0xFF)
+        X, C = p.empty(2, 9, n, dtype=torch.float32), p.empty(2, 9, w.d)
+        csat.csat_recover_hadamard(p.dims, to_dev(Y, "f32"), to_dev_raw(rows), to_dev_raw(signs), w.lam, mu, iters, X, p.V, C, p.ws)
+        torch.cuda.synchronize()
+        out.append((to_np(X), to_np(C)))
+    for name, a, b in zip("XC", *out):
+        assert_close(name, a, b, TOL["f32"])
+    if N <= 2048:
+        i, j = rows[:, None].astype(np.int64), np.arange(n)[None, :]
+        bits = np.zeros(i.shape[:1] + j.shape[1:], np.int64)
+        both = i & j
+        while both.any():
+            bits ^= both & 1
+            both >>= 1
+        P = (1 - 2 * bits) * signs[:n] / np.sqrt(m)
+        x = np.zeros((18, n))
+        for _ in range(iters):
+            u = x + mu * ((Y.reshape(18, m) - x @ P.T) @ P)
+            x = np.sign(u) * np.maximum(np.abs(u) - mu * w.lam, 0)
+        assert_close("X against float64", out[0][0].reshape(18, n), x, TOL["f32"])
+
+
+def _selection(m, n):
+    N = 1 << (n - 1).bit_length()
+    rng = np.random.default_rng(m + n)
+    return np.sort(rng.permutation(N)[:m]).astype(np.int32), (rng.integers(0, 2, N) * 2 - 1).astype(np.int8)
+
+
+def to_dev_raw(a):
+    return torch.from_numpy(a).to(DEV)

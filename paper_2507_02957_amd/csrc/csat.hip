@@ -379,15 +379,17 @@ template <typename TI, typename TO>
 csat_status pack_rows(const TI* src, long long lds_, TO* dst, long long ldd, long long rows, int cols, hipStream_t st) {
     const int vec = lds_ % 4 == 0 && ldd % 4 == 0 && reinterpret_cast<uintptr_t>(src) % (4 * sizeof(TI)) == 0 &&
                     reinterpret_cast<uintptr_t>(dst) % (4 * sizeof(TO)) == 0;
-    hipLaunchKernelGGL((pack_rows_kernel<TI, TO>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, src, lds_, dst, ldd, rows, cols, vec);
+    hipLaunchKernelGGL((pack_rows_kernel<TI, TO>), dim3((unsigned)((rows + 3) / 4), (unsigned)((ldd + kPackCols - 1) / kPackCols)), dim3(256), 0, st, src, lds_, dst, ldd, rows, cols, vec);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
 
 template <typename T>
-csat_status transpose_pack(const T* src, T* dst, long long ldd, int batch, int R, int Cc, hipStream_t st) {
+csat_status transpose_pack(const T* src, T* dst, long long ldd, int batch, int R, int Cc, hipStream_t st, const T* src2 = nullptr) {
+    const int one = batch;      // batches of src; as many of src2 behind them
+    if (src2) batch *= 2;
     dim3 grid((unsigned)((ldd + 31) / 32), (unsigned)((Cc + 31) / 32), (unsigned)batch);
-    hipLaunchKernelGGL((transpose_pack_kernel<T>), grid, dim3(32, 8), 0, st, src, (long long)R * Cc, dst, ldd,
+    hipLaunchKernelGGL((transpose_pack_kernel<T>), grid, dim3(32, 8), 0, st, src, src2, one, (long long)R * Cc, dst, ldd,
                        (long long)Cc * ldd, R, Cc);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
@@ -440,6 +442,9 @@ bool synthesis_is_direct(const csat_dims& d) {
     return sizeof(T) == 2 && (d.d == 64 || d.d == 128) && (*tl_opt)[CSAT_OPT_SYNTHESIS] != 2;
 }
 // ... and whether it reads Phi as the caller holds it (rows 16-byte aligned), so that no operand copy is needed
+// (phi_is_operand: the caller's Phi has the layout of that copy; float only, bf16's rows are padded to 64)
+template <typename T>
+bool phi_is_operand(const csat_dims& d, const void* Phi) { return sizeof(T) == 4 && d.n % 8 == 0 && aligned16(Phi); }
 template <typename T>
 bool measure_reads_raw_phi(const csat_dims& d, bool separate) { return measure_is_direct<T>(d, separate) && d.n % 8 == 0; }
 
@@ -505,19 +510,32 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
             return CSAT_OK;
         }
     }
+    // Both products in one launch (and both transposes) where they share the matrix and the copies are adjacent: small
+    // problems are bound by launches of a few workgroups (256 x 256, m = 64 in float: a launch of each kind less, 18 us).
+    const bool pair = !separate && want_v && 2ll * BH <= 65535 && w.VT == w.KT + (size_t)BH * d.d * w.ldn * sizeof(T);
+    // Phi as the caller holds it where that is the operand layout already
+    const void* A = PhiV && !separate && phi_is_operand<T>(d, PhiV) ? (const void*)PhiV : w.PhiP;
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
-        CSAT_TRY(transpose_pack<T>(K, (T*)w.KT, w.ldn, BH, d.n, d.d, st));
+        CSAT_TRY(transpose_pack<T>(K, (T*)w.KT, w.ldn, BH, d.n, d.d, st, pair ? V : nullptr));
         // (vt_ready says what the caller needs afterwards; the V product below reads the transposed copy either way)
-        if (!vt_ready || want_v) CSAT_TRY(transpose_pack<T>(V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
-        if (VcT) CSAT_TRY(fill_zero(VcT, (size_t)BH * d.d * w.ldm * sizeof(T), st));
+        if (!pair && (!vt_ready || want_v)) CSAT_TRY(transpose_pack<T>(V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
+        if (VcT && w.ldm > d.m) CSAT_TRY(fill_zero(VcT, (size_t)BH * d.d * w.ldm * sizeof(T), st));
     }
     if (separate) {
         Timed tl(w, CSAT_K_LAYOUT, st);
         CSAT_TRY((pack_rows<T, T>(PhiK, d.n, (T*)w.PhiP, w.ldn, d.m, d.n, st)));
     }
     Timed tm(w, CSAT_K_MEASURE, st);
-    GemmArgs g{w.PhiP, w.ldn, 0, w.KT, w.ldn, (long long)d.d * w.ldn, d.m, d.d, d.n, 0};
+    GemmArgs g{A, w.ldn, 0, w.KT, w.ldn, (long long)d.d * w.ldn, d.m, d.d, d.n, 0};
+    const EpiStore<T> ev{Vc, d.d, (long long)d.m * d.d, VcT, w.ldm, (long long)d.d * w.ldm, 1.f, d.m, d.d};
+    if (pair) {
+        if constexpr (sizeof(T) == 2) {
+            if (split_k)
+                return gemm<T>(g, d.d, 2 * BH, EpiPair<EpiMeasureSplit, EpiStore<T>>{{(bf16_t*)Kc, w.KcHL, d.m, d.d}, ev, BH}, st);
+        }
+        return gemm<T>(g, d.d, 2 * BH, EpiPair<EpiStore<T>, EpiStore<T>>{{Kc, d.d, (long long)d.m * d.d, nullptr, 0, 0, 1.f, d.m, d.d}, ev, BH}, st);
+    }
     if constexpr (sizeof(T) == 2) {
         if (split_k) {
             EpiMeasureSplit ek{(bf16_t*)Kc, w.KcHL, d.m, d.d};
@@ -531,7 +549,6 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
     if (separate) CSAT_TRY((pack_rows<T, T>(PhiV, d.n, (T*)w.PhiP, w.ldn, d.m, d.n, st)));
     if (!want_v) return CSAT_OK;      // (V~ only feeds the compressed output Z: a forward without Z does not need it)
     g.Bt = w.VT;
-    EpiStore<T> ev{Vc, d.d, (long long)d.m * d.d, VcT, w.ldm, (long long)d.d * w.ldm, 1.f, d.m, d.d};
     CSAT_TRY((gemm<T>(g, d.d, BH, ev, st)));
     return CSAT_OK;
 }
@@ -999,7 +1016,7 @@ template <typename T>
 csat_status measure_t(const csat_dims& d, const Workspace& w, const void* PhiK, const void* Phi, const void* K,
                       const void* V, void* Kc, void* Vc, hipStream_t st) {
     const bool separate = PhiK && PhiK != Phi;
-    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !measure_reads_raw_phi<T>(d, separate), 0, st));
+    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !(measure_reads_raw_phi<T>(d, separate) || (!separate && phi_is_operand<T>(d, Phi))), 0, st));
     return run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)Kc, (T*)Vc, nullptr, measure_is_direct<T>(d, separate), false, st, (const T*)PhiK,
                           (const T*)Phi);
 }
@@ -1045,7 +1062,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
                       const void* PhiK, const void* Phi, float lambda, float mu, int iters, void* C, void* Z,
                       float* X, hipStream_t st) {
     const bool separate = PhiK && PhiK != Phi;
-    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !measure_reads_raw_phi<T>(d, separate), iters, st));
+    CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, !(measure_reads_raw_phi<T>(d, separate) || (!separate && phi_is_operand<T>(d, Phi))), iters, st));
     const bool need_z = Z || iters == 0;
     T* zdst = (iters == 0) ? (T*)C : (T*)Z;
     bool kc_packed = false, v_packed = false;

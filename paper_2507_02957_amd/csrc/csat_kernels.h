@@ -228,6 +228,16 @@ struct EpiStore {
     }
 };
 
+// Batches below z2 end in `a`, the others in `b`: two products of one launch.
+template <typename EA, typename EB>
+struct EpiPair {
+    EA a; EB b; int z2;
+    __device__ __forceinline__ void operator()(int z, long long r, long long c, float v) const {
+        if (z < z2) a(z, r, c, v);
+        else b(z - z2, r, c, v);
+    }
+};
+
 // C[r][c] = v, written with the non-temporal hint: for a large result that is read once by the next kernel and
 // should not push that kernel's other inputs out of the caches (matching pursuit's correlations, where the pick is not
 // taken in the product).
@@ -657,23 +667,30 @@ template <typename E> struct has_tile_epilogue<E, std::enable_if_t<E::kTile>> : 
 // Layout helpers (HBM-bound, off the dominant path).
 // ----------------------------------------------------------------------------------------
 
-// dst[r][0..ldd) = convert(src[r][0..cols)) with zero fill up to ldd.  A wavefront per row, four elements per lane; vec: rows
+// dst[r][0..ldd) = convert(src[r][0..cols)) with zero fill up to ldd.  A wavefront per row and kPackCols columns (few long
+// rows, like Phi's, still fill the chip), four elements per lane; vec: rows
 // of both sides 16-byte (float) or 8-byte (bf16) aligned in steps of four elements.  Bound by memory: 76 800 x 392 floats to
 // bf16 82 us with a thread per element, which spent its time on the row's 64-bit division; 37 us now.
+constexpr int kPackCols = 256;
 template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void pack_rows_kernel(const TI* src, long long lds_, TO* dst, long long ldd, long long rows, int cols, int vec) {
+__global__ __launch_bounds__(256) void pack_rows_kernel(const TI* __restrict__ src, long long lds_, TO* __restrict__ dst, long long ldd, long long rows, int cols, int vec) {
     const int lane = threadIdx.x & 63;
     const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (r >= rows) return;
     const TI* s = src + r * lds_;
     TO* d = dst + r * ldd;
     if (!vec) {
-        for (long long c = lane; c < ldd; c += 64) Elem<TO>::store(d + c, c < cols ? Elem<TI>::load(s + c) : 0.f);
+#pragma unroll
+        for (int i = 0; i < kPackCols / 64; ++i) {
+            const long long c = (long long)blockIdx.y * kPackCols + lane + 64 * i;
+            if (c < ldd) Elem<TO>::store(d + c, c < cols ? Elem<TI>::load(s + c) : 0.f);
+        }
         return;
     }
     struct alignas(4 * sizeof(TI)) In { TI v[4]; };
     struct alignas(4 * sizeof(TO)) Out { TO v[4]; };
-    for (long long c = lane * 4; c < ldd; c += 256) {
+    const long long c = (long long)blockIdx.y * kPackCols + lane * 4;
+    if (c < ldd) {
         Out o;
         if (c + 4 <= cols) {
             const In q = *(const In*)(s + c);
@@ -687,15 +704,15 @@ __global__ __launch_bounds__(256) void pack_rows_kernel(const TI* src, long long
     }
 }
 
-// dst[z][c][r] = src[z][r][c] for r < R, c < Cc; dst rows have ld = ldd >= R, zero filled.
-// 32x32 tiles through LDS so both sides are coalesced.
+// dst[z][c][r] = src[z][r][c] for r < R, c < Cc; dst rows have ld = ldd >= R, zero filled.  Batches from z2 on come from
+// src2 (K and V in one launch).  32x32 tiles through LDS so both sides are coalesced.
 template <typename T>
-__global__ void transpose_pack_kernel(const T* src, long long strideS, T* dst, long long ldd, long long strideD,
+__global__ void transpose_pack_kernel(const T* src, const T* src2, int z2, long long strideS, T* dst, long long ldd, long long strideD,
                                       int R, int Cc) {
     __shared__ T tile[32][33];
     const int z = blockIdx.z;
     const int r0 = blockIdx.x * 32, c0 = blockIdx.y * 32;
-    const T* s = src + (long long)z * strideS;
+    const T* s = z < z2 ? src + (long long)z * strideS : src2 + (long long)(z - z2) * strideS;
     T* d = dst + (long long)z * strideD;
     for (int i = threadIdx.y; i < 32; i += blockDim.y) {
         int r = r0 + i, c = c0 + threadIdx.x;

@@ -219,7 +219,7 @@ static __global__ void hadamard_inverse_scatter_kernel(const int* rows_of_h, int
 // barriers (N <= 4096).  The iterate is kept with the column signs applied (the threshold is odd), so the signs
 // only matter when it is written out.
 // Bound by the vector units: 22 adds per index and iteration, 6 other instructions; short_video (N = 2048, 76 800 rows,
-// 20 iterations) 3921 us a launch with the residual gathered through LDS, 2350 now; N = 1024 1240 -> 650 us a forward
+// 20 iterations) 3921 us a launch with the residual gathered through LDS, 2340 now; N = 1024 1240 -> 650 us a forward
 // (64 000 rows, 10 iterations), N = 4096 1710 -> 1260, N = 16 384 2820 -> 2220.
 template <typename T, int NT, int VPT>
 __global__ __launch_bounds__(NT, 4) void ista_hadamard_reg_kernel(HadamardArgs a, const int* __restrict__ inv) {

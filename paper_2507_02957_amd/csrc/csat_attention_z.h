@@ -20,6 +20,8 @@
 // read the copy back); floor: 100 MB of Q and Z = 21 us, 3.2e6 wavefront scores x 30 cycles of vector issue = 22 us.
 // 48 heads x 1600 queries, m = 392, K~ as a pair, Z^T wanted (two tiles at a time): 29 us against 86 + 44.
 #pragma once
+#include <cfloat>
+
 #include "csat_ista_fused.h"      // slab_slot
 #include "csat_kernels.h"
 
@@ -151,7 +153,7 @@ __global__ __launch_bounds__(64 * kAttnZWaves, NZ <= 2 ? 4 : 2) void attention_z
                 mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
             }
             if (__builtin_amdgcn_ballot_w64((mx - ref) * sl > 8.f) != 0) {      // (both lanes of a pair agree)
-                const float nm = fmaxf(mx, ref), alpha = __builtin_amdgcn_exp2f((ref - nm) * sl);     // first step: 2^(-inf) = 0
+                const float nm = fmaxf(mx, ref), alpha = __builtin_amdgcn_exp2f((ref - fmaxf(nm, -FLT_MAX)) * sl);     // first step: 2^(-inf) = 0
                 ref = nm;
                 sum *= alpha;
 #pragma unroll
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(64 * kAttnZWaves, NZ <= 2 ? 4 : 2) void attention_z
 #pragma unroll
                     for (int v = 0; v < 16; ++v) zacc[dt][v] *= alpha;
             }
-            const float off = -ref * sl;
+            const float off = -fmaxf(ref, -FLT_MAX) * sl;    // (only scores of -inf so far: their weights are 0)
 #pragma unroll
             for (int t = 0; t < PT; ++t) {
                 float e[16];

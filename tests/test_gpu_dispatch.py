@@ -86,6 +86,40 @@ def test_compressed_attention_moves_its_reference_score():
     assert_close("Z", to_np(Zg), Z, TOL["bf16"])
 
 
+# the row's first finite score in the second pair of tiles, in the last tile, nowhere in one row
+@pytest.mark.parametrize("d,m,first", [(64, 128, 64), (64, 200, 193), (128, 330, 300), (32, 700, 129)])
+def test_compressed_attention_with_scores_of_minus_infinity(d, m, first):
+    """Scores of -inf have weight 0 wherever they come in the row, also where a row of the same tile has finite ones
+    there; a row without any finite score is NaN, as its softmax is."""
+    n_q = 70
+    w = _small("z_minus_inf", B=1, H=2, n_q=n_q, n=max(m, 256), d=d, m=m, dtype="bf16")
+    rng = np.random.default_rng(m)
+    Q = gen.quantize(rng.uniform(0.5, 2.0, (2, n_q, d)).astype(np.float32), "bf16")
+    Q[:, 1::3] *= 2.0 ** -124                                # these rows' scores are finite everywhere
+    Kc = gen.quantize(rng.standard_normal((2, m, d)).astype(np.float32), "bf16")
+    Vc = gen.quantize(rng.standard_normal((2, m, d)).astype(np.float32), "bf16")
+    Kc[:, :first] = -2.0 ** 127                              # (times 0.5 to 2, summed over d: beyond the largest float)
+    Kc[1, first::2] = -2.0 ** 127
+    p = _problem(w, Q, np.zeros((2, w.n, d), np.float32), np.zeros((2, w.n, d), np.float32), gen.make_workload_phi(w))
+    s = np.matmul(Q.astype(np.float64), Kc.astype(np.float64).transpose(0, 2, 1)) / np.sqrt(d)
+    s[s < -1e38] = -np.inf
+    e = np.exp(s - s.max(-1, keepdims=True))
+    want = np.matmul(e / e.sum(-1, keepdims=True), Vc.astype(np.float64))
+    assert np.isinf(s[:, 0, :first]).all() and np.isfinite(s[:, 1]).all() and np.isfinite(s[0, 0, first:]).all()
+    Zg = p.empty(2, n_q, d)
+    csat.csat_compressed_attention(p.dims, p.Q, to_dev(Kc, "bf16"), to_dev(Vc, "bf16"), None, Zg, p.ws)
+    torch.cuda.synchronize()
+    assert_close("Z", to_np(Zg), want, TOL["bf16"])
+    if m <= 512:
+        _, Zf = p.attention(to_dev(Kc, "bf16"), to_dev(Vc, "bf16"))
+        assert_close("Z with A~", to_np(Zf), want, TOL["bf16"])
+    Kc[:] = -2.0 ** 127                                      # no finite score but in the small rows
+    csat.csat_compressed_attention(p.dims, p.Q, to_dev(Kc, "bf16"), to_dev(Vc, "bf16"), None, Zg, p.ws)
+    torch.cuda.synchronize()
+    Z = to_np(Zg)
+    assert np.isnan(Z[:, 0::3]).all() and np.isfinite(Z[:, 1::3]).all()
+
+
 # few workgroups and a long contraction: two groups of wavefronts split it (n = 512 is where that begins; 511 stays with one)
 @pytest.mark.parametrize("n,m,d,zero_iters", [(511, 40, 64, True), (512, 40, 64, True), (700, 97, 128, True), (1025, 64, 128, False),
                                               (1500, 33, 64, False), (4097, 65, 64, True)])

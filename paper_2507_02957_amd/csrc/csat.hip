@@ -671,6 +671,8 @@ csat_status run_attention_z(const csat_dims& d, const Workspace& w, const T* Q, 
     a.ldT = 2 * w.ldn; a.strideT = (long long)d.d * a.ldT;
     a.n_q = d.n_q; a.m = d.m; a.MT = w.MT;
     a.scale_log2e = 1.4426950408889634f / sqrtf((float)d.d);
+    a.shift = 8.f;
+    for (long long v = 1; v < d.m; v *= 2) a.shift += 1.f;
     a.tiles_per_head = (d.n_q + 31) / 32;
     if (!kc_packed || !v_packed) {
         Timed tm(w, CSAT_K_LAYOUT, st);

@@ -7,8 +7,9 @@
 // Z, once each.  So the scores of two tiles of m at a time go through one softmax step with a running maximum and
 // sum per row, which keeps a wavefront at 128 registers (d <= 64): four wavefronts per SIMD fill each other's waits,
 // where the kernel that also delivers A~ has to hold all of a row's scores until its maximum is known.  The running
-// maximum is only moved (and the output rescaled) when a row's scores grow by more than 2^8 over it: the weights
-// 2^(s - ref) then stay below 2^8, and after the first step that almost never happens.
+// maximum is only moved (and the output rescaled) when a row's scores grow by more than 2^8 over it, and after the
+// first step that almost never happens.  The weights are 2^(s - ref - shift) with 2^shift >= 256 m: their sum is at most
+// 1, so the unnormalised output cannot overflow where the normalised one does not.
 //
 // Layout as in csat_attention.h: everything transposed, S^T = K~ Q^T puts a query row into one lane pair, and the
 // scores' accumulator layout is the B operand of Z^T = V~^T P^T.  The fragments of K~ and V~ of a head sit in LDS:
@@ -37,6 +38,7 @@ struct AttentionZArgs {
     int n_q, m, MT;
     int tiles_per_head, rounds, wg_per_head;
     float scale_log2e;
+    float shift;                   // 8 + log2(m), rounded up
 };
 
 // K~ rows [heads][m][PARTS * d] and V~ rows [heads][m][d] -> the fragments above, zero beyond m; either source may be
@@ -123,7 +125,9 @@ __global__ __launch_bounds__(64 * kAttnZWaves, NZ <= 2 ? 4 : 2) void attention_z
         for (int dt = 0; dt < NZ; ++dt)
 #pragma unroll
             for (int v = 0; v < 16; ++v) zacc[dt][v] = 0.f;
-        float ref = -INFINITY, sum = 0.f;                    // the row's reference score and this lane's share of its sum
+        // the row's reference score, what a weight's exponent takes off for it (scores of -inf have weight 0, also before the
+        // row's first finite one) and this lane's share of the row's sum
+        float ref = -INFINITY, off = __builtin_fmaf(FLT_MAX, sl, -a.shift), sum = 0.f;
         auto step = [&](int p, const uint4* slot) {
             f32x16 s[PT];
 #pragma unroll
@@ -153,15 +157,15 @@ __global__ __launch_bounds__(64 * kAttnZWaves, NZ <= 2 ? 4 : 2) void attention_z
                 mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
             }
             if (__builtin_amdgcn_ballot_w64((mx - ref) * sl > 8.f) != 0) {      // (both lanes of a pair agree)
-                const float nm = fmaxf(mx, ref), alpha = __builtin_amdgcn_exp2f((ref - fmaxf(nm, -FLT_MAX)) * sl);     // first step: 2^(-inf) = 0
+                const float nm = fmaxf(mx, ref), base = fmaxf(nm, -FLT_MAX), alpha = __builtin_amdgcn_exp2f((ref - base) * sl);     // first step: 2^(-inf) = 0
                 ref = nm;
+                off = __builtin_fmaf(-base, sl, -a.shift);
                 sum *= alpha;
 #pragma unroll
                 for (int dt = 0; dt < NZ; ++dt)
 #pragma unroll
                     for (int v = 0; v < 16; ++v) zacc[dt][v] *= alpha;
             }
-            const float off = -fmaxf(ref, -FLT_MAX) * sl;    // (only scores of -inf so far: their weights are 0)
 #pragma unroll
             for (int t = 0; t < PT; ++t) {
                 float e[16];

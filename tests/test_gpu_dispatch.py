@@ -120,6 +120,25 @@ def test_compressed_attention_with_scores_of_minus_infinity(d, m, first):
     assert np.isnan(Z[:, 0::3]).all() and np.isfinite(Z[:, 1::3]).all()
 
 
+@pytest.mark.parametrize("d,m", [(64, 16), (64, 256), (128, 390), (96, 1000)])
+def test_compressed_attention_of_large_values(d, m):
+    """Values of V~ whose sum over m is beyond the largest float, but not their average: equal scores, and scores that rise
+    by less than the kernel moves its reference for."""
+    n_q = 64
+    w = _small("z_large_values", B=1, H=2, n_q=n_q, n=max(m, 256), d=d, m=m, dtype="bf16")
+    rng = np.random.default_rng(m)
+    Q = gen.quantize(rng.standard_normal((2, n_q, d)).astype(np.float32), "bf16")
+    Kc = np.zeros((2, m, d), np.float32)
+    Kc[1] = gen.quantize((np.linspace(0.0, 4.0, m)[:, None] * Q[1, :1] / np.sqrt(d)).astype(np.float32), "bf16")
+    Vc = gen.quantize((rng.uniform(0.5, 1.0, (2, m, d)) * 3e38).astype(np.float32), "bf16")
+    p = _problem(w, Q, np.zeros((2, w.n, d), np.float32), np.zeros((2, w.n, d), np.float32), gen.make_workload_phi(w))
+    _, want = orc.compressed_attention(Q, Kc, Vc)
+    Zg = p.empty(2, n_q, d)
+    csat.csat_compressed_attention(p.dims, p.Q, to_dev(Kc, "bf16"), to_dev(Vc, "bf16"), None, Zg, p.ws)
+    torch.cuda.synchronize()
+    assert_close("Z", to_np(Zg), want, TOL["bf16"])
+
+
 # few workgroups and a long contraction: two groups of wavefronts split it (n = 512 is where that begins; 511 stays with one)
 @pytest.mark.parametrize("n,m,d,zero_iters", [(511, 40, 64, True), (512, 40, 64, True), (700, 97, 128, True), (1025, 64, 128, False),
                                               (1500, 33, 64, False), (4097, 65, 64, True)])

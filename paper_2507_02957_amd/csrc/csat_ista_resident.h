@@ -338,14 +338,19 @@ __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF
                 y[mt][k][e] = l < a.m ? a.Y[erow * a.ldY + l] : 0.f;
                 special |= !(fabsf(y[mt][k][e]) <= 1e18f);
             }
-    // (the vote goes through `red`: the compiler's own would need LDS beyond the 160 KB that the largest instance fills)
-    if (tid == 0) *(volatile int*)red = 0;
-    __syncthreads();
-    if (special) *(volatile int*)red = 1;
-    __syncthreads();
-    const bool plain = *(volatile int*)red != 0;
-    __syncthreads();
-    if (plain) {
+    // Whether any thread of the workgroup says so, through `red` (the compiler's own vote would need LDS beyond the 160 KB
+    // that the largest instance fills)
+    auto any = [&](bool mine) {
+        __syncthreads();
+        if (tid == 0) *(volatile int*)red = 0;
+        __syncthreads();
+        if (mine) *(volatile int*)red = 1;
+        __syncthreads();
+        const bool r = *(volatile int*)red != 0;
+        __syncthreads();
+        return r;
+    };
+    if (any(special)) {
         resident_f32_plain(a, row0, (float*)lds, tid);
         return;
     }
@@ -463,6 +468,19 @@ __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF
                 }
         }
         if (!last) residual(false);
+    }
+    // An iterate or a residual that left the range of float (a step far too large) stays infinite or NaN in its row: NaN
+    // parts make every later product of the row NaN.
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < CPW; ++i) {
+        if (wave + 4 * i >= nct) continue;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) bad |= !__builtin_isfinite(x[i][v]);
+    }
+    if (any(bad)) {
+        resident_f32_plain(a, row0, (float*)lds, tid);
+        return;
     }
     if (!row_ok) return;
 #pragma unroll

@@ -276,6 +276,38 @@ def test_float_decoder_with_phi_in_lds(n_q, n, m, iters, resident, options):
         assert_close("finite rows", to_np(got[rows_ok]), to_np(old[rows_ok]), TOL["f32"])
 
 
+@pytest.mark.parametrize("n_q,n,m", [(40, 128, 64), (33, 224, 96), (70, 65, 20), (20, 160, 128)])
+def test_float_decoder_in_lds_leaves_the_range_of_float(n_q, n, m, options):
+    """Finite inputs whose iterates overflow, in some rows of a tile from the first residual on and in others later: what
+    the float products make of them (sums of one sign, so that the order of a sum does not matter).  -inf after two
+    iterations, 0 after three (the threshold takes a NaN to 0), finite again after four."""
+    w = _small("f32_overflow", B=1, H=2, n_q=n_q, n=n, d=64, m=m, dtype="f32", lam=0.01)
+    rng = np.random.default_rng(n)
+    Phi = (rng.uniform(0.5, 1.0, (m, n)) * 1e15).astype(np.float32)
+    Q, K, V = gen.make_qkv(w)
+    p = _problem(w, Q, K, V, Phi)
+    Y = (rng.uniform(0.5, 1.0, (2, n_q, m)) * 1e10).astype(np.float32)
+    Y[:, 1::3] *= 1e-30                                        # these rows stay finite for two iterations
+    X, C = p.empty(2, n_q, n, dtype=torch.float32), p.empty(2, n_q, w.d)
+    for iters in (2, 3, 4, 5):
+        out = []
+        for gemm in (0, 1):
+            options("gemm", gemm)
+            p.ws.fill_(0xFF)
+            csat.csat_recover(p.dims, to_dev(Y, "f32"), p.Phi, w.lam, 1.0, iters, X, p.V, C, p.ws)
+            torch.cuda.synchronize()
+            assert csat.csat_profile_decoder_kernel() == (-1 if gemm else 5)
+            out.append((to_np(X), to_np(C)))
+        (Xg, Cg), (Xo, Co) = out
+        if iters == 2:
+            assert np.isneginf(Xo[:, 0]).all() and np.isfinite(Xo[:, 1]).all()
+        for got, old in ((Xg, Xo), (Cg, Co)):
+            assert (np.isnan(got) == np.isnan(old)).all() and (np.isposinf(got) == np.isposinf(old)).all() and (np.isneginf(got) == np.isneginf(old)).all()
+            rows_ok = np.isfinite(old).all(-1)
+            if rows_ok.any():
+                assert_close(f"finite rows, {iters} iterations", got[rows_ok], old[rows_ok], TOL["f32"], slices_axis0=False)
+
+
 # (n_q, n, m, iterations): the fewest chunks this decoder gets, one to thirteen tiles of m (odd and even), odd and even
 # chunk counts modulo its ring of five, a ragged last chunk and row tile, one and two iterations
 SHARED_TILE_CASES = [(33, 513, 20, 4), (40, 544, 64, 3), (64, 577, 90, 1), (31, 700, 128, 2), (70, 609, 160, 5), (32, 416, 416, 3), (5, 500, 390, 4),

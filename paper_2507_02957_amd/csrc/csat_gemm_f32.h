@@ -1,7 +1,7 @@
 // float "NT" GEMM  C[M,N] = sum_k A[M,k] * Bt[N,k]  on the bf16 matrix cores, without giving up float precision.
 //
-// The float MFMA (32x32x2) tops out at 157 TFLOP/s, a sixteenth of the bf16 one.  A float is the exact sum of three
-// bf16 values (hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid: 8 bits each, round to nearest), so the product of
+// The float MFMA (32x32x2) tops out at 157 TFLOP/s, a sixteenth of the bf16 one.  A float of at least 2^-109 is the exact
+// sum of three bf16 values (hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid: 8 bits each, round to nearest), so the product of
 // two floats is nine bf16 products, each exact in the MFMA's float accumulation.  The three smallest (mid lo, lo mid,
 // lo lo) are below 2^-26 of the product, less than the rounding of one float accumulation step, and are left out: six
 // bf16 MFMAs in place of eight float ones that each take twice as long: 6/16 of the time.
@@ -18,8 +18,9 @@
 // for all six products it was up to 1.4 of it, where the operand is sparse.
 //
 // Infinities and NaN: inf - inf in the split, or inf times a zero mid part, makes an accumulator NaN that the float
-// product would have as inf.  A workgroup that finds a non-finite accumulator therefore computes its tile again with
-// the float MFMA.
+// product would have as inf.  Operands below 2^-109 lose the bits that their parts would hold below bf16's smallest number
+// (at 10^-37 all but ten); where that matters, in rows without larger ones, the sums are as small.  A workgroup that
+// finds an accumulator that is not finite, or not zero but below 2^-90, therefore computes its tile again with the float MFMA.
 #pragma once
 #include "csat_kernels.h"
 
@@ -32,6 +33,17 @@ __device__ __forceinline__ void split3(float x0, float x1, uint32_t& hi, uint32_
     mid = f2bf_pk(r0, r1);
     lo = f2bf_pk(r0 - __uint_as_float(mid << 16), r1 - __uint_as_float(mid & 0xffff0000u));
 }
+
+// Whether results of split operands may not be what float arithmetic gives (see above)
+struct SplitSuspect {
+    uint32_t low = 0xffffffffu, high = 0u;      // smallest non-zero and largest magnitude, as bits shifted left
+    __device__ __forceinline__ void add(float v) {
+        const uint32_t u = __float_as_uint(v) << 1;
+        low = low < u - 1 ? low : u - 1;        // (zero: 2^32 - 1)
+        high = high > u ? high : u;
+    }
+    __device__ __forceinline__ bool any() const { return low < 2 * __float_as_uint(0x1p-90f) - 1 || high >= 0xff000000u; }
+};
 
 constexpr int kF32TileM = 128, kF32TileN = 64;
 
@@ -130,7 +142,7 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
         __syncthreads();
     }
 
-    bool bad = false;
+    SplitSuspect suspect;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -138,9 +150,9 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 acc[i][j][v] += corr[i][j][v];
-                bad |= !__builtin_isfinite(acc[i][j][v]);
+                suspect.add(acc[i][j][v]);
             }
-    if (__syncthreads_or(bad)) {      // the tile again on the float MFMA, one K step at a time
+    if (__syncthreads_or(suspect.any())) {      // the tile again on the float MFMA, one K step at a time
         clear();
         for (int ks = 0; ks < ksteps; ++ks) {
             load_global(ks);

@@ -258,8 +258,8 @@ constexpr int ista_resident_f32_chunks(int MT, int nct) {
     return MT == 1 ? (c <= 3 ? 3 : 6) : MT == 2 ? 3 : 2;
 }
 
-// One tile in plain float arithmetic: infinities and NaN then come out as the float products give them (EpiIstaUpdate's
-// threshold turns a NaN into 0).  The residuals are in LDS (32 x m floats), the iterate where the result goes.
+// One tile in plain float arithmetic: infinities, NaN and the smallest numbers then come out as the float products give
+// them (EpiIstaUpdate's threshold turns a NaN into 0).  The residuals are in LDS (32 x m floats), the iterate where the result goes.
 static __device__ __noinline__ void resident_f32_plain(const IstaResidentF32Args& a, long long row0, float* r, int tid) {
     const int rows = a.rows - row0 < 32 ? (int)(a.rows - row0) : 32;
     float* X = a.Xs ? a.Xs + row0 * a.ldS : a.Xout + row0 * a.n;
@@ -470,15 +470,16 @@ __global__ __launch_bounds__(256, 1) void ista_resident_f32_kernel(IstaResidentF
         if (!last) residual(false);
     }
     // An iterate or a residual that left the range of float (a step far too large) stays infinite or NaN in its row: NaN
-    // parts make every later product of the row NaN.
-    bool bad = false;
+    // parts make every later product of the row NaN.  A row of measurements so small that their parts lose bits has an
+    // iterate as small.
+    SplitSuspect suspect;
 #pragma unroll
     for (int i = 0; i < CPW; ++i) {
         if (wave + 4 * i >= nct) continue;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) bad |= !__builtin_isfinite(x[i][v]);
+        for (int v = 0; v < 16; ++v) suspect.add(x[i][v]);
     }
-    if (any(bad)) {
+    if (any(suspect.any())) {
         resident_f32_plain(a, row0, (float*)lds, tid);
         return;
     }

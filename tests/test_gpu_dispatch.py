@@ -231,6 +231,34 @@ def test_float_products_keep_float_precision(rows, n, m, options):
     assert rows == 1 or Xo.isinf().any()
 
 
+@pytest.mark.parametrize("rows,n,m,iters", [(130, 300, 100, 1), (130, 300, 100, 3), (70, 128, 64, 3), (40, 161, 128, 2)])
+@pytest.mark.parametrize("scale", [1e-33, 1e-37])
+def test_float_decoder_of_small_numbers(rows, n, m, iters, scale):
+    """Measurements near the smallest floats, in every row or in some rows of a tile (beside ordinary ones): their bf16
+    parts would not hold all of their bits.  Without a threshold X is linear in y, so its error in a row is held to the
+    row's own size: at most m / 2 (n / 2) roundings of 2^-24 in a product, one product of each kind per iteration, and C's."""
+    w = _small("f32_small_numbers", B=1, H=1, n_q=rows, n=n, d=64, m=m, dtype="f32", iters=iters)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    P, V64 = Phi.astype(np.float64), V.reshape(n, w.d).astype(np.float64)
+    for mixed in (False, True):
+        Y = np.random.default_rng(rows).standard_normal((rows, m)) * scale
+        if mixed:
+            Y[::2] /= scale
+        Y = Y.astype(np.float32)
+        X, C = p.empty(1, rows, n, dtype=torch.float32), p.empty(1, rows, w.d)
+        csat.csat_recover(p.dims, to_dev(Y, "f32"), p.Phi, 0.0, mu, iters, X, p.V, C, p.ws)
+        torch.cuda.synchronize()
+        x = np.zeros((rows, n))
+        for _ in range(iters):
+            x = x + mu * ((Y.astype(np.float64) - x @ P.T) @ P)
+        bound = 2.0 ** -24 * (m / 2 + n / 2 + 4) * iters
+        for got, want in ((to_np(X)[0], x), (to_np(C)[0], x @ V64)):
+            assert (np.linalg.norm(got - want, axis=-1) <= bound * np.linalg.norm(want, axis=-1)).all()
+
+
 # (n_q, n, m, iterations, in LDS): chunks per wavefront below, at and beyond one, idle wavefronts, one to four tiles of m,
 # the largest Phi that fits and the first that does not, ragged rows, unaligned n
 FLOAT_RESIDENT_CASES = [(33, 40, 8, 2, True), (32, 128, 32, 5, True), (50, 131, 64, 4, True), (64, 160, 128, 3, True), (7, 161, 128, 3, False),

@@ -97,28 +97,37 @@ __device__ __forceinline__ void mfma_group<float>(const uint4& a, const uint4& b
     for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[s], bv[s], acc, 0, 0, 0);
 }
 
-// Rows of a lane's 16 accumulators of a tile, r0 + off(v), for epilogues that read as well as write: a tile that lies
-// wholly above row M runs without conditions, the last one reads a row past the end as its own first (a branch around
-// each read costs the read's latency each time: the unrolled decoder's layer of 32 rows 16.5 us against 15).
-template <bool WHOLE>
+// Addresses of a lane's 16 accumulators of a tile (rows r0 + row(v), column c) for epilogues that read as well as write, and
+// want all reads before the first store, which the compiler cannot tell from them.  A row's base is uniform over the
+// wavefront, so it stays in scalar registers: with a 64-bit address per element the 128 x 128 kernel fell from three
+// wavefronts per SIMD to one or two (ISTA update of 80 000 rows, n = 128, m = 8: 45 against 32 us).
 struct TileRows {
-    long long left;            // rows from r0 on
-    __device__ __forceinline__ static constexpr int at(int v) { return 8 * (v / 4) + (v % 4); }
-    __device__ __forceinline__ long long operator()(int v) const { return at(v); }
-    __device__ __forceinline__ bool in(int v) const { return WHOLE || at(v) < left; }
-    __device__ __forceinline__ long long read(int v) const { return in(v) ? at(v) : 0; }
+    long long r0;              // the tile's first row ...
+    int c0;                    // ... and column
+    int lr, lc;                // this lane's within the tile
+    __device__ __forceinline__ TileRows(long long r, long long c) {
+        const int lane = threadIdx.x & 63;
+        lr = 4 * (lane >> 5);
+        lc = lane & 31;
+        r -= lr;
+        r0 = (long long)(((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(r >> 32)) << 32) |
+                         (uint32_t)__builtin_amdgcn_readfirstlane((int)r));
+        c0 = __builtin_amdgcn_readfirstlane((int)c - lc);
+        asm volatile("" : "+s"(r0), "+s"(c0));      // (addresses formed per tile, not for all tiles ahead: registers)
+    }
+    __device__ __forceinline__ static constexpr int row(int v) { return 8 * (v / 4) + (v % 4); }
+    __device__ __forceinline__ bool whole(long long M) const { return r0 + 32 <= M; }
+    template <typename P>
+    __device__ __forceinline__ P& at(P* p, long long ld, int v) const {
+        return (p + (r0 + row(v)) * ld + c0)[(uint32_t)(lr * (int)ld + lc)];
+    }
 };
-template <typename F>
-__device__ __forceinline__ void tile_rows(long long r0, long long M, F&& body) {
-    if (M - r0 > 27) body(TileRows<true>{M - r0});
-    else body(TileRows<false>{M - r0});
-}
 
 template <typename E, typename = void> struct has_rows_epilogue : std::false_type {};
 template <typename E> struct has_rows_epilogue<E, std::enable_if_t<E::kRows>> : std::true_type {};
 
 template <typename T, int BM, int BN, int WM, int WN, typename Epi>
-__global__ __launch_bounds__(256) void gemm_nt_kernel(GemmArgs g, Epi epi) {
+__global__ __launch_bounds__(256, BN == 128 ? 3 : 4) void gemm_nt_kernel(GemmArgs g, Epi epi) {
     static_assert(WM * WN == 4, "four wavefronts per workgroup");
     constexpr int TM = BM / (WM * 32), TN = BN / (WN * 32);
     static_assert(TM >= 1 && TN >= 1, "tile too small for the wavefront grid");
@@ -310,21 +319,21 @@ struct EpiResidual {
         float out = (c < N) ? Y[r * ldY + c] - v : 0.f;
         Elem<TO>::store(R + r * ldR + c, out);
     }
-    // one lane's 16 accumulators of a tile (rows r0 + 8 (v / 4) + v % 4): all reads before the first store, which the
-    // compiler cannot tell from them
+    // one lane's 16 accumulators of a tile; a tile that ends beyond the last row goes element by element
     static constexpr bool kRows = true;
     __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {
-        if (c >= ldR || r0 >= M) return;
-        tile_rows(r0, M, [&](auto off) {
-            const float* yr = Y + r0 * ldY + (c < N ? c : N - 1);
-            TO* out = R + r0 * ldR + c;
-            float y[16];
+        const TileRows t(r0, c);
+        if (!t.whole(M)) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) y[v] = yr[off.read(v) * ldY];
+            for (int v = 0; v < 16; ++v) (*this)(0, t.r0 + t.lr + t.row(v), t.c0 + t.lc, acc[v]);
+            return;
+        }
+        if (c >= ldR) return;
+        float y[16];
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (off.in(v)) Elem<TO>::store(out + off(v) * ldR, c < N ? y[v] - acc[v] : 0.f);
-        });
+        for (int v = 0; v < 16; ++v) y[v] = c < N ? t.at(Y, ldY, v) : 0.f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) Elem<TO>::store(&t.at(R, ldR, v), c < N ? y[v] - acc[v] : 0.f);
     }
 };
 
@@ -352,26 +361,28 @@ struct EpiIstaUpdate {
     }
     static constexpr bool kRows = true;       // as EpiResidual::rows
     __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {
-        if (c >= ldS || r0 >= M) return;
-        tile_rows(r0, M, [&](auto off) {
-            const long long at = r0 * ldS + c;
-            float old[16];
-            if (!first) {
+        const TileRows t(r0, c);
+        if (!t.whole(M)) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) old[v] = Xs[at + off.read(v) * ldS];
-            }
+            for (int v = 0; v < 16; ++v) (*this)(0, t.r0 + t.lr + t.row(v), t.c0 + t.lc, acc[v]);
+            return;
+        }
+        if (c >= ldS) return;
+        float old[16];
+        if (!first) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                float u = mu * acc[v];
-                if (!first) u += old[v];
-                const float a = fabsf(u) - theta;
-                const float x = c < N && a > 0.f ? copysignf(a, u) : 0.f;
-                if (!off.in(v)) continue;
-                if (Xo && c < N) Xo[(r0 + off(v)) * (long long)N + c] = x;
-                Xs[at + off(v) * ldS] = x;
-                if (Xb) Xb[at + off(v) * ldS] = f2bf(x);
-            }
-        });
+            for (int v = 0; v < 16; ++v) old[v] = t.at(Xs, ldS, v);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            float u = mu * acc[v];
+            if (!first) u += old[v];
+            const float a = fabsf(u) - theta;
+            const float x = c < N && a > 0.f ? copysignf(a, u) : 0.f;
+            if (Xo && c < N) t.at(Xo, N, v) = x;
+            t.at(Xs, ldS, v) = x;
+            if (Xb) t.at(Xb, ldS, v) = f2bf(x);
+        }
     }
 };
 
@@ -400,25 +411,27 @@ struct EpiListaUpdate {
     }
     static constexpr bool kRows = true;       // as EpiResidual::rows
     __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {
-        if (c >= ldS || r0 >= M) return;
-        tile_rows(r0, M, [&](auto off) {
-            const long long at = r0 * ldS + c;
-            float old[16], w[16];
+        const TileRows t(r0, c);
+        if (!t.whole(M)) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                old[v] = Xold[at + off.read(v) * ldS];
-                w[v] = W[at + off.read(v) * ldS];
-            }
+            for (int v = 0; v < 16; ++v) (*this)(0, t.r0 + t.lr + t.row(v), t.c0 + t.lc, acc[v]);
+            return;
+        }
+        if (c >= ldS) return;
+        float old[16], w[16];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float u = old[v] + acc[v] + w[v];
-                const float x = c < N ? u - __builtin_amdgcn_fmed3f(u, -theta, theta) : 0.f;
-                if (!off.in(v)) continue;
-                if (Xo && c < N) Xo[(r0 + off(v)) * (long long)N + c] = x;
-                Xnew[at + off(v) * ldS] = x;
-                if (Xb) Xb[at + off(v) * ldS] = f2bf(x);
-            }
-        });
+        for (int v = 0; v < 16; ++v) {
+            old[v] = t.at(Xold, ldS, v);
+            w[v] = t.at(W, ldS, v);
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const float u = old[v] + acc[v] + w[v];
+            const float x = c < N ? u - __builtin_amdgcn_fmed3f(u, -theta, theta) : 0.f;
+            if (Xo && c < N) t.at(Xo, N, v) = x;
+            t.at(Xnew, ldS, v) = x;
+            if (Xb) t.at(Xb, ldS, v) = f2bf(x);
+        }
     }
 };
 

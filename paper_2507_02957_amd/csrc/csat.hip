@@ -379,7 +379,10 @@ template <typename TI, typename TO>
 csat_status pack_rows(const TI* src, long long lds_, TO* dst, long long ldd, long long rows, int cols, hipStream_t st) {
     const int vec = lds_ % 4 == 0 && ldd % 4 == 0 && reinterpret_cast<uintptr_t>(src) % (4 * sizeof(TI)) == 0 &&
                     reinterpret_cast<uintptr_t>(dst) % (4 * sizeof(TO)) == 0;
-    hipLaunchKernelGGL((pack_rows_kernel<TI, TO>), dim3((unsigned)((rows + 3) / 4), (unsigned)((ldd + kPackCols - 1) / kPackCols)), dim3(256), 0, st, src, lds_, dst, ldd, rows, cols, vec);
+    int lshift = 0;      // lanes per row: four columns each, at most a wavefront
+    while (lshift < 6 && (4ll << lshift) < ldd) ++lshift;
+    hipLaunchKernelGGL((pack_rows_kernel<TI, TO>), dim3((unsigned)(((rows << lshift) + 255) / 256), (unsigned)((ldd + kPackCols - 1) / kPackCols)), dim3(256), 0, st,
+                       src, lds_, dst, ldd, rows, cols, vec, lshift);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }

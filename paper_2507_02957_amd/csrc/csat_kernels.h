@@ -694,22 +694,23 @@ template <typename E> struct has_tile_epilogue<E, std::enable_if_t<E::kTile>> : 
 // Layout helpers (HBM-bound, off the dominant path).
 // ----------------------------------------------------------------------------------------
 
-// dst[r][0..ldd) = convert(src[r][0..cols)) with zero fill up to ldd.  A wavefront per row and kPackCols columns (few long
-// rows, like Phi's, still fill the chip), four elements per lane; vec: rows
-// of both sides 16-byte (float) or 8-byte (bf16) aligned in steps of four elements.  Bound by memory: 76 800 x 392 floats to
-// bf16 82 us with a thread per element, which spent its time on the row's 64-bit division; 37 us now.
+// dst[r][0..ldd) = convert(src[r][0..cols)) with zero fill up to ldd.  2^lshift lanes per row and four times as many columns (a
+// whole wavefront per kPackCols columns of a long row; few long rows, like Phi's, still fill the chip), four elements per
+// lane; vec: rows of both sides 16-byte (float) or 8-byte (bf16) aligned in steps of four elements.  Bound by memory:
+// 76 800 x 392 floats to bf16 82 us with a thread per element, which spent its time on the row's 64-bit division; 37 us
+// now.  80 000 x 8 floats: 9 us with a wavefront per row, of which two lanes had work, 3 us now.
 constexpr int kPackCols = 256;
 template <typename TI, typename TO>
-__global__ __launch_bounds__(256) void pack_rows_kernel(const TI* __restrict__ src, long long lds_, TO* __restrict__ dst, long long ldd, long long rows, int cols, int vec) {
-    const int lane = threadIdx.x & 63;
-    const long long r = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+__global__ __launch_bounds__(256) void pack_rows_kernel(const TI* __restrict__ src, long long lds_, TO* __restrict__ dst, long long ldd, long long rows, int cols, int vec, int lshift) {
+    const int lanes = 1 << lshift, lane = threadIdx.x & (lanes - 1);
+    const long long r = ((long long)blockIdx.x * 256 + threadIdx.x) >> lshift;
     if (r >= rows) return;
     const TI* s = src + r * lds_;
     TO* d = dst + r * ldd;
     if (!vec) {
 #pragma unroll
-        for (int i = 0; i < kPackCols / 64; ++i) {
-            const long long c = (long long)blockIdx.y * kPackCols + lane + 64 * i;
+        for (int i = 0; i < 4; ++i) {
+            const long long c = (long long)blockIdx.y * kPackCols + lane + lanes * i;
             if (c < ldd) Elem<TO>::store(d + c, c < cols ? Elem<TI>::load(s + c) : 0.f);
         }
         return;

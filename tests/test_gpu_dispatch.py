@@ -336,6 +336,43 @@ def test_float_decoder_in_lds_leaves_the_range_of_float(n_q, n, m, options):
                 assert_close(f"finite rows, {iters} iterations", got[rows_ok], old[rows_ok], TOL["f32"], slices_axis0=False)
 
 
+# widths around the lanes a row gets (four columns each: 1, 2, 4 ... 64), one beyond a wavefront's 256 columns; aligned and not
+@pytest.mark.parametrize("dtype,m", [("f32", 3), ("f32", 8), ("f32", 9), ("f32", 33), ("f32", 64), ("f32", 130), ("f32", 257), ("bf16", 20), ("bf16", 63), ("bf16", 300)])
+def test_row_packing_widths(dtype, m, options):
+    """One iteration without a threshold is X = mu Phi^T y on the packed rows of y and the packed Phi; the workspace holds
+    NaN patterns, so a pad that was not written shows."""
+    rows, n = 37, max(m, 40) + 1
+    w = _small("pack_widths", B=1, H=1, n_q=rows, n=n, d=8, m=m, dtype=dtype, iters=1)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    p = _problem(w, Q, K, V, Phi)
+    options("decoder", 1)
+    Y = gen.quantize(np.random.default_rng(m).standard_normal((1, rows, m)).astype(np.float32), dtype)
+    X = p.empty(1, rows, n, dtype=torch.float32)
+    csat.csat_recover(p.dims, to_dev(Y, "f32"), p.Phi, 0.0, 0.5, 1, X, None, None, p.ws)
+    torch.cuda.synchronize()
+    assert_close("X", to_np(X)[0], 0.5 * (Y[0].astype(np.float64) @ Phi.astype(np.float64)), TOL[dtype], slices_axis0=False)
+
+
+def test_more_rows_than_wavefronts_fit_a_launch():
+    """2^26 rows of eight: a wavefront per row would be more threads than a launch may have."""
+    rows, n, m, d = (1 << 26) + 70, 9, 8, 8
+    free, _ = torch.cuda.mem_get_info()
+    if free < 40 << 30:
+        pytest.skip("needs 40 GB")
+    dims = csat.make_dims(1, 1, rows, n, d, m, "f32")
+    Phi = gen.make_phi("gaussian", m, n, seed=3)
+    V = np.random.default_rng(4).standard_normal((n, d)).astype(np.float32)
+    Y = torch.randn(rows, m, device=DEV)
+    C = torch.empty(rows, d, device=DEV)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, 1), dtype=torch.uint8, device=DEV)
+    csat.csat_recover(dims, Y, to_dev(Phi, "f32"), 0.0, 0.5, 1, None, to_dev(V, "f32"), C, ws)
+    torch.cuda.synchronize()
+    at = torch.tensor([0, 1, rows // 2, rows - 65, rows - 1], device=DEV)
+    y = to_np(Y[at])
+    assert_close("C", to_np(C[at]), 0.5 * (y @ Phi.astype(np.float64)) @ V.astype(np.float64), TOL["f32"], slices_axis0=False)
+
+
 # (n_q, n, m, iterations): the fewest chunks this decoder gets, one to thirteen tiles of m (odd and even), odd and even
 # chunk counts modulo its ring of five, a ragged last chunk and row tile, one and two iterations
 SHARED_TILE_CASES = [(33, 513, 20, 4), (40, 544, 64, 3), (64, 577, 90, 1), (31, 700, 128, 2), (70, 609, 160, 5), (32, 416, 416, 3), (5, 500, 390, 4),

@@ -366,11 +366,13 @@ csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi
 // The ISTA decoder's products and its synthesis: in float, on the bf16 matrix cores (csat_gemm_f32.h).  The measurement,
 // the output product, the unrolled decoder's layers and matching pursuit's correlations stay on the float MFMA: no
 // case spends its time on the first two, and what the last two amplify (a layer's S is not a contraction; a pick is a
-// comparison) would move their outputs further than two correct float implementations are allowed to differ.
+// comparison) would move their outputs further than two correct float implementations are allowed to differ.  Narrow
+// products over a contraction of one step stay there too: the split's start costs more than it saves (one iteration of
+// 256 to 20 000 rows, n = 40 or 64, m = 8 or 32: 23 to 26.5 us against 25 to 28; n = 200 33 to 46 against 32 to 39).
 template <typename T, typename Epi>
 csat_status decoder_gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
-        if (gemm_choice() != 1) return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
+        if (gemm_choice() != 1 && (g.K > 32 || n_cover > 128)) return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
     }
     return gemm<T>(g, n_cover, batch, epi, st);
 }

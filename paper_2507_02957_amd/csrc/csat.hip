@@ -267,11 +267,6 @@ bool decoder_options_free() {
 bool decoder_is_resident(const Workspace& w) {
     return decoder_options_free() && w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
 }
-// ... and its float form.  (One iteration is one product: nothing to keep in LDS.)
-bool decoder_is_resident_f32(const csat_dims& d, const Workspace& w, int iters) {
-    return d.dtype == CSAT_F32 && iters >= 2 && decoder_options_free() && gemm_choice() != 1 && ista_resident_f32_chunks(w.MT, w.nct) != 0;
-}
-
 // CUs of the current device (persistent grids and work-distribution heuristics)
 int cu_count() {
     static const int n = [] {
@@ -281,6 +276,15 @@ int cu_count() {
         return v;
     }();
     return n;
+}
+
+// ... and its float form.  One iteration is one product: nothing to keep in LDS.  Every 32-row tile splits Phi anew, so two
+// or three iterations of many tiles are better off on the products unless Phi is one tile of m (n = 64, m = 64, two
+// iterations: 20 000 rows 42 us against 54 on the products, 80 000 rows 116 against 96, 200 000 rows 274 against 189, three
+// iterations 333 against 282; m = 32: 64 against 86 and 135 against 158).
+bool decoder_is_resident_f32(const csat_dims& d, const Workspace& w, int iters) {
+    return d.dtype == CSAT_F32 && iters >= 2 && decoder_options_free() && gemm_choice() != 1 && ista_resident_f32_chunks(w.MT, w.nct) != 0 &&
+           (iters >= 4 || w.MT == 1 || w.rows_pad / 32 <= 4ll * cu_count());
 }
 
 struct Timed {   // brackets the launches issued during its lifetime

@@ -336,6 +336,28 @@ def test_float_decoder_in_lds_leaves_the_range_of_float(n_q, n, m, options):
                 assert_close(f"finite rows, {iters} iterations", got[rows_ok], old[rows_ok], TOL["f32"], slices_axis0=False)
 
 
+# (rows, m, iterations, in LDS): two or three iterations of more than four tiles per CU go to the products if Phi is more than
+# one tile of m
+@pytest.mark.parametrize("rows,m,iters,resident", [(32768, 40, 2, True), (32769, 40, 3, False), (32769, 32, 2, True), (32769, 40, 4, True)])
+def test_float_decoder_of_many_rows(rows, m, iters, resident):
+    n, d = 70, 8
+    dims = csat.make_dims(1, 1, rows, n, d, m, "f32")
+    Phi = gen.make_phi("gaussian", m, n, seed=5).astype(np.float32)
+    mu = _mu(Phi)
+    Y = np.random.default_rng(m).standard_normal((rows, m)).astype(np.float32)
+    X = torch.empty(rows, n, device=DEV)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    csat.csat_recover(dims, to_dev(Y, "f32"), to_dev(Phi, "f32"), 0.1, mu, iters, X, None, None, ws)
+    torch.cuda.synchronize()
+    assert csat.csat_profile_decoder_kernel() == (5 if resident else -1)
+    at = np.array([0, 31, 32, rows // 2, rows - 2, rows - 1])
+    P, x = Phi.astype(np.float64), np.zeros((len(at), n))
+    for _ in range(iters):
+        u = x + mu * ((Y[at].astype(np.float64) - x @ P.T) @ P)
+        x = np.sign(u) * np.maximum(np.abs(u) - mu * 0.1, 0)
+    assert_close("X", to_np(X[torch.from_numpy(at).to(DEV)]), x, TOL["f32"], slices_axis0=False)
+
+
 # widths around the lanes a row gets (four columns each: 1, 2, 4 ... 64), one beyond a wavefront's 256 columns; aligned and not
 @pytest.mark.parametrize("dtype,m", [("f32", 3), ("f32", 8), ("f32", 9), ("f32", 33), ("f32", 64), ("f32", 130), ("f32", 257), ("bf16", 20), ("bf16", 63), ("bf16", 300)])
 def test_row_packing_widths(dtype, m, options):

@@ -508,9 +508,14 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
         else hipLaunchKernelGGL((measure_direct_kernel<DT, KS, PD, false, KG>), grid, dim3(256 * KG), 0, st, a);        \
     } while (0)
             const bool deep = d.n >= 4096;
-            // No more workgroups than CUs: two groups of wavefronts split the contraction (csat_measure.h), once it is long
-            // enough to pay for the meeting of the sums.
-            const bool two = (long long)BH * a.blocks_per_head <= cu_count() && d.n >= 512;
+            // No more workgroups than CUs: two groups of wavefronts split the contraction (csat_measure.h).  They walk n in
+            // rounds of 512 rows (d = 64) or 256 (d = 128), one group in rounds of 128, or 256 from n = 4096 on, so a
+            // round that is mostly empty can cost more than they save: d = 64, 48 heads, m = 256: n = 512 8.0 us with one
+            // group and 8.5 with two, 700 12.3 and 13.9, 1024 12.1 and 11.5, 1600 17.1 and 17.6, 2048 20.0 and 17.6, 8192 61.8 and
+            // 51.3; d = 128, 12 heads, m = 256: n = 512 12.2 and 10.5, 1600 29.3 and 22.6.  With more heads than half the CUs
+            // memory is the bound (d = 64, 256 heads, m = 64: n = 700 13.4 and 16.7, 4096 42.4 and 44.6).
+            const bool rounds_full = d.d == 128 ? d.n >= 512 : d.n >= 2048 || (d.n >= 1024 && (d.n - 1) % 512 >= 384);
+            const bool two = (long long)BH * a.blocks_per_head <= cu_count() && 2 * BH <= cu_count() && rounds_full;
             if (d.d == 64) { if (two) MD(2, 64, 4, 2); else if (deep) MD(2, 64, 4, 1); else MD(2, 64, 2, 1); }
             else { if (two) MD(4, 32, 4, 2); else if (deep) MD(4, 64, 4, 1); else MD(4, 64, 2, 1); }
 #undef MD

@@ -139,8 +139,10 @@ def test_compressed_attention_of_large_values(d, m):
     assert_close("Z", to_np(Zg), want, TOL["bf16"])
 
 
-# few workgroups and a long contraction: two groups of wavefronts split it (n = 512 is where that begins; 511 stays with one)
+# few workgroups and a long contraction: two groups of wavefronts split it (from n = 512 on at d = 128; at d = 64 from 1024 on
+# where the last round of 512 is at least three quarters full, and from 2048 on always)
 @pytest.mark.parametrize("n,m,d,zero_iters", [(511, 40, 64, True), (512, 40, 64, True), (700, 97, 128, True), (1025, 64, 128, False),
+                                              (511, 40, 128, True), (512, 40, 128, False), (1024, 40, 64, True), (1408, 70, 64, False), (1409, 70, 64, True), (2050, 33, 64, True),
                                               (1500, 33, 64, False), (4097, 65, 64, True)])
 def test_measurement_with_a_split_contraction(n, m, d, zero_iters, options):
     w = _small("split", B=1, H=3, n_q=40, n=n, d=d, m=m, dtype="bf16", iters=0 if zero_iters else 2, lam=0.02)

@@ -526,14 +526,24 @@ csat_status run_measure(const csat_dims& d, const Workspace& w, const T* K, cons
     }
     // Both products in one launch (and both transposes) where they share the matrix and the copies are adjacent: small
     // problems are bound by launches of a few workgroups (256 x 256, m = 64 in float: a launch of each kind less, 18 us).
-    const bool pair = !separate && want_v && 2ll * BH <= 65535 && w.VT == w.KT + (size_t)BH * d.d * w.ldn * sizeof(T);
+    const bool pair_t = !separate && want_v && 2ll * BH <= 65535 && w.VT == w.KT + (size_t)BH * d.d * w.ldn * sizeof(T);
+    // The products of 128-wide tiles run three workgroups per CU, so what one launch saves or costs is in how full the last
+    // round is (cost of a round of one, two and three per CU: 1.6 : 2.2 : 3, from float, d = 128, n = 1024): 48 heads, m = 1024 (384
+    // workgroups each) 231 us against 304 with two launches, 128 heads, m = 392 (512 each) 392 against 356, 256 heads (1024) n = 512
+    // 382 against 412.  64-wide tiles (d <= 64): one launch is never slower.
+    auto rounds = [](long long tiles) {
+        const long long cus = cu_count(), rest = tiles % (3 * cus);
+        return tiles / (3 * cus) * 30 + (rest == 0 ? 0 : rest <= cus ? 16 : rest <= 2 * cus ? 22 : 30);
+    };
+    const long long tiles = (long long)BH * ((d.m + 127) / 128) * ((d.d + 127) / 128);
+    const bool pair = pair_t && (d.d <= 64 || rounds(2 * tiles) <= 2 * rounds(tiles));
     // Phi as the caller holds it where that is the operand layout already
     const void* A = PhiV && !separate && phi_is_operand<T>(d, PhiV) ? (const void*)PhiV : w.PhiP;
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
-        CSAT_TRY(transpose_pack<T>(K, (T*)w.KT, w.ldn, BH, d.n, d.d, st, pair ? V : nullptr));
+        CSAT_TRY(transpose_pack<T>(K, (T*)w.KT, w.ldn, BH, d.n, d.d, st, pair_t ? V : nullptr));
         // (vt_ready says what the caller needs afterwards; the V product below reads the transposed copy either way)
-        if (!pair && (!vt_ready || want_v)) CSAT_TRY(transpose_pack<T>(V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
+        if (!pair_t && (!vt_ready || want_v)) CSAT_TRY(transpose_pack<T>(V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
         if (VcT && w.ldm > d.m) CSAT_TRY(fill_zero(VcT, (size_t)BH * d.d * w.ldm * sizeof(T), st));
     }
     if (separate) {

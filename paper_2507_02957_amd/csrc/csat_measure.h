@@ -71,8 +71,10 @@ __global__ __launch_bounds__(256 * KG) void measure_direct_kernel(MeasureDirectA
     constexpr int STAGE = OFF_A + MROWS * PA;
     static_assert(DT == 2 || DT == 4, "d = 64 or 128");
     __shared__ __attribute__((aligned(16))) char lds_all[KG * 2 * STAGE];      // [group][stage][K | V (if wanted) | Phi]
-    // (no mask for one group: with it the compiler loses the offsets it can fold; synthesis of 32 rows, n = 2048, 16.6 -> 18.4 us)
-    const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0, tid = KG > 1 ? threadIdx.x & 255 : threadIdx.x;
+    // (The mask changes what the compiler makes of one group's addresses, measured both ways: without V~ it costs, synthesis of
+    // 32 rows, n = 2048, 16.6 -> 18.4 us; with V~ it gains, d = 128, 128 heads, m = 392, n = 1600, 112 -> 102 us.)
+    constexpr bool kMask = KG > 1 || WANT_V;
+    const int kg = KG > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0, tid = kMask ? threadIdx.x & 255 : threadIdx.x;
     char* const lds = lds_all + kg * 2 * STAGE;
     // workgroup id -> (head, block of tiles): XCD x = id % 8 takes heads x, x + 8, ...
     const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;

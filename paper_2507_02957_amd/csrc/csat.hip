@@ -676,10 +676,18 @@ bool attention_is_fused(const csat_dims& d, const Workspace& w, bool split_k) {
 }
 
 // Whether a call that wants Z but not A~ takes the kernel that never stores A~ (csat_attention_z.h): bf16, d a multiple
-// of 32 up to 128, every m and n_q.
+// of 32 up to 128.  parts: 2 where K~ comes as its (hi | lo) pair.  A short query side is one workgroup per head that walks
+// all of m, where the three kernels spread m over workgroups; that shows at d = 128, whose workgroups have a CU each
+// (kAttnZChain fragments per tile of m and more), with few heads.  Stage call, d = 128, m = 1024, one query: 4 heads 30 us
+// against 35 without A~, 48 heads 39 against 42, 192 heads 99 against 98; 33 queries 33 and 35, 65 queries 36 and 36, 300 queries
+// 69 and 37; m = 512, one query: 24 and 23.  As a pair, m = 1024, 4 heads: one query 53 and 58, 200 queries 61 and 65, 300
+// queries 101 and 67.  At d = 32 to 96 nothing like it (one query, m = 1024: d = 64 26 and 24, d = 96 30 and 31).
+constexpr long long kAttnZChain = 384;
 template <typename T>
-bool attention_z_applies(const csat_dims& d) {
-    return sizeof(T) == 2 && d.d % 32 == 0 && d.d <= 128 && (*tl_opt)[CSAT_OPT_ATTENTION] == 0;
+bool attention_z_applies(const csat_dims& d, int parts) {
+    if (sizeof(T) != 2 || d.d % 32 != 0 || d.d > 128 || (*tl_opt)[CSAT_OPT_ATTENTION] != 0) return false;
+    const long long chain = (d.m + 31) / 32 * (long long)(parts + 1) * (d.d / 16);
+    return !(d.d == 128 && chain >= kAttnZChain && (long long)d.B * d.H <= 48 && d.n_q <= (parts == 2 ? 255 : 64));
 }
 // Z and / or ZT (see run_attention) without A~.  Ksrc: K~ rows [BH][m][kparts * d]; Vc: V~ rows.  kc_packed / v_packed: their
 // fragments are in w.KcPack / w.VcT already.
@@ -1051,7 +1059,7 @@ template <typename T>
 csat_status attention_t(const csat_dims& d, const Workspace& w, const void* Q, const void* Kc, const void* Vc,
                         float* A, void* Z, hipStream_t st) {
     const int BH = d.B * d.H;
-    if (!A && attention_z_applies<T>(d))
+    if (!A && attention_z_applies<T>(d, 1))
         return run_attention_z<T>(d, w, (const T*)Q, (const T*)Kc, 1, false, (const T*)Vc, false, (T*)Z, (T*)nullptr, st);
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
@@ -1094,7 +1102,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
     bool kc_packed = false, v_packed = false;
     const bool direct = measure_is_direct<T>(d, separate);
     // no decoder: A~ is not wanted
-    const bool z_only = iters == 0 && attention_z_applies<T>(d);
+    const bool z_only = iters == 0 && attention_z_applies<T>(d, 2);
     // (then nothing reads V^T: the one-kernel measurement takes V as it is)
     const bool syn = iters > 0 && synthesis_in_decoder(d, w) && direct;
     CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, need_z && (direct || !z_only) ? (T*)w.VcT : nullptr,
@@ -1154,7 +1162,7 @@ csat_status forward_rd_t(const csat_dims& d, const Workspace& w, const Workspace
     const long long rows = (long long)BH * d.d;          // decoder problems
     const csat_dims dr = rd_dims(d);
     CSAT_TRY(prepare_phi<T>(d, w, (const T*)Phi, true, 0, st));
-    const bool direct = measure_is_direct<T>(d, PhiK && PhiK != Phi), z_only = attention_z_applies<T>(d);
+    const bool direct = measure_is_direct<T>(d, PhiK && PhiK != Phi), z_only = attention_z_applies<T>(d, 2);
     bool kc_packed = false, v_packed = false;
     CSAT_TRY(run_measure<T>(d, w, (const T*)K, (const T*)V, (T*)w.Kc, (T*)w.Vc, direct || !z_only ? (T*)w.VcT : nullptr,
                             direct, true, st, (const T*)PhiK, (const T*)Phi, true, z_only ? &kc_packed : nullptr, z_only ? &v_packed : nullptr));
@@ -1490,7 +1498,7 @@ csat_status forward_hadamard_t(const csat_dims& d, const Workspace& w, const voi
     CSAT_TRY(measure_hadamard_t<T>(d, rows_of_h, signs, K, V, w.Kc, w.Vc, w.prof, st, kBf16 ? w.KcHL : nullptr));
     const bool need_z = Z || iters == 0;
     T* zdst = (iters == 0) ? (T*)C : (T*)Z;
-    if (iters == 0 && attention_z_applies<T>(d)) {
+    if (iters == 0 && attention_z_applies<T>(d, 2)) {
         CSAT_TRY(run_attention_z<T>(d, w, (const T*)Q, (const T*)w.KcHL, 2, false, (const T*)w.Vc, false, zdst, (T*)nullptr, st));
     } else {
         if (need_z) {
@@ -1520,7 +1528,7 @@ csat_status forward_rd_hadamard_t(const csat_dims& d, const Workspace& w, const 
     const csat_dims dr = rd_dims(d);
     CSAT_TRY(measure_hadamard_t<T>(d, rows_of_h, signs, K, V, w.Kc, w.Vc, w.prof, st, kBf16 ? w.KcHL : nullptr));
     auto attention = [&](T* Zdst, T* ZTdst) -> csat_status {      // (nothing here reads A~)
-        if (attention_z_applies<T>(d))
+        if (attention_z_applies<T>(d, 2))
             return run_attention_z<T>(d, w, (const T*)Q, (const T*)w.KcHL, 2, false, (const T*)w.Vc, false, Zdst, ZTdst, st);
         {
             Timed tm(w, CSAT_K_LAYOUT, st);

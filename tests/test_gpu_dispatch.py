@@ -41,7 +41,9 @@ def test_separate_matrices_read_only_what_the_call_wrote(d, iters):
 # n_q around a wavefront's 32 rows and a workgroup's 256; m around a tile, around the last pair of tiles and on both
 # sides of what fits LDS (d = 64: 20 tiles; d = 128: 10)
 Z_ONLY_CASES = [(1, 5, 5, 32), (33, 31, 31, 32), (32, 33, 33, 64), (257, 96, 64, 64), (70, 640, 640, 64), (70, 641, 641, 64),
-                (300, 1100, 1055, 64), (65, 200, 97, 96), (40, 320, 320, 128), (290, 330, 321, 128), (1, 400, 353, 128)]
+                (300, 1100, 1055, 64), (65, 200, 97, 96), (40, 320, 320, 128), (290, 330, 321, 128), (1, 400, 353, 128),
+                # the lines between that kernel and the three for a short query side at d = 128
+                (64, 740, 737, 128), (65, 740, 737, 128), (64, 736, 736, 128), (255, 490, 490, 128), (256, 490, 490, 128), (33, 480, 480, 128)]
 
 
 @pytest.mark.parametrize("n_q,n,m,d", Z_ONLY_CASES)

@@ -1349,9 +1349,12 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
     }
     for (int it = 0; it < k; ++it) {
         // correlations of every residual with every column, and each row's largest: in the product's epilogue where the
-        // large-tile kernel runs (EpiOmpBest; the same picks)
+        // large-tile kernel runs (EpiOmpBest; the same picks) and has more to do than a few tiles, whose epilogue then takes
+        // longer than the search's own launch: 16 picks, m = 32, n = 128 (one column tile): 1024 rows 334 us against 305 with the
+        // search, 4096 rows 4 % more, 8192 rows 5 % less; n = 300: 1024 rows 337 against 328, 4096 rows 4 % less; n = 640: 1024 rows 2 % less.
         GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
-        const bool in_product = use_big_gemm<T>(g, d.n);
+        const long long col_tiles = (d.n + 255) / 256;
+        const bool in_product = use_big_gemm<T>(g, d.n) && (col_tiles >= 3 || rows * col_tiles >= 8192);
         OmpCand* cand = in_product ? (OmpCand*)x.Cm : nullptr;
         const int nseg = (d.n + 127) / 128;
         {

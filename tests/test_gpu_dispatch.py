@@ -430,7 +430,9 @@ def test_decoder_with_a_tile_shared_by_eight_wavefronts(n_q, n, m, iters, option
 
 # (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
 # picked in the end (m = n = picks), several column tiles
-PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20)]
+PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20),
+              # ... the product takes over from the search at 8192 rows times column tiles, or three column tiles
+              (2730, 128, 20, 5), (2731, 128, 20, 5), (1365, 257, 30, 9), (1366, 512, 30, 9), (90, 512, 40, 3)]
 
 
 @pytest.mark.parametrize("n_q,n,m,picks", PICK_CASES)

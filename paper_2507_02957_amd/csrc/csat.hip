@@ -825,18 +825,23 @@ int fused_segments(long long groups, int iters, int cus, double overhead) {
 }
 
 // Which fused decoder kernel a launch gets: 0 / 1 one chunk per step with dense / sparse state, 2 one 32-row tile per
-// workgroup, 3 / 4 two chunks per step with dense / sparse state.
-int fused_variant(int MT, long long rows_pad, int nct) {
+// workgroup, 3 / 4 two chunks per step with dense / sparse state, 6 one 32-row tile shared by eight wavefronts.  iters only
+// decides between 2 and 6.
+int fused_variant(int MT, long long rows_pad, int nct, int iters) {
     const int cus = cu_count();
-    // few rows: one 32-row tile per workgroup, so that every tile has a CU of its own
     // Few rows: eight wavefronts share a tile, one tile per CU at a time (csat_ista_coop.h).  A CU's 128-row group takes
     // about as long as two such tiles at thirteen tiles of m (0.59 against 1.08 us a chunk) and as three at three (0.24
     // against 0.7), so the line is at one tile per CU, two up to four tiles of m.  Measured, forward of 10 iterations:
     // m = 392, 300 tiles 682 against 631 us on groups; m = 192, 256 tiles 190 against 202 (with a single wavefront per
     // tile), 512 tiles 334 against 329; m = 90, 384 tiles 195 against 285, 512 tiles 234 against 312; m = 40, 304 tiles
-    // 114 against 182, 608 tiles 207 against 190.
-    if (decoder_options_free() && MT <= kCoopMaxMT && rows_pad / 32 <= (MT <= 4 ? 2 : 1) * cus) return 6;
-    const bool thin = rows_pad / 32 <= cus && (*tl_opt)[CSAT_OPT_FUSED_THIN] != 1;      // (14 tiles of m and more: only when forced)
+    // 114 against 182, 608 tiles 207 against 190; m = 128, n = 1600, 512 tiles 350 against 486.  Not for two or
+    // three iterations over an iterate larger than the Infinity Cache: that is bound by memory, and one wavefront per tile
+    // leaves more of it to the loads (n = 16 384, 256 tiles, m = 200: two iterations 1053 us with a wavefront per tile, 1315 with
+    // eight, three 1477 and 1655, ten 0.9 of the time with eight; at 256 MB, n = 8192, two 0.87).
+    const bool streams = iters <= 3 && (long long)rows_pad * nct * 128 > 256ll << 20;
+    if (decoder_options_free() && MT <= kCoopMaxMT && rows_pad / 32 <= (MT <= 4 ? 2 : 1) * cus && !(streams && rows_pad / 32 <= cus)) return 6;
+    // (one 32-row tile per workgroup; 14 tiles of m and more: only when forced)
+    const bool thin = rows_pad / 32 <= cus && (*tl_opt)[CSAT_OPT_FUSED_THIN] != 1;
     int variant = thin ? 2 : (sparse_state((size_t)rows_pad * nct * 32 * 4) ? 1 : 0);
     // 128-row workgroups on rows of at least five chunks and three tiles of m: two chunks per step (the schedule
     // looks two steps ahead, and spreads each threshold over more than one group of MFMAs)
@@ -850,7 +855,7 @@ int fused_variant(int MT, long long rows_pad, int nct) {
 // 32-row tiles per head, and V's fragments must fit the buffer of V^T they replace.
 bool synthesis_in_decoder(const csat_dims& d, const Workspace& w) {
     if (!w.fused || decoder_is_resident(w) || d.dtype != CSAT_BF16 || d.d != 64 || d.n_q % 32 != 0 || (*tl_opt)[CSAT_OPT_SYNTHESIS] >= 1) return false;
-    const int v = fused_variant(w.MT, w.rows_pad, w.nct);
+    const int v = fused_variant(w.MT, w.rows_pad, w.nct, 0);
     if (v != 3 && v != 4) return false;
     return (long long)((w.nct + 1) / 2 * 2) * 32 <= w.ldn;
 }
@@ -871,7 +876,7 @@ csat_status launch_ista_resident(const csat_dims& d, const Workspace& w, IstaRes
 
 csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipStream_t st) {
     const int cus = cu_count();
-    const int variant = fused_variant(MT, rows_pad, a.nct);
+    const int variant = fused_variant(MT, rows_pad, a.nct, a.iters);
     const bool thin = variant == 2;
     a.groups = variant == 6 ? (int)((a.rows + 31) / 32) : (int)(rows_pad / (thin ? 32 : 128));
     const int nct_real = a.nct;
@@ -1123,7 +1128,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
     bool y_tiled = false;
     if constexpr (sizeof(T) == 2) {
         y_tiled = iters > 0 && w.fused && !decoder_is_resident(w) && d.n_q % 32 == 0 && (*tl_opt)[CSAT_OPT_Y_LAYOUT] != 1 &&
-                  (fused_variant(w.MT, w.rows_pad, w.nct) == 3 || fused_variant(w.MT, w.rows_pad, w.nct) == 4) && attention_is_fused<T>(d, w, true) &&
+                  (fused_variant(w.MT, w.rows_pad, w.nct, iters) == 3 || fused_variant(w.MT, w.rows_pad, w.nct, iters) == 4) && attention_is_fused<T>(d, w, true) &&
                   attention_single_sweep(w.MT, 2 * ((d.d + 15) / 16)) &&
                   (v_packed || (!need_z && attention_mtp(w.MT, true) == 13));
     }

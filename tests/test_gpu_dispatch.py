@@ -405,6 +405,28 @@ SHARED_TILE_CASES = [(33, 513, 20, 4), (40, 544, 64, 3), (64, 577, 90, 1), (31, 
                      (97, 900, 217, 3), (160, 1600, 392, 2), (33, 353, 300, 6), (20, 330, 330, 2), (45, 1333, 352, 3)]
 
 
+@pytest.mark.parametrize("tiles,iters,kernel", [(130, 3, 2), (130, 4, 6), (128, 2, 6)])
+def test_few_iterations_over_an_iterate_beyond_the_infinity_cache(tiles, iters, kernel, options):
+    """Two or three iterations over more than 256 MB of iterate stay with one wavefront per 32-row tile; same bits."""
+    rows, n, m, d = 32 * tiles, 16384, 40, 64
+    dims = csat.make_dims(1, 1, rows, n, d, m, "bf16")
+    Phi = gen.quantize(gen.make_phi("gaussian", m, n, seed=9).astype(np.float32), "bf16")
+    rng = np.random.default_rng(tiles)
+    Y = to_dev(rng.standard_normal((rows, m)).astype(np.float32), "f32")
+    V = to_dev(gen.quantize(rng.standard_normal((n, d)).astype(np.float32), "bf16"), "bf16")
+    ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    C, C1 = torch.empty(rows, d, dtype=torch.bfloat16, device=DEV), torch.empty(rows, d, dtype=torch.bfloat16, device=DEV)
+    csat.csat_recover(dims, Y, to_dev(Phi, "bf16"), 0.05, 0.002, iters, None, V, C, ws)
+    assert csat.csat_profile_decoder_kernel() == kernel
+    assert csat.csat_decoder_status(ws) == 0
+    options("fused_thin", 1)
+    csat.csat_recover(dims, Y, to_dev(Phi, "bf16"), 0.05, 0.002, iters, None, V, C1, ws)
+    torch.cuda.synchronize()
+    assert csat.csat_profile_decoder_kernel() in (0, 1)
+    assert C.isfinite().all() and C.abs().max() > 0
+    assert torch.equal(C, C1)
+
+
 @pytest.mark.parametrize("n_q,n,m,iters", SHARED_TILE_CASES)
 def test_decoder_with_a_tile_shared_by_eight_wavefronts(n_q, n, m, iters, options):
     """Launches with few rows and a Phi too large for LDS: the bits of the 128-row decoder, and the oracle."""

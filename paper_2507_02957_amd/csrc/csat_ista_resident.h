@@ -214,8 +214,9 @@ __global__ __launch_bounds__(256, 1) void ista_resident_kernel(IstaResidentArgs 
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int col = 32 * i + 8 * g + 4 * lh;
-                if (a.Xb && col < a.ldxb)      // (zero beyond n)
-                    *(uint2*)(a.Xb + row * a.ldxb + col) = uint2{f2bf_pk(x[i][4 * g], x[i][4 * g + 1]), f2bf_pk(x[i][4 * g + 2], x[i][4 * g + 3])};
+                if (a.Xb && col < a.ldxb)      // (zero beyond n; the instance's chunks beyond the row's hold NaN where y is infinite)
+                    *(uint2*)(a.Xb + row * a.ldxb + col) =
+                        i < nct ? uint2{f2bf_pk(x[i][4 * g], x[i][4 * g + 1]), f2bf_pk(x[i][4 * g + 2], x[i][4 * g + 3])} : uint2{0u, 0u};
                 if (a.Xout) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e)

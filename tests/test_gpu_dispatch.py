@@ -194,6 +194,28 @@ def test_decoder_with_phi_in_lds(n_q, n, m, iters, kernel, options):
     assert same
 
 
+def test_decoder_with_phi_in_lds_keeps_infinities_out_of_the_pads(options):
+    """11 chunks on the instance for 12, and a synthesis that reads the operand's pads: an infinite row of positive products is
+    infinite, as on the decoder that streams Phi, not NaN."""
+    n_q, n, m, d = 260, 352, 64, 136
+    w = _small("resident_pads", B=1, H=1, n_q=n_q, n=n, d=d, m=m, dtype="bf16", iters=1)
+    rng = np.random.default_rng(1)
+    draw = lambda *s: gen.quantize(rng.uniform(0.5, 1.0, s).astype(np.float32), "bf16")
+    p = _problem(w, draw(1, n_q, d), draw(1, n, d), draw(1, n, d), draw(m, n))
+    Y = rng.uniform(0.5, 1.0, (1, n_q, m)).astype(np.float32)
+    Y[0, 5, 7] = np.inf
+    out = []
+    for thin, kernel in ((0, (5,)), (1, (0, 1, 3, 4))):
+        options("fused_thin", thin)
+        X, C = p.recover(to_dev(Y, "f32"), 0.01, 0.01, 1)
+        torch.cuda.synchronize()
+        assert csat.csat_profile_decoder_kernel() in kernel
+        out.append((to_np(X), to_np(C)))
+    assert np.isposinf(out[1][1][0, 5]).all()
+    for a, b in zip(*out):
+        assert (np.isposinf(a) == np.isposinf(b)).all() and (np.isfinite(a) == np.isfinite(b)).all()
+
+
 # (rows, n, m): rows around the 128-row tile, columns around the 64-wide one, contractions around a step of 32 and shorter
 FLOAT_PRODUCTS = [(127, 130, 96), (128, 64, 64), (129, 65, 33), (5, 9, 8), (257, 1056, 130), (33, 33, 31), (1, 31, 1), (1025, 1099, 1000)]
 

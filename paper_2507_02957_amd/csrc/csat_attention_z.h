@@ -18,7 +18,7 @@
 //
 // Measured, stage call without A~ (rocprofv3): 48 heads x 8192 queries, m = 256, d = 64: 42 us plus 5 us of packing, where
 // the kernel that keeps whole rows plus a product GEMM took 197 + 78 + 10 us (it wrote A~ and its bf16 copy, 0.6 GB, and
-// read the copy back); floor: 100 MB of Q and Z = 21 us, 3.2e6 wavefront scores x 30 cycles of vector issue = 22 us.
+// read the copy back); floor: 100 MB of Q and Z = 21 us, 1.6e6 wavefront scores x 30 cycles of vector issue = 22 us.
 // 48 heads x 1600 queries, m = 392, K~ as a pair, Z^T wanted (two tiles at a time): 29 us against 86 + 44.
 #pragma once
 #include <cfloat>

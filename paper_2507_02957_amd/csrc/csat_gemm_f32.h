@@ -3,8 +3,9 @@
 // The float MFMA (32x32x2) tops out at 157 TFLOP/s, a sixteenth of the bf16 one.  A float of at least 2^-109 is the exact
 // sum of three bf16 values (hi = bf16(x), mid = bf16(x - hi), lo = x - hi - mid: 8 bits each, round to nearest), so the product of
 // two floats is nine bf16 products, each exact in the MFMA's float accumulation.  The three smallest (mid lo, lo mid,
-// lo lo) are below 2^-26 of the product, less than the rounding of one float accumulation step, and are left out: six
-// bf16 MFMAs in place of eight float ones that each take twice as long: 6/16 of the time.
+// lo lo) are left out: together at most 2^-24 of the product (mid is up to 2^-8 of its operand, lo up to 2^-17), the size of one
+// float accumulation step's rounding, and usually far less.  Six bf16 MFMAs in place of eight float ones that each take
+// twice as long: 6/16 of the time.
 //
 // Workgroup: 4 wavefronts (2 x 2), tile 128 x 64, 32 floats of K per step.  The operands are split on the way from the
 // prefetch registers into LDS (5.5 vector instructions per element, under the other workgroups' MFMAs: three workgroups
@@ -71,11 +72,10 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
     f32x4 ra[RA], rb[RB];
     auto load_global = [&](int ks) {
         const int kc = ks * 8 + lchunk;
-        const int kca = g.a_kwrap > 0 ? kc % g.a_kwrap : kc;
 #pragma unroll
         for (int i = 0; i < RA; ++i) {
             const long long r = row0 + lrow + 32 * i;
-            ra[i] = r < g.M && kc < kchunks ? *(const f32x4*)(A + r * g.lda + (long long)kca * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+            ra[i] = r < g.M && kc < kchunks ? *(const f32x4*)(A + r * g.lda + (long long)kc * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
 #pragma unroll
         for (int i = 0; i < RB; ++i) {

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256, 1) void ista_resident_kernel(IstaResidentArgs 
 // n (wavefront w takes chunks w, w + 4, ...), and once per iteration their partial sums of Phi x meet in LDS, one tile
 // of m at a time, where every thread forms two elements of y - Phi x and writes their parts as the next operands.
 // Splitting a tile over the four SIMDs matters because these launches have few tiles: 256 x 256 with m = 64 (8 tiles)
-// took 20 products of two or eight workgroups each, 445 us a forward with the launches between them; now 139 us, 41 of
+// took 20 products of two or eight workgroups each, 445 us a forward with the launches between them; now 106 us, 41 of
 // them this kernel.  Errors against float64 are at most those of the float MFMA's products (the residual's sums meet in a
 // fixed order).
 // ----------------------------------------------------------------------------------------

@@ -223,13 +223,15 @@ FLOAT_PRODUCTS = [(127, 130, 96), (128, 64, 64), (129, 65, 33), (5, 9, 8), (257,
 @pytest.mark.parametrize("rows,n,m", FLOAT_PRODUCTS)
 def test_float_products_keep_float_precision(rows, n, m, options):
     """The float decoder's products run as six bf16 ones over the operands' three parts.  One iteration without a
-    threshold is X = mu Phi^T y, and C = X V.  Bound per element: parts and dropped products 2^-25 of sum |a b|, one
-    rounding (2^-24) of a partial sum per 16 of the contraction and three at the end; 2^-23 for the iterate itself."""
+    threshold is X = mu Phi^T y, and C = X V.  Bound per element: dropped products 2^-24 of sum |a b| (reached by operands
+    like 1 + 2^-8 - 2^-17, whose parts are 1, 2^-8 and -2^-17: one row holds only such), one rounding (2^-24) of a partial sum per
+    16 of the contraction and three at the end; 2^-23 for the iterate itself."""
     w = _small("f32_products", B=1, H=1, n_q=rows, n=n, d=64, m=m, dtype="f32", iters=1)
     Q, K, V = gen.make_qkv(w)
     Phi = gen.make_workload_phi(w)
     p = _problem(w, Q, K, V, Phi)
     Y = np.random.default_rng(rows).standard_normal((rows, m)).astype(np.float32)
+    Y[rows // 4] = 1 + 2.0 ** -8 - 2.0 ** -17
     X, C = p.empty(1, rows, n, dtype=torch.float32), p.empty(1, rows, w.d)
 
     def decode(y):
@@ -238,7 +240,7 @@ def test_float_products_keep_float_precision(rows, n, m, options):
         return X.clone(), C.clone()
 
     def bound(k):
-        return 2.0 ** -25 + 2.0 ** -24 * (k / 16 + 3)
+        return 2.0 ** -24 + 2.0 ** -24 * (k / 16 + 3)
 
     Xg, Cg = (to_np(t)[0].astype(np.float64) for t in decode(Y))
     P, V64 = Phi.astype(np.float64), V.reshape(n, w.d).astype(np.float64)

@@ -339,7 +339,7 @@ def test_fused_decoder_segments_are_bit_identical(segments, thin, options):
     """The fused decoder hands its residual operands from one segment of the iterations to the next;
     however the iterations are cut, the arithmetic is the same, so the results must not change by a bit.
     Both work shapes: 128-row workgroups (thin = 0, what large launches get) and one 32-row tile per
-    workgroup (what a launch this small gets by default)."""
+    workgroup (what a launch this small gets once an option asks for segments)."""
     w = _small("segments_bf16", B=2, H=3, n_q=150, n=203, d=64, m=75, dtype="bf16", iters=7)
     Q, K, V = gen.make_qkv(w)
     Phi = gen.make_workload_phi(w)
@@ -488,9 +488,9 @@ FUSED_CASES = [w for w in SMALL if w.dtype == "bf16" and w.m <= 416 and w.n > 64
 
 @pytest.mark.parametrize("w", FUSED_CASES, ids=lambda w: w.name)
 def test_fused_decoder_with_128_row_workgroups(w, options):
-    """Launches this small get one 32-row tile per workgroup by default; large ones get 128-row workgroups.
-    The small cases again on that shape, element by element against the oracle, and bit for bit against the
-    default shape (same arithmetic per row)."""
+    """Launches this small get the decoder with Phi in LDS, or a 32-row tile shared by eight wavefronts, by default; large
+    ones get 128-row workgroups.  The small cases again on that shape, element by element against the oracle, and bit for
+    bit against the default (same arithmetic per row)."""
     Q, K, V = gen.make_qkv(w)
     Phi = gen.make_workload_phi(w)
     mu = _mu(Phi)

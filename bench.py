@@ -19,6 +19,11 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
+# float arithmetic as six bf16 products over the operands' three parts (the float ISTA decoder)
+SPLIT_PEAK_TFLOPS = MFMA_PEAK_TFLOPS["bf16"] / 6
+# csat_profile_decoder_kernel: what ran the ISTA decoder in one launch
+DECODER_KERNELS = {0: "ista_fused_kernel", 1: "ista_fused_kernel", 2: "ista_fused_kernel", 3: "ista_fused2_kernel", 4: "ista_fused2_kernel",
+                   5: "ista_resident_kernel", 6: "ista_coop_kernel"}
 
 
 def nominal_flops(w, mode="rows", picks=8):
@@ -359,19 +364,27 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     T = w.iters
     fused = prof["residual"][1] == 0 and args.mode in ("rows", "columns")          # one launch runs every ISTA iteration
     hadamard = args.mode in ("hadamard", "columns_hadamard")
+    code = csat.csat_profile_decoder_kernel()
+    mfma_peak = MFMA_PEAK_TFLOPS[w.dtype]
+    if w.dtype == "f32" and args.mode in ("rows", "columns"):      # the decoder's products, in LDS or as launches
+        mfma_peak = SPLIT_PEAK_TFLOPS
     if hadamard:
-        dom, kname = "update", "ista_hadamard_kernel"
         N = 1
         while N < w.n:
             N *= 2
+        dom, kname = "update", "ista_hadamard_reg_kernel" if N >= 512 else "ista_hadamard_kernel"
         flops_dom = (2.0 * T - 1.0) * N * np.log2(N) * rows
         bytes_dom = rows * (4.0 * w.m + 2.0 * w.n)       # y in, the bf16 iterate out: nothing else leaves the chip
     elif fused:
-        dom, kname = "update", ("ista_fused2_kernel" if csat.csat_profile_decoder_kernel() >= 3 else "ista_fused_kernel")
+        dom, kname = "update", DECODER_KERNELS[code]
         # per launch: all T iterations.  Algorithmic bytes: the fp32 iterate is written T-1 times and
         # read T-1 times (8n bytes per row and iteration), y is read once per iteration.
         flops_dom = (4.0 * T - 2.0) * w.m * w.n * rows
         bytes_dom = rows * ((T - 1) * 8.0 * w.n + T * 4.0 * w.m)
+        if code == 5:      # the iterate stays in registers: y and Phi in, the iterate's operand copy out
+            esz = 2.0 if w.dtype == "bf16" else 4.0
+            kname = "ista_resident_kernel" if w.dtype == "bf16" else "ista_resident_f32_kernel"
+            bytes_dom = rows * (4.0 * w.m + esz * w.n) + esz * w.m * w.n
         if args.mode == "rows" and prof["synthesis"][1] == 0:      # the kernel also formed C = X V (no product kernel ran)
             flops_dom += 2.0 * rows * w.n * w.d
             bytes_dom += rows * 2.0 * w.d
@@ -379,11 +392,16 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
         dom = max(("update", "residual"), key=lambda k: prof[k][0])
         big = w.dtype == "bf16" and rows >= 256      # the large-tile kernel takes the decoder's bf16 GEMM pair
         kname = (("gemm_nt_bf16_big_kernel<EpiIstaUpdateTiled>" if dom == "update" else "gemm_nt_bf16_big_kernel<EpiResidualTiled>")
-                 if big else ("gemm_nt_kernel<EpiIstaUpdate>" if dom == "update" else "gemm_nt_kernel<EpiResidual>"))
+                 if big else ("<EpiIstaUpdate>" if dom == "update" else "<EpiResidual>"))
+        if not big:
+            kname = ("gemm_nt_f32_split_kernel" if mfma_peak == SPLIT_PEAK_TFLOPS else "gemm_nt_kernel") + kname
         esz = 2.0 if w.dtype == "bf16" else 0.0      # bf16 operand copy next to the fp32 state
-        if args.mode == "omp":                         # correlations R Phi: reads bf16 r, writes fp32 correlations
-            dom = "update"
-            kname = "gemm_nt_bf16_big_kernel<EpiStore<float>>" if big else "gemm_nt_kernel<EpiStore<float>>"
+        col_tiles = -(-w.n // 256)
+        in_product = args.mode == "omp" and big and w.n >= 128 and (col_tiles >= 3 or rows * col_tiles >= 8192)
+        if args.mode == "omp":                         # correlations R Phi: reads bf16 r, writes fp32 correlations or, in_product,
+            dom = "update"                             # each row's best per 128 columns
+            kname = ("gemm_nt_bf16_big_kernel<EpiOmpBest>" if in_product else
+                     "gemm_nt_bf16_big_kernel<EpiStoreStream>" if big else "gemm_nt_kernel<EpiStoreStream>")
         if args.mode == "lista":                       # one layer: (S - I) alpha, K = n
             dom = "update"
             kname = "gemm_nt_bf16_big_kernel<EpiListaUpdateTiled>" if big else "gemm_nt_kernel<EpiListaUpdate>"
@@ -391,6 +409,8 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
         bytes_dom = {"update": rows * ((4.0 * w.n + max(esz, 4.0) * w.m) if args.mode == "omp" else
                                        ((8.0 + esz) * w.n + (max(esz, 4.0) * w.m if args.mode != "lista" else (4.0 + esz) * w.n))),
                      "residual": rows * (max(esz, 4.0) * w.n + (4.0 + max(esz, 4.0)) * w.m)}[dom]
+        if in_product:
+            bytes_dom = rows * (8.0 * -(-w.n // 128) + 2.0 * w.m) + 2.0 * w.n * w.m
     ms_dom, n_dom = prof[dom]
     avg_s = ms_dom / max(n_dom, 1) / 1e3
     # HBM bytes per launch measured with rocprofv3 (FETCH_SIZE + WRITE_SIZE), if on record for this kernel
@@ -406,7 +426,7 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     # algorithmic figure, which assumes a dense iterate streamed every iteration), else the algorithmic ones.
     ai = flops_dom / bytes_dom
     ai_roof = flops_dom / traffic if traffic else ai
-    ridge = MFMA_PEAK_TFLOPS[w.dtype] * 1e12 / (HBM_PEAK_GBS * 1e9)
+    ridge = mfma_peak * 1e12 / (HBM_PEAK_GBS * 1e9)
     if hadamard:      # plain fp32 additions on the vector units: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz x 2 (fma peak) = 157.3 TFLOP/s
         roof = {"bound": "alu", "achieved": flops_dom / avg_s / 1e12, "peak": 157.3, "unit": "TFLOP/s",
                 # butterflies are single additions (no fused multiply-add) and packed fp32 is compiled out on the test machines:
@@ -415,7 +435,7 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     elif ai_roof < ridge:
         roof = {"bound": "hbm", "achieved": bytes_dom / avg_s / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s"}
     else:
-        roof = {"bound": "mfma", "achieved": flops_dom / avg_s / 1e12, "peak": MFMA_PEAK_TFLOPS[w.dtype],
+        roof = {"bound": "mfma", "achieved": flops_dom / avg_s / 1e12, "peak": mfma_peak,
                 "unit": "TFLOP/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
     roof["traffic"] = traffic
@@ -428,12 +448,15 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     roof["arithmetic_intensity_flop_per_byte"] = ai
     roof["arithmetic_intensity_measured_traffic"] = ai_roof if traffic else None
     # Flops the dominant kernel executes per launch, padding included (nothing is skipped: the decoder is dense);
-    # `achieved` counts only the algorithmic ones.  Fused decoder: every 32-row tile runs 2*MT MFMAs (32x32x16) per
-    # chunk and product; large-tile GEMM: whole 256x256 tiles over K padded to 64.
+    # `achieved` counts only the algorithmic ones.  One-launch decoders: every 32-row tile (in groups of four on the 128-row
+    # kernels) runs 2*MT MFMAs (32x32x16; six of them as one float product) per chunk and product, the decoder in LDS over
+    # its instance's chunks in bf16; large-tile GEMM: whole 256x256 tiles over K padded to 64.
     executed = None
     if fused and not hadamard:
         mt, nct = -(-w.m // 32), -(-w.n // 32)
-        executed = (-(-rows // 128) * 4) * nct * (2.0 * T - 1.0) * (2 * mt) * 2.0 * 32 * 32 * 16
+        if code == 5 and w.dtype == "bf16":
+            nct = next(c for c in (3, 5, 7, 9, 12, 16) if nct <= c)
+        executed = (-(-rows // 32) if code in (2, 5, 6) else -(-rows // 128) * 4) * nct * (2.0 * T - 1.0) * (2 * mt) * 2.0 * 32 * 32 * 16
     elif kname.startswith("gemm_nt_bf16_big_kernel"):
         up = lambda v, q: -(-v // q) * q
         n_out, k_in = ((w.n, w.n) if args.mode == "lista" else (w.n, w.m)) if dom == "update" else (w.m, w.n)
@@ -441,7 +464,7 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     roof["executed_flops"] = executed
     roof["executed_over_algorithmic"] = executed / flops_dom if executed else None
     roof["mfma_tflops"] = flops_dom / avg_s / 1e12
-    roof["mfma_frac"] = flops_dom / avg_s / 1e12 / MFMA_PEAK_TFLOPS[w.dtype]
+    roof["mfma_frac"] = flops_dom / avg_s / 1e12 / mfma_peak
     roof["hbm_algorithmic_gbs"] = bytes_dom / avg_s / 1e9
     roof["hbm_algorithmic_frac"] = bytes_dom / avg_s / 1e9 / HBM_PEAK_GBS
     # the same figures against what this device delivers on the two reference kernels (context; `frac` stays

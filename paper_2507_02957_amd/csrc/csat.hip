@@ -1305,19 +1305,28 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
 
 // Buffers of the matching-pursuit decoder, carved after the main workspace.
 struct OmpExtra {
-    float* Cm;     // [rows, ldn]    correlations of the current residuals with every column
-    float* Rf;     // [rows, mq]     fp32 residuals
-    float* Qb;     // [rows, k, mq]  orthonormalised picked columns
+    float* Cm;     // [rows, ldn]    correlations of the current residuals with every column; or, where the pick is taken
+                   //                with the product, its candidates [rows, splits]
+    uint32_t* taken;  // [row tiles of 32, nct, 32]  columns that a row may not pick, a bit per row (bf16)
     float* Tri;    // [rows, k, k]   triangular factor
+    float* Fac;    // [rows, k (k + 1) / 2]  ... by columns, with 1 / its diagonal
     float* Z;      // [rows, k]      Q^T y
     int* picks;    // [rows, k]
-    int mq;
+    char* PhiQ;    // [n, 64, pitch]  columns of Phi in the update's order
+    float* Rf;     // [rows, mq]     fp32 residuals and ...
+    float* Qb;     // [rows, k, mq]  ... orthonormalised picked columns, beyond the picks that the update holds in registers
+    int mq, MQ;    // m in whole 64s; values of an m-vector per lane of the update
     size_t bytes;
 };
+// Picks whose orthonormal vectors the update keeps in registers: 128 registers at most; at one value per lane (m <= 64) reading them
+// back is cheaper than forming more than eight again (float, 8192 rows, n = 64, m = 32, 16 picks: 361 us against 341).
+int omp_held_picks(int MQ) { return MQ == 1 || MQ == 16 ? 8 : 16; }
 OmpExtra carve_omp(const csat_dims& d, const Workspace& w, int k, char* base) {
     const long long rows = (long long)d.B * d.H * d.n_q;
     OmpExtra x{};
     x.mq = (int)round_up(d.m, 64);
+    x.MQ = x.mq <= 512 ? x.mq / 64 : 16;
+    const bool stored = k > omp_held_picks(x.MQ);
     size_t off = 0;
     auto take = [&](size_t nbytes) {
         char* p = base + off;
@@ -1325,13 +1334,72 @@ OmpExtra carve_omp(const csat_dims& d, const Workspace& w, int k, char* base) {
         return p;
     };
     x.Cm = (float*)take((size_t)rows * w.ldn * 4);
-    x.Rf = (float*)take((size_t)rows * x.mq * 4);
-    x.Qb = (float*)take((size_t)rows * k * x.mq * 4);
+    x.taken = (uint32_t*)take(d.dtype == CSAT_BF16 ? (size_t)((rows + 31) / 32) * w.nct * 128 : 0);
     x.Tri = (float*)take((size_t)rows * k * k * 4);
+    x.Fac = (float*)take((size_t)rows * (k * (k + 1) / 2) * 4);
     x.Z = (float*)take((size_t)rows * k * 4);
     x.picks = (int*)take((size_t)rows * k * 4);
+    x.PhiQ = take((size_t)d.n * 64 * omp_column_pitch(x.MQ, (int)esize(d.dtype)) * esize(d.dtype));
+    x.Rf = (float*)take(stored ? (size_t)rows * x.mq * 4 : 0);
+    x.Qb = (float*)take(stored ? (size_t)rows * k * x.mq * 4 : 0);
     x.bytes = off;
     return x;
+}
+
+constexpr int kOmpMaxSplits = 32;     // (a candidate is 8 bytes, a row of Cm at least 256)
+constexpr int kOmpPickStart = 4;      // a workgroup's start, its residuals' way from memory or L2, in steps
+// Row blocks that run whole, as many as fill the chip evenly, and the shares of n that the others are cut into, as many as need the
+// fewest passes over the chip.  76 800 rows, n = 1600, m = 392 (300 blocks of 50 steps): every block in three shares 137 us, 256
+// whole and 44 in five 119.
+void omp_pick_plan(OmpPickArgs& a) {
+    const int KS = (int)(a.ldm / 64), steps = (a.nct + omp_pick_chunks(KS) - 1) / omp_pick_chunks(KS);
+    const long long blocks = (a.rows + omp_pick_rows(KS) - 1) / omp_pick_rows(KS), slots = (long long)cu_count() * omp_pick_per_cu(KS);
+    a.whole = (int)(blocks / slots * slots);
+    a.splits = 1;
+    long long best = -1;
+    for (int s = 1; s <= kOmpMaxSplits && s <= steps; ++s) {
+        const long long cost = ((blocks - a.whole) * s + slots - 1) / slots * ((steps + s - 1) / s + kOmpPickStart);
+        if (best < 0 || cost < best) { best = cost; a.splits = s; }
+    }
+}
+csat_status launch_omp_pick(const OmpPickArgs& a, hipStream_t st) {
+    const int KS = (int)(a.ldm / 64);
+    const long long blocks = (a.rows + omp_pick_rows(KS) - 1) / omp_pick_rows(KS);
+    const dim3 grid((unsigned)(a.whole + (blocks - a.whole + 7) / 8 * 8 * a.splits));
+    const size_t lds = omp_pick_lds_bytes(KS);
+    switch (KS) {
+#define CSAT_OMP_PICK(N)                                                                                                       \
+    case N:                                                                                                                    \
+        HIP_TRY(hipFuncSetAttribute((const void*)omp_pick_product_kernel<N>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+        hipLaunchKernelGGL((omp_pick_product_kernel<N>), grid, dim3(64 * omp_pick_waves(N)), lds, st, a);                          \
+        break;
+        CSAT_OMP_PICK(1) CSAT_OMP_PICK(2) CSAT_OMP_PICK(3) CSAT_OMP_PICK(4) CSAT_OMP_PICK(5) CSAT_OMP_PICK(6) CSAT_OMP_PICK(7) CSAT_OMP_PICK(8)
+        CSAT_OMP_PICK(9) CSAT_OMP_PICK(10) CSAT_OMP_PICK(11) CSAT_OMP_PICK(12) CSAT_OMP_PICK(13) CSAT_OMP_PICK(14) CSAT_OMP_PICK(15) CSAT_OMP_PICK(16)
+#undef CSAT_OMP_PICK
+        default: return CSAT_ERR_SHAPE;
+    }
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+
+template <typename T>
+csat_status launch_omp_update(const OmpUpdateArgs<T>& a, int MQ, float* Rf, hipStream_t st) {
+    const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
+    const int form = a.k > omp_held_picks(MQ) ? 2 : a.it < 8 ? 0 : 1;
+    switch (MQ) {
+#define CSAT_OMP_UPDATE(M)                                                                                             \
+    case M:                                                                                                           \
+        if (form == 2) hipLaunchKernelGGL((omp_update_stored_kernel<T, M>), grid, block, 0, st, a, Rf);                \
+        else if (form == 0 || M == 16) hipLaunchKernelGGL((omp_update_kernel<T, M, 8>), grid, block, 0, st, a);         \
+        else hipLaunchKernelGGL((omp_update_kernel<T, M, (M == 16 ? 8 : 16)>), grid, block, 0, st, a);                  \
+        break;
+        CSAT_OMP_UPDATE(1) CSAT_OMP_UPDATE(2) CSAT_OMP_UPDATE(3) CSAT_OMP_UPDATE(4) CSAT_OMP_UPDATE(5) CSAT_OMP_UPDATE(6) CSAT_OMP_UPDATE(7) CSAT_OMP_UPDATE(8)
+        CSAT_OMP_UPDATE(16)
+#undef CSAT_OMP_UPDATE
+        default: return CSAT_ERR_SHAPE;
+    }
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
 }
 
 template <typename T>
@@ -1345,48 +1413,54 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
         if (want_c) CSAT_TRY(fill_zero(C, (size_t)rows * d.d * sizeof(T), st));
         return CSAT_OK;
     }
-    const unsigned row_blocks = (unsigned)((rows + 3) / 4);
+    const bool in_product = sizeof(T) == 2 && gemm_choice() != 1;
+    OmpCand* cand = in_product ? (OmpCand*)x.Cm : nullptr;
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         CSAT_TRY(transpose_pack<T>((const T*)Phi, (T*)w.PhiT, w.ldm, 1, d.m, d.n, st));
         CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));        // r = y
-        CSAT_TRY((pack_rows<float, float>(Y, d.m, x.Rf, x.mq, rows, d.m, st)));
+        const int pitch = omp_column_pitch(x.MQ, (int)sizeof(T));
+        const long long total = (long long)d.n * 64;
+        if (k > 1) hipLaunchKernelGGL((omp_pack_columns_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m,
+                           pitch, (T*)x.PhiQ, total);
+        HIP_TRY(hipGetLastError());
+        if (in_product) {
+            const long long words = (rows + 31) / 32 * w.nct * 32;
+            hipLaunchKernelGGL(omp_taken_init_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, x.taken, d.n, w.nct, words);
+            HIP_TRY(hipGetLastError());
+        }
     }
+    OmpPickArgs p{(const bf16_t*)w.PhiT, (const bf16_t*)w.R, w.ldm, rows, x.taken, cand, d.n, w.nct, 0, 1};
+    if (in_product) omp_pick_plan(p);
+    OmpUpdateArgs<T> u{(const T*)w.PhiT, w.ldm, k > 1 ? (const T*)x.PhiQ : nullptr, Y, cand, p.splits, (long long)p.whole * omp_pick_rows((int)(w.ldm / 64)), x.picks, k, 0, x.taken, w.nct, x.Tri, x.Z, x.Fac, x.Qb, (T*)w.R, w.ldm, rows, d.m, x.mq};
     for (int it = 0; it < k; ++it) {
-        // correlations of every residual with every column, and each row's largest: in the product's epilogue where the
-        // large-tile kernel runs (EpiOmpBest; the same picks) and has more to do than a few tiles, whose epilogue then takes
-        // longer than the search's own launch: 16 picks, m = 32, n = 128 (one column tile): 1024 rows 334 us against 305 with the
-        // search, 4096 rows 4 % more, 8192 rows 5 % less; n = 300: 1024 rows 337 against 328, 4096 rows 4 % less; n = 640: 1024 rows 2 % less.
-        GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
-        const long long col_tiles = (d.n + 255) / 256;
-        const bool in_product = use_big_gemm<T>(g, d.n) && (col_tiles >= 3 || rows * col_tiles >= 8192);
-        OmpCand* cand = in_product ? (OmpCand*)x.Cm : nullptr;
-        const int nseg = (d.n + 127) / 128;
-        {
+        u.it = it;
+        if (in_product) {
             Timed tm(w, CSAT_K_UPDATE, st);
-            if (in_product) {
-                g.K = (int)round_up(g.K, 64);
-                CSAT_TRY(launch_gemm_big(g, d.n, 1, EpiOmpBest{cand, nseg, x.picks, k, it, rows, d.n}, st));
-            } else {
+            CSAT_TRY(launch_omp_pick(p, st));
+        }
+        if (!in_product) {
+            GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
+            {
+                Timed tm(w, CSAT_K_UPDATE, st);
                 EpiStoreStream ec{x.Cm, w.ldn, (int)rows, d.n};
                 CSAT_TRY((gemm<T>(g, d.n, 1, ec, st)));
             }
+            Timed tm(w, CSAT_K_RESIDUAL, st);
+            hipLaunchKernelGGL(omp_pick_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, x.Cm, w.ldn, rows, d.n, x.picks, k, it);
+            HIP_TRY(hipGetLastError());
         }
         Timed tm(w, CSAT_K_RESIDUAL, st);
-        if (!in_product)
-            hipLaunchKernelGGL(omp_pick_kernel, dim3(row_blocks), dim3(256), 0, st, x.Cm, w.ldn, rows, d.n, x.picks, k, it);
-#define CSAT_OMP_UPDATE(MQ_)                                                                                              \
-    hipLaunchKernelGGL((omp_update_kernel<T, MQ_>), dim3(row_blocks), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m, cand, nseg, \
-                       x.picks, k, it, x.Qb, x.Tri, x.Z, x.Rf, x.mq, (T*)w.R, w.ldm, rows)
-        if (x.mq <= 256) CSAT_OMP_UPDATE(4);
-        else if (x.mq <= 512) CSAT_OMP_UPDATE(8);
-        else CSAT_OMP_UPDATE(16);
-#undef CSAT_OMP_UPDATE
-        HIP_TRY(hipGetLastError());
+        CSAT_TRY(launch_omp_update<T>(u, x.MQ, x.Rf, st));
     }
     Timed tm(w, CSAT_K_SYNTHESIS, st);
-    hipLaunchKernelGGL((omp_finish_kernel<T>), dim3(row_blocks), dim3(256), 0, st, x.Tri, x.Z, x.picks, k, rows, d.n_q, d.n, d.d,
-                       X, picks, want_c ? (const T*)V : nullptr, want_c ? (T*)C : nullptr);
+#define CSAT_OMP_FINISH(KM)                                                                                                          \
+    hipLaunchKernelGGL((omp_finish_kernel<T, KM>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, x.Tri, x.Z, x.picks, k, rows, d.n_q, \
+                       d.n, d.d, X, picks, want_c ? (const T*)V : nullptr, want_c ? (T*)C : nullptr)
+    if (k <= 8) CSAT_OMP_FINISH(8);
+    else if (k <= 16) CSAT_OMP_FINISH(16);
+    else CSAT_OMP_FINISH(kOmpMaxPicks);
+#undef CSAT_OMP_FINISH
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }

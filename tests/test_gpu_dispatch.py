@@ -510,6 +510,41 @@ def test_matching_pursuit_picks_in_the_product(n_q, n, m, picks, options):
     assert_close("C = X V", C, X.astype(np.float64) @ V.reshape(3, n, w.d).astype(np.float64), TOL["bf16"])
 
 
+# (rows, n, m, picks): 1 to 16 slabs of 64 rows of Phi and their chunks per step, rings of two and three steps, four and eight
+# wavefronts; whole row blocks (rows past 256 of them) with and without a cut remainder; 8, 9, 16 and 17 picks; a chunk of one column
+PICK_KERNEL_CASES = [(33, 129, 64, 8), (300, 97, 65, 9), (40, 193, 192, 16), (70, 255, 250, 17), (257, 353, 300, 3), (90, 450, 448, 8),
+                     (130, 545, 512, 4), (90, 640, 600, 9), (20, 833, 832, 2), (150, 900, 890, 3), (60, 1056, 1024, 10), (65600, 200, 150, 2),
+                     (131072, 65, 40, 2), (131200, 33, 8, 3)]
+
+
+@pytest.mark.parametrize("rows,n,m,picks", PICK_KERNEL_CASES)
+def test_matching_pursuit_picks_while_the_columns_pass(rows, n, m, picks, options):
+    """bf16: each row's largest correlation is kept while the columns of Phi pass.  The same sums in the same order as the
+    product with stored correlations and their search (forced), so the same picks, coefficients and output."""
+    d = 64
+    dims = csat.make_dims(1, 1, rows, n, d, m, "bf16")
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).bfloat16()
+    V = torch.randn(n, d, generator=g, device=DEV).bfloat16()
+    Y = torch.randn(rows, m, generator=g, device=DEV)
+    ws = torch.empty(csat.csat_omp_workspace_bytes(dims, picks), dtype=torch.uint8, device=DEV)
+    out = []
+    for gemm in (0, 1):
+        options("gemm", gemm)
+        ws.fill_(0xFF)
+        X, C = torch.empty(rows, n, device=DEV), torch.empty(rows, d, dtype=torch.bfloat16, device=DEV)
+        S = torch.empty(rows, picks, dtype=torch.int32, device=DEV)
+        csat.csat_recover_omp(dims, Y, Phi, picks, X, S, V, C, ws)
+        torch.cuda.synchronize()
+        out.append((S, X, C))
+    S, X, C = out[0]
+    assert (S >= 0).all() and (S < n).all() and (S.sort(-1).values.diff(dim=-1) > 0).all()
+    assert X.isfinite().all() and (X != 0).any()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
 # (n, m, iterations): every length of the register-resident transforms, n at and off multiples of the thread count, just
 # above half the length and equal to it, one and two iterations
 HADAMARD_CASES = [(257, 30, 3), (512, 512, 2), (513, 100, 1), (1000, 64, 4), (1088, 200, 3), (2048, 300, 2), (2049, 90, 3), (4100, 1000, 2), (8200, 40, 2)]

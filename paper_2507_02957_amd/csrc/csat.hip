@@ -15,6 +15,7 @@
 #include "csat_launch.h"
 #include "csat_peaks.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -149,6 +150,7 @@ bool sparse_state(size_t dense_state_bytes) {
 // 154 groups: 7.3 against 9.1 ms; short_video's shape at m = 512, 600 groups: 5.2 against 8.3 ms per forward), not
 // below: a group's iterations are a chain, so the launch lasts as long with 40 groups as with 150 (cross_modal's rows
 // with fewer heads, forward: 39 groups 6.5 against 3.8 ms, 97 groups 7.5 against 7.2, 121 groups 7.9 against 7.6).
+constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_static's workspace
 constexpr int kFusedMaxMT = 16;
 constexpr int kFused2MaxMT = 13;
 constexpr long long kFusedWideMinGroups = 128;
@@ -185,9 +187,33 @@ struct Workspace {
     char* Z;      // [rows, d]
     int split;    // > 1: the residual product runs as this many partial products along K (few output tiles)
     float* SplitP;  // [split, rows, ldm]  their outputs
+    int tile_split;  // > 1: workgroups per 32-row tile of the shared-tile decoder
+    int* TileSync;   // [2 + 2 * tiles * tile_split]  ... their counter and flags
+    f32x4* Xchg;     // [tiles, tile_split, 2, MT, 4, 64]  ... and their parts of the residual (in SplitP's place)
     size_t bytes;
     Profiler* prof;   // never null during a call
 };
+
+// Workgroups that share a 32-row tile of the shared-tile decoder (csat_ista_coop.h), each with its share of the columns: as
+// many as make an iteration shortest by these fits to measured ones (us): a chunk 0.25 + 0.025 MT (two more for the
+// pipeline's ramp), the exchange of the parts of the residual 1.5 + (0.4 + 0.035 MT) a member and up to 3 with the chip full of
+// members.  20 iterations, one to sixteen members: 96 tiles, m = 392, n = 1600 593, 422 us; 30 tiles 589, 388, three 316, four 310,
+// eight 342; 8 tiles four 277, six 261, eight 270; n = 3000, m = 130, 10 tiles 762, 451, four 295, eight 233, sixteen 257; n = 16 384,
+// m = 64, 8 tiles 2894, 1527, sixteen 415; n = 512, m = 392, 120 tiles 237, 261.
+// Not for fewer than four iterations, whose sums so keep the order of the other decoders, nor to save less than
+// kTileSplitMinUs of a call.
+constexpr int kTileSplitMinIters = 4, kTileSplitMax = 16;
+constexpr double kTileSplitMinUs = 20;
+double coop_iteration_us(int MT, long long tiles, int nct, int members) {
+    const double exchange = members == 1 ? 0 : 1.5 + members * (0.4 + 0.035 * MT) + (double)(tiles * members) / 256 * 3;
+    return ((nct + members - 1) / members + 2) * (0.25 + 0.025 * MT) + exchange;
+}
+int coop_tile_split(int MT, long long tiles, int nct) {
+    int best = 1;
+    for (int g = 2; MT <= kCoopMaxMT && g <= kTileSplitMax && g * tiles <= 256 && g * 4 <= nct; ++g)
+        if (coop_iteration_us(MT, tiles, nct, g) < coop_iteration_us(MT, tiles, nct, best)) best = g;
+    return best;
+}
 
 Workspace carve(const csat_dims& d, char* base) {
     Workspace w{};
@@ -242,7 +268,20 @@ Workspace carve(const csat_dims& d, char* base) {
         for (int s = 2; s <= 8; ++s)
             if (ksteps % s == 0 && tiles * s <= 256) w.split = s;
     }
-    w.SplitP = (float*)take(w.split > 1 ? (size_t)w.split * rows * w.ldm * 4 : 0);
+    // ... and the parts of the residual of the shared-tile decoder, where several workgroups share a tile: never both
+    const long long tiles32 = (rows + 31) / 32;
+    const size_t split_bytes = w.split > 1 ? (size_t)w.split * rows * w.ldm * 4 : 0;
+    w.tile_split = fused_ok ? coop_tile_split(w.MT, tiles32, w.nct) : 1;
+    const size_t before = off;
+    auto parts = [&](size_t bytes) { return w.tile_split > 1 ? std::max(bytes, (size_t)tiles32 * w.tile_split * 2 * w.MT * 4096) : bytes; };
+    w.SplitP = (float*)take(parts(split_bytes));
+    w.TileSync = (int*)take(w.tile_split > 1 ? (size_t)(2 + 2 * tiles32 * w.tile_split) * 4 : 0);
+    if (off > kStaticScratchBytes && before + round_up((long long)split_bytes, 256) <= (long long)kStaticScratchBytes) {   // (what fits the static array without still does)
+        w.tile_split = 1;
+        off = before;
+        w.SplitP = (float*)take(split_bytes);
+    }
+    w.Xchg = (f32x4*)w.SplitP;
     w.bytes = off;
     return w;
 }
@@ -898,7 +937,7 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     if ((*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] != 0) a.spin_limit = (*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] < 0 ? 0 : (*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT];
     // (a.sync was cleared together with the status word: run_ista)
     const long long units = a.tape > 0 ? a.tape : (long long)a.groups * a.segs;
-    const unsigned grid = (unsigned)(variant == 6 ? a.groups : units < cus ? units : cus);
+    const unsigned grid = (unsigned)(variant == 6 ? a.groups * a.tile_split : units < cus ? units : cus);
     *tl_decoder_kernel = variant;
     switch (MT) {
 #define CSAT_FUSED_CASE(N) case N: HIP_TRY(ista_fused_launch_mt##N(variant, a, grid, st)); return CSAT_OK;
@@ -938,14 +977,21 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
     }
     // word 0 of the status block: set by the fused decoder when its bounded wait gives up
     // (and, in the same launch, the fused decoder's unit counter and progress words: 2 + one per group of 32 rows at most)
-    const long long sync_words = w.fused ? 2 + w.rows_pad / 32 : 0;
+    const long long tiles = (rows + 31) / 32;
+    const bool shared = w.fused && w.tile_split > 1 && iters >= kTileSplitMinIters && tiles * w.tile_split <= cu_count() &&
+                        iters * (coop_iteration_us(w.MT, tiles, w.nct, 1) - coop_iteration_us(w.MT, tiles, w.nct, w.tile_split)) >= kTileSplitMinUs &&
+                        fused_variant(w.MT, w.rows_pad, w.nct, iters) == 6;
+    int* sync = shared ? w.TileSync : w.FusedSync;
+    const long long sync_words = !w.fused ? 0 : shared ? 2 + 2 * tiles * w.tile_split : 2 + w.rows_pad / 32;
     hipLaunchKernelGGL(set_word_kernel, dim3((unsigned)(sync_words > 256 ? (sync_words + 255) / 256 : 1)), dim3(256), 0, st, w.Status,
-                       (w.fused && (*tl_opt)[CSAT_OPT_INJECT_DECODER_ERROR]) ? 1 : 0, (uint32_t*)w.FusedSync, sync_words);
+                       (w.fused && (*tl_opt)[CSAT_OPT_INJECT_DECODER_ERROR]) ? 1 : 0, (uint32_t*)sync, sync_words);
     HIP_TRY(hipGetLastError());
     *tl_decoder_kernel = -1;
     if (w.fused) {
         IstaFusedArgs a{w.PhiPack, Y, w.Xs, w.Mask, w.Xb, Xout, rows, d.n, w.nct, (int)ldY, (int)w.ldn, iters, mu, theta,
-                        0, 1, w.FusedSync, w.Hand, w.Status, kFusedSpinLimit};
+                        0, 1, sync, w.Hand, w.Status, kFusedSpinLimit};
+        a.tile_split = shared ? w.tile_split : 1;
+        a.xchg = w.Xchg;
         // Vsyn (the caller checked synthesis_in_decoder): C = X V in the kernel's last iteration, from V's fragments in
         // the buffer of V^T; no bf16 copy of the iterate then
         a.y_tiled = y_tiled ? 1 : 0;
@@ -1678,7 +1724,6 @@ bool hadamard_fits_lds(int n, int m) {
 
 // Scratch of csat_forward_static: the workspace of a small problem, held in the code object's own device memory
 // so that the call allocates nothing.  Every device the library is used on holds its own copy until the process ends.
-constexpr size_t kStaticScratchBytes = (size_t)48 << 20;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mutex;

@@ -64,6 +64,10 @@ struct IstaFusedArgs {
     // Two-chunk kernel only: Y is laid out in accumulator tiles, [tile of 32 rows][MT][4][64 lanes] float4 (what lane
     // (row, h) holds as elements 4 g .. 4 g + 3 of tile mt), rows a multiple of 32: the attention kernel wrote it so.
     int y_tiled;
+    // Shared-tile kernel only (csat_ista_coop.h): workgroups per tile, each with its share of the columns, and their parts of the
+    // residual, [tile][member][iteration parity][MT][4][64] float4.  sync: [2 + 2 per workgroup] then, the parts' flags.
+    int tile_split;
+    f32x4* xchg;
     int state_stream;      // one-chunk schedule: the iterate's loads and stores carry the non-temporal hint
 };
 

@@ -474,6 +474,32 @@ def test_decoder_with_a_tile_shared_by_eight_wavefronts(n_q, n, m, iters, option
     assert same
 
 
+# (n_q, n, m, iterations) with two to sixteen workgroups per tile: one tile and 96, one to thirteen tiles of m (odd and even),
+# shares of unequal length, ragged last chunk and row tile, the fewest iterations and more
+MEMBER_CASES = [(5, 1600, 392, 8), (33, 1571, 197, 8), (70, 3000, 130, 6), (40, 4500, 20, 7), (200, 1333, 352, 6), (512, 1000, 416, 8),
+                (31, 2000, 64, 5), (3, 8192, 90, 4), (100, 1800, 300, 5)]
+
+
+@pytest.mark.parametrize("n_q,n,m,iters", MEMBER_CASES)
+def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters):
+    """Fewer row tiles than CUs: several workgroups share a tile and exchange their parts of the residual; against the oracle, and
+    the same bits in every call."""
+    w = _small("shared_members", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, lam=0.002)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    C, _, X = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() == 6
+    assert csat.csat_decoder_status(p.ws) == 0
+    ref = orc.forward(Q, K, V, Phi, w.lam, mu, iters)
+    assert_close("X", to_np(X), ref["X"], TOL["bf16"])
+    assert_close("C", to_np(C), ref["C"], TOL["bf16"])
+    p.ws.fill_(0xFF)
+    C1, _, X1 = p.forward(w.lam, mu, iters)
+    assert torch.equal(X, X1) and torch.equal(C, C1)
+
+
 # (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
 # picked in the end (m = n = picks), several column tiles
 PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20),

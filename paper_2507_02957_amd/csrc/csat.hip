@@ -9,6 +9,7 @@
 #include "csat_fwht.h"
 #include "csat_gemm_big.h"
 #include "csat_gemm_f32.h"
+#include "csat_gemm_deep.h"
 #include "csat_attention.h"
 #include "csat_attention_z.h"
 #include "csat_measure.h"
@@ -392,6 +393,27 @@ csat_status launch_gemm_f32(GemmArgs g, long long n_cover, int batch, const Epi&
     return CSAT_OK;
 }
 
+// Products that would be so few 128-wide tiles that most CUs had none go to small tiles whose workgroups share the contraction
+// (csat_gemm_deep.h): 32 x 32, or 64 x 64 in bf16 from two of the small ones per CU on.  Measurement of K and V (with its
+// transposes), 128-wide against 32-wide (64-wide) tiles, us: float, n = 1600, m = 392, d = 64: one head 73.8, 21.0 (57.3), 12 heads (96 tiles of
+// 128 x 64) 82.4, 58.2 (65.4), 48 heads (384) 142, 168; 64 heads of n = 300, m = 96 (128) 30.2, 30.3; bf16: 10 heads of
+// n = 1571, m = 197, d = 80 (40) 41.2, 29.8 (30.1), 4 heads of n = 16 384, m = 1024, d = 80 (64) 247, 210 (160), 392 x 3072 over
+// 3200 (96) equal, 16 heads of n = 4096, m = 512, d = 96 (128) 83.6, 121 (95.5).
+template <typename T>
+bool few_tiles(const GemmArgs& g, long long n_cover, int batch) {
+    const long long wide = n_cover <= 64 ? 64 : 128, tiles = (g.M + 127ll) / 128 * ((n_cover + wide - 1) / wide) * batch;
+    return tiles * 8 <= (sizeof(T) == 4 ? 3ll : 2ll) * cu_count() && gemm_choice() != 1;
+}
+
+template <typename T, int T32, bool SPLIT, typename Epi>
+csat_status launch_gemm_deep(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
+    constexpr int BT = 32 * T32;
+    const dim3 grid((unsigned)((g.M + BT - 1) / BT), (unsigned)((n_cover + BT - 1) / BT), (unsigned)batch);
+    hipLaunchKernelGGL((gemm_nt_deep_kernel<T, T32, SPLIT, Epi>), grid, dim3(64 * kDeepWaves), 0, st, g, epi);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+
 template <typename T, typename Epi>
 csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     if constexpr (sizeof(T) == 2) {
@@ -400,6 +422,12 @@ csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi
             GemmArgs gb = g;
             gb.K = (int)Kp;
             return launch_gemm_big<Epi>(gb, n_cover, batch, epi, st);
+        }
+    }
+    if constexpr (!has_rows_epilogue<Epi>::value) {
+        if (few_tiles<T>(g, n_cover, batch)) {
+            if (sizeof(T) == 2 && (g.M + 31ll) / 32 * ((n_cover + 31) / 32) * batch > 2 * cu_count()) return launch_gemm_deep<T, 2, false, Epi>(g, n_cover, batch, epi, st);
+            return launch_gemm_deep<T, 1, false, Epi>(g, n_cover, batch, epi, st);
         }
     }
     if (n_cover <= 64) return launch_gemm<T, 128, 64, 2, 2, Epi>(g, n_cover, batch, epi, st);
@@ -415,6 +443,9 @@ csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi
 template <typename T, typename Epi>
 csat_status decoder_gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
+        if constexpr (!has_rows_epilogue<Epi>::value) {
+            if (few_tiles<T>(g, n_cover, batch)) return launch_gemm_deep<T, 1, true, Epi>(g, n_cover, batch, epi, st);
+        }
         if (gemm_choice() != 1 && (g.K > 32 || n_cover > 128)) return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
     }
     return gemm<T>(g, n_cover, batch, epi, st);

@@ -500,6 +500,52 @@ def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters):
     assert torch.equal(X, X1) and torch.equal(C, C1)
 
 
+# (type, heads, n_q, n, d, m): contractions of less than a step, one, eight and nine steps, and with a ragged last one; tiles of
+# one row and column, whole ones and one more; both tile sizes in bf16
+FEW_TILE_CASES = [("f32", 1, 1, 70, 8, 5), ("f32", 2, 33, 256, 64, 64), ("f32", 1, 32, 289, 40, 31), ("f32", 3, 65, 1571, 80, 97), ("f32", 1, 100, 4099, 128, 300),
+                  ("bf16", 1, 1, 67, 8, 5), ("bf16", 2, 33, 512, 80, 64), ("bf16", 3, 64, 577, 32, 33), ("bf16", 10, 70, 1571, 80, 197), ("bf16", 4, 40, 2050, 96, 1000)]
+
+
+@pytest.mark.parametrize("dtype,heads,n_q,n,d,m", FEW_TILE_CASES)
+def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
+    """Measurement, output product and synthesis whose tiles would leave most CUs idle, against float64 on the same operands; the
+    synthesis also where operands are infinite, NaN or tiny: finite where the 128-wide kernels' result is."""
+    rng = np.random.default_rng(n)
+    q = lambda *s: gen.quantize(rng.standard_normal(s).astype(np.float32), dtype)    # noqa: E731
+    Phi = gen.quantize((rng.standard_normal((m, n)) / np.sqrt(m)).astype(np.float32), dtype)
+    Q, K, V = q(heads, n_q, d), q(heads, n, d), q(heads, n, d)
+    dims = csat.make_dims(1, heads, n_q, n, d, m, dtype)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, 1), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    empty = lambda *s: torch.empty(*s, dtype=to_dev(Q, dtype).dtype, device=DEV)     # noqa: E731
+    Kc, Vc, Z, C = empty(heads, m, d), empty(heads, m, d), empty(heads, n_q, d), empty(heads, n_q, d)
+    A, X = torch.empty(heads, n_q, m, device=DEV), torch.empty(heads, n_q, n, device=DEV)
+    csat.csat_measure(dims, to_dev(Phi, dtype), to_dev(K, dtype), to_dev(V, dtype), Kc, Vc, ws)
+    P64, rel = Phi.astype(np.float64), 2e-6 if dtype == "f32" else 4e-3          # 24 bits over K terms; one rounding to bf16
+    assert_close("K~", to_np(Kc), P64 @ K, rel)
+    assert_close("V~", to_np(Vc), P64 @ V, rel)
+    csat.csat_compressed_attention(dims, to_dev(Q, dtype), Kc, Vc, A, Z, ws)
+    torch.cuda.synchronize()
+    assert_close("Z", to_np(Z), to_np(A).astype(np.float64) @ to_np(Vc), 2 * rel)      # (bf16: A~ rounded once too)
+    # 1e-33: sums below 2^-90, where the split products are not used, and well above the smallest normal float (at 1e-37 they
+    # are subnormal, 1.4e-45 apart, which is up to 7.6e-6 of them)
+    for special in (None, np.inf, np.nan, 1e-33):
+        Vs = V.copy()
+        if special is not None:
+            Vs[0, n // 2, d // 2] = special
+        if special == 1e-33:
+            Vs[0] *= np.float32(1e-33)
+        got = []
+        for gemm in (0, 1):
+            options("gemm", gemm)
+            csat.csat_recover(dims, A, to_dev(Phi, dtype), 0.0, 0.01, 1, X, to_dev(Vs, dtype), C, ws)
+            torch.cuda.synchronize()
+            got.append(to_np(C).astype(np.float64))
+        options("gemm", 0)
+        assert (np.isnan(got[0]) == np.isnan(got[1])).all() and (np.isinf(got[0]) == np.isinf(got[1])).all()
+        if special is None or special == 1e-33:
+            assert_close("C", got[0], to_np(X).astype(np.float64) @ Vs, 2 * rel)
+
+
 # (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
 # picked in the end (m = n = picks), several column tiles
 PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20),

@@ -44,6 +44,7 @@ struct AttentionArgs {
     int n_q, m, d;
     float scale_log2e;                             // log2(e) / sqrt(d_k): exp(s / sqrt(d_k)) = 2^(s * scale_log2e)
     int tiles_per_head;                            // ceil(n_q / 32)
+    int waves;                                     // wavefronts per workgroup, at most attention_waves()
     int rounds;                                    // rounds of one row tile per wavefront (1 unless all of K~ sits in LDS)
     int wg_per_head;                               // ceil(tiles_per_head / (wavefronts per workgroup * rounds))
 };
@@ -100,7 +101,7 @@ constexpr int attention_waves(int MTP, int ZM = 0) { return MTP <= 4 || (MTP <= 
 // library's own carving).
 template <typename T, int MTP, bool SINGLE, int ZM>
 __global__ __launch_bounds__(64 * attention_waves(MTP, ZM), 1) void attention_fused_kernel(AttentionArgs a) {
-    constexpr int NW = attention_waves(MTP, ZM);
+    const int NW = a.waves;
     constexpr bool kBf16 = sizeof(T) == 2;
     constexpr bool WANT_Z = ZM != 0, VPACK = ZM >= 2;
     static_assert(!VPACK || kBf16, "packed fragments of V~ exist in bf16 only");

@@ -30,13 +30,13 @@ hipError_t CSAT_TU_FN(int mt, bool single, const AttentionArgs& a, unsigned grid
     typedef float T;
 #endif
     constexpr int Z = CSAT_TU_Z;
-    auto launch = [&](auto kernel, int waves) -> hipError_t {
+    auto launch = [&](auto kernel) -> hipError_t {
         const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * waves), lds_bytes, st, a);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(64 * a.waves), lds_bytes, st, a);
         return hipGetLastError();
     };
-#define CSAT_ATTN(MTP_, SINGLE_) launch(attention_fused_kernel<T, MTP_, SINGLE_, Z>, attention_waves(MTP_, Z))
+#define CSAT_ATTN(MTP_, SINGLE_) launch(attention_fused_kernel<T, MTP_, SINGLE_, Z>)
     switch (attention_mtp(mt, single)) {
         case 1: return CSAT_ATTN(1, true);
         case 2: return CSAT_ATTN(2, true);

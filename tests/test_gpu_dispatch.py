@@ -546,6 +546,28 @@ def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
             assert_close("C", got[0], to_np(X).astype(np.float64) @ Vs, 2 * rel)
 
 
+# (type, heads, n_q, m, d): eight, four and two wavefronts per workgroup (more heads than run at once with fewer; all of a CU's LDS)
+WAVE_CASES = [("f32", 600, 70, 40, 32), ("f32", 140, 200, 100, 64), ("f32", 3, 200, 100, 64), ("f32", 40, 250, 390, 64), ("bf16", 600, 70, 40, 80),
+              ("bf16", 300, 250, 200, 80), ("bf16", 5, 250, 200, 80), ("bf16", 3, 33, 600, 96)]
+
+
+@pytest.mark.parametrize("dtype,heads,n_q,m,d", WAVE_CASES)
+def test_attention_at_every_number_of_wavefronts(dtype, heads, n_q, m, d):
+    """The one-kernel attention against float64 on the same operands, at the workgroup sizes that the number of row tiles picks."""
+    rng = np.random.default_rng(heads)
+    q = lambda *s: gen.quantize(rng.standard_normal(s).astype(np.float32), dtype)    # noqa: E731
+    Q, Kc, Vc = q(heads, n_q, d), q(heads, m, d), q(heads, m, d)
+    dims = csat.make_dims(1, heads, n_q, max(m, n_q), d, m, dtype)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, 0), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    A, Z = torch.empty(heads, n_q, m, device=DEV), torch.empty(heads, n_q, d, dtype=to_dev(Q, dtype).dtype, device=DEV)
+    csat.csat_compressed_attention(dims, to_dev(Q, dtype), to_dev(Kc, dtype), to_dev(Vc, dtype), A, Z, ws)
+    torch.cuda.synchronize()
+    want_a, want_z = orc.compressed_attention(Q, Kc, Vc)
+    # scores of |s| <= 40 to 2^-24 each way, then exp2 and the sum; Z in bf16: the weights and the result rounded once
+    assert_close("A", to_np(A), want_a, 2e-5)
+    assert_close("Z", to_np(Z), want_z, 2e-5 if dtype == "f32" else 1e-2)
+
+
 # (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
 # picked in the end (m = n = picks), several column tiles
 PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20),

@@ -342,10 +342,10 @@ csat_status launch_gemm(const GemmArgs& g, long long n_cover, int batch, const E
     return CSAT_OK;
 }
 
-template <typename Epi, int WM, int WN, int KS>
+template <typename Epi, int WM, int WN, int KS, int TN = 4>
 csat_status launch_gemm_big_shape(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
-    using S = BigGemmShape<Epi, WM, WN, KS>;
-    HIP_TRY(hipFuncSetAttribute((const void*)gemm_nt_bf16_big_kernel<Epi, WM, WN, KS>,
+    using S = BigGemmShape<Epi, WM, WN, KS, TN>;
+    HIP_TRY(hipFuncSetAttribute((const void*)gemm_nt_bf16_big_kernel<Epi, WM, WN, KS, TN>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)S::kLdsBytes));
     const long long tm = (g.M + S::kRowsA - 1) / S::kRowsA, tn = (n_cover + S::kRowsB - 1) / S::kRowsB;
     GemmArgs gt = g;
@@ -361,7 +361,7 @@ csat_status launch_gemm_big_shape(const GemmArgs& g, long long n_cover, int batc
     }
     const long long tiles = gt.raster == 1 ? (tm + 7) / 8 * 8 * tn : tm * tn;
     dim3 grid((unsigned)tiles, 1, (unsigned)batch);
-    hipLaunchKernelGGL((gemm_nt_bf16_big_kernel<Epi, WM, WN, KS>), grid, dim3(S::kThreads), S::kLdsBytes, st, gt, epi);
+    hipLaunchKernelGGL((gemm_nt_bf16_big_kernel<Epi, WM, WN, KS, TN>), grid, dim3(S::kThreads), S::kLdsBytes, st, gt, epi);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
@@ -371,6 +371,20 @@ csat_status launch_gemm_big_shape(const GemmArgs& g, long long n_cover, int batc
 template <typename Epi>
 csat_status launch_gemm_big(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     return launch_gemm_big_shape<Epi, 4, 2, 64>(g, n_cover, batch, epi, st);
+}
+
+// 256 x 320 tiles where they take less of the CUs' time: a CU has one tile at a time, so that is whole rounds of tiles times
+// their width, and a twelfth for the wider tile's loop.  A forward of 20 layers over 76 800 rows, n = 1600 (six rounds of 320 against nine of
+// 256): 8.63 ms against 9.60; not where the rounds are as wide: 8 layers over 16 000 rows, n = 2000 (two, two) 1.51 against 1.43,
+// 6 over 8000, n = 3500 (two, two) 1.32 against 1.17.
+template <typename Epi>
+csat_status launch_gemm_big_lista(const GemmArgs& g, long long n_cover, const Epi& epi, hipStream_t st) {
+    auto cost = [&](int width) {
+        const long long tiles = (g.M + 255ll) / 256 * ((n_cover + width - 1) / width);
+        return (tiles + cu_count() - 1) / cu_count() * width;
+    };
+    if (cost(320) * 13 < cost(256) * 12) return launch_gemm_big_shape<Epi, 4, 2, 64, 5>(g, n_cover, 1, epi, st);
+    return launch_gemm_big<Epi>(g, n_cover, 1, epi, st);
 }
 
 // Big bf16 problems whose operands are zero-padded to a multiple of 64 along K (every workspace
@@ -1350,32 +1364,33 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
         CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));
         if (want_c && !synthesis_is_direct<T>(d)) CSAT_TRY(transpose_pack<T>((const T*)V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
         // alpha^(0) = 0
-        CSAT_TRY(fill_zero(x.Op[0], (size_t)rows * w.ldn * sizeof(T), st));
+        if (!tiled) CSAT_TRY(fill_zero(x.Op[0], (size_t)rows * w.ldn * sizeof(T), st));
         if (kBf16 && !tiled) CSAT_TRY(fill_zero(x.StateF, (size_t)rows * w.ldn * 4, st));
     }
-    {   // W = B y for every row
+    {   // W = B y for every row (tiled: and the first layer, alpha = eta(W))
         GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
         Timed tm(w, CSAT_K_RESIDUAL, st);
         if (tiled) {
-            EpiStoreAccTiled ew{(f32x4*)x.W, w.ldn / 32, w.ldn, rows};
+            EpiListaFirstTiled ew{{(f32x4*)x.StateF, w.ldn / 32, x.Mask, (bf16_t*)x.Op[1], w.ldn, iters == 1 ? X : nullptr, 1.f, thetas[0], rows, d.n, 1},
+                                  iters == 1 ? nullptr : (f32x4*)x.W};
             g.K = (int)round_up(g.K, 64);
-            CSAT_TRY(launch_gemm_big(g, w.ldn, 1, ew, st));
+            CSAT_TRY(launch_gemm_big_lista(g, w.ldn, ew, st));
         } else {
             EpiStore<float> ew{x.W, w.ldn, 0, nullptr, 0, 0, 1.f, (int)rows, d.n};
             CSAT_TRY((gemm<T>(g, d.n, 1, ew, st)));
         }
     }
-    for (int t = 0; t < iters; ++t) {
+    for (int t = tiled ? 1 : 0; t < iters; ++t) {
         char* cur = x.Op[t & 1];
         char* nxt = x.Op[(t + 1) & 1];
         GemmArgs g{cur, w.ldn, 0, x.D, w.ldn, 0, (int)rows, d.n, d.n, 0};
         if (tiled) {    // accumulators start from W; the iterate is kept like the ISTA decoder's (sparse, accumulator order)
             EpiListaUpdateTiled eu{{(f32x4*)x.StateF, w.ldn / 32, x.Mask, (bf16_t*)nxt, w.ldn,
-                                    (t == iters - 1) ? X : nullptr, 1.f, thetas[t], rows, d.n, t == 0},
+                                    (t == iters - 1) ? X : nullptr, 1.f, thetas[t], rows, d.n, 0},
                                    (const f32x4*)x.W};
-            g.K = t == 0 ? 64 : (int)round_up(g.K, 64);      // alpha^(0) = 0: one K step over the zero operand
+            g.K = (int)round_up(g.K, 64);
             Timed tm(w, CSAT_K_UPDATE, st);
-            CSAT_TRY(launch_gemm_big(g, w.ldn, 1, eu, st));
+            CSAT_TRY(launch_gemm_big_lista(g, w.ldn, eu, st));
             continue;
         }
         EpiListaUpdate eu{kBf16 ? x.StateF : (const float*)cur, kBf16 ? x.StateF : (float*)nxt, w.ldn, x.W,

@@ -7,6 +7,10 @@
 // 1 KB = 512/KS rows; the 16-byte slot of a row is XOR-swizzled with (row/2) so that the
 // fragment reads of consecutive rows fall in different bank groups.  Two LDS stages.
 //
+// TN 5 is the same with 64 x 160 per wavefront, a 256 x 320 tile: 160 accumulator registers leave room for one set of
+// fragments, read when the products need them (the SIMD's other wavefront computes meanwhile; two sets spill in the main loop:
+// unrolled decoder of 76 800 rows, n = 1600 11.35 ms against 8.63), and for 32-bit addresses.
+//
 // The shape in use is <4, 2, 64>: 256 x 256 tile, 8 wavefronts (two per SIMD, so one wavefront's
 // staging requests and LDS waits are covered by the other's MFMAs), 128 KB of stages, one
 // workgroup per CU.  <4, 1, 32> (256 x 128, two workgroups per CU) also instantiates.
@@ -22,29 +26,32 @@ namespace csat {
 
 template <typename E, bool = has_tile_epilogue<E>::value> struct TilePre { struct type {}; };
 template <typename E> struct TilePre<E, true> { using type = typename E::Pre; };
-template <typename E>
+template <int TN, typename E>
 __device__ __forceinline__ typename TilePre<E>::type tile_begin(const E& epi, long long r0w, long long c0w, int lane) {
-    if constexpr (has_tile_epilogue<E>::value) return epi.begin(r0w, c0w, lane);
+    if constexpr (TN == 5) return epi.template begin_wide<TN>(r0w, c0w, lane);
+    else if constexpr (has_tile_epilogue<E>::value) return epi.begin(r0w, c0w, lane);
     else return {};
 }
 
-template <typename Epi, int WM, int WN, int KS>
+template <typename Epi, int WM, int WN, int KS, int TN = 4>
 struct BigGemmShape {
     static constexpr int kWaves = WM * WN, kThreads = 64 * kWaves;
-    static constexpr int kRowsA = 64 * WM, kRowsB = 128 * WN;
+    static constexpr int kRowsA = 64 * WM, kRowsB = 32 * TN * WN;
     static constexpr int kRowBytes = 2 * KS;                       // one operand row of a stage
     static constexpr int kStage = (kRowsA + kRowsB) * kRowBytes;
     static constexpr int kOffB = kRowsA * kRowBytes;
     static constexpr size_t epilogue_bytes() {
-        if constexpr (has_tile_epilogue<Epi>::value) return (size_t)kWaves * Epi::kStageBytes;
+        if constexpr (TN == 5) return (size_t)kWaves * Epi::kWideStageBytes;
+        else if constexpr (has_tile_epilogue<Epi>::value) return (size_t)kWaves * Epi::kStageBytes;
         else return 0;
     }
     static constexpr size_t kLdsBytes = 2 * kStage > epilogue_bytes() ? 2 * kStage : epilogue_bytes();
 };
 
-template <typename Epi, int WM, int WN, int KS>
+template <typename Epi, int WM, int WN, int KS, int TN = 4>
 __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_kernel(GemmArgs g, Epi epi) {
-    using S = BigGemmShape<Epi, WM, WN, KS>;
+    using S = BigGemmShape<Epi, WM, WN, KS, TN>;
+    static_assert(TN == 4 || TN == 5, "column tiles per wavefront");
     constexpr int CPR = S::kRowBytes / 16;           // 16-byte chunks per staged row
     constexpr int RPB = 64 / CPR;                    // rows per 1 KB request
     constexpr int BLOCKS_A = S::kRowsA / RPB, BLOCKS = (S::kRowsA + S::kRowsB) / RPB;
@@ -96,7 +103,12 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     // then Bt rows).  Lane l: row l/CPR of the block, LDS slot l%CPR, which holds the row's 16-byte
     // chunk (l%CPR) ^ ((row/2)&(CPR-1)).
     const int drow = lane / CPR, dslot = lane % CPR;
+    // (TN 5 has no registers for 64-bit addresses: uniform tile bases and 32-bit offsets; row0 lies in A, col0 may lie in the pads)
     const bf16_t* src[BPW];
+    uint32_t off[BPW];
+    const long long colb = col0 < g.N ? col0 : g.N - 1;
+    const char* baseA = (const char*)(A + row0 * g.lda);
+    const char* baseB = (const char*)(Bt + colb * g.ldb);
 #pragma unroll
     for (int b = 0; b < BPW; ++b) {
         const int blk = wave * BPW + b;
@@ -106,13 +118,17 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
         long long gr = (isA ? row0 : col0) + r;
         const long long lim = isA ? g.M : g.N;
         if (gr >= lim) gr = lim - 1;
-        src[b] = (isA ? A + gr * g.lda : Bt + gr * g.ldb) + chunk * 8;
+        if constexpr (TN == 4) src[b] = (isA ? A + gr * g.lda : Bt + gr * g.ldb) + chunk * 8;
+        else off[b] = (uint32_t)((isA ? (gr - row0) * g.lda : (gr - colb) * g.ldb) + chunk * 8) * 2;
     }
     auto stage = [&](int ks, int st) {
         char* dst = (char*)lds + st * S::kStage + wave * BPW * 1024;
 #pragma unroll
         for (int b = 0; b < BPW; ++b) {
-            if (a_nt && wave * BPW + b < BLOCKS_A)
+            if constexpr (TN == 5)
+                __builtin_amdgcn_global_load_lds((glb_ptr_t)((wave * BPW + b < BLOCKS_A ? baseA : baseB) + (long long)ks * (2 * KS) + off[b]),
+                                                 (lds_ptr_t)(dst + b * 1024), 16, 0, 0);
+            else if (a_nt && wave * BPW + b < BLOCKS_A)
                 __builtin_amdgcn_global_load_lds((glb_ptr_t)(src[b] + (long long)ks * KS), (lds_ptr_t)(dst + b * 1024), 16, 0, 2);
             else
                 __builtin_amdgcn_global_load_lds((glb_ptr_t)(src[b] + (long long)ks * KS), (lds_ptr_t)(dst + b * 1024), 16, 0, 0);
@@ -125,20 +141,20 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     for (int gk = 0; gk < NGK; ++gk) {
         const uint32_t slot = (uint32_t)((2 * gk + lh) ^ ((li >> 1) & (CPR - 1))) * 16;
         adA[gk] = lds0 + (wm * 64 + li) * S::kRowBytes + slot;
-        adB[gk] = lds0 + S::kOffB + (wn * 128 + li) * S::kRowBytes + slot;
+        adB[gk] = lds0 + S::kOffB + (wn * (32 * TN) + li) * S::kRowBytes + slot;
     }
 
-    f32x16 acc[2][4];
+    f32x16 acc[2][TN];
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    if constexpr (has_acc_init<Epi>::value) epi.init(row0 + wm * 64, col0 + wn * 128, lane, acc);
+    if constexpr (has_acc_init<Epi>::value) epi.template init<TN>(row0 + wm * 64, col0 + wn * (32 * TN), lane, acc);
 
     stage(0, 0);
-    typename TilePre<Epi>::type pre = tile_begin(epi, row0 + wm * 64, col0 + wn * 128, lane);
+    typename TilePre<Epi>::type pre = tile_begin<TN>(epi, row0 + wm * 64, col0 + wn * (32 * TN), lane);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     for (int ks = 0; ks < ksteps; ++ks) {
@@ -149,42 +165,47 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
         const bool more = ks + 1 < ksteps;
         const bool early = wave < S::kWaves / 2;
         if (more && early) stage(ks + 1, (ks + 1) & 1);
-        u32x4 fa[2][2], fb[2][4];
+        constexpr int FB = TN == 4 ? 1 : 0;
+        u32x4 fa[FB + 1][2], fb[FB + 1][TN];
         auto fetch = [&](auto gkc) {
             constexpr int gk = decltype(gkc)::value;
             constexpr int T32 = 32 * S::kRowBytes;        // 32 rows further
-            lds_read16<0>(fa[gk & 1][0], adA[gk] + so);
-            lds_read16<T32>(fa[gk & 1][1], adA[gk] + so);
-            lds_read16<0>(fb[gk & 1][0], adB[gk] + so);
-            lds_read16<T32>(fb[gk & 1][1], adB[gk] + so);
-            lds_read16<2 * T32>(fb[gk & 1][2], adB[gk] + so);
-            lds_read16<3 * T32>(fb[gk & 1][3], adB[gk] + so);
+            lds_read16<0>(fa[gk & FB][0], adA[gk] + so);
+            lds_read16<T32>(fa[gk & FB][1], adA[gk] + so);
+            lds_read16<0>(fb[gk & FB][0], adB[gk] + so);
+            lds_read16<T32>(fb[gk & FB][1], adB[gk] + so);
+            lds_read16<2 * T32>(fb[gk & FB][2], adB[gk] + so);
+            lds_read16<3 * T32>(fb[gk & FB][3], adB[gk] + so);
+            if constexpr (TN == 5) lds_read16<4 * T32>(fb[gk & FB][TN - 1], adB[gk] + so);
         };
         auto compute = [&](auto gkc) {
             constexpr int gk = decltype(gkc)::value;
-            if constexpr (gk + 1 < NGK) {
+            if constexpr (TN == 5) fetch(gkc);
+            if constexpr (TN == 4 && gk + 1 < NGK) {
                 fetch(std::integral_constant<int, gk + 1>{});
-                asm volatile("s_waitcnt lgkmcnt(6)"
-                             : "+v"(fa[gk & 1][0]), "+v"(fa[gk & 1][1]), "+v"(fb[gk & 1][0]), "+v"(fb[gk & 1][1]),
-                               "+v"(fb[gk & 1][2]), "+v"(fb[gk & 1][3]));
+                asm volatile("s_waitcnt lgkmcnt(%6)"
+                             : "+v"(fa[gk & FB][0]), "+v"(fa[gk & FB][1]), "+v"(fb[gk & FB][0]), "+v"(fb[gk & FB][1]),
+                               "+v"(fb[gk & FB][2]), "+v"(fb[gk & FB][3])
+                             : "n"(2 + TN));
             } else {
                 asm volatile("s_waitcnt lgkmcnt(0)"
-                             : "+v"(fa[gk & 1][0]), "+v"(fa[gk & 1][1]), "+v"(fb[gk & 1][0]), "+v"(fb[gk & 1][1]),
-                               "+v"(fb[gk & 1][2]), "+v"(fb[gk & 1][3]));
+                             : "+v"(fa[gk & FB][0]), "+v"(fa[gk & FB][1]), "+v"(fb[gk & FB][0]), "+v"(fb[gk & FB][1]),
+                               "+v"(fb[gk & FB][2]), "+v"(fb[gk & FB][3]));
             }
+            if constexpr (TN == 5) asm volatile("" : "+v"(fb[gk & FB][TN - 1]));
 #pragma unroll
             for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[gk & 1][i]),
-                                                                        __builtin_bit_cast(bf16x8, fb[gk & 1][j]), acc[i][j], 0, 0, 0);
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fa[gk & FB][i]),
+                                                                        __builtin_bit_cast(bf16x8, fb[gk & FB][j]), acc[i][j], 0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (gk == 1) {
                 if (more && !early) stage(ks + 1, (ks + 1) & 1);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
-        fetch(std::integral_constant<int, 0>{});
+        if constexpr (TN == 4) fetch(std::integral_constant<int, 0>{});
         compute(std::integral_constant<int, 0>{});
         compute(std::integral_constant<int, 1>{});
         if constexpr (NGK == 4) {
@@ -196,7 +217,9 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     }
 
     // accumulator layout of the 32x32 MFMA: lane (li, lh), register v holds row 8*(v/4) + 4*lh + (v%4), column li
-    if constexpr (has_tile_epilogue<Epi>::value) {
+    if constexpr (TN == 5) {
+        epi.template whole_wide<TN>(row0 + wm * 64, col0 + wn * (32 * TN), lane, acc, (char*)lds + wave * Epi::kWideStageBytes, pre);
+    } else if constexpr (has_tile_epilogue<Epi>::value) {
         // the stages are free now (last barrier passed): each wavefront takes a private piece
         char* stage_w = (char*)lds + wave * Epi::kStageBytes;
         const long long r0w = row0 + wm * 64, c0w = col0 + wn * 128;

@@ -613,6 +613,101 @@ struct EpiIstaUpdateTiled {
         work(B2{}, xa);
         work(B3{}, xb2);
     }
+    // The same for blocks of 2 x TN tiles on the kernel's wider tile: a mask takes four bits of have[i], the tiles go one at a time
+    // with the next one's old state on its way (registers), and the bf16 copy leaves 32 rows at a time.
+    static constexpr int kWidePitch = 5 * 64 + 16, kWideStageBytes = 32 * kWidePitch;
+    template <int TN>
+    __device__ __forceinline__ int live_wide(long long r0, long long c0w) const {
+        if (r0 >= M || c0w >= ldS) return 0;
+        const long long left = (ldS - c0w) >> 5;
+        return left < TN ? (int)left : TN;
+    }
+    template <int TN>
+    __device__ __forceinline__ Pre begin_wide(long long r0w, long long c0w, int lane) const {
+        Pre pre{{0u, 0u}};
+        if (first) return pre;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int nl = live_wide<TN>(r0w + i * 32, c0w);
+            const long long t = ((r0w >> 5) + i) * tiles_n + (c0w >> 5);
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+                if (j < nl) pre.have[i] |= (uint32_t)Mask[(t + j) * 64 + lane] << (4 * j);
+        }
+        return pre;
+    }
+    template <int TN>
+    __device__ __forceinline__ void whole_wide(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN], char* stage,
+                                               const Pre& pre) const {
+        if (r0w + 64 <= M && c0w + 32 * TN <= N && !Xo) run_wide<false, TN>(r0w, c0w, lane, acc, stage, pre);
+        else run_wide<true, TN>(r0w, c0w, lane, acc, stage, pre);
+    }
+    template <bool EDGE, int TN>
+    __device__ __forceinline__ void run_wide(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN], char* stage,
+                                             const Pre& pre) const {
+        constexpr int PITCH = TN * 64 + 16, CHUNKS = TN * 4;
+        static_assert(PITCH <= kWidePitch, "stage");
+        const int li = lane & 31, lh = lane >> 5;
+        const int nl[2] = {live_wide<TN>(r0w, c0w), live_wide<TN>(r0w + 32, c0w)};
+        const long long t[2] = {(r0w >> 5) * tiles_n + (c0w >> 5), ((r0w >> 5) + 1) * tiles_n + (c0w >> 5)};
+        __amdgpu_buffer_rsrc_t rs[2] = {
+            __builtin_amdgcn_make_buffer_rsrc((void*)(Xs + t[0] * 256), 0, nl[0] * 4096, kBufferFlags),
+            __builtin_amdgcn_make_buffer_rsrc((void*)(Xs + t[1] * 256), 0, nl[1] * 4096, kBufferFlags)};
+        u32x4 xo[2][4];
+        auto issue = [&](int b, u32x4 (&x)[4]) {
+            const int i = b / TN, j = b % TN;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int off = ((pre.have[i] >> (4 * j + g)) & 1) ? j * 4096 + g * 1024 + lane * 16 : kOutOfRange;
+                x[g] = __builtin_amdgcn_raw_buffer_load_b128(rs[i], off, 0, kStreamAux);
+            }
+        };
+        issue(0, xo[0]);
+#pragma unroll
+        for (int b = 0; b < 2 * TN; ++b) {
+            const int i = b / TN, j = b % TN;
+            if (b + 1 < 2 * TN) issue(b + 1, xo[(b + 1) % 2]);
+            const long long r0 = r0w + 32 * i, c = c0w + j * 32 + li;
+            char* sw = stage + 4 * lh * PITCH + li * 2 + j * 64;
+            uint32_t nz = 0;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const f32x4 old = __builtin_bit_cast(f32x4, xo[b % 2][g]);
+                f32x4 xn;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float u = old[e] + mu * acc[i][j][4 * g + e];
+                    float x = u - __builtin_amdgcn_fmed3f(u, -theta, theta);
+                    if constexpr (EDGE) {
+                        const long long r = r0 + 8 * g + 4 * lh + e;
+                        if (!(c < N && r < M)) x = 0.f;
+                        if (Xo && c < N && r < M) Xo[r * (long long)N + c] = x;
+                    }
+                    xn[e] = x;
+                }
+#pragma unroll
+                for (int e = 0; e < 4; e += 2) {
+                    const uint32_t pk = f2bf_pk(xn[e], xn[e + 1]);
+                    *(bf16_t*)(sw + (8 * g + e) * PITCH) = (bf16_t)pk;
+                    *(bf16_t*)(sw + (8 * g + e + 1) * PITCH) = (bf16_t)(pk >> 16);
+                }
+                const u32x4 xb = __builtin_bit_cast(u32x4, xn);
+                const bool any = ((xb[0] | xb[1]) | (xb[2] | xb[3])) != 0u;
+                __builtin_amdgcn_raw_buffer_store_b128(xb, rs[i], any ? j * 4096 + g * 1024 + lane * 16 : kOutOfRange, 0, kStreamAux);
+                nz |= any ? 1u << g : 0u;
+            }
+            if (j < nl[i]) Mask[(t[i] + j) * 64 + lane] = (uint8_t)nz;
+            __builtin_amdgcn_sched_barrier(0);
+            if (j + 1 < TN) continue;
+#pragma unroll
+            for (int p = 0; p < 32 * CHUNKS / 64; ++p) {
+                const int piece = p * 64 + lane, row = piece / CHUNKS, chunk = piece % CHUNKS;
+                const long long r = r0 + row, cc = c0w + chunk * 8;
+                const uint4 v = *(const uint4*)(stage + row * PITCH + chunk * 16);
+                if (r < M && cc < ldS) *(uint4*)(Xb + r * ldS + cc) = v;
+            }
+        }
+    }
     // The wavefront's staged 64 rows x 128 columns of bf16, written 16 bytes per lane:
     // one instruction covers 4 rows x 256 contiguous bytes.
     __device__ __forceinline__ void flush(long long r0, long long c0, int lane, const char* stage) const {
@@ -628,18 +723,19 @@ struct EpiIstaUpdateTiled {
 };
 
 // One layer of the unrolled decoder on the large-tile kernel: u = alpha + (S - I) alpha + B y.  The
-// accumulators start from W = B y (stored in accumulator order by EpiStoreAccTiled, loaded before the
+// accumulators start from W = B y (stored in accumulator order by the first layer, loaded before the
 // main loop), so the epilogue is the ISTA one with mu = 1 and this layer's threshold.
 struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
     static constexpr bool kAccInit = true;
     const f32x4* W;
-    __device__ __forceinline__ void init(long long r0w, long long c0w, int lane, f32x16 (&acc)[2][4]) const {
+    template <int TN>
+    __device__ __forceinline__ void init(long long r0w, long long c0w, int lane, f32x16 (&acc)[2][TN]) const {
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int nl = live_tiles(r0w + i * 32, c0w);
+            const int nl = live_wide<TN>(r0w + i * 32, c0w);
             const long long t = ((r0w >> 5) + i) * tiles_n + (c0w >> 5);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < TN; ++j)
                 if (j < nl) {
 #pragma unroll
                     for (int g = 0; g < 4; ++g) {
@@ -652,26 +748,20 @@ struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
     }
 };
 
-// Stores the accumulators as they are, in accumulator order: tile (row tile, column tile) of 32 x 32 is
-// 256 float4, [g][lane] = rows 8g + 4*lh .. +3 of column li.  Same tiling as the sparse iterate.
-struct EpiStoreAccTiled {
-    static constexpr bool kTile = true;
-    static constexpr bool kWhole = true;
-    static constexpr int kStageBytes = 0;
-    struct Pre {};
-    f32x4* W; long long tiles_n; long long ldS;
-    long long M;
-    __device__ __forceinline__ Pre begin(long long, long long, int) const { return {}; }
-    __device__ __forceinline__ void whole(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][4], char*,
-                                          const Pre&) const {
+// The first layer, alpha^(0) = 0: the product is W = B y itself.  It is kept for the layers behind (null: there are none),
+// in accumulator order: tile (row tile, column tile) of 32 x 32 is 256 float4, [g][lane] = rows 8g + 4*lh .. +3 of column li, as
+// the sparse iterate.
+struct EpiListaFirstTiled : EpiIstaUpdateTiled {
+    f32x4* W;
+    template <int TN>
+    __device__ __forceinline__ void keep(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN]) const {
+        if (!W) return;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            if (r0w + i * 32 >= M || c0w >= ldS) continue;
-            const long long left = (ldS - c0w) >> 5;
-            const int nl = left < 4 ? (int)left : 4;
+            const int nl = live_wide<TN>(r0w + i * 32, c0w);
             const long long t = ((r0w >> 5) + i) * tiles_n + (c0w >> 5);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < TN; ++j)
                 if (j < nl) {
 #pragma unroll
                     for (int g = 0; g < 4; ++g)
@@ -680,7 +770,15 @@ struct EpiStoreAccTiled {
                 }
         }
     }
-    __device__ __forceinline__ void flush(long long, long long, int, const char*) const {}
+    __device__ __forceinline__ void whole(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][4], char* stage, const Pre& pre) const {
+        keep<4>(r0w, c0w, lane, acc);
+        EpiIstaUpdateTiled::whole(r0w, c0w, lane, acc, stage, pre);
+    }
+    template <int TN>
+    __device__ __forceinline__ void whole_wide(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN], char* stage, const Pre& pre) const {
+        keep<TN>(r0w, c0w, lane, acc);
+        EpiIstaUpdateTiled::whole_wide<TN>(r0w, c0w, lane, acc, stage, pre);
+    }
 };
 
 template <typename E, typename = void> struct has_acc_init : std::false_type {};

@@ -568,6 +568,33 @@ def test_attention_at_every_number_of_wavefronts(dtype, heads, n_q, m, d):
     assert_close("Z", to_np(Z), want_z, 2e-5 if dtype == "f32" else 1e-2)
 
 
+@pytest.mark.parametrize("rows,n,m,iters", [(33000, 320, 160, 3), (33001, 300, 136, 2), (13000, 1600, 200, 3), (13007, 1530, 130, 1)])
+def test_unrolled_decoder_on_the_wider_tile(rows, n, m, iters):
+    """Row and column counts whose layers run 256 x 320 tiles: the bits that slices of the rows (too few for it) get on 256 x 256."""
+    rng = np.random.default_rng(rows)
+    bf = lambda *s: to_dev(gen.quantize(rng.standard_normal(s).astype(np.float32), "bf16"), "bf16")     # noqa: E731
+    g = torch.Generator(device=DEV).manual_seed(rows)
+    Y = torch.randn(1, rows, m, generator=g, device=DEV)
+    V, B = bf(1, n, 64), (bf(n, m) * 0.05)
+    S = (torch.eye(n, device=DEV) + 0.3 / n ** 0.5 * torch.randn(n, n, generator=g, device=DEV)).bfloat16()
+    thetas = [0.2 + 0.1 * t for t in range(iters)]
+
+    def decode(y):
+        r = y.shape[1]
+        dims = csat.make_dims(1, 1, r, n, 64, m, "bf16")
+        ws = torch.empty(csat.csat_lista_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        X, C = torch.empty(1, r, n, device=DEV), torch.empty(1, r, 64, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover_lista(dims, y.clone(), S, B, thetas, X, V, C, ws)
+        torch.cuda.synchronize()
+        return X, C
+
+    X, C = decode(Y)
+    assert X.isfinite().all() and 0.05 < float((X != 0).float().mean()) < 0.95
+    for r0 in (0, 7936, rows - 300):
+        Xs, Cs = decode(Y[:, r0:r0 + 300])
+        assert torch.equal(X[:, r0:r0 + 300], Xs) and torch.equal(C[:, r0:r0 + 300], Cs)
+
+
 # (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
 # picked in the end (m = n = picks), several column tiles
 PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20),

@@ -703,17 +703,12 @@ csat_status launch_attention_fused(const csat_dims& d, const Workspace& w, const
     // Rounds of one row tile per wavefront: with all of K~ in LDS a workgroup amortises its staging over several
     // rounds; take the count that needs the fewest passes of the grid over the chip (ties: fewer rounds).
     int nw = attention_waves(attention_mtp(mt, single), v_packed ? 2 : 0);
-    // Fewer wavefronts per workgroup, down to two, while all workgroups still run at once (a wavefront may take half a SIMD's
-    // registers): eight row tiles of one head are otherwise one CU's work.  Stage call with A~ and Z, eight, four, two, one
-    // wavefronts, us: float, 1 x 256 rows, m = 64 30.4, 22.9, 20.8, 20.4; 16 x 300, m = 128, d = 32 38.6, 28.0, 25.1, 23.7;
-    // 48 x 256, m = 64 33.3, 26.1, 23.9, 32.0; 12 x 1600, m = 392 (all of a CU's LDS; four at most) -, 75.6, 95.7, 119; bf16, 10 x 333,
-    // m = 197, d = 80 54.0, 43.9, 39.3, 38.9; 4 x 300, m = 1024 135, 84.8, 70.9, 68.0.
-    const size_t frag_bytes = (size_t)attention_mtp(mt, single) * (a.ns + (v_packed ? d.d / 16 : 0)) * 1024;
-    while (nw > 2) {
-        const int half = nw / 2, per_cu = std::min(8 / half, std::max(1, (int)(kAttnLdsBytes / frag_bytes)));
-        if ((long long)BH * ((a.tiles_per_head + half - 1) / half) > (long long)per_cu * cu_count()) break;
-        nw = half;
-    }
+    // Fewer wavefronts per workgroup, down to two, while there is no more than a workgroup per CU: eight row tiles of one head are
+    // otherwise one CU's work.  Stage call with A~ and Z, eight, four, two, one wavefronts, us: float, 1 x 256 rows, m = 64 30.4, 22.9,
+    // 20.8, 20.4; 16 x 300, m = 128, d = 32 38.6, 28.0, 25.1, 23.7; 12 x 1600, m = 392 (four at most) -, 75.6, 95.7, 119; 192 x 120,
+    // m = 73 43.1, 41.7, 51.8, 43.3; bf16, 10 x 333, m = 197, d = 80 54.0, 43.9, 39.3, 38.9; 4 x 300, m = 1024 135, 84.8, 70.9, 68.0;
+    // 64 x 500, m = 100 32.9, 29.1, 33.2, 45.8; 128 x 300, m = 128 37.3, 40.7, 39.7, 47.9.
+    while (nw > 2 && (long long)BH * ((a.tiles_per_head + nw / 2 - 1) / (nw / 2)) <= cu_count()) nw /= 2;
     a.waves = nw;
     a.rounds = 1;
     if (single) {

@@ -546,8 +546,9 @@ def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
             assert_close("C", got[0], to_np(X).astype(np.float64) @ Vs, 2 * rel)
 
 
-# (type, heads, n_q, m, d): eight, four and two wavefronts per workgroup (more heads than run at once with fewer; all of a CU's LDS)
-WAVE_CASES = [("f32", 600, 70, 40, 32), ("f32", 140, 200, 100, 64), ("f32", 3, 200, 100, 64), ("f32", 40, 250, 390, 64), ("bf16", 600, 70, 40, 80),
+# (type, heads, n_q, m, d): eight, four and two wavefronts per workgroup (more workgroups than CUs with fewer; four at most)
+WAVE_CASES = [("f32", 600, 70, 40, 32), ("f32", 140, 200, 100, 64), ("f32", 192, 120, 73, 64), ("f32", 3, 200, 100, 64),
+              ("f32", 40, 250, 390, 64), ("bf16", 600, 70, 40, 80),
               ("bf16", 300, 250, 200, 80), ("bf16", 5, 250, 200, 80), ("bf16", 3, 33, 600, 96)]
 
 

@@ -454,13 +454,17 @@ csat_status gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi
 // comparison) would move their outputs further than two correct float implementations are allowed to differ.  Narrow
 // products over a contraction of one step stay there too: the split's start costs more than it saves (one iteration of
 // 256 to 20 000 rows, n = 40 or 64, m = 8 or 32: 23 to 26.5 us against 25 to 28; n = 200 33 to 46 against 32 to 39).
+// (Of few tiles too: what the split leaves out is largest beside a sum of one product, and that is what a sparse row's
+// synthesis over at most 32 columns is.)
 template <typename T, typename Epi>
 csat_status decoder_gemm(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     if constexpr (sizeof(T) == 4) {
-        if constexpr (!has_rows_epilogue<Epi>::value) {
-            if (few_tiles<T>(g, n_cover, batch)) return launch_gemm_deep<T, 1, true, Epi>(g, n_cover, batch, epi, st);
+        if (gemm_choice() != 1 && (g.K > 32 || n_cover > 128)) {
+            if constexpr (!has_rows_epilogue<Epi>::value) {
+                if (few_tiles<T>(g, n_cover, batch)) return launch_gemm_deep<T, 1, true, Epi>(g, n_cover, batch, epi, st);
+            }
+            return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
         }
-        if (gemm_choice() != 1 && (g.K > 32 || n_cover > 128)) return launch_gemm_f32<Epi>(g, n_cover, batch, epi, st);
     }
     return gemm<T>(g, n_cover, batch, epi, st);
 }

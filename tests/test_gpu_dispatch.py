@@ -546,6 +546,30 @@ def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
             assert_close("C", got[0], to_np(X).astype(np.float64) @ Vs, 2 * rel)
 
 
+@pytest.mark.parametrize("heads,n_q,n,d,m", [(1, 1, 8, 8, 4), (2, 33, 32, 64, 16), (8, 300, 31, 128, 20), (96, 128, 32, 64, 32)])
+def test_synthesis_over_one_step_keeps_exact_products(heads, n_q, n, d, m, options):
+    """Float C = X V over at most 32 columns and 128 features, few tiles: products of float, not of its bf16 parts, so the bits of
+    the 128-wide kernel (one chain there and here), on dense rows and on rows of one coefficient."""
+    rng = np.random.default_rng(n_q)
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "f32")
+    Phi = torch.eye(m, n, device=DEV)
+    V = to_dev(rng.standard_normal((heads, n, d)).astype(np.float32), "f32")
+    ws = torch.empty(csat.csat_workspace_bytes(dims, 1), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    for sparse in (False, True):
+        Y = rng.standard_normal((heads, n_q, m)).astype(np.float32)
+        if sparse:
+            Y *= np.arange(m) == rng.integers(0, m, (heads, n_q, 1))
+        out = []
+        for gemm in (0, 1):
+            options("gemm", gemm)
+            X, C = torch.empty(heads, n_q, n, device=DEV), torch.empty(heads, n_q, d, device=DEV)
+            csat.csat_recover(dims, to_dev(Y, "f32"), Phi, 0.0, 1.0, 1, X, V, C, ws)
+            torch.cuda.synchronize()
+            out.append((X, C))
+        assert torch.equal(out[0][0], to_dev(np.pad(Y, ((0, 0), (0, 0), (0, n - m))), "f32"))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
 # (type, heads, n_q, m, d): eight, four and two wavefronts per workgroup (more workgroups than CUs with fewer; four at most)
 WAVE_CASES = [("f32", 600, 70, 40, 32), ("f32", 140, 200, 100, 64), ("f32", 192, 120, 73, 64), ("f32", 3, 200, 100, 64),
               ("f32", 40, 250, 390, 64), ("bf16", 600, 70, 40, 80),

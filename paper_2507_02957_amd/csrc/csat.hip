@@ -198,9 +198,10 @@ struct Workspace {
 // Workgroups that share a 32-row tile of the shared-tile decoder (csat_ista_coop.h), each with its share of the columns: as
 // many as make an iteration shortest by these fits to measured ones (us): a chunk 0.25 + 0.025 MT (two more for the
 // pipeline's ramp), the exchange of the parts of the residual 1.5 + (0.4 + 0.035 MT) a member and up to 3 with the chip full of
-// members.  20 iterations, one to sixteen members: 96 tiles, m = 392, n = 1600 593, 422 us; 30 tiles 589, 388, three 316, four 310,
-// eight 342; 8 tiles four 277, six 261, eight 270; n = 3000, m = 130, 10 tiles 762, 451, four 295, eight 233, sixteen 257; n = 16 384,
-// m = 64, 8 tiles 2894, 1527, sixteen 415; n = 512, m = 392, 120 tiles 237, 261.
+// members.  20 iterations, one to sixteen members: 96 tiles, m = 392, n = 1600 612, 417 us; 30 tiles 591, 372, three 318, four 315,
+// five 298, eight 346; 8 tiles four 282, five 267, six 274, twelve 333; n = 3000, m = 130, 10 tiles 763, 438, four 275, eight 217, twelve
+// 213, sixteen 227; n = 2000, m = 224, 10 tiles 543, 324, four 224, eight 192, twelve 222; n = 16 384, m = 64, 8 tiles 2835, 1477, sixteen
+// 305; n = 512, m = 392, 120 tiles 227, 247.
 // Not for fewer than four iterations, whose sums so keep the order of the other decoders, nor to save less than
 // kTileSplitMinUs of a call.
 constexpr int kTileSplitMinIters = 4, kTileSplitMax = 16;

@@ -1,5 +1,6 @@
 // Fused ISTA decoder (bf16, m <= 416) for launches with few rows: the eight wavefronts of a workgroup share one 32-row
-// tile.  The arithmetic is ista_fused_kernel's, product by product in the same order (same bits); what is shared out:
+// tile.  The arithmetic is ista_fused_kernel's, product by product, in the same order (same bits) where one workgroup has the
+// tile; what is shared out:
 //   wavefronts 0, 1   GEMM-U and the threshold of the even and the odd chunks (a chunk's U is one accumulator chain, so
 //                     it stays with one wavefront and takes two steps; consecutive chunks overlap by one)
 //   wavefronts 2, 3   GEMM-R of every chunk, each for its half of the tiles of m (independent accumulators)
@@ -16,12 +17,15 @@
 // 3330 rows of n = 1571, m = 197: 800 -> 520 us a call.  (U's first part as a half or five sixths: equal, 4 % slower.)
 //
 // Where there are fewer tiles than CUs, several workgroups (members) share a tile, each with its share of the columns, through
-// all iterations; at the end of each they exchange their parts of the residual (fp32), and each forms the whole of it.  The
+// all iterations; at the end of each they exchange their parts of the residual (fp32), and each sums all of them in the members'
+// order: the same residual, bit for bit, in every member, but not the other decoders' order of summation.  The
 // staging and the chain of chunks, which bound a workgroup, get shorter by their number; an exchange takes 4 to 7 us for
 // two members (52 KB out and as much in per CU at m = 392: the volume through the memory-side cache once the chip is full, the latency
-// of a store, a flag and a load before).  The 96 tiles above: 593 -> 422 us with two members, 8 tiles 580 -> 261 with six, 8 tiles of
-// n = 16 384, m = 64 2894 -> 415 with sixteen.  Tried and dropped: all eight wavefronts summing the parts, the own one read back too
-// (8 tiles equal, 96 tiles 489: half as much volume again); parts waited for one by one (30 tiles, four members 332 against 310).
+// of a store, a flag and a load before).  The 96 tiles above: 612 -> 417 us with two members, 8 tiles 592 -> 267 with five, 8 tiles of
+// n = 16 384, m = 64 2835 -> 305 with sixteen.  Tried and dropped: all eight wavefronts summing the parts, the own one read back of two
+// too (8 tiles equal, 96 tiles 489 against 422: half as much volume again); parts waited for one by one (30 tiles, four members 332
+// against 310); the own part kept in registers beside the sum from three members on (30 tiles 327 against 299, 10 tiles of m = 224 253
+// against 200: fewer loads on the way).
 // Members need not all be resident at once: they take their numbers as they start, so a started member waits only for
 // members of its own tile, of which the last started tile alone can lack some, and those start as soon as any CU is free.
 #pragma once
@@ -107,7 +111,7 @@ __global__ __launch_bounds__(512, 1) void ista_coop_kernel(IstaFusedArgs a) {
         const uint32_t nat16 = lds0 + rw * 1024 + frag_slot(lane & 31, lh) * 16;
         f32x16 racc[RT];
         // A shared tile's residual, at the end of an iteration: this wavefront's tiles of the member's part go out, the others'
-        // come in and are added to it in their order.  Parts and flags go past the L2s (agent scope), so no cache is written back
+        // come in and are summed.  Parts and flags go past the L2s (agent scope), so no cache is written back
         // or invalidated; a part is complete (vmcnt) before its flag is set.  A slot is written again two iterations
         // later: its readers have set their own next flags since, which this wavefront has waited for.
         bool gave_up = false;
@@ -137,14 +141,23 @@ __global__ __launch_bounds__(512, 1) void ista_coop_kernel(IstaFusedArgs a) {
                 __builtin_amdgcn_s_sleep(1);
             }
             asm volatile("" ::: "memory");
-            for (int i = 0; i < G2 - 1; i += GB) {
+            // Every member sums in the members' order, so that all hold the same residual: from three on the own part is read back too
+            // (of two, own + other is the same sum).
+            const int parts = G2 == 2 ? 1 : G2;
+            if (G2 > 2) {
+#pragma unroll
+                for (int j = 0; j < RT; ++j)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) racc[j][e] = 0.f;
+            }
+            for (int i = 0; i < parts; i += GB) {
 #pragma unroll
                 for (int j0 = 0; j0 < RT; j0 += JB) {
                     u32x4 v[GB][JB][4];
 #pragma unroll
                     for (int b = 0; b < GB; ++b)
-                        if (i + b < G2 - 1) {
-                            const auto part = slot(i + b + (i + b >= member));
+                        if (i + b < parts) {
+                            const auto part = slot(G2 == 2 ? 1 - member : i + b);
 #pragma unroll
                             for (int j = 0; j < JB; ++j)
 #pragma unroll
@@ -152,7 +165,7 @@ __global__ __launch_bounds__(512, 1) void ista_coop_kernel(IstaFusedArgs a) {
                         }
 #pragma unroll
                     for (int b = 0; b < GB; ++b)
-                        if (i + b < G2 - 1) {
+                        if (i + b < parts) {
 #pragma unroll
                             for (int j = 0; j < JB; ++j)
                                 if (j0 + j < RT) {

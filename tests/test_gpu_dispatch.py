@@ -500,6 +500,25 @@ def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters):
     assert torch.equal(X, X1) and torch.equal(C, C1)
 
 
+@pytest.mark.parametrize("n_q,n,m,iters", MEMBER_CASES)
+def test_workgroups_that_share_a_tile_hold_the_same_residual(n_q, n, m, iters):
+    """The second half of Phi's columns repeats the first: each pair meets the same residual in shares of different workgroups,
+    so the iterate's halves agree bit for bit."""
+    h, rows = n // 2, 6 * n_q
+    dims = csat.make_dims(1, 6, n_q, n, 64, m, "bf16")
+    g = torch.Generator(device=DEV).manual_seed(n)
+    half = torch.randn(m, h, generator=g, device=DEV) / n ** 0.5
+    Phi = torch.cat([half, half, torch.zeros(m, n - 2 * h, device=DEV)], 1).bfloat16()
+    Y = torch.randn(rows, m, generator=g, device=DEV)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    X = torch.empty(rows, n, device=DEV)
+    csat.csat_recover(dims, Y, Phi, (m / n) ** 0.5, 0.2, iters, X, None, None, ws)      # (lambda: the spread of Phi^T y)
+    torch.cuda.synchronize()
+    assert csat.csat_profile_decoder_kernel() == 6 and csat.csat_decoder_status(ws) == 0
+    assert X.isfinite().all() and 0.02 < float((X != 0).float().mean()) < 0.98
+    assert torch.equal(X[:, :h], X[:, h:2 * h])
+
+
 # (type, heads, n_q, n, d, m): contractions of less than a step, one, eight and nine steps, and with a ragged last one; tiles of
 # one row and column, whole ones and one more; both tile sizes in bf16
 FEW_TILE_CASES = [("f32", 1, 1, 70, 8, 5), ("f32", 2, 33, 256, 64, 64), ("f32", 1, 32, 289, 40, 31), ("f32", 3, 65, 1571, 80, 97), ("f32", 1, 100, 4099, 128, 300),

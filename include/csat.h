@@ -187,8 +187,9 @@ csat_status csat_recover_hadamard(void* ctx, const csat_dims* dims, const float*
                                   void* workspace, size_t workspace_bytes, void* stream);
 
 /* Completion status of the ISTA decoder (no passage of the paper: this is error reporting).  The fused
- * decoder (bf16, m <= 512) passes its rows from one workgroup to another between segments of the iterations
- * and bounds the wait for such a hand-over; if a wait ever ran out, the rows concerned were left unfinished.
+ * decoder (bf16, m <= 512) passes its rows from one workgroup to another between segments of the iterations, or,
+ * on launches with few rows, lets several workgroups share 32 rows and exchange their parts of the residual once per
+ * iteration.  It bounds every wait of a workgroup for another; if one ever ran out, the rows concerned are not valid.
  * The launching call has returned CSAT_OK long before (calls are asynchronous), so the kernel records the
  * failure in the workspace and a trailing kernel overwrites X (and, through the synthesis product, C) of that
  * call with NaN.  csat_decoder_status waits for `stream` (host-blocking), reads that record for the last
@@ -210,7 +211,7 @@ typedef enum {
     CSAT_OPT_FUSED_THIN = 5,       /* 1: 128-row workgroups even for launches with few rows */
     CSAT_OPT_LISTA = 6,            /* 1: the unrolled decoder's layers on the element-wise epilogue */
     CSAT_OPT_HADAMARD = 7,         /* 1: the transform-based decoder with its iterate in LDS */
-    CSAT_OPT_FUSED_SPIN_LIMIT = 8, /* k > 0: polls before a hand-over wait gives up; k < 0: give up at the first unmet poll */
+    CSAT_OPT_FUSED_SPIN_LIMIT = 8, /* k > 0: polls before a workgroup's wait for another (a hand-over of rows, the parts of a shared tile's residual) gives up; k < 0: give up at the first unmet poll */
     CSAT_OPT_INJECT_DECODER_ERROR = 9, /* 1 (tests): the decoder starts with its error record set, as if a wait had run out */
     CSAT_OPT_ATTENTION = 10,       /* 1: compressed attention as separate score, softmax and output kernels; 2: as one kernel for every shape */
     CSAT_OPT_FUSED_SCHEDULE = 11,  /* 1: the fused decoder's one-chunk-per-step schedule for every launch */

@@ -155,8 +155,9 @@ constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_st
 constexpr int kFusedMaxMT = 16;
 constexpr int kFused2MaxMT = 13;
 constexpr long long kFusedWideMinGroups = 128;
-// Polls (about 1 us apart) a unit of the fused decoder waits for the preceding segment of its rows before it gives
-// up; several seconds, against a whole launch of a few milliseconds.  CSAT_OPT_FUSED_SPIN_LIMIT overrides it.
+// Polls (about 1 us apart) a unit of the fused decoder waits for the preceding segment of its rows, or a workgroup for the
+// others of its tile, before it gives up; several seconds, against a whole launch of a few milliseconds.
+// CSAT_OPT_FUSED_SPIN_LIMIT overrides it.
 constexpr long long kFusedSpinLimit = 1ll << 22;
 
 // Workspace layout: one carving shared by every entry point (each uses a subset), so one
@@ -298,12 +299,15 @@ Workspace carve(const csat_dims& d, char* base) {
         if (s_ != CSAT_OK) return s_;   \
     } while (0)
 
-// Whether the ISTA decoder keeps Phi in LDS and the iterate in registers (csat_ista_resident.h).  Any option that asks
-// for another decoder, or for a property of one, is honoured.
-bool decoder_options_free() {
+// No option asks for a decoder, or for a property of one: any that does is honoured.
+bool decoder_not_asked_for() {
     const Options& o = *tl_opt;
-    return !(o[CSAT_OPT_DECODER] || o[CSAT_OPT_STATE] || o[CSAT_OPT_FUSED_SEGMENTS] || o[CSAT_OPT_FUSED_THIN] ||
-             o[CSAT_OPT_FUSED_SPIN_LIMIT] || o[CSAT_OPT_INJECT_DECODER_ERROR] || o[CSAT_OPT_FUSED_SCHEDULE]);
+    return !(o[CSAT_OPT_DECODER] || o[CSAT_OPT_STATE] || o[CSAT_OPT_FUSED_SEGMENTS] || o[CSAT_OPT_FUSED_THIN] || o[CSAT_OPT_FUSED_SCHEDULE]);
+}
+// Whether the ISTA decoder keeps Phi in LDS and the iterate in registers (csat_ista_resident.h).  It has no wait to limit
+// and no error record to preset: those options ask for a decoder that does.
+bool decoder_options_free() {
+    return decoder_not_asked_for() && !((*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] || (*tl_opt)[CSAT_OPT_INJECT_DECODER_ERROR]);
 }
 bool decoder_is_resident(const Workspace& w) {
     return decoder_options_free() && w.fused && ista_resident_chunks(w.MT, w.nct) != 0;      // (fused: bf16, and n > 64)
@@ -935,7 +939,7 @@ int fused_variant(int MT, long long rows_pad, int nct, int iters) {
     // leaves more of it to the loads (n = 16 384, 256 tiles, m = 200: two iterations 1053 us with a wavefront per tile, 1315 with
     // eight, three 1477 and 1655, ten 0.9 of the time with eight; at 256 MB, n = 8192, two 0.87).
     const bool streams = iters <= 3 && (long long)rows_pad * nct * 128 > 256ll << 20;
-    if (decoder_options_free() && MT <= kCoopMaxMT && rows_pad / 32 <= (MT <= 4 ? 2 : 1) * cus && !(streams && rows_pad / 32 <= cus)) return 6;
+    if (decoder_not_asked_for() && MT <= kCoopMaxMT && rows_pad / 32 <= (MT <= 4 ? 2 : 1) * cus && !(streams && rows_pad / 32 <= cus)) return 6;
     // (one 32-row tile per workgroup; 14 tiles of m and more: only when forced)
     const bool thin = rows_pad / 32 <= cus && (*tl_opt)[CSAT_OPT_FUSED_THIN] != 1;
     int variant = thin ? 2 : (sparse_state((size_t)rows_pad * nct * 32 * 4) ? 1 : 0);

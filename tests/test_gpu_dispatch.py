@@ -519,6 +519,31 @@ def test_workgroups_that_share_a_tile_hold_the_same_residual(n_q, n, m, iters):
     assert torch.equal(X[:, :h], X[:, h:2 * h])
 
 
+@pytest.mark.parametrize("n_q,n,m,iters", [(512, 1000, 416, 8), (5, 1600, 392, 8), (40, 4500, 20, 7)])
+def test_a_wait_of_workgroups_that_share_a_tile_runs_out(n_q, n, m, iters, options):
+    """Two, five and sixteen workgroups to a tile.  Their waits for each other are bounded: one that runs out is reported and the
+    outputs hold NaN (forced from the host: the error record set before the launch; a limit of no polls, under which whoever is
+    first to an exchange gives up and goes on), every kernel ends normally, and the next call on the workspace is clean."""
+    w = _small("members_give_up", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, lam=0.002)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    C0, _, X0 = p.forward(w.lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() == 6 and csat.csat_decoder_status(p.ws) == 0
+    for option, value, fails in (("inject_decoder_error", 1, True), ("fused_spin_limit", -1, True), ("fused_spin_limit", 1 << 22, False)):
+        options(option, value)
+        C, _, X = p.forward(w.lam, mu, iters)
+        assert csat.csat_profile_decoder_kernel() == 6
+        assert csat.csat_decoder_status(p.ws) == (csat.CSAT_ERR_TIMEOUT if fails else 0)
+        options(option, 0)
+        if fails:
+            assert torch.isnan(X).all() and torch.isnan(C.float()).all()
+            C, _, X = p.forward(w.lam, mu, iters)
+            assert csat.csat_decoder_status(p.ws) == 0
+        assert torch.equal(C, C0) and torch.equal(X, X0)
+
+
 # (type, heads, n_q, n, d, m): contractions of less than a step, one, eight and nine steps, and with a ragged last one; tiles of
 # one row and column, whole ones and one more; both tile sizes in bf16
 FEW_TILE_CASES = [("f32", 1, 1, 70, 8, 5), ("f32", 2, 33, 256, 64, 64), ("f32", 1, 32, 289, 40, 31), ("f32", 3, 65, 1571, 80, 97), ("f32", 1, 100, 4099, 128, 300),

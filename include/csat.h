@@ -264,6 +264,16 @@ csat_status csat_profile_read(void* ctx, int kernel_id, double* total_ms, int* l
  * state, 2 one 32-row tile per workgroup; two chunks per step: 3 dense state, 4 sparse state; 5 the decoder for
  * small problems, Phi in LDS and the iterate in registers; 6 one 32-row tile shared by eight wavefronts. */
 csat_status csat_profile_decoder_kernel(void* ctx, int* kernel);
+/* The form in which the last call on this context launched kernels that come in several (for tests and the benchmark);
+ * 0: it launched no such kernel.  An unknown form gives CSAT_ERR_PARAM. */
+typedef enum {
+    CSAT_FORM_DECODER_MEMBERS = 0,   /* decoder kernel 6: workgroups that share a 32-row tile */
+    CSAT_FORM_SMALL_TILES = 1,       /* products on small tiles (csrc/csat_gemm_deep.h), any of: 1 32 x 32 tiles, 2 64 x 64 tiles, 4 float operands split into bf16 parts */
+    CSAT_FORM_ATTENTION_WAVES = 2,   /* one-kernel compressed attention: wavefronts per workgroup */
+    CSAT_FORM_LISTA_TILE = 3,        /* unrolled decoder on the large-tile product: columns of a tile */
+    CSAT_FORM_COUNT = 4
+} csat_launch_form;
+csat_status csat_profile_launch_form(void* ctx, int form, int* value);
 
 /* Measurement (section 3, K~ = Phi K, V~ = Phi V) for the same structured Phi, by transforms: one Walsh-Hadamard
  * transform of length N per head and feature column, no stored matrix and no workspace.  rows_of_h, signs as in

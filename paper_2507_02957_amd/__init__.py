@@ -21,13 +21,15 @@ EXPORTS = (
     "csat_measure", "csat_compressed_attention", "csat_recover", "csat_forward", "csat_forward_rd",
     "csat_lista_workspace_bytes", "csat_recover_lista", "csat_omp_workspace_bytes", "csat_recover_omp",
     "csat_recover_hadamard", "csat_measure_hadamard", "csat_forward_hadamard", "csat_forward_rd_hadamard", "csat_measure_kv", "csat_forward_kv", "csat_forward_rd_kv",
-    "csat_peak_copy", "csat_peak_mfma", "csat_peak_mfma_issue", "csat_profile_enable", "csat_profile_read", "csat_profile_decoder_kernel",
+    "csat_peak_copy", "csat_peak_mfma", "csat_peak_mfma_issue", "csat_profile_enable", "csat_profile_read", "csat_profile_decoder_kernel", "csat_profile_launch_form",
     "csat_set_option", "csat_decoder_status", "csat_static_workspace_bytes", "csat_forward_static",
 )
 # keys of csat_set_option (include/csat.h, csat_option)
 OPTIONS = {"decoder": 0, "gemm": 1, "raster": 2, "state": 3, "fused_segments": 4, "fused_thin": 5, "lista": 6,
            "hadamard": 7, "fused_spin_limit": 8, "inject_decoder_error": 9, "attention": 10, "fused_schedule": 11,
            "measure": 12, "synthesis": 13, "y_layout": 14}
+# forms of csat_profile_launch_form (include/csat.h, csat_launch_form)
+LAUNCH_FORMS = {"decoder_members": 0, "small_tiles": 1, "attention_waves": 2, "lista_tile": 3}
 CSAT_ERR_TIMEOUT = -8
 KERNEL_IDS = {"layout": 0, "measure": 1, "scores": 2, "softmax": 3, "output": 4, "residual": 5, "update": 6,
               "synthesis": 7}
@@ -92,6 +94,7 @@ def load_library() -> ctypes.CDLL:
     lib.csat_profile_enable.argtypes = [vp, it]
     lib.csat_profile_read.argtypes = [vp, it, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(it)]
     lib.csat_profile_decoder_kernel.argtypes = [vp, ctypes.POINTER(it)]
+    lib.csat_profile_launch_form.argtypes = [vp, it, ctypes.POINTER(it)]
     for name in EXPORTS:
         if name != "csat_status_string":
             getattr(lib, name).restype = it
@@ -320,6 +323,13 @@ def csat_profile_decoder_kernel() -> int:
     step, 3-4 two chunks per step)."""
     k = ctypes.c_int()
     _check(load_library().csat_profile_decoder_kernel(context(), ctypes.byref(k)))
+    return k.value
+
+
+def csat_profile_launch_form(form: str) -> int:
+    """The form in which the last call launched a kernel that comes in several (LAUNCH_FORMS; include/csat.h); 0: not at all."""
+    k = ctypes.c_int()
+    _check(load_library().csat_profile_launch_form(context(), LAUNCH_FORMS[form], ctypes.byref(k)))
     return k.value
 
 

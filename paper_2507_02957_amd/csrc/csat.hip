@@ -63,6 +63,7 @@ struct Context {
     Profiler prof;
     Options opt;
     int decoder_kernel = -1;     // what the last decoder call on this context launched (csat_profile_decoder_kernel)
+    int forms[CSAT_FORM_COUNT] = {};     // ... and the last call of any kind (csat_profile_launch_form)
 };
 constexpr uint32_t kMagic = 0x43534154u;   // "CSAT"
 
@@ -72,14 +73,19 @@ const Options kDefaultOptions{};
 thread_local const Options* tl_opt = &kDefaultOptions;
 int tl_decoder_kernel_sink = -1;
 thread_local int* tl_decoder_kernel = &tl_decoder_kernel_sink;
+thread_local int tl_forms_sink[CSAT_FORM_COUNT];
+thread_local int* tl_forms = tl_forms_sink;
 struct OptionScope {
     const Options* prev;
-    int* prev_kernel;
-    explicit OptionScope(void* ctx) : prev(tl_opt), prev_kernel(tl_decoder_kernel) {
-        tl_opt = &static_cast<Context*>(ctx)->opt;
-        tl_decoder_kernel = &static_cast<Context*>(ctx)->decoder_kernel;
+    int *prev_kernel, *prev_forms;
+    explicit OptionScope(void* ctx) : prev(tl_opt), prev_kernel(tl_decoder_kernel), prev_forms(tl_forms) {
+        Context* c = static_cast<Context*>(ctx);
+        tl_opt = &c->opt;
+        tl_decoder_kernel = &c->decoder_kernel;
+        if (tl_forms != c->forms) std::memset(c->forms, 0, sizeof c->forms);      // (a call within a call adds to it)
+        tl_forms = c->forms;
     }
-    ~OptionScope() { tl_opt = prev; tl_decoder_kernel = prev_kernel; }
+    ~OptionScope() { tl_opt = prev; tl_decoder_kernel = prev_kernel; tl_forms = prev_forms; }
 };
 
 inline long long round_up(long long v, long long a) { return (v + a - 1) / a * a; }
@@ -388,7 +394,9 @@ csat_status launch_gemm_big_lista(const GemmArgs& g, long long n_cover, const Ep
         const long long tiles = (g.M + 255ll) / 256 * ((n_cover + width - 1) / width);
         return (tiles + cu_count() - 1) / cu_count() * width;
     };
-    if (cost(320) * 13 < cost(256) * 12) return launch_gemm_big_shape<Epi, 4, 2, 64, 5>(g, n_cover, 1, epi, st);
+    const bool wide = cost(320) * 13 < cost(256) * 12;
+    tl_forms[CSAT_FORM_LISTA_TILE] = wide ? 320 : 256;
+    if (wide) return launch_gemm_big_shape<Epi, 4, 2, 64, 5>(g, n_cover, 1, epi, st);
     return launch_gemm_big<Epi>(g, n_cover, 1, epi, st);
 }
 
@@ -428,6 +436,7 @@ template <typename T, int T32, bool SPLIT, typename Epi>
 csat_status launch_gemm_deep(const GemmArgs& g, long long n_cover, int batch, const Epi& epi, hipStream_t st) {
     constexpr int BT = 32 * T32;
     const dim3 grid((unsigned)((g.M + BT - 1) / BT), (unsigned)((n_cover + BT - 1) / BT), (unsigned)batch);
+    tl_forms[CSAT_FORM_SMALL_TILES] |= T32 | (SPLIT ? 4 : 0);
     hipLaunchKernelGGL((gemm_nt_deep_kernel<T, T32, SPLIT, Epi>), grid, dim3(64 * kDeepWaves), 0, st, g, epi);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
@@ -719,6 +728,7 @@ csat_status launch_attention_fused(const csat_dims& d, const Workspace& w, const
     // 64 x 500, m = 100 32.9, 29.1, 33.2, 45.8; 128 x 300, m = 128 37.3, 40.7, 39.7, 47.9.
     while (nw > 2 && (long long)BH * ((a.tiles_per_head + nw / 2 - 1) / (nw / 2)) <= cu_count()) nw /= 2;
     a.waves = nw;
+    tl_forms[CSAT_FORM_ATTENTION_WAVES] = nw;
     a.rounds = 1;
     if (single) {
         const int cus = cu_count();
@@ -1000,6 +1010,7 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     const long long units = a.tape > 0 ? a.tape : (long long)a.groups * a.segs;
     const unsigned grid = (unsigned)(variant == 6 ? a.groups * a.tile_split : units < cus ? units : cus);
     *tl_decoder_kernel = variant;
+    if (variant == 6) tl_forms[CSAT_FORM_DECODER_MEMBERS] = a.tile_split;
     switch (MT) {
 #define CSAT_FUSED_CASE(N) case N: HIP_TRY(ista_fused_launch_mt##N(variant, a, grid, st)); return CSAT_OK;
         CSAT_FUSED_CASE(1) CSAT_FUSED_CASE(2) CSAT_FUSED_CASE(3) CSAT_FUSED_CASE(4)
@@ -2008,6 +2019,14 @@ csat_status csat_profile_decoder_kernel(void* ctx, int* kernel) {
     CSAT_TRY(check_ctx(ctx));
     if (!kernel) return CSAT_ERR_NULL;
     *kernel = static_cast<Context*>(ctx)->decoder_kernel;
+    return CSAT_OK;
+}
+
+csat_status csat_profile_launch_form(void* ctx, int form, int* value) {
+    CSAT_TRY(check_ctx(ctx));
+    if (!value) return CSAT_ERR_NULL;
+    if (form < 0 || form >= CSAT_FORM_COUNT) return CSAT_ERR_PARAM;
+    *value = static_cast<Context*>(ctx)->forms[form];
     return CSAT_OK;
 }
 

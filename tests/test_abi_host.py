@@ -250,6 +250,11 @@ def test_options_and_decoder_status_arguments(lib):
     assert lib.csat_profile_decoder_kernel(None, ctypes.byref(k)) == -1
     assert lib.csat_profile_decoder_kernel(ctx, None) == -1
     assert lib.csat_profile_decoder_kernel(ctx, ctypes.byref(k)) == 0 and -1 <= k.value <= 6
+    assert lib.csat_profile_launch_form(None, 0, ctypes.byref(k)) == -1
+    assert lib.csat_profile_launch_form(ctx, 0, None) == -1
+    assert lib.csat_profile_launch_form(ctx, -1, ctypes.byref(k)) == -6
+    assert lib.csat_profile_launch_form(ctx, len(csat.LAUNCH_FORMS), ctypes.byref(k)) == -6
+    assert lib.csat_profile_launch_form(ctx, 0, ctypes.byref(k)) == 0 and k.value == 0
     n = ctypes.c_size_t()
     assert lib.csat_static_workspace_bytes(None) == -1
     assert lib.csat_static_workspace_bytes(ctypes.byref(n)) == 0 and n.value == 48 << 20

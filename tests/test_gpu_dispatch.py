@@ -474,14 +474,17 @@ def test_decoder_with_a_tile_shared_by_eight_wavefronts(n_q, n, m, iters, option
     assert same
 
 
-# (n_q, n, m, iterations) with two to sixteen workgroups per tile: one tile and 96, one to thirteen tiles of m (odd and even),
-# shares of unequal length, ragged last chunk and row tile, the fewest iterations and more
-MEMBER_CASES = [(5, 1600, 392, 8), (33, 1571, 197, 8), (70, 3000, 130, 6), (40, 4500, 20, 7), (200, 1333, 352, 6), (512, 1000, 416, 8),
-                (31, 2000, 64, 5), (3, 8192, 90, 4), (100, 1800, 300, 5)]
+# (n_q, n, m, iterations, workgroups per tile): one tile and 96, one to thirteen tiles of m (odd and even), shares of unequal length,
+# ragged last chunk and row tile, the fewest iterations and more
+MEMBER_CASES = [(5, 1600, 392, 8, 5), (33, 1571, 197, 8, 5), (70, 3000, 130, 6, 8), (40, 4500, 20, 7, 9), (200, 1333, 352, 6, 4), (512, 1000, 416, 8, 2),
+                (31, 2000, 64, 5, 7), (3, 8192, 90, 4, 13), (100, 1800, 300, 5, 6), (20, 16384, 20, 5, 16),
+                # the lines: four iterations; 20 us of a call to be saved; two workgroups for every CU's one tile
+                (5, 1600, 392, 4, 5), (5, 1600, 392, 3, 1), (300, 900, 200, 8, 3), (300, 900, 200, 7, 1), (682, 1600, 392, 8, 2), (683, 1600, 392, 8, 1)]
+SHARED_MEMBER_CASES = [c[:4] for c in MEMBER_CASES if c[4] > 1]
 
 
-@pytest.mark.parametrize("n_q,n,m,iters", MEMBER_CASES)
-def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters):
+@pytest.mark.parametrize("n_q,n,m,iters,members", MEMBER_CASES)
+def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters, members):
     """Fewer row tiles than CUs: several workgroups share a tile and exchange their parts of the residual; against the oracle, and
     the same bits in every call."""
     w = _small("shared_members", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, lam=0.002)
@@ -490,7 +493,7 @@ def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters):
     mu = _mu(Phi)
     p = _problem(w, Q, K, V, Phi)
     C, _, X = p.forward(w.lam, mu, iters)
-    assert csat.csat_profile_decoder_kernel() == 6
+    assert csat.csat_profile_decoder_kernel() == 6 and csat.csat_profile_launch_form("decoder_members") == members
     assert csat.csat_decoder_status(p.ws) == 0
     ref = orc.forward(Q, K, V, Phi, w.lam, mu, iters)
     assert_close("X", to_np(X), ref["X"], TOL["bf16"])
@@ -500,7 +503,7 @@ def test_decoder_with_a_tile_shared_by_workgroups(n_q, n, m, iters):
     assert torch.equal(X, X1) and torch.equal(C, C1)
 
 
-@pytest.mark.parametrize("n_q,n,m,iters", MEMBER_CASES)
+@pytest.mark.parametrize("n_q,n,m,iters", SHARED_MEMBER_CASES)
 def test_workgroups_that_share_a_tile_hold_the_same_residual(n_q, n, m, iters):
     """The second half of Phi's columns repeats the first: each pair meets the same residual in shares of different workgroups,
     so the iterate's halves agree bit for bit."""
@@ -514,13 +517,13 @@ def test_workgroups_that_share_a_tile_hold_the_same_residual(n_q, n, m, iters):
     X = torch.empty(rows, n, device=DEV)
     csat.csat_recover(dims, Y, Phi, (m / n) ** 0.5, 0.2, iters, X, None, None, ws)      # (lambda: the spread of Phi^T y)
     torch.cuda.synchronize()
-    assert csat.csat_profile_decoder_kernel() == 6 and csat.csat_decoder_status(ws) == 0
+    assert csat.csat_profile_launch_form("decoder_members") > 1 and csat.csat_decoder_status(ws) == 0
     assert X.isfinite().all() and 0.02 < float((X != 0).float().mean()) < 0.98
     assert torch.equal(X[:, :h], X[:, h:2 * h])
 
 
-@pytest.mark.parametrize("n_q,n,m,iters", [(512, 1000, 416, 8), (5, 1600, 392, 8), (40, 4500, 20, 7)])
-def test_a_wait_of_workgroups_that_share_a_tile_runs_out(n_q, n, m, iters, options):
+@pytest.mark.parametrize("n_q,n,m,iters,members", [(512, 1000, 416, 8, 2), (5, 1600, 392, 8, 5), (20, 16384, 20, 5, 16)])
+def test_a_wait_of_workgroups_that_share_a_tile_runs_out(n_q, n, m, iters, members, options):
     """Two, five and sixteen workgroups to a tile.  Their waits for each other are bounded: one that runs out is reported and the
     outputs hold NaN (forced from the host: the error record set before the launch; a limit of no polls, under which whoever is
     first to an exchange gives up and goes on), every kernel ends normally, and the next call on the workspace is clean."""
@@ -530,11 +533,11 @@ def test_a_wait_of_workgroups_that_share_a_tile_runs_out(n_q, n, m, iters, optio
     mu = _mu(Phi)
     p = _problem(w, Q, K, V, Phi)
     C0, _, X0 = p.forward(w.lam, mu, iters)
-    assert csat.csat_profile_decoder_kernel() == 6 and csat.csat_decoder_status(p.ws) == 0
+    assert csat.csat_profile_launch_form("decoder_members") == members and csat.csat_decoder_status(p.ws) == 0
     for option, value, fails in (("inject_decoder_error", 1, True), ("fused_spin_limit", -1, True), ("fused_spin_limit", 1 << 22, False)):
         options(option, value)
         C, _, X = p.forward(w.lam, mu, iters)
-        assert csat.csat_profile_decoder_kernel() == 6
+        assert csat.csat_profile_launch_form("decoder_members") == members
         assert csat.csat_decoder_status(p.ws) == (csat.CSAT_ERR_TIMEOUT if fails else 0)
         options(option, 0)
         if fails:
@@ -544,14 +547,17 @@ def test_a_wait_of_workgroups_that_share_a_tile_runs_out(n_q, n, m, iters, optio
         assert torch.equal(C, C0) and torch.equal(X, X0)
 
 
-# (type, heads, n_q, n, d, m): contractions of less than a step, one, eight and nine steps, and with a ragged last one; tiles of
-# one row and column, whole ones and one more; both tile sizes in bf16
-FEW_TILE_CASES = [("f32", 1, 1, 70, 8, 5), ("f32", 2, 33, 256, 64, 64), ("f32", 1, 32, 289, 40, 31), ("f32", 3, 65, 1571, 80, 97), ("f32", 1, 100, 4099, 128, 300),
-                  ("bf16", 1, 1, 67, 8, 5), ("bf16", 2, 33, 512, 80, 64), ("bf16", 3, 64, 577, 32, 33), ("bf16", 10, 70, 1571, 80, 197), ("bf16", 4, 40, 2050, 96, 1000)]
+# (type, heads, n_q, n, d, m, forms of the small-tile products in measurement, attention and synthesis): contractions of less than a
+# step, one, eight and nine steps, and with a ragged last one; tiles of one row and column, whole ones and one more; both
+# tile sizes in bf16; the output product where it is one; the line (96 of the 128-wide tiles in float, 64 in bf16)
+FEW_TILE_CASES = [("f32", 1, 1, 70, 8, 5, 1, 0, 5), ("f32", 2, 33, 256, 64, 64, 1, 0, 5), ("f32", 1, 32, 289, 40, 31, 1, 0, 5), ("f32", 3, 65, 1571, 80, 97, 1, 1, 5),
+                  ("f32", 1, 100, 4099, 128, 300, 1, 1, 5), ("f32", 48, 128, 300, 64, 96, 1, 0, 5), ("f32", 49, 256, 300, 64, 96, 0, 0, 0),
+                  ("bf16", 1, 1, 67, 8, 5, 1, 0, 1), ("bf16", 2, 33, 512, 80, 64, 1, 0, 1), ("bf16", 3, 64, 577, 32, 33, 1, 0, 1), ("bf16", 10, 70, 1571, 80, 197, 1, 1, 1),
+                  ("bf16", 4, 40, 2050, 96, 1000, 2, 1, 1), ("bf16", 32, 128, 300, 80, 96, 2, 0, 1), ("bf16", 33, 256, 300, 80, 96, 0, 0, 0)]
 
 
-@pytest.mark.parametrize("dtype,heads,n_q,n,d,m", FEW_TILE_CASES)
-def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
+@pytest.mark.parametrize("dtype,heads,n_q,n,d,m,measurement,attention,synthesis", FEW_TILE_CASES)
+def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, measurement, attention, synthesis, options):
     """Measurement, output product and synthesis whose tiles would leave most CUs idle, against float64 on the same operands; the
     synthesis also where operands are infinite, NaN or tiny: finite where the 128-wide kernels' result is."""
     rng = np.random.default_rng(n)
@@ -564,10 +570,12 @@ def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
     Kc, Vc, Z, C = empty(heads, m, d), empty(heads, m, d), empty(heads, n_q, d), empty(heads, n_q, d)
     A, X = torch.empty(heads, n_q, m, device=DEV), torch.empty(heads, n_q, n, device=DEV)
     csat.csat_measure(dims, to_dev(Phi, dtype), to_dev(K, dtype), to_dev(V, dtype), Kc, Vc, ws)
+    assert csat.csat_profile_launch_form("small_tiles") == measurement
     P64, rel = Phi.astype(np.float64), 2e-6 if dtype == "f32" else 4e-3          # 24 bits over K terms; one rounding to bf16
     assert_close("K~", to_np(Kc), P64 @ K, rel)
     assert_close("V~", to_np(Vc), P64 @ V, rel)
     csat.csat_compressed_attention(dims, to_dev(Q, dtype), Kc, Vc, A, Z, ws)
+    assert csat.csat_profile_launch_form("small_tiles") == attention
     torch.cuda.synchronize()
     assert_close("Z", to_np(Z), to_np(A).astype(np.float64) @ to_np(Vc), 2 * rel)      # (bf16: A~ rounded once too)
     # 1e-33: sums below 2^-90, where the split products are not used, and well above the smallest normal float (at 1e-37 they
@@ -582,6 +590,7 @@ def test_products_of_few_tiles(dtype, heads, n_q, n, d, m, options):
         for gemm in (0, 1):
             options("gemm", gemm)
             csat.csat_recover(dims, A, to_dev(Phi, dtype), 0.0, 0.01, 1, X, to_dev(Vs, dtype), C, ws)
+            assert csat.csat_profile_launch_form("small_tiles") == (0 if gemm else synthesis)
             torch.cuda.synchronize()
             got.append(to_np(C).astype(np.float64))
         options("gemm", 0)
@@ -614,14 +623,15 @@ def test_synthesis_over_one_step_keeps_exact_products(heads, n_q, n, d, m, optio
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
-# (type, heads, n_q, m, d): eight, four and two wavefronts per workgroup (more workgroups than CUs with fewer; four at most)
-WAVE_CASES = [("f32", 600, 70, 40, 32), ("f32", 140, 200, 100, 64), ("f32", 192, 120, 73, 64), ("f32", 3, 200, 100, 64),
-              ("f32", 40, 250, 390, 64), ("bf16", 600, 70, 40, 80),
-              ("bf16", 300, 250, 200, 80), ("bf16", 5, 250, 200, 80), ("bf16", 3, 33, 600, 96)]
+# (type, heads, n_q, m, d, wavefronts per workgroup): eight, four and two (more workgroups than CUs with fewer; four at most); K~ in LDS as a
+# whole and in parts; 0: the three kernels
+WAVE_CASES = [("f32", 600, 70, 40, 32, 8), ("f32", 140, 200, 100, 64, 8), ("f32", 192, 120, 73, 64, 4), ("f32", 3, 200, 100, 64, 2),
+              ("f32", 70, 250, 390, 64, 4), ("f32", 40, 250, 390, 64, 2), ("bf16", 600, 70, 40, 80, 8),
+              ("bf16", 300, 250, 200, 80, 8), ("bf16", 5, 250, 200, 80, 2), ("bf16", 4, 300, 1024, 80, 2), ("bf16", 3, 33, 600, 96, 0)]
 
 
-@pytest.mark.parametrize("dtype,heads,n_q,m,d", WAVE_CASES)
-def test_attention_at_every_number_of_wavefronts(dtype, heads, n_q, m, d):
+@pytest.mark.parametrize("dtype,heads,n_q,m,d,waves", WAVE_CASES)
+def test_attention_at_every_number_of_wavefronts(dtype, heads, n_q, m, d, waves):
     """The one-kernel attention against float64 on the same operands, at the workgroup sizes that the number of row tiles picks."""
     rng = np.random.default_rng(heads)
     q = lambda *s: gen.quantize(rng.standard_normal(s).astype(np.float32), dtype)    # noqa: E731
@@ -630,6 +640,7 @@ def test_attention_at_every_number_of_wavefronts(dtype, heads, n_q, m, d):
     ws = torch.empty(csat.csat_workspace_bytes(dims, 0), dtype=torch.uint8, device=DEV).fill_(0xFF)
     A, Z = torch.empty(heads, n_q, m, device=DEV), torch.empty(heads, n_q, d, dtype=to_dev(Q, dtype).dtype, device=DEV)
     csat.csat_compressed_attention(dims, to_dev(Q, dtype), to_dev(Kc, dtype), to_dev(Vc, dtype), A, Z, ws)
+    assert csat.csat_profile_launch_form("attention_waves") == waves
     torch.cuda.synchronize()
     want_a, want_z = orc.compressed_attention(Q, Kc, Vc)
     # scores of |s| <= 40 to 2^-24 each way, then exp2 and the sum; Z in bf16: the weights and the result rounded once
@@ -654,6 +665,7 @@ def test_unrolled_decoder_on_the_wider_tile(rows, n, m, iters):
         ws = torch.empty(csat.csat_lista_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
         X, C = torch.empty(1, r, n, device=DEV), torch.empty(1, r, 64, dtype=torch.bfloat16, device=DEV)
         csat.csat_recover_lista(dims, y.clone(), S, B, thetas, X, V, C, ws)
+        assert csat.csat_profile_launch_form("lista_tile") == (320 if r == rows else 256)
         torch.cuda.synchronize()
         return X, C
 

@@ -61,6 +61,20 @@ def test_static_scratch_forward_matches_workspace_forward(dtype):
     assert torch.equal(Cz, Zz)
 
 
+def test_static_scratch_forward_with_shared_tiles():
+    """Few rows, so that workgroups share the decoder's tiles: in the static array too, where their parts of the residual fit it; one
+    row more and only the problem without them does (it keeps fitting): one workgroup per tile."""
+    limit = csat.csat_static_workspace_bytes()
+    for n_q, members in ((736, 5), (737, 1)):
+        w = _case(f"static_members_{members}", H=2, n_q=n_q, n=1600, d=64, m=392, dtype="bf16", iters=5, lam=0.01)
+        (C0, Z0, X0), (C, Z, X), ref, p, _ = _both(w)
+        assert csat.csat_profile_launch_form("decoder_members") == members
+        assert csat.csat_workspace_bytes(p.dims, w.iters) <= limit
+        assert torch.equal(C, C0) and torch.equal(Z, Z0) and torch.equal(X, X0)
+        assert_close("X", to_np(X), ref["X"], TOL[w.dtype])
+        assert_close("C", to_np(C), ref["C"], TOL[w.dtype])
+
+
 def test_static_scratch_limit_and_arguments():
     """A problem whose carving exceeds the static array is refused before anything is launched."""
     limit = csat.csat_static_workspace_bytes()

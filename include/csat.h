@@ -271,7 +271,8 @@ typedef enum {
     CSAT_FORM_SMALL_TILES = 1,       /* products on small tiles (csrc/csat_gemm_deep.h), any of: 1 32 x 32 tiles, 2 64 x 64 tiles, 4 float operands split into bf16 parts */
     CSAT_FORM_ATTENTION_WAVES = 2,   /* one-kernel compressed attention: wavefronts per workgroup */
     CSAT_FORM_LISTA_TILE = 3,        /* unrolled decoder on the large-tile product: columns of a tile */
-    CSAT_FORM_COUNT = 4
+    CSAT_FORM_OMP_SHARES = 4,        /* matching pursuit's pick while Phi's columns pass: shares of the columns for rows that do not fill the chip */
+    CSAT_FORM_COUNT = 5
 } csat_launch_form;
 csat_status csat_profile_launch_form(void* ctx, int form, int* value);
 

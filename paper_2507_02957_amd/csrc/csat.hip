@@ -1465,27 +1465,31 @@ OmpExtra carve_omp(const csat_dims& d, const Workspace& w, int k, char* base) {
     return x;
 }
 
-constexpr int kOmpMaxSplits = 32;     // (a candidate is 8 bytes, a row of Cm at least 256)
+constexpr int kOmpMaxSplits = 128;    // (at most a chunk of 32 columns each: a candidate is 8 bytes, a row of Cm four a column)
 constexpr int kOmpPickStart = 4;      // a workgroup's start, its residuals' way from memory or L2, in steps
 // Row blocks that run whole, as many as fill the chip evenly, and the shares of n that the others are cut into, as many as need the
 // fewest passes over the chip.  76 800 rows, n = 1600, m = 392 (300 blocks of 50 steps): every block in three shares 137 us, 256
-// whole and 44 in five 119.
+// whole and 44 in five 119.  The shares of a block run on one XCD unless they take fewer passes spread over all: a few blocks would
+// leave whole XCDs idle.
 void omp_pick_plan(OmpPickArgs& a) {
     const int KS = (int)(a.ldm / 64), steps = (a.nct + omp_pick_chunks(KS) - 1) / omp_pick_chunks(KS);
     const long long blocks = (a.rows + omp_pick_rows(KS) - 1) / omp_pick_rows(KS), slots = (long long)cu_count() * omp_pick_per_cu(KS);
     a.whole = (int)(blocks / slots * slots);
     a.splits = 1;
+    a.group = 8;
     long long best = -1;
     for (int s = 1; s <= kOmpMaxSplits && s <= steps; ++s) {
-        const long long cost = ((blocks - a.whole) * s + slots - 1) / slots * ((steps + s - 1) / s + kOmpPickStart);
-        if (best < 0 || cost < best) { best = cost; a.splits = s; }
+        const long long cut = blocks - a.whole, here = ((cut + 7) / 8 * s + slots / 8 - 1) / (slots / 8), spread = (cut * s + slots - 1) / slots;
+        const long long cost = std::min(here, spread) * ((steps + s - 1) / s + kOmpPickStart);
+        if (best < 0 || cost < best) { best = cost; a.splits = s; a.group = here <= spread ? 8 : (int)cut; }
     }
 }
 csat_status launch_omp_pick(const OmpPickArgs& a, hipStream_t st) {
     const int KS = (int)(a.ldm / 64);
     const long long blocks = (a.rows + omp_pick_rows(KS) - 1) / omp_pick_rows(KS);
-    const dim3 grid((unsigned)(a.whole + (blocks - a.whole + 7) / 8 * 8 * a.splits));
+    const dim3 grid((unsigned)(a.whole + (blocks - a.whole + a.group - 1) / a.group * a.group * a.splits));
     const size_t lds = omp_pick_lds_bytes(KS);
+    tl_forms[CSAT_FORM_OMP_SHARES] = a.splits;
     switch (KS) {
 #define CSAT_OMP_PICK(N)                                                                                                       \
     case N:                                                                                                                    \
@@ -1549,7 +1553,7 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
             HIP_TRY(hipGetLastError());
         }
     }
-    OmpPickArgs p{(const bf16_t*)w.PhiT, (const bf16_t*)w.R, w.ldm, rows, x.taken, cand, d.n, w.nct, 0, 1};
+    OmpPickArgs p{(const bf16_t*)w.PhiT, (const bf16_t*)w.R, w.ldm, rows, x.taken, cand, d.n, w.nct, 0, 1, 8};
     if (in_product) omp_pick_plan(p);
     OmpUpdateArgs<T> u{(const T*)w.PhiT, w.ldm, k > 1 ? (const T*)x.PhiQ : nullptr, Y, cand, p.splits, (long long)p.whole * omp_pick_rows((int)(w.ldm / 64)), x.picks, k, 0, x.taken, w.nct, x.Tri, x.Z, x.Fac, x.Qb, (T*)w.R, w.ldm, rows, d.m, x.mq};
     for (int it = 0; it < k; ++it) {

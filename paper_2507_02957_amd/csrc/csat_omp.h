@@ -67,7 +67,8 @@ struct OmpPickArgs {
     const uint32_t* taken;
     OmpCand* cand;                           // [rows, splits]
     int n, nct;
-    int whole, splits;                       // row blocks that one workgroup takes all of n for; shares of n of the others
+    int whole, splits, group;                // row blocks that one workgroup takes all of n for; shares of n of the others, and how
+                                             // many blocks follow each other before the next share
 };
 constexpr int omp_pick_waves(int KS) { return KS <= 8 ? 8 : 4; }                              // KS: m in 64s
 constexpr int omp_pick_rows(int KS) { return omp_pick_waves(KS) * 32; }
@@ -94,17 +95,17 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
     extern __shared__ uint4 lds[];
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // the shares of a row block run on one XCD, one after the other: its residuals (256 rows are 230 KB at m = 392) come from
-    // memory once and then from that L2
+    // groups of eight: the shares of a row block run on one XCD, one after the other: its residuals (256 rows are 230 KB at m = 392)
+    // come from memory once and then from that L2
     int split = 0, splits = 1;
     long long block = blockIdx.x;
     if (block >= a.whole) {
-        const int id = (int)(block - a.whole), slot_id = id >> 3;
+        const int id = (int)(block - a.whole), slot_id = id / a.group;
         splits = a.splits;
         split = slot_id % splits;
-        block = a.whole + (long long)(slot_id / splits) * 8 + (id & 7);
+        block = a.whole + (long long)(slot_id / splits) * a.group + id % a.group;
     }
-    if (block * (W * 32 * TR) >= a.rows) return;                 // (the grid is padded to whole groups of eight row blocks)
+    if (block * (W * 32 * TR) >= a.rows) return;                 // (the grid is padded to whole groups of row blocks)
     const long long tile0 = (block * W + wave) * TR, row0 = tile0 * 32 + li;
     const int steps = (a.nct + CPS - 1) / CPS, share = (steps + splits - 1) / splits;
     const int s0 = split * share, s1 = s0 + share < steps ? s0 + share : steps;
@@ -367,7 +368,11 @@ template <typename T>
 __device__ __forceinline__ int omp_take_pick(const OmpUpdateArgs<T>& a, long long r, int lane) {
     if (!a.cand) return a.picks[r * a.k + a.it];
     const int nc = r < a.rows_whole ? 1 : a.splits;
-    OmpCand b = lane < nc ? a.cand[r * a.splits + lane] : OmpCand{-1.f, 0x7fffffff};
+    OmpCand b{-1.f, 0x7fffffff};
+    for (int q = lane; q < nc; q += 64) {
+        const OmpCand o = a.cand[r * a.splits + q];
+        if (o.val > b.val) b = o;                       // ascending columns per lane
+    }
     if (nc > 1) {                                       // largest value, lowest index on a tie
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {

@@ -719,10 +719,27 @@ PICK_KERNEL_CASES = [(33, 129, 64, 8), (300, 97, 65, 9), (40, 193, 192, 16), (70
                      (131072, 65, 40, 2), (131200, 33, 8, 3)]
 
 
+# (rows, n, m, picks): row blocks that are fewer than the XCDs or not a multiple of them, more candidates than lanes, four and eight
+# wavefronts
+FEW_ROW_PICK_CASES = [(1, 16384, 64, 3), (70, 16384, 130, 2), (300, 8192, 512, 3), (500, 9000, 576, 2), (130, 5000, 1000, 3), (1100, 4096, 900, 2),
+                      (2304, 4100, 200, 2), (4600, 2048, 40, 2)]
+
+
+@pytest.mark.parametrize("rows,n,m,picks", FEW_ROW_PICK_CASES)
+def test_matching_pursuit_shares_the_columns_over_the_chip(rows, n, m, picks, options):
+    """Few row blocks: as many shares of the columns as give most CUs one, and the picks of the search over stored correlations."""
+    blocks = -(-rows // (256 if m <= 512 else 128))
+    _pick_forms_agree(rows, n, m, picks, options, lambda: csat.csat_profile_launch_form("omp_shares") * blocks >= 128)
+
+
 @pytest.mark.parametrize("rows,n,m,picks", PICK_KERNEL_CASES)
 def test_matching_pursuit_picks_while_the_columns_pass(rows, n, m, picks, options):
     """bf16: each row's largest correlation is kept while the columns of Phi pass.  The same sums in the same order as the
     product with stored correlations and their search (forced), so the same picks, coefficients and output."""
+    _pick_forms_agree(rows, n, m, picks, options, lambda: csat.csat_profile_launch_form("omp_shares") > 0)
+
+
+def _pick_forms_agree(rows, n, m, picks, options, form):
     d = 64
     dims = csat.make_dims(1, 1, rows, n, d, m, "bf16")
     g = torch.Generator(device=DEV)
@@ -738,6 +755,7 @@ def test_matching_pursuit_picks_while_the_columns_pass(rows, n, m, picks, option
         X, C = torch.empty(rows, n, device=DEV), torch.empty(rows, d, dtype=torch.bfloat16, device=DEV)
         S = torch.empty(rows, picks, dtype=torch.int32, device=DEV)
         csat.csat_recover_omp(dims, Y, Phi, picks, X, S, V, C, ws)
+        assert form() == (gemm == 0)
         torch.cuda.synchronize()
         out.append((S, X, C))
     S, X, C = out[0]

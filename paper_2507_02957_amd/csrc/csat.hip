@@ -1471,7 +1471,8 @@ constexpr int kOmpPickStart = 4;      // a workgroup's start, its residuals' way
 // fewest passes over the chip.  76 800 rows, n = 1600, m = 392 (300 blocks of 50 steps): every block in three shares 137 us, 256
 // whole and 44 in five 119.  The shares of a block run on one XCD unless they take fewer passes spread over all: a few blocks would
 // leave whole XCDs idle.
-void omp_pick_plan(OmpPickArgs& a) {
+// Returns the steps that one place on the chip then walks.
+long long omp_pick_plan(OmpPickArgs& a) {
     const int KS = (int)(a.ldm / 64), steps = (a.nct + omp_pick_chunks(KS) - 1) / omp_pick_chunks(KS);
     const long long blocks = (a.rows + omp_pick_rows(KS) - 1) / omp_pick_rows(KS), slots = (long long)cu_count() * omp_pick_per_cu(KS);
     a.whole = (int)(blocks / slots * slots);
@@ -1483,6 +1484,16 @@ void omp_pick_plan(OmpPickArgs& a) {
         const long long cost = std::min(here, spread) * ((steps + s - 1) / s + kOmpPickStart);
         if (best < 0 || cost < best) { best = cost; a.splits = s; a.group = here <= spread ? 8 : (int)cut; }
     }
+    return a.whole / slots * (steps + kOmpPickStart) + best;
+}
+// Above m = 512 the kernel has room for one wavefront per SIMD, and what it has over the 256 x 256 tiles is only that it needs no whole
+// rounds of them.  The line is where a round of tiles, in units of a step's time per 64 of m, is 60 + 26 / 3 of m in 64s (fits to 210
+// products of n = 1100 to 16 384, 256 to 65 536 rows; none it sends the wrong way costs more than 8 %).  A pick, the columns passing and tiles, us:
+// n = 1100, m = 640: 256 rows 13, 26; 16 384 rows 47, 49; n = 4096, m = 768: 1024 rows 21, 28; 4096 rows 49, 32; 65 536 rows 623, 450;
+// n = 16 384, m = 1024: 256 rows 22, 33; 1024 rows 54, 38; 16 384 rows 647, 526.
+bool omp_pick_on_tiles(const GemmArgs& g, int n, long long pick_steps) {
+    const long long KS = g.ldb / 64, tiles = (g.M + 255ll) / 256 * ((n + 255ll) / 256);
+    return KS > 8 && use_big_gemm<bf16_t>(g, n) && (tiles + cu_count() - 1) / cu_count() * (180 + 26 * KS) < 3 * pick_steps * KS;
 }
 csat_status launch_omp_pick(const OmpPickArgs& a, hipStream_t st) {
     const int KS = (int)(a.ldm / 64);
@@ -1538,6 +1549,15 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
     }
     const bool in_product = sizeof(T) == 2 && gemm_choice() != 1;
     OmpCand* cand = in_product ? (OmpCand*)x.Cm : nullptr;
+    GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
+    OmpPickArgs p{(const bf16_t*)w.PhiT, (const bf16_t*)w.R, w.ldm, rows, x.taken, cand, d.n, w.nct, 0, 1, 8};
+    const bool on_tiles = in_product && omp_pick_on_tiles(g, d.n, omp_pick_plan(p));
+    tl_forms[CSAT_FORM_OMP_PICK] = on_tiles ? 3 : in_product ? 2 : 1;
+    if (on_tiles) {
+        g.K = (int)round_up(g.K, 64);
+        p.whole = 0;
+        p.splits = (d.n + 127) / 128;
+    }
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         CSAT_TRY(transpose_pack<T>((const T*)Phi, (T*)w.PhiT, w.ldm, 1, d.m, d.n, st));
@@ -1547,23 +1567,22 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
         if (k > 1) hipLaunchKernelGGL((omp_pack_columns_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m,
                            pitch, (T*)x.PhiQ, total);
         HIP_TRY(hipGetLastError());
-        if (in_product) {
+        if (in_product && !on_tiles) {
             const long long words = (rows + 31) / 32 * w.nct * 32;
             hipLaunchKernelGGL(omp_taken_init_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, x.taken, d.n, w.nct, words);
             HIP_TRY(hipGetLastError());
         }
     }
-    OmpPickArgs p{(const bf16_t*)w.PhiT, (const bf16_t*)w.R, w.ldm, rows, x.taken, cand, d.n, w.nct, 0, 1, 8};
-    if (in_product) omp_pick_plan(p);
-    OmpUpdateArgs<T> u{(const T*)w.PhiT, w.ldm, k > 1 ? (const T*)x.PhiQ : nullptr, Y, cand, p.splits, (long long)p.whole * omp_pick_rows((int)(w.ldm / 64)), x.picks, k, 0, x.taken, w.nct, x.Tri, x.Z, x.Fac, x.Qb, (T*)w.R, w.ldm, rows, d.m, x.mq};
+    OmpUpdateArgs<T> u{(const T*)w.PhiT, w.ldm, k > 1 ? (const T*)x.PhiQ : nullptr, Y, cand, p.splits, (long long)p.whole * omp_pick_rows((int)(w.ldm / 64)), x.picks, k, 0, on_tiles ? nullptr : x.taken, w.nct, x.Tri, x.Z, x.Fac, x.Qb, (T*)w.R, w.ldm, rows, d.m, x.mq};
     for (int it = 0; it < k; ++it) {
         u.it = it;
-        if (in_product) {
+        if (on_tiles) {
+            Timed tm(w, CSAT_K_UPDATE, st);
+            CSAT_TRY(launch_gemm_big(g, d.n, 1, EpiOmpBest{cand, p.splits, x.picks, k, it, rows, d.n}, st));
+        } else if (in_product) {
             Timed tm(w, CSAT_K_UPDATE, st);
             CSAT_TRY(launch_omp_pick(p, st));
-        }
-        if (!in_product) {
-            GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
+        } else {
             {
                 Timed tm(w, CSAT_K_UPDATE, st);
                 EpiStoreStream ec{x.Cm, w.ldn, (int)rows, d.n};

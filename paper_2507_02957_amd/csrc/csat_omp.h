@@ -3,8 +3,8 @@
 // pick the column of Phi most correlated with the residual (largest |phi_j^T r|, lowest index on a
 // tie, never a column twice), refit the picked coefficients by least squares, update the residual.
 //
-// Two launches per pick: the correlations R Phi with each row's largest (bf16: omp_pick_product_kernel; float: the
-// product and omp_pick_kernel), and omp_update_kernel, which refits the picked coefficients and forms the next residual.
+// Two launches per pick: the correlations R Phi with each row's largest (bf16: omp_pick_product_kernel, or EpiOmpBest on the large-tile
+// product; float: the product and omp_pick_kernel), and omp_update_kernel, which refits the picked coefficients and forms the next residual.
 #pragma once
 #include "csat_kernels.h"
 
@@ -58,6 +58,74 @@ static __global__ __launch_bounds__(256) void omp_pick_kernel(const float* Cm, l
 // that stage.)  The row blocks beyond whole rounds of the chip are cut into shares of n; the update takes the best of their
 // candidates.
 struct OmpCand { float val; int idx; };
+
+// Epilogue of the correlation product on the large-tile GEMM, for m > 512 where its rounds of tiles take less time: the best column of
+// each row within the wavefront's 128 (largest |c|, lowest index on a tie, earlier picks left out).  The update kernel takes the
+// best of those.  Nine K steps and more cover a tile's start and the search; omp_pick_product_kernel has one wavefront per SIMD there.
+struct EpiOmpBest {
+    static constexpr bool kTile = true, kWhole = true;
+    static constexpr int kPitch = 33 * 8;                       // 32 candidates and a pad against bank conflicts
+    static constexpr int kStageBytes = 64 * kPitch + 64 * 16;
+    struct Pre { uint4 ex; };                                   // columns of this block that row r0w + lane may not pick
+    OmpCand* cand; int nseg;                                    // [M][nseg], one per 128 columns
+    const int* picks; int k, it;                                // [M][k], `it` made so far
+    long long M; int N;
+    // (before the main loop: the reads of the earlier picks hide behind the first operands', eight at a time)
+    __device__ __forceinline__ Pre begin(long long r0w, long long c0w, int lane) const {
+        uint32_t ex[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const long long left = N - c0w - 32 * j;
+            ex[j] = left >= 32 ? 0u : left <= 0 ? 0xffffffffu : 0xffffffffu << left;
+        }
+        const long long row = r0w + lane < M ? r0w + lane : M - 1;
+        for (int s0 = 0; s0 < it; s0 += 8) {
+            int p[8];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) p[s] = picks[row * k + (s0 + s < it ? s0 + s : 0)];
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const int q = p[s] - (int)c0w;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) ex[j] |= (q >> 5) == j ? 1u << (q & 31) : 0u;
+            }
+        }
+        return Pre{uint4{ex[0], ex[1], ex[2], ex[3]}};
+    }
+    __device__ __forceinline__ void whole(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][4], char* stage,
+                                          const Pre& pre) const {
+        if (r0w >= M || c0w >= N) return;                       // (uniform)
+        const int li = lane & 31, lh = lane >> 5;
+        const long long row = r0w + lane;
+        uint4* mask = (uint4*)(stage + 64 * kPitch);
+        mask[lane] = pre.ex;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int rr = 32 * i + 8 * (v / 4) + 4 * lh + (v % 4);
+                const uint4 e = mask[rr];
+                const uint32_t w[4] = {e.x, e.y, e.z, e.w};
+                OmpCand b{-1.f, 0x7fffffff};
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int c = (int)c0w + 32 * j + li;
+                    const float a = (w[j] >> li) & 1u ? -2.f : fabsf(acc[i][j][v]);
+                    if (a > b.val) b = OmpCand{a, c};
+                }
+                *(OmpCand*)(stage + rr * kPitch + li * 8) = b;
+            }
+        OmpCand b{-1.f, 0x7fffffff};
+#pragma unroll
+        for (int q = 0; q < 32; ++q) {
+            const OmpCand o = *(const OmpCand*)(stage + lane * kPitch + q * 8);
+            if (o.val > b.val || (o.val == b.val && o.idx < b.idx)) b = o;
+        }
+        if (row < M) cand[row * nseg + (c0w >> 7)] = b;
+    }
+    __device__ __forceinline__ void flush(long long, long long, int, const char*) const {}
+};
+
 // Columns that a row may not pick (picked before, or beyond n): [row tile of 32][chunk][32 words], a bit per row.  Word
 // omp_taken_word(c) is column c of the chunk, so that words 2 v and 2 v + 1 are the lane mask of accumulator register v.
 constexpr __host__ __device__ int omp_taken_word(int c) { return 2 * ((c >> 3) * 4 + (c & 3)) + ((c >> 2) & 1); }
@@ -289,7 +357,7 @@ struct OmpUpdateArgs {
     const OmpCand* cand; int splits;          // the pick is the best of these and is written to picks; null: picks holds it
     long long rows_whole;                     // ... rows before this one have a single candidate
     int* picks; int k, it;                    // [rows, k]
-    uint32_t* taken; int nct;                 // as in OmpPickArgs (with cand)
+    uint32_t* taken; int nct;                 // as in OmpPickArgs (omp_pick_product_kernel only)
     float* Tri; float* Z;                     // [rows, k, k] triangular factor (column `it` written here), [rows, k] q^T y
     float* Fac;                               // [rows, k (k + 1) / 2] the same factor by columns, with 1 / its diagonal
     float* Qb;                                // [rows, k, mq] orthonormal vectors (omp_update_stored_kernel)
@@ -369,8 +437,8 @@ __device__ __forceinline__ int omp_take_pick(const OmpUpdateArgs<T>& a, long lon
     if (!a.cand) return a.picks[r * a.k + a.it];
     const int nc = r < a.rows_whole ? 1 : a.splits;
     OmpCand b{-1.f, 0x7fffffff};
-    for (int q = lane; q < nc; q += 64) {
-        const OmpCand o = a.cand[r * a.splits + q];
+    for (int q = 0; q < nc; q += 64) {
+        const OmpCand o = q + lane < nc ? a.cand[r * a.splits + q + lane] : OmpCand{-1.f, 0x7fffffff};
         if (o.val > b.val) b = o;                       // ascending columns per lane
     }
     if (nc > 1) {                                       // largest value, lowest index on a tie
@@ -384,7 +452,7 @@ __device__ __forceinline__ int omp_take_pick(const OmpUpdateArgs<T>& a, long lon
     const int j = __builtin_amdgcn_readfirstlane(b.val >= 0.f ? b.idx : 0);     // (0: every correlation is NaN)
     if (lane == 0) {
         a.picks[r * a.k + a.it] = j;
-        if (a.it + 1 < a.k) atomicOr(a.taken + ((r >> 5) * a.nct + (j >> 5)) * 32 + omp_taken_word(j & 31), 1u << (r & 31));
+        if (a.taken && a.it + 1 < a.k) atomicOr(a.taken + ((r >> 5) * a.nct + (j >> 5)) * 32 + omp_taken_word(j & 31), 1u << (r & 31));
     }
     return j;
 }

@@ -732,11 +732,23 @@ def test_matching_pursuit_shares_the_columns_over_the_chip(rows, n, m, picks, op
     _pick_forms_agree(rows, n, m, picks, options, lambda: csat.csat_profile_launch_form("omp_shares") * blocks >= 128)
 
 
+# (rows, n, m, picks): m > 512 and enough rows and columns for rounds of 256 x 256 tiles; ragged tiles and last 128 columns, 8, 9 and 17
+# picks, more candidates than lanes
+TILE_PICK_CASES = [(1024, 16384, 640, 3), (1021, 16001, 577, 2), (2045, 8180, 1000, 8), (4090, 4090, 830, 9), (16400, 2049, 700, 17), (4097, 4500, 1024, 2)]
+
+
+@pytest.mark.parametrize("rows,n,m,picks", TILE_PICK_CASES)
+def test_matching_pursuit_picks_on_large_tiles(rows, n, m, picks, options):
+    """bf16, long columns and whole rounds of tiles: the pick in the large-tile product, with the picks, coefficients and output of the
+    search over stored correlations."""
+    _pick_forms_agree(rows, n, m, picks, options, lambda: csat.csat_profile_launch_form("omp_pick") == 3)
+
+
 @pytest.mark.parametrize("rows,n,m,picks", PICK_KERNEL_CASES)
 def test_matching_pursuit_picks_while_the_columns_pass(rows, n, m, picks, options):
     """bf16: each row's largest correlation is kept while the columns of Phi pass.  The same sums in the same order as the
     product with stored correlations and their search (forced), so the same picks, coefficients and output."""
-    _pick_forms_agree(rows, n, m, picks, options, lambda: csat.csat_profile_launch_form("omp_shares") > 0)
+    _pick_forms_agree(rows, n, m, picks, options, lambda: csat.csat_profile_launch_form("omp_pick") == 2)
 
 
 def _pick_forms_agree(rows, n, m, picks, options, form):

@@ -366,8 +366,10 @@ struct OmpUpdateArgs {
 };
 
 // The sum over a wavefront, in the order of a butterfly over lane distances 32, 16, 8, 4, 2, 1 (after the first three the
-// values repeat every eight lanes, so a rotation by four is that exchange).
+// values repeat every eight lanes, so a rotation by four is that exchange).  The same bits in every lane: no addition is contracted
+// with a product that v is (one value per lane, m <= 64), whose two lanes would round differently.
 __device__ __forceinline__ float wave_sum(float v) {
+#pragma clang fp contract(off)
     v += __shfl_xor(v, 32, 64);
     v += __shfl_xor(v, 16, 64);
 #define CSAT_DPP(CTRL) __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(v), CTRL, 0xf, 0xf, false))

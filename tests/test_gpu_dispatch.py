@@ -777,6 +777,29 @@ def _pick_forms_agree(rows, n, m, picks, options, form):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,picks", [("f32", 1), ("f32", 5), ("f32", 12), ("bf16", 4), ("bf16", 12)])
+def test_matching_pursuit_sums_alike_in_every_lane(dtype, picks):
+    """m = 64, one value of an m-vector per lane: with the two halves of the measurements exchanged, every sum of the refit has the same
+    two operands at its first step and the same ones after, so rows that pick the same columns get the same coefficients, bit for bit."""
+    rows, n, m = 2000, 300, 64
+    t = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    g = torch.Generator(device=DEV).manual_seed(picks)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).to(t)
+    Y = torch.randn(rows, m, generator=g, device=DEV)
+    dims = csat.make_dims(1, 1, rows, n, 64, m, dtype)
+    out = []
+    for shift in (0, 32):
+        ws = torch.empty(csat.csat_omp_workspace_bytes(dims, picks), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        X, S = torch.empty(rows, n, device=DEV), torch.empty(rows, picks, dtype=torch.int32, device=DEV)
+        csat.csat_recover_omp(dims, Y.roll(shift, 1).contiguous(), Phi.roll(shift, 0).contiguous(), picks, X, S, None, None, ws)
+        torch.cuda.synchronize()
+        out.append((X, S))
+    (X, S), (X1, S1) = out
+    same = (S == S1).all(-1)             # (correlations are summed in another order: near-ties may go the other way)
+    assert float(same.float().mean()) > 0.98
+    assert torch.equal(X[same], X1[same])
+
+
 # (n, m, iterations): every length of the register-resident transforms, n at and off multiples of the thread count, just
 # above half the length and equal to it, one and two iterations
 HADAMARD_CASES = [(257, 30, 3), (512, 512, 2), (513, 100, 1), (1000, 64, 4), (1088, 200, 3), (2048, 300, 2), (2049, 90, 3), (4100, 1000, 2), (8200, 40, 2)]

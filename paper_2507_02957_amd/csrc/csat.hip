@@ -1428,24 +1428,37 @@ struct OmpExtra {
                    //                with the product, its candidates [rows, splits]
     uint32_t* taken;  // [row tiles of 32, nct, 32]  columns that a row may not pick, a bit per row (bf16)
     float* Tri;    // [rows, k, k]   triangular factor
-    float* Fac;    // [rows, k (k + 1) / 2]  ... by columns, with 1 / its diagonal
+    float* Fac;    // [rows, k (k + 1) / 2]  ... by columns, with 1 / its diagonal (held vectors)
     float* Z;      // [rows, k]      Q^T y
     int* picks;    // [rows, k]
-    char* PhiQ;    // [n, 64, pitch]  columns of Phi in the update's order
+    bool stored;   // the update stores the orthonormal vectors (omp_stores_vectors)
+    char* PhiQ;    // [n, 64, pitch]  columns of Phi in the update's order: held vectors, more than one pick
     float* Rf;     // [rows, mq]     fp32 residuals and ...
-    float* Qb;     // [rows, k, mq]  ... orthonormalised picked columns, beyond the picks that the update holds in registers
+    float* Qb;     // [rows, k, mq]  ... orthonormalised picked columns: stored vectors
     int mq, MQ;    // m in whole 64s; values of an m-vector per lane of the update
     size_t bytes;
 };
 // Picks whose orthonormal vectors the update keeps in registers: 128 registers at most; at one value per lane (m <= 64) reading them
 // back is cheaper than forming more than eight again (float, 8192 rows, n = 64, m = 32, 16 picks: 361 us against 341).
 int omp_held_picks(int MQ) { return MQ == 1 || MQ == 16 ? 8 : 16; }
+// Held vectors need Phi's columns packed first, a pass over all of Phi for the few columns that few rows pick.  Vectors are stored
+// instead, also of fewer picks, where their buffers are no larger than the packed columns and the packing takes longer than it
+// saves: in bf16 a launch of 4 us and 1.3 ps an element against MQ (0.5 + 0.18 k) us (fits); in float few rows gain nothing from
+// held vectors.  Calls, held and stored, us: float, n = 16 384, m = 1024, 256 rows, 4 picks 599, 557; n = 2048, m = 1000, one row, 2
+// picks 58, 52; bf16, n = 16 384, m = 1024, 512 rows, 2 picks 125, 117, 64 rows, 8 picks 255, 273; n = 1600, m = 392, 64 rows, 4 picks
+// 64, 68; n = 16 384, m = 64, 512 rows, 8 picks 123, 116.
+bool omp_stores_vectors(const csat_dims& d, int MQ, int mq, int k, size_t packed_bytes) {
+    if (k > omp_held_picks(MQ)) return true;
+    if (k == 1 || (size_t)d.B * d.H * d.n_q * (k + 1) * mq * 4 > packed_bytes) return false;
+    return d.dtype == CSAT_F32 || 4 + 1.3e-6 * d.n * d.m > MQ * (0.5 + 0.18 * k);
+}
 OmpExtra carve_omp(const csat_dims& d, const Workspace& w, int k, char* base) {
     const long long rows = (long long)d.B * d.H * d.n_q;
     OmpExtra x{};
     x.mq = (int)round_up(d.m, 64);
     x.MQ = x.mq <= 512 ? x.mq / 64 : 16;
-    const bool stored = k > omp_held_picks(x.MQ);
+    const size_t packed_bytes = (size_t)d.n * 64 * omp_column_pitch(x.MQ, (int)esize(d.dtype)) * esize(d.dtype);
+    x.stored = omp_stores_vectors(d, x.MQ, x.mq, k, packed_bytes);
     size_t off = 0;
     auto take = [&](size_t nbytes) {
         char* p = base + off;
@@ -1455,12 +1468,12 @@ OmpExtra carve_omp(const csat_dims& d, const Workspace& w, int k, char* base) {
     x.Cm = (float*)take((size_t)rows * w.ldn * 4);
     x.taken = (uint32_t*)take(d.dtype == CSAT_BF16 ? (size_t)((rows + 31) / 32) * w.nct * 128 : 0);
     x.Tri = (float*)take((size_t)rows * k * k * 4);
-    x.Fac = (float*)take((size_t)rows * (k * (k + 1) / 2) * 4);
+    x.Fac = (float*)take(x.stored ? 0 : (size_t)rows * (k * (k + 1) / 2) * 4);
     x.Z = (float*)take((size_t)rows * k * 4);
     x.picks = (int*)take((size_t)rows * k * 4);
-    x.PhiQ = take((size_t)d.n * 64 * omp_column_pitch(x.MQ, (int)esize(d.dtype)) * esize(d.dtype));
-    x.Rf = (float*)take(stored ? (size_t)rows * x.mq * 4 : 0);
-    x.Qb = (float*)take(stored ? (size_t)rows * k * x.mq * 4 : 0);
+    x.PhiQ = take(x.stored || k == 1 ? 0 : packed_bytes);
+    x.Rf = (float*)take(x.stored ? (size_t)rows * x.mq * 4 : 0);
+    x.Qb = (float*)take(x.stored ? (size_t)rows * k * x.mq * 4 : 0);
     x.bytes = off;
     return x;
 }
@@ -1517,9 +1530,10 @@ csat_status launch_omp_pick(const OmpPickArgs& a, hipStream_t st) {
 }
 
 template <typename T>
-csat_status launch_omp_update(const OmpUpdateArgs<T>& a, int MQ, float* Rf, hipStream_t st) {
+csat_status launch_omp_update(const OmpUpdateArgs<T>& a, int MQ, bool stored, float* Rf, hipStream_t st) {
     const dim3 grid((unsigned)((a.rows + 3) / 4)), block(256);
-    const int form = a.k > omp_held_picks(MQ) ? 2 : a.it < 8 ? 0 : 1;
+    const int form = stored ? 2 : a.it < 8 ? 0 : 1;
+    tl_forms[CSAT_FORM_OMP_REFIT] = stored ? 2 : 1;
     switch (MQ) {
 #define CSAT_OMP_UPDATE(M)                                                                                             \
     case M:                                                                                                           \
@@ -1564,7 +1578,7 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
         CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));        // r = y
         const int pitch = omp_column_pitch(x.MQ, (int)sizeof(T));
         const long long total = (long long)d.n * 64;
-        if (k > 1) hipLaunchKernelGGL((omp_pack_columns_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m,
+        if (k > 1 && !x.stored) hipLaunchKernelGGL((omp_pack_columns_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const T*)w.PhiT, w.ldm, d.m,
                            pitch, (T*)x.PhiQ, total);
         HIP_TRY(hipGetLastError());
         if (in_product && !on_tiles) {
@@ -1573,7 +1587,7 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
             HIP_TRY(hipGetLastError());
         }
     }
-    OmpUpdateArgs<T> u{(const T*)w.PhiT, w.ldm, k > 1 ? (const T*)x.PhiQ : nullptr, Y, cand, p.splits, (long long)p.whole * omp_pick_rows((int)(w.ldm / 64)), x.picks, k, 0, on_tiles ? nullptr : x.taken, w.nct, x.Tri, x.Z, x.Fac, x.Qb, (T*)w.R, w.ldm, rows, d.m, x.mq};
+    OmpUpdateArgs<T> u{(const T*)w.PhiT, w.ldm, k > 1 && !x.stored ? (const T*)x.PhiQ : nullptr, Y, cand, p.splits, (long long)p.whole * omp_pick_rows((int)(w.ldm / 64)), x.picks, k, 0, on_tiles ? nullptr : x.taken, w.nct, x.Tri, x.Z, x.Fac, x.Qb, (T*)w.R, w.ldm, rows, d.m, x.mq};
     for (int it = 0; it < k; ++it) {
         u.it = it;
         if (on_tiles) {
@@ -1593,7 +1607,7 @@ csat_status omp_t(const csat_dims& d, const Workspace& w, const OmpExtra& x, con
             HIP_TRY(hipGetLastError());
         }
         Timed tm(w, CSAT_K_RESIDUAL, st);
-        CSAT_TRY(launch_omp_update<T>(u, x.MQ, x.Rf, st));
+        CSAT_TRY(launch_omp_update<T>(u, x.MQ, x.stored, x.Rf, st));
     }
     Timed tm(w, CSAT_K_SYNTHESIS, st);
 #define CSAT_OMP_FINISH(KM)                                                                                                          \

@@ -352,14 +352,15 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
 template <typename T>
 struct OmpUpdateArgs {
     const T* PhiT; long long ldp;             // [n, ldp] columns of Phi as rows
-    const T* PhiQ;                            // [n, 64, pitch] the same in the lanes' order, pads zero (omp_pack_columns_kernel); a single pick: null
+    const T* PhiQ;                            // [n, 64, pitch] the same in the lanes' order, pads zero (omp_pack_columns_kernel); a single pick, or
+                                              // stored vectors: null
     const float* Y;                           // [rows, m]
     const OmpCand* cand; int splits;          // the pick is the best of these and is written to picks; null: picks holds it
     long long rows_whole;                     // ... rows before this one have a single candidate
     int* picks; int k, it;                    // [rows, k]
     uint32_t* taken; int nct;                 // as in OmpPickArgs (omp_pick_product_kernel only)
     float* Tri; float* Z;                     // [rows, k, k] triangular factor (column `it` written here), [rows, k] q^T y
-    float* Fac;                               // [rows, k (k + 1) / 2] the same factor by columns, with 1 / its diagonal
+    float* Fac;                               // [rows, k (k + 1) / 2] the same factor by columns, with 1 / its diagonal (omp_update_kernel)
     float* Qb;                                // [rows, k, mq] orthonormal vectors (omp_update_stored_kernel)
     T* R; long long ldr;                      // [rows, ldr] residual as the next product's operand, pads zero
     long long rows; int m, mq;
@@ -476,7 +477,7 @@ __device__ __forceinline__ void omp_finish_update(const OmpUpdateArgs<T>& a, lon
     zt = wave_sum(zt);
     if (lane == 0) {
         a.Tri[(r * a.k + a.it) * a.k + a.it] = nrm;
-        a.Fac[r * (a.k * (a.k + 1) / 2) + a.it * (a.it + 1) / 2 + a.it] = inv;
+        if (!q_out) a.Fac[r * (a.k * (a.k + 1) / 2) + a.it * (a.it + 1) / 2 + a.it] = inv;
         a.Z[r * a.k + a.it] = zt;
     }
     if (a.it + 1 == a.k) return;                         // no product follows
@@ -546,7 +547,7 @@ __global__ __launch_bounds__(256) void omp_update_kernel(OmpUpdateArgs<T> a) {
     omp_finish_update<T, MQ>(a, r, lane, v, rv, nullptr, nullptr);
 }
 
-// More picks than that: orthonormal vectors and (in Rf) residuals stored.
+// More picks than that, or few rows: orthonormal vectors and (in Rf) residuals stored.
 template <typename T, int MQ>
 __global__ __launch_bounds__(256) void omp_update_stored_kernel(OmpUpdateArgs<T> a, float* Rf) {
     const int lane = threadIdx.x & 63;

@@ -122,6 +122,10 @@ def test_argument_validation_without_device(lib):
     assert o(ctx, rd, P, P, 9, P, None, None, None, P, need_o, None) == -6               # more picks than measurements
     assert o(ctx, rd, P, P, 4, P, odd, None, None, P, need_o, None) == -4
     assert o(ctx, rd, P, P, 4, P, None, None, None, P, need, None) == -5
+    # few rows of a large Phi: no second copy of it
+    for dtype, e in (("f32", 4), ("bf16", 2)):
+        one = csat.make_dims(1, 1, 1, 16384, 64, 1024, dtype)
+        assert csat.csat_omp_workspace_bytes(one, 4) - csat.csat_workspace_bytes(one, 0) < 16384 * 1024 * e // 4
     with pytest.raises(csat.CsatError) as e:
         csat.csat_omp_workspace_bytes(csat.make_dims(1, 1, 8, 64, 8, 40, "f32"), 33)
     assert e.value.status == -6

@@ -777,6 +777,37 @@ def _pick_forms_agree(rows, n, m, picks, options, form):
         assert torch.equal(a, b)
 
 
+# (type, rows, few, n, m, picks): one to sixteen values of an m-vector per lane, up to eight picks and beyond
+REFIT_CASES = [("f32", 900, 40, 700, 60, 8), ("f32", 1500, 90, 900, 300, 9), ("f32", 700, 100, 1500, 700, 4), ("bf16", 700, 20, 700, 64, 8), ("bf16", 2000, 60, 1100, 128, 6),
+               ("bf16", 1000, 30, 1000, 190, 4), ("bf16", 3000, 200, 16384, 1000, 2)]
+
+
+@pytest.mark.parametrize("dtype,rows,few,n,m,picks", REFIT_CASES)
+def test_matching_pursuit_few_rows_store_their_vectors(dtype, rows, few, n, m, picks):
+    """Few rows of many columns: the orthonormal vectors stored, Phi's columns not packed; the bits that the same rows get among
+    more, whose vectors are formed again."""
+    t = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
+    g = torch.Generator(device=DEV).manual_seed(n)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).to(t)
+    V = torch.randn(n, 64, generator=g, device=DEV).to(t)
+    Y = torch.randn(rows, m, generator=g, device=DEV)
+
+    def decode(y, stored):
+        r = y.shape[0]
+        dims = csat.make_dims(1, 1, r, n, 64, m, dtype)
+        ws = torch.empty(csat.csat_omp_workspace_bytes(dims, picks), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        X, C, S = torch.empty(r, n, device=DEV), torch.empty(r, 64, dtype=t, device=DEV), torch.empty(r, picks, dtype=torch.int32, device=DEV)
+        csat.csat_recover_omp(dims, y, Phi, picks, X, S, V, C, ws)
+        assert csat.csat_profile_launch_form("omp_refit") == (2 if stored else 1)
+        torch.cuda.synchronize()
+        return X, C, S
+
+    whole = decode(Y, False)
+    assert whole[0].isfinite().all() and (whole[2].sort(-1).values.diff(dim=-1) > 0).all()
+    for a, b in zip(whole, decode(Y[rows - few:].contiguous(), True)):
+        assert torch.equal(a[rows - few:], b)
+
+
 @pytest.mark.parametrize("dtype,picks", [("f32", 1), ("f32", 5), ("f32", 12), ("bf16", 4), ("bf16", 12)])
 def test_matching_pursuit_sums_alike_in_every_lane(dtype, picks):
     """m = 64, one value of an m-vector per lane: with the two halves of the measurements exchanged, every sum of the refit has the same

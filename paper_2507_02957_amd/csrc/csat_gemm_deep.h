@@ -10,8 +10,8 @@
 // error: eight chains of an eighth of the length.
 //
 // SPLIT (float): the products of csat_gemm_f32.h, the operands split in registers.  Synthesis of 1600 x 64 over 1600:
-// 202 -> 156 us a call of two iterations; 77 x 64 over 4096, eight heads 369 -> 252; error against float64 0.3 to 1.0 of the
-// 128 x 64 kernel's.  A tile with a suspect sum (there) is formed again on the float MFMA, as the chain it always was.
+// 65 -> 19 us; 77 x 64 over 4096, eight heads 157 -> 39; error against float64 0.74 to 1.0 of the 128 x 64 kernel's, on dense
+// rows and on rows of a few coefficients (1.5 to 1.8 with the two sets of products added before the wavefronts' sums meet).  A tile with a suspect sum (there) is formed again on the float MFMA, as the chain it always was.
 #pragma once
 #include "csat_gemm_f32.h"
 
@@ -21,8 +21,8 @@ constexpr int kDeepWaves = 8;
 
 template <typename T, int T32, bool SPLIT, typename Epi>
 __global__ __launch_bounds__(512, T32 == 2 || SPLIT ? 2 : 4) void gemm_nt_deep_kernel(GemmArgs g, Epi epi) {
-    constexpr int EPC = Elem<T>::per_chunk, NT = T32 * T32, SLOTS = kDeepWaves / 2;
-    __shared__ f32x4 part[SLOTS][NT * 4][64];
+    constexpr int EPC = Elem<T>::per_chunk, NT = T32 * T32, SLOTS = kDeepWaves / 2, SETS = SPLIT ? 2 : 1;
+    __shared__ f32x4 part[SLOTS][SETS * NT * 4][64];
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int z = blockIdx.z;
@@ -123,18 +123,14 @@ __global__ __launch_bounds__(512, T32 == 2 || SPLIT ? 2 : 4) void gemm_nt_deep_k
         if (ks + 2 * kDeepWaves < ksteps) load(ks + 2 * kDeepWaves, B0{});
         if (ks + kDeepWaves < ksteps) multiply(ks + kDeepWaves, B1{}, std::false_type{});
     }
-    if constexpr (SPLIT) {
-#pragma unroll
-        for (int i = 0; i < T32; ++i)
-#pragma unroll
-            for (int j = 0; j < T32; ++j) acc[i][j] += corr[i][j];
-    }
 
-    // the wavefronts' sums, in a fixed order: 4 .. 7 into 0 .. 3, then those
+    // the wavefronts' sums, in a fixed order: 4 .. 7 into 0 .. 3, then those.  SPLIT: the first products' and the smaller ones' apart up
+    // to the end, as in one chain.  A few first products sum exactly, so that a row of few coefficients is rounded once.
+    auto set = [&](int i) -> f32x16& { return i < NT * 4 ? acc[i / 4 / T32][i / 4 % T32] : corr[i / 4 % NT / T32][i / 4 % T32]; };
     auto put = [&](int s) {
 #pragma unroll
-        for (int i = 0; i < NT * 4; ++i) {
-            const f32x16& a = acc[i / 4 / T32][i / 4 % T32];
+        for (int i = 0; i < SETS * NT * 4; ++i) {
+            const f32x16& a = set(i);
             part[s][i][lane] = f32x4{a[4 * (i & 3)], a[4 * (i & 3) + 1], a[4 * (i & 3) + 2], a[4 * (i & 3) + 3]};
         }
     };
@@ -142,10 +138,10 @@ __global__ __launch_bounds__(512, T32 == 2 || SPLIT ? 2 : 4) void gemm_nt_deep_k
     __syncthreads();
     if (wave < SLOTS) {
 #pragma unroll
-        for (int i = 0; i < NT * 4; ++i) {
+        for (int i = 0; i < SETS * NT * 4; ++i) {
             const f32x4 v = part[wave][i][lane];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc[i / 4 / T32][i / 4 % T32][4 * (i & 3) + e] += v[e];
+            for (int e = 0; e < 4; ++e) set(i)[4 * (i & 3) + e] += v[e];
         }
         put(wave);
     }
@@ -160,6 +156,12 @@ __global__ __launch_bounds__(512, T32 == 2 || SPLIT ? 2 : 4) void gemm_nt_deep_k
         sum[n] = part[0][i][lane];
 #pragma unroll
         for (int s = 1; s < SLOTS; ++s) sum[n] += part[s][i][lane];
+        if constexpr (SPLIT) {
+            f32x4 small = part[0][NT * 4 + i][lane];
+#pragma unroll
+            for (int s = 1; s < SLOTS; ++s) small += part[s][NT * 4 + i][lane];
+            sum[n] += small;
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) suspect.add(sum[n][e]);
     }

@@ -623,6 +623,26 @@ def test_synthesis_over_one_step_keeps_exact_products(heads, n_q, n, d, m, optio
         assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
 
 
+@pytest.mark.parametrize("heads,n_q,n,d", [(2, 78, 271, 8), (1, 135, 358, 128), (8, 216, 700, 96)])
+def test_synthesis_of_sparse_rows_rounds_once(heads, n_q, n, d):
+    """Float C = X V on small tiles, three coefficients per row in K steps of different wavefronts: their first products (8 bits each) sum
+    exactly but for wide spreads of their exponents, so the result is rounded once: at most 2^-24 / sqrt(3) of it in the 2-norm (as the
+    kernel with one chain per sum: 2.7e-8; with every wavefront's sum rounded before they meet it was 4.2e-8 to 5.2e-8)."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    dims = csat.make_dims(1, heads, n_q, n, d, n, "f32")
+    at = torch.rand(heads, n_q, n, generator=g, device=DEV).topk(3, -1).indices
+    Y = torch.zeros(heads, n_q, n, device=DEV).scatter_(-1, at, torch.randn(heads, n_q, 3, generator=g, device=DEV))
+    V = torch.randn(heads, n, d, generator=g, device=DEV)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, 1), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    X, C = torch.empty(heads, n_q, n, device=DEV), torch.empty(heads, n_q, d, device=DEV)
+    csat.csat_recover(dims, Y, torch.eye(n, device=DEV), 0.0, 1.0, 1, X, V, C, ws)
+    assert csat.csat_profile_launch_form("small_tiles") == 5
+    torch.cuda.synchronize()
+    assert torch.equal(X, Y)
+    ref = to_np(Y).astype(np.float64) @ to_np(V).astype(np.float64)
+    assert np.linalg.norm(to_np(C) - ref) <= 2.0 ** -24 / np.sqrt(3) * np.linalg.norm(ref)
+
+
 # (type, heads, n_q, m, d, wavefronts per workgroup): eight, four and two (more workgroups than CUs with fewer; four at most); K~ in LDS as a
 # whole and in parts; 0: the three kernels
 WAVE_CASES = [("f32", 600, 70, 40, 32, 8), ("f32", 140, 200, 100, 64, 8), ("f32", 192, 120, 73, 64, 4), ("f32", 3, 200, 100, 64, 2),

@@ -150,6 +150,8 @@ bool sparse_state(size_t dense_state_bytes) {
     return dense_state_bytes > ((size_t)128 << 20);
 }
 
+constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_static's workspace
+
 // Largest m (in 32-wide tiles) the fused decoder takes.  Its residual accumulators need 16 registers per tile: up to
 // 13 tiles they fit next to the operands of the two-chunk schedule; 14 to 16 tiles fill the accumulator file and run
 // on the one-chunk schedule with 128-row workgroups (a few dozen spilled registers).  That still beats the large-tile
@@ -157,7 +159,6 @@ bool sparse_state(size_t dense_state_bytes) {
 // 154 groups: 7.3 against 9.1 ms; short_video's shape at m = 512, 600 groups: 5.2 against 8.3 ms per forward), not
 // below: a group's iterations are a chain, so the launch lasts as long with 40 groups as with 150 (cross_modal's rows
 // with fewer heads, forward: 39 groups 6.5 against 3.8 ms, 97 groups 7.5 against 7.2, 121 groups 7.9 against 7.6).
-constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_static's workspace
 constexpr int kFusedMaxMT = 16;
 constexpr int kFused2MaxMT = 13;
 constexpr long long kFusedWideMinGroups = 128;
@@ -420,8 +421,8 @@ csat_status launch_gemm_f32(GemmArgs g, long long n_cover, int batch, const Epi&
     return CSAT_OK;
 }
 
-// Products that would be so few 128-wide tiles that most CUs had none go to small tiles whose workgroups share the contraction
-// (csat_gemm_deep.h): 32 x 32, or 64 x 64 in bf16 from two of the small ones per CU on.  Measurement of K and V (with its
+// Products that would be so few 128-wide tiles that most CUs had none go to small tiles, a workgroup each, whose wavefronts share the
+// contraction (csat_gemm_deep.h): 32 x 32, or 64 x 64 in bf16 from two of the small ones per CU on.  Measurement of K and V (with its
 // transposes), 128-wide against 32-wide (64-wide) tiles, us: float, n = 1600, m = 392, d = 64: one head 73.8, 21.0 (57.3), 12 heads (96 tiles of
 // 128 x 64) 82.4, 58.2 (65.4), 48 heads (384) 142, 168; 64 heads of n = 300, m = 96 (128) 30.2, 30.3; bf16: 10 heads of
 // n = 1571, m = 197, d = 80 (40) 41.2, 29.8 (30.1), 4 heads of n = 16 384, m = 1024, d = 80 (64) 247, 210 (160), 392 x 3072 over
@@ -1440,7 +1441,7 @@ struct OmpExtra {
 };
 // Picks whose orthonormal vectors the update keeps in registers: 128 registers at most; at one value per lane (m <= 64) reading them
 // back is cheaper than forming more than eight again (float, 8192 rows, n = 64, m = 32, 16 picks: 361 us against 341).
-int omp_held_picks(int MQ) { return MQ == 1 || MQ == 16 ? 8 : 16; }
+constexpr int omp_held_picks(int MQ) { return MQ == 1 || MQ == 16 ? 8 : 16; }
 // Held vectors need Phi's columns packed first, a pass over all of Phi for the few columns that few rows pick.  Vectors are stored
 // instead, also of fewer picks, where their buffers are no larger than the packed columns and the packing takes longer than it
 // saves: in bf16 a launch of 4 us and 1.3 ps an element against MQ (0.5 + 0.18 k) us (fits); in float few rows gain nothing from
@@ -1538,8 +1539,8 @@ csat_status launch_omp_update(const OmpUpdateArgs<T>& a, int MQ, bool stored, fl
 #define CSAT_OMP_UPDATE(M)                                                                                             \
     case M:                                                                                                           \
         if (form == 2) hipLaunchKernelGGL((omp_update_stored_kernel<T, M>), grid, block, 0, st, a, Rf);                \
-        else if (form == 0 || M == 16) hipLaunchKernelGGL((omp_update_kernel<T, M, 8>), grid, block, 0, st, a);         \
-        else hipLaunchKernelGGL((omp_update_kernel<T, M, (M == 16 ? 8 : 16)>), grid, block, 0, st, a);                  \
+        else if (form == 0 || omp_held_picks(M) == 8) hipLaunchKernelGGL((omp_update_kernel<T, M, 8>), grid, block, 0, st, a); \
+        else hipLaunchKernelGGL((omp_update_kernel<T, M, omp_held_picks(M)>), grid, block, 0, st, a);                   \
         break;
         CSAT_OMP_UPDATE(1) CSAT_OMP_UPDATE(2) CSAT_OMP_UPDATE(3) CSAT_OMP_UPDATE(4) CSAT_OMP_UPDATE(5) CSAT_OMP_UPDATE(6) CSAT_OMP_UPDATE(7) CSAT_OMP_UPDATE(8)
         CSAT_OMP_UPDATE(16)

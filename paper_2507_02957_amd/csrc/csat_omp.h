@@ -155,7 +155,7 @@ static __global__ void omp_taken_init_kernel(uint32_t* taken, int n, int nct, lo
 
 template <int KS>
 __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * omp_pick_per_cu(KS)) void omp_pick_product_kernel(OmpPickArgs a) {
-    constexpr int W = omp_pick_waves(KS), TR = 1 /* row tiles */, CPS = omp_pick_chunks(KS), NS = CPS * KS, STAGE = omp_pick_stage_bytes(KS),
+    constexpr int W = omp_pick_waves(KS), CPS = omp_pick_chunks(KS), NS = CPS * KS, STAGE = omp_pick_stage_bytes(KS),
                   RING = omp_pick_ring(KS);
     constexpr int SLOTS = KS == 1 ? 4 : 4 * KS - 4;             // pairs of MFMAs of a chunk that the search of the chunk before is spread over
     typedef uint64_t u64x8 __attribute__((ext_vector_type(8)));
@@ -173,8 +173,8 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
         split = slot_id % splits;
         block = a.whole + (long long)(slot_id / splits) * a.group + id % a.group;
     }
-    if (block * (W * 32 * TR) >= a.rows) return;                 // (the grid is padded to whole groups of row blocks)
-    const long long tile0 = (block * W + wave) * TR, row0 = tile0 * 32 + li;
+    if (block * (W * 32) >= a.rows) return;                 // (the grid is padded to whole groups of row blocks)
+    const long long tile = block * W + wave, row = tile * 32 + li;
     const int steps = (a.nct + CPS - 1) / CPS, share = (steps + splits - 1) / splits;
     const int s0 = split * share, s1 = s0 + share < steps ? s0 + share : steps;
     const uint32_t lds0 = (uint32_t)(size_t)(lds_ptr_t)lds;
@@ -204,54 +204,41 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
 #pragma unroll
     for (int g = 0; g < 4; ++g) ad[g] = lds0 + li * 128 + ((2 * g + lh) ^ ((li >> 1) & 7)) * 16;
 
-    float best[TR];
-    int at[TR], off[TR];
-    mask_ptr_t taken[TR];
-    bf16x8 rb[TR][4 * KS];
+    bf16x8 rb[4 * KS];
     if (s0 < s1) stage_all(s0, 0);
     if (RING == 3 && s0 + 1 < s1) stage_all(s0 + 1, STAGE);
-    const long long tiles = (a.rows + 31) / 32;
+    const long long tiles = (a.rows + 31) / 32, rc = row < a.rows ? row : a.rows - 1;
+    const mask_ptr_t taken = (mask_ptr_t)(const void*)(a.taken + (tile < tiles ? tile : tiles - 1) * a.nct * 32);
 #pragma unroll
-    for (int r = 0; r < TR; ++r) {
-        const long long rc = row0 + 32 * r < a.rows ? row0 + 32 * r : a.rows - 1;
-        best[r] = -1.f;
-        at[r] = 0x7fffffff;
-        taken[r] = (mask_ptr_t)(const void*)(a.taken + (tile0 + r < tiles ? tile0 + r : tiles - 1) * a.nct * 32);
-#pragma unroll
-        for (int f = 0; f < 4 * KS; ++f) rb[r][f] = __builtin_bit_cast(bf16x8, *(const uint4*)(a.R + rc * a.ldm + f * 16 + lh * 8));
-    }
-    f32x16 u[2][TR];                       // the correlations being formed, and those of the chunk before being searched
-    u64x8 ex[TR][2], exn[TR][2];           // ... and the rows that may not pick its columns (asked for a chunk ahead: a read from memory)
+    for (int f = 0; f < 4 * KS; ++f) rb[f] = __builtin_bit_cast(bf16x8, *(const uint4*)(a.R + rc * a.ldm + f * 16 + lh * 8));
+    float best = -1.f;
+    int at = 0x7fffffff, off = -1;
+    f32x16 u[2];                           // the correlations being formed, and those of the chunk before being searched
+    u64x8 ex[2], exn[2];                   // ... and the rows that may not pick its columns (asked for a chunk ahead: a read from memory)
     int c0 = 0;
-    // Elements [E0, E1) of the 16 TR of buffer b: register v is column 8 (v / 4) + 4 lh + v % 4, ascending columns so that the
+    // Elements [E0, E1) of the 16 of buffer b: register v is column 8 (v / 4) + 4 lh + v % 4, ascending columns so that the
     // first maximum stays.
     auto search = [&](auto bc, auto e0c, auto e1c) {
         constexpr int b = decltype(bc)::value, E0 = decltype(e0c)::value, E1 = decltype(e1c)::value;
 #pragma unroll
-        for (int e = E0; e < E1; ++e) {
-            const int r = e / 16, v = e % 16;
-            if (v == 0) off[r] = -1;
-            const float c = fabsf(u[b][r][v]);
-            const bool larger = __builtin_amdgcn_inverse_ballot_w64(~ex[r][v / 8][v % 8] & __builtin_amdgcn_ballot_w64(c > best[r]));
-            best[r] = larger ? c : best[r];
-            off[r] = larger ? 8 * (v / 4) + v % 4 : off[r];
-            if (v == 15) at[r] = off[r] >= 0 ? c0 + 4 * lh + off[r] : at[r];
+        for (int v = E0; v < E1; ++v) {
+            if (v == 0) off = -1;
+            const float c = fabsf(u[b][v]);
+            const bool larger = __builtin_amdgcn_inverse_ballot_w64(~ex[v / 8][v % 8] & __builtin_amdgcn_ballot_w64(c > best));
+            best = larger ? c : best;
+            off = larger ? 8 * (v / 4) + v % 4 : off;
+            if (v == 15) at = off >= 0 ? c0 + 4 * lh + off : at;
         }
     };
     auto ask_taken = [&](int ch) {
         ch = ch < a.nct ? ch : a.nct - 1;
-#pragma unroll
-        for (int r = 0; r < TR; ++r) {
-            exn[r][0] = taken[r][2 * ch];
-            exn[r][1] = taken[r][2 * ch + 1];
-        }
+        exn[0] = taken[2 * ch];
+        exn[1] = taken[2 * ch + 1];
     };
     auto take_taken = [&](int ch) {
         c0 = 32 * ch;
 #pragma unroll
-        for (int r = 0; r < TR; ++r)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) ex[r][h] = CPS > 1 && c0 >= a.n ? (u64x8)(~0ull) : exn[r][h];
+        for (int h = 0; h < 2; ++h) ex[h] = CPS > 1 && c0 >= a.n ? (u64x8)(~0ull) : exn[h];
     };
     // everything but the requests of the last step asked for has landed
     auto step_end = [&](bool requested) {
@@ -285,17 +272,14 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
                 lds_wait<(s + 1 < NS ? 4 : 0)>(fr[s & 1][0], fr[s & 1][1], fr[s & 1][2], fr[s & 1][3]);
                 auto slot = [&](auto gc) {
                     constexpr int g = decltype(gc)::value, i = (s % KS) * 4 + g;
+                    f32x16 acc = u[cur];
+                    if constexpr (i == 0)
 #pragma unroll
-                    for (int r = 0; r < TR; ++r) {
-                        f32x16 acc = u[cur][r];
-                        if constexpr (i == 0)
-#pragma unroll
-                            for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-                        u[cur][r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[s & 1][g]), rb[r][i], acc, 0, 0, 0);
-                    }
+                        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+                    u[cur] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, fr[s & 1][g]), rb[i], acc, 0, 0, 0);
                     if constexpr (i < SLOTS)
-                        search(std::integral_constant<int, cur ^ 1>{}, std::integral_constant<int, i * 16 * TR / SLOTS>{},
-                               std::integral_constant<int, (i + 1) * 16 * TR / SLOTS>{});
+                        search(std::integral_constant<int, cur ^ 1>{}, std::integral_constant<int, i * 16 / SLOTS>{},
+                               std::integral_constant<int, (i + 1) * 16 / SLOTS>{});
                     __builtin_amdgcn_sched_barrier(0);
                 };
                 if constexpr (s % KS == 0) ask_taken(step * CPS + c);
@@ -312,13 +296,9 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
         run(run, std::integral_constant<int, 0>{});
         step_end(more);
     };
+    ex[0] = ex[1] = ~0ull;                                       // nothing to search before the first chunk
 #pragma unroll
-    for (int r = 0; r < TR; ++r) {                               // nothing to search before the first chunk
-        ex[r][0] = ~0ull;
-        ex[r][1] = ~0ull;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) u[1][r][v] = 0.f;
-    }
+    for (int v = 0; v < 16; ++v) u[1][v] = 0.f;
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     uint32_t so = 0, sn = (RING - 1) * STAGE;                    // the step's slot, and the one that is free
@@ -332,16 +312,13 @@ __global__ __launch_bounds__(64 * omp_pick_waves(KS), omp_pick_waves(KS) / 4 * o
         }
     }
     using E0 = std::integral_constant<int, 0>;
-    using E1 = std::integral_constant<int, 16 * TR>;
+    using E1 = std::integral_constant<int, 16>;
     if (CPS % 2 == 0 || (s1 - s0) % 2 == 0) search(std::integral_constant<int, 1>{}, E0{}, E1{});
     else search(std::integral_constant<int, 0>{}, E0{}, E1{});
-#pragma unroll
-    for (int r = 0; r < TR; ++r) {
-        const float ob = __shfl_xor(best[r], 32, 64);
-        const int oa = __shfl_xor(at[r], 32, 64);
-        if (ob > best[r] || (ob == best[r] && oa < at[r])) { best[r] = ob; at[r] = oa; }
-        if (row0 + 32 * r < a.rows && lh == 0) a.cand[(row0 + 32 * r) * a.splits + split] = OmpCand{best[r], at[r]};
-    }
+    const float ob = __shfl_xor(best, 32, 64);
+    const int oa = __shfl_xor(at, 32, 64);
+    if (ob > best || (ob == best && oa < at)) { best = ob; at = oa; }
+    if (row < a.rows && lh == 0) a.cand[row * a.splits + split] = OmpCand{best, at};
 }
 
 // ---- refit and residual ----

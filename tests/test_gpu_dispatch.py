@@ -547,6 +547,40 @@ def test_a_wait_of_workgroups_that_share_a_tile_runs_out(n_q, n, m, iters, membe
         assert torch.equal(C, C0) and torch.equal(X, X0)
 
 
+def test_tiles_shared_by_workgroups_on_two_streams_and_in_a_graph():
+    """Two calls at once, together more workgroups than CUs, so that workgroups of one tile may start apart; then one of them as replays
+    of a captured graph, whose counter and flags its own kernels clear: the bits of the call alone each time."""
+    problems = []
+    for n_q, n, m, iters, members in ((512, 1000, 416, 8, 2), (200, 1333, 352, 8, 4)):
+        w = _small("members_streams", B=2, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, lam=0.002)
+        Q, K, V = gen.make_qkv(w)
+        Phi = gen.make_workload_phi(w)
+        p = _problem(w, Q, K, V, Phi)
+        args = (p.dims, p.Q, p.K, p.V, p.Phi, w.lam, _mu(Phi), iters)
+        C0, _, X0 = p.forward(w.lam, args[6], iters)
+        assert csat.csat_profile_launch_form("decoder_members") == members
+        problems.append((p, args, C0, X0, torch.empty_like(C0), torch.empty_like(X0), torch.cuda.Stream()))
+    torch.cuda.synchronize()
+    for _ in range(5):
+        for p, args, _, _, C, X, stream in problems:
+            with torch.cuda.stream(stream):
+                csat.csat_forward(*args, C, None, X, p.ws)
+    torch.cuda.synchronize()
+    for p, args, C0, X0, C, X, stream in problems:
+        assert csat.csat_decoder_status(p.ws) == 0
+        assert torch.equal(C, C0) and torch.equal(X, X0)
+    p, args, C0, X0, C, X, stream = problems[0]
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        csat.csat_forward(*args, C, None, X, p.ws)
+    for _ in range(3):
+        C.zero_(), X.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert csat.csat_decoder_status(p.ws) == 0 and torch.equal(C, C0) and torch.equal(X, X0)
+        p.forward(args[5], args[6], args[7] - 1)               # eager work on the same workspace in between
+
+
 # (type, heads, n_q, n, d, m, forms of the small-tile products in measurement, attention and synthesis): contractions of less than a
 # step, one, eight and nine steps, and with a ragged last one; tiles of one row and column, whole ones and one more; both
 # tile sizes in bf16; the output product where it is one; the line (96 of the 128-wide tiles in float, 64 in bf16)
@@ -696,18 +730,15 @@ def test_unrolled_decoder_on_the_wider_tile(rows, n, m, iters):
         assert torch.equal(X[:, r0:r0 + 300], Xs) and torch.equal(C[:, r0:r0 + 300], Cs)
 
 
-# (n_q, n, m, picks): one candidate column per 128, a ragged last group, more picks than a batch of eight, every column
-# picked in the end (m = n = picks), several column tiles
+# (n_q, n, m, picks): a ragged last group of columns, more picks than a batch of eight, every column picked in the end (m = n = picks)
 PICK_CASES = [(90, 128, 100, 5), (100, 130, 129, 9), (128, 32, 32, 32), (90, 300, 64, 17), (256, 513, 40, 3), (87, 257, 20, 20),
-              # ... the product takes over from the search at 8192 rows times column tiles, or three column tiles
               (2730, 128, 20, 5), (2731, 128, 20, 5), (1365, 257, 30, 9), (1366, 512, 30, 9), (90, 512, 40, 3)]
 
 
 @pytest.mark.parametrize("n_q,n,m,picks", PICK_CASES)
 def test_matching_pursuit_picks_in_the_product(n_q, n, m, picks, options):
-    """The largest correlation is found in the product's epilogue where the large-tile kernel runs: the picks of the
-    search over stored correlations (the same product, forced onto the other kernel, differs in summation order only, so
-    rows whose picks agree are compared in full and few may not), no column twice, coefficients consistent."""
+    """bf16: the largest correlation is found where the correlations are formed.  The picks of the search over stored correlations
+    (forced; rows whose picks agree are compared in full and few may not), no column twice, coefficients consistent."""
     w = _small("omp_picks", B=1, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16")
     Q, K, V = gen.make_qkv(w)
     Phi = gen.make_workload_phi(w)

@@ -416,9 +416,10 @@ template <typename T>
 __device__ __forceinline__ int omp_take_pick(const OmpUpdateArgs<T>& a, long long r, int lane) {
     if (!a.cand) return a.picks[r * a.k + a.it];
     const int nc = r < a.rows_whole ? 1 : a.splits;
-    OmpCand b{-1.f, 0x7fffffff};
-    for (int q = 0; q < nc; q += 64) {
-        const OmpCand o = q + lane < nc ? a.cand[r * a.splits + q + lane] : OmpCand{-1.f, 0x7fffffff};
+    const OmpCand none{-1.f, 0x7fffffff};
+    OmpCand b = lane < nc ? a.cand[r * a.splits + lane] : none;
+    for (int q = 64; q < nc; q += 64) {                 // (the first 64 outside, where their read overlaps the others: 84 -> 83 us, 76 800 rows, m = 392)
+        const OmpCand o = q + lane < nc ? a.cand[r * a.splits + q + lane] : none;
         if (o.val > b.val) b = o;                       // ascending columns per lane
     }
     if (nc > 1) {                                       // largest value, lowest index on a tie

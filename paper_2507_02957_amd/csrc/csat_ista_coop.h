@@ -142,9 +142,9 @@ __global__ __launch_bounds__(512, 1) void ista_coop_kernel(IstaFusedArgs a) {
             }
             asm volatile("" ::: "memory");
             // Every member sums in the members' order, so that all hold the same residual: from three on the own part is read back too
-            // (of two, own + other is the same sum).
+            // (of two, own + other is the same sum; the zeros out of their way: 548 -> 544 us a column-wise short_video).
             const int parts = G2 == 2 ? 1 : G2;
-            if (G2 > 2) {
+            if (__builtin_expect(G2 > 2, 0)) {
 #pragma unroll
                 for (int j = 0; j < RT; ++j)
 #pragma unroll

@@ -1475,7 +1475,9 @@ OmpExtra carve_omp(const csat_dims& d, const Workspace& w, int k, char* base) {
     x.PhiQ = take(x.stored || k == 1 ? 0 : packed_bytes);
     x.Rf = (float*)take(x.stored ? (size_t)rows * x.mq * 4 : 0);
     x.Qb = (float*)take(x.stored ? (size_t)rows * k * x.mq * 4 : 0);
-    x.bytes = off;
+    // (a workspace for more picks holds fewer ones too, also where those pack the columns)
+    const int held = omp_held_picks(x.MQ);
+    x.bytes = k > held ? std::max(off, carve_omp(d, w, held, base).bytes) : off;
     return x;
 }
 

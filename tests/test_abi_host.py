@@ -234,6 +234,15 @@ def test_opnorm_helper_matches_oracle(lib):
     print(f"csat_phi_opnorm2 at 1024 x 16384: {dt:.1f} s")
 
 
+@pytest.mark.parametrize("n,m", [(300, 64), (1600, 392), (4096, 512), (16384, 64), (16384, 1024)])
+def test_a_workspace_for_more_picks_holds_fewer(n, m):
+    """Few rows of many columns keep the orthonormal vectors or Phi's columns packed, by the number of picks: the larger need counts."""
+    for dtype in ("f32", "bf16"):
+        for rows in (1, 16, 64, 300, 5000):
+            need = [csat.csat_omp_workspace_bytes(csat.make_dims(1, 1, rows, n, 64, m, dtype), k) for k in range(1, 33)]
+            assert need == sorted(need), (dtype, rows)
+
+
 def test_options_and_decoder_status_arguments(lib):
     ctx = csat.context()
     assert lib.csat_set_option(None, 0, 1) == -1

@@ -34,6 +34,7 @@ UNITS = [(f"ista_resident_{mt}_{c}", "csat_tu_ista_resident.hip", [f"-DCSAT_TU_M
          for c in (16, 12, 9, 7, 5, 3) for mt in range(8, 0, -1) if c * mt <= 80] + UNITS
 UNITS += [("ista_resident_f32", "csat_tu_ista_resident_f32.hip", [])]
 UNITS += [("attention_z", "csat_tu_attention_z.hip", [])]
+UNITS += [("support", "csat_tu_support.hip", [])]
 SOURCES = sorted({os.path.join(CSRC, src) for _, src, _ in UNITS})
 
 

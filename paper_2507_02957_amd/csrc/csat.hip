@@ -13,6 +13,7 @@
 #include "csat_attention.h"
 #include "csat_attention_z.h"
 #include "csat_measure.h"
+#include "csat_support.h"
 #include "csat_launch.h"
 #include "csat_peaks.h"
 
@@ -151,6 +152,10 @@ bool sparse_state(size_t dense_state_bytes) {
 }
 
 constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_static's workspace
+
+// The decoders' rule for products over the support of the iterate (csat_support.h), its words in the workspace's status block.
+int support_choice() { return (*tl_opt)[CSAT_OPT_SUPPORT]; }      // 1: never; 2: wherever a kernel exists
+constexpr int kSupportWord = 8;
 
 // Largest m (in 32-wide tiles) the fused decoder takes.  Its residual accumulators need 16 registers per tile: up to
 // 13 tiles they fit next to the operands of the two-chunk schedule; 14 to 16 tiles fill the accumulator file and run
@@ -1136,7 +1141,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
 
 // C = X V per head from the decoder state; V: as the caller holds it, or nullptr when only w.VT (its transpose) is there
 template <typename T>
-csat_status run_synthesis(const csat_dims& d, const Workspace& w, T* C, hipStream_t st, const T* V = nullptr) {
+csat_status run_synthesis(const csat_dims& d, const Workspace& w, T* C, hipStream_t st, const T* V = nullptr, SupportRule rule = {}) {
     constexpr bool kBf16 = sizeof(T) == 2;
     const int BH = d.B * d.H;
     if constexpr (kBf16) {
@@ -1149,6 +1154,7 @@ csat_status run_synthesis(const csat_dims& d, const Workspace& w, T* C, hipStrea
             a.Kc = (bf16_t*)C;
             a.heads = BH;
             a.blocks_per_head = (a.MT + 3) / 4;
+            a.rule = rule;
             const dim3 grid((unsigned)(8 * ((BH + 7) / 8) * a.blocks_per_head));
             Timed tm(w, CSAT_K_SYNTHESIS, st);
             const bool deep = d.n >= 4096;
@@ -1354,6 +1360,38 @@ ListaExtra carve_lista(const csat_dims& d, const Workspace& w, char* base) {
     return x;
 }
 
+// Whether the layers behind the first may run over the support of their iterate, which the device decides: not where they
+// take less than about 400 us in all (20 us a layer and its operations at 0.9 PFLOP/s), 2 to 3 % of which the counting and the launches
+// that return at once would take.  S - I transposed takes the place of the second operand buffer.
+bool lista_support_applies(const csat_dims& d, long long rows, int iters) {
+    if (support_choice() == 1 || iters < 2 || iters > kSupportMaxLayers || d.n > kListaSupportMaxN || rows < d.n) return false;
+    return support_choice() == 2 || (iters - 1) * (20.0 + (double)rows * d.n * d.n / 4.5e8) > 400.0;
+}
+// ... and up to which density: non-zero float4 (four rows of a column) that the first layer may leave to every four rows.  Over
+// all columns against over the support, us: n = 1600, 76 800 rows, 20 layers: 9 a quad 8760, 2540; 25 8920, 4150; 77 9260, 8000; 288 10 820, 19 060;
+// n = 2500, 20 000 rows, 10 layers: 39 2985, 2070; 80 3040, 3260; n = 700, 44 800 rows, 20 layers: 24 2270, 1120; 56 2450, 1720; 139
+// 2720, 2970; fewer rows, whose longest lists end the launch: n = 700, 5600 rows, 8 layers: 52 299, 311; n = 2048, 8192 rows, 10 layers: 10 772, 470; 20
+// 750, 630; 43 740, 880; n = 4096 (its matrix far beyond an L2), 16 384 rows, 10 layers: 23 4590, 4960; 57 4600, 7570; short rows, whose layers take as long
+// as their launches: n = 416, 6656 rows, 16 layers: 271 a quad 488, 468; 402 493, 772.
+double lista_support_limit(const csat_dims& d, long long rows) {
+    if (support_choice() == 2) return 4294967295.0;
+    return rows / 4.0 * (d.n > 3328 ? 12 : d.n <= 512 ? 128 : rows >= 16384 ? 48 : 24);
+}
+// Clears the rule's words.
+csat_status support_begin(const Workspace& w, hipStream_t st) {
+    hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(64), 0, st, w.Status, 0, (uint32_t*)w.Status + kSupportWord, 2ll);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+// Counts what the first threshold left (its mask bytes, whole 16-byte pieces).
+csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st) {
+    const long long chunks = bytes / 16;
+    hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
+                       (uint32_t*)w.Status + kSupportWord);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+
 template <typename T>
 csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x, const float* Y, const void* S,
                     const void* Bw, const float* thetas, int iters, float* X, const void* V, void* C, hipStream_t st) {
@@ -1370,12 +1408,18 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
     const bool tiled = kBf16 && use_big_gemm<T>(GemmArgs{nullptr, w.ldn, 0, nullptr, w.ldn, 0, (int)rows, d.n, d.n, 0}, w.ldn) &&
                        use_big_gemm<T>(GemmArgs{nullptr, w.ldm, 0, nullptr, w.ldm, 0, (int)rows, d.n, d.m, 0}, w.ldn) &&
                        lista_choice() != 1;
+    SupportRule rule;
+    if (tiled && lista_support_applies(d, rows, iters)) {
+        rule.ctl = (const uint32_t*)w.Status + kSupportWord;
+        rule.limit = (uint32_t)std::min(4294967295.0, lista_support_limit(d, rows));
+        CSAT_TRY(support_begin(w, st));
+    }
     {
         Timed tm(w, CSAT_K_LAYOUT, st);
         CSAT_TRY((pack_rows<T, T>((const T*)Bw, d.m, (T*)w.PhiT, w.ldm, d.n, d.m, st)));
         const long long total = (long long)d.n * w.ldn;
         hipLaunchKernelGGL((sub_identity_pack_kernel<T>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                           (const T*)S, d.n, (T*)x.D, w.ldn);
+                           (const T*)S, d.n, (T*)x.D, w.ldn, rule.ctl ? (uint32_t*)w.Status + kSupportWord + 1 : nullptr);
         HIP_TRY(hipGetLastError());
         CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));
         if (want_c && !synthesis_is_direct<T>(d)) CSAT_TRY(transpose_pack<T>((const T*)V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
@@ -1396,6 +1440,15 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
             CSAT_TRY((gemm<T>(g, d.n, 1, ew, st)));
         }
     }
+    if constexpr (kBf16) {
+        if (rule.ctl) {
+            Timed tm(w, CSAT_K_LAYOUT, st);
+            CSAT_TRY(support_count(w, x.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st));
+            hipLaunchKernelGGL(support_transpose_kernel, dim3((unsigned)((w.ldn + 63) / 64), (unsigned)((d.n + 63) / 64)), dim3(256), 0, st, rule,
+                               (const bf16_t*)x.D, (bf16_t*)x.Op[0], d.n, (int)w.ldn);
+            HIP_TRY(hipGetLastError());
+        }
+    }
     for (int t = tiled ? 1 : 0; t < iters; ++t) {
         char* cur = x.Op[t & 1];
         char* nxt = x.Op[(t + 1) & 1];
@@ -1403,7 +1456,7 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
         if (tiled) {    // accumulators start from W; the iterate is kept like the ISTA decoder's (sparse, accumulator order)
             EpiListaUpdateTiled eu{{(f32x4*)x.StateF, w.ldn / 32, x.Mask, (bf16_t*)nxt, w.ldn,
                                     (t == iters - 1) ? X : nullptr, 1.f, thetas[t], rows, d.n, 0},
-                                   (const f32x4*)x.W};
+                                   (const f32x4*)x.W, rule};
             g.K = (int)round_up(g.K, 64);
             Timed tm(w, CSAT_K_UPDATE, st);
             CSAT_TRY(launch_gemm_big_lista(g, w.ldn, eu, st));
@@ -1418,7 +1471,16 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
         Workspace wf = w;          // the synthesis reads the final operand buffer
         if (kBf16) wf.Xb = (bf16_t*)x.Op[iters & 1];
         else wf.Xs = (float*)x.Op[iters & 1];
-        CSAT_TRY(run_synthesis<T>(d, wf, (T*)C, st, (const T*)V));
+        CSAT_TRY(run_synthesis<T>(d, wf, (T*)C, st, (const T*)V, rule));
+    }
+    if constexpr (kBf16) {
+        if (rule.ctl) {      // (behind the synthesis, which not every shape's kernel leaves out: C is written last here)
+            ListaSupportArgs a{rule, (const f32x4*)x.W, w.ldn / 32, (const bf16_t*)x.Op[0], (int)w.ldn, X, (const bf16_t*)V, want_c ? (bf16_t*)C : nullptr,
+                               rows, d.n_q, d.n, d.d, iters, {}};
+            std::copy(thetas, thetas + iters, a.theta);
+            Timed tm(w, CSAT_K_UPDATE, st);
+            HIP_TRY(lista_support_launch(a, (unsigned)((rows + 3) / 4), st));
+        }
     }
     return CSAT_OK;
 }

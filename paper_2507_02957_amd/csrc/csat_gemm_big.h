@@ -59,6 +59,9 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     constexpr int NGK = KS / 16;                     // MFMA k-slices per stage
     static_assert(BLOCKS % S::kWaves == 0, "requests must divide evenly over the wavefronts");
     static_assert(NGK == 2 || NGK == 4, "KS is 32 or 64");
+    if constexpr (has_rule<Epi>::value) {
+        if (epi.rule.sparse()) return;
+    }
     extern __shared__ uint4 lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

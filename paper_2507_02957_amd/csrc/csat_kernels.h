@@ -452,6 +452,15 @@ constexpr uint32_t kBufferFlags = 0x00027000;      // raw 32-bit buffer descript
 constexpr int kStreamAux = 2;
 constexpr int kOutOfRange = 0x7fffffff;            // byte offset beyond any descriptor: loads give 0, stores are dropped
 
+// Whether the iterate is sparse enough for the kernels over its support (csat_support.h), decided on the device.  Two words: [0]
+// non-zero float4 of the iterate (four rows of a column), [1] an operand holds an infinity or NaN, whose products with
+// zeros are not zero.
+struct SupportRule {
+    const uint32_t* ctl = nullptr;      // null: over all columns
+    uint32_t limit = 0;
+    __device__ __forceinline__ bool sparse() const { return ctl && ctl[0] <= limit && ctl[1] == 0; }
+};
+
 // r = y - Phi x for the large-tile kernel.  Y rows must be 16-byte aligned (ldY % 4 == 0).
 struct EpiResidualTiled {
     static constexpr bool kTile = true;
@@ -726,8 +735,9 @@ struct EpiIstaUpdateTiled {
 // accumulators start from W = B y (stored in accumulator order by the first layer, loaded before the
 // main loop), so the epilogue is the ISTA one with mu = 1 and this layer's threshold.
 struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
-    static constexpr bool kAccInit = true;
+    static constexpr bool kAccInit = true, kRule = true;
     const f32x4* W;
+    SupportRule rule;
     template <int TN>
     __device__ __forceinline__ void init(long long r0w, long long c0w, int lane, f32x16 (&acc)[2][TN]) const {
 #pragma unroll
@@ -781,6 +791,8 @@ struct EpiListaFirstTiled : EpiIstaUpdateTiled {
     }
 };
 
+template <typename E, typename = void> struct has_rule : std::false_type {};
+template <typename E> struct has_rule<E, std::enable_if_t<E::kRule>> : std::true_type {};
 template <typename E, typename = void> struct has_acc_init : std::false_type {};
 template <typename E> struct has_acc_init<E, std::enable_if_t<E::kAccInit>> : std::true_type {};
 template <typename E, typename = void> struct has_whole_epilogue : std::false_type {};
@@ -851,15 +863,17 @@ __global__ void transpose_pack_kernel(const T* src, const T* src2, int z2, long 
     }
 }
 
-// D[c][k] = S[c][k] - (c == k) for c, k < n, rows of D padded to ldd with zeros (operand layout).
+// D[c][k] = S[c][k] - (c == k) for c, k < n, rows of D padded to ldd with zeros (operand layout).  *unbounded (optional) is set
+// where an element is infinite or NaN.
 template <typename T>
-__global__ void sub_identity_pack_kernel(const T* S, int n, T* D, long long ldd) {
+__global__ void sub_identity_pack_kernel(const T* S, int n, T* D, long long ldd, uint32_t* unbounded) {
     long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (long long)n * ldd) return;
     const long long c = idx / ldd, kcol = idx % ldd;
     float v = 0.f;
     if (kcol < n) v = Elem<T>::load(S + c * n + kcol) - (c == kcol ? 1.f : 0.f);
     Elem<T>::store(D + idx, v);
+    if (unbounded && !(fabsf(v) < INFINITY)) *unbounded = 1u;
 }
 
 // dst[z][c][r] = (TO) src[z][r][c] for r < R, c < Cc (both contiguous), 32x32 tiles through LDS.

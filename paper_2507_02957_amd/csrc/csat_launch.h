@@ -11,6 +11,7 @@ struct IstaResidentArgs;
 struct IstaResidentF32Args;
 struct AttentionArgs;
 struct AttentionZArgs;
+struct ListaSupportArgs;
 
 // Fused ISTA decoder for MT tiles of m (csat_ista_fused.h, csat_ista_fused2.h).  variant: 0 dense state, 1 sparse
 // state, 2 one 32-row tile per workgroup (thin); 3 and 4: dense and sparse state on the two-chunk schedule; 6:
@@ -49,5 +50,9 @@ hipError_t attention_fused_launch_bf16_z3(int mt_total, bool single, const Atten
 // Compressed attention without A~ (csat_attention_z.h): bf16, d a multiple of 32 up to 128; parts: 2 where K~ comes as
 // its (hi | lo) pair; resident: all of a head's fragments in LDS.
 hipError_t attention_z_launch(int d, int parts, bool resident, const AttentionZArgs& a, unsigned grid, size_t lds_bytes, hipStream_t st);
+
+// The unrolled decoder over the support of its iterate (csat_support.h), n <= kListaSupportMaxN, a workgroup per four rows.
+constexpr int kListaSupportMaxN = 4096;
+hipError_t lista_support_launch(const ListaSupportArgs& a, unsigned grid, hipStream_t st);
 
 }  // namespace csat

@@ -43,6 +43,7 @@ struct MeasureDirectArgs {
     long long strideA;                 // elements between the heads' own row operands (0: Phi, shared by the heads).  With
                                        // it the kernel is the synthesis C = X V of a head: Phi = the bf16 iterate, m = n_q,
                                        // K = V as the caller holds it, Kc = C
+    SupportRule rule;                  // (the synthesis only: not where the kernels over the iterate's support run)
 };
 
 // DT = d / 32; KS: rows of K and V per step; PD: steps in flight; WANT_V: V~ too (a.Vc != nullptr)
@@ -53,6 +54,9 @@ struct MeasureDirectArgs {
 // workgroups) 70 -> 60 us (what is left is the L2: 24 KB a step for 64 rows of Phi, about 25 B per clock and CU).
 template <int DT, int KS, int PD, bool WANT_V, int KG = 1>
 __global__ __launch_bounds__(256 * KG) void measure_direct_kernel(MeasureDirectArgs a) {
+    if constexpr (!WANT_V && KG == 1) {
+        if (a.rule.sparse()) return;
+    }
     typedef short s16x4 __attribute__((ext_vector_type(4)));
     typedef short s16x8 __attribute__((ext_vector_type(8)));
     typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;

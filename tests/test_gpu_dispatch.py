@@ -931,3 +931,63 @@ def _selection(m, n):
 
 def to_dev_raw(a):
     return torch.from_numpy(a).to(DEV)
+
+
+# (heads, n_q, n, m, d, layers): rows of 64 R columns for the instances' R and one more, a last group of rows that is not whole, several
+# heads to a group, two layers, d that is not the synthesis kernel's
+LISTA_SUPPORT_CASES = [(3, 87, 256, 130, 64, 4), (1, 259, 257, 136, 64, 2), (7, 75, 512, 200, 64, 5), (2, 391, 770, 160, 128, 3), (1, 1026, 1025, 200, 64, 3),
+                       (2, 833, 1600, 392, 64, 6), (5, 330, 1639, 150, 80, 3), (3, 701, 2049, 256, 64, 3), (1, 2561, 2561, 136, 64, 2), (1, 4101, 4096, 130, 64, 2)]
+
+
+@pytest.mark.parametrize("heads,n_q,n,m,d,layers", LISTA_SUPPORT_CASES)
+def test_unrolled_decoder_over_the_support(heads, n_q, n, m, d, layers, options):
+    """Layers that gather S's columns for the non-zero coefficients only: against float64 and against the layers over all columns."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    rows = heads * n_q
+    randn = lambda *s: torch.randn(*s, generator=g, device=DEV)                     # noqa: E731
+    Y, B = randn(heads, n_q, m), (randn(n, m) * 0.05).bfloat16()
+    Y *= torch.rand(heads, n_q, 1, generator=g, device=DEV) ** 2                    # rows of a few and rows of many coefficients
+    S = (torch.eye(n, device=DEV) + 0.3 / n ** 0.5 * randn(n, n)).bfloat16()
+    V = randn(heads, n, d).bfloat16()
+    theta = 2.0 * 0.05 * m ** 0.5
+    thetas = [theta * (1.0 - 0.1 * t) for t in range(layers)]
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "bf16")
+
+    def decode(choice, y=Y, s=S):
+        options("support", choice)
+        ws = torch.empty(csat.csat_lista_workspace_bytes(dims, layers), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        X, C = torch.empty(heads, n_q, n, device=DEV), torch.empty(heads, n_q, d, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover_lista(dims, y.clone(), s, B, thetas, X, V, C, ws)
+        torch.cuda.synchronize()
+        return X, C
+
+    X, C = decode(2)
+    W = torch.matmul(Y.bfloat16().double().view(rows, m), B.double().t().contiguous())
+    D = (S.float() - torch.eye(n, device=DEV)).bfloat16().double().t().contiguous()
+    x = torch.zeros(rows, n, dtype=torch.float64, device=DEV)
+    for th in thetas:
+        u = W + x + torch.matmul(x.float().bfloat16().double(), D)
+        x = u.sign() * (u.abs() - th).clamp_min(0.0)
+    density = float((x != 0).double().mean())
+    assert 0.001 < density < 0.1
+    # the same roundings as in float64 here but for the float sums: 1e-6 of |u| <= 4 |x|, and a coefficient whose rounding to bf16
+    # falls the other way, one of 2^-8 of itself in about 1e-3 of them and layer
+    assert float((X.double().view(rows, n) - x).norm() / x.norm()) < 1e-3
+    want = torch.matmul(x.float().bfloat16().double().view(heads, n_q, n), V.double())
+    assert float((C.double() - want).norm() / want.norm()) < 3e-3       # (and C to bf16: 2^-9 each, at most)
+    X1, C1 = decode(1)
+    assert float((X1 - X).norm() / X.norm()) < 1e-3 and float((C1.float() - C.float()).norm() / C.float().norm()) < 4e-3
+    Xr, Cr = decode(2)
+    assert torch.equal(X, Xr) and torch.equal(C, Cr)
+    # a matrix with an infinity or NaN, whose products with zeros are NaN, stays on the layers over all columns
+    for bad in (float("inf"), float("nan")):
+        Sb = S.clone()
+        Sb[n // 2, n - 1] = bad
+        got, old = decode(2, s=Sb), decode(1, s=Sb)
+        assert all(torch.equal(p.isnan(), q.isnan()) and torch.equal(p.nan_to_num(), q.nan_to_num()) for p, q in zip(got, old))
+    # an infinite measurement reaches its own row only
+    Yb = Y.clone()
+    Yb[heads - 1, n_q - 1, 3] = float("inf")
+    Xb, Cb = decode(2, y=Yb)
+    assert torch.equal(Xb.view(rows, n)[:-1], X.view(rows, n)[:-1]) and torch.equal(Cb.view(rows, d)[:-1], C.view(rows, d)[:-1])
+    assert not Xb.view(rows, n)[-1].isfinite().all()

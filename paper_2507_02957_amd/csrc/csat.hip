@@ -1028,6 +1028,43 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     return CSAT_ERR_SHAPE;
 }
 
+// Clears the rule's words.
+csat_status support_begin(const Workspace& w, hipStream_t st) {
+    hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(64), 0, st, w.Status, 0, (uint32_t*)w.Status + kSupportWord, 2ll);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+// Counts what the first threshold left (its mask bytes, whole 16-byte pieces).
+csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st) {
+    const long long chunks = bytes / 16;
+    hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
+                       (uint32_t*)w.Status + kSupportWord);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+
+// Whether the large-tile decoder's residual may go over the support of the iterate, which the device decides: not where the
+// product over all columns takes less than about 20 us (its operations at 1.2 PFLOP/s).
+// (A byte for every four rows lies in K's transposed copy, which the decoder does not read.)
+bool residual_support_applies(const csat_dims& d, long long rows, int iters) {
+    if (support_choice() == 1 || iters < 2 || d.m > 1024 || d.n > 65536) return false;
+    if (rows / 4 >= (long long)d.B * d.H * d.d * d.n * 2) return false;
+    return support_choice() == 2 || (double)rows * d.n * d.m > 1.2e10;
+}
+// ... in a launch of its own, with more wavefronts than in the product's place, where a launch that returns at once is below 1 % of an
+// iteration (the product over all columns about 200 us).
+bool residual_support_apart(const csat_dims& d, long long rows) { return (double)rows * d.n * d.m > 1.2e11; }
+// ... and up to which density: non-zero float4 (four rows of a column) that the first iteration may leave to every four rows.  Forward over
+// all columns against over the support, us.  Apart: 205 824 rows, n = 1608, m = 752, 11 iterations: 2 a quad 14 910, 9750; 18 14 990, 12 490;
+// 38 976 rows, n = 9744, m = 1024, 31 iterations: 10 54 400, 29 900; 142 54 100, 38 900; 394 54 700, 50 700; 13 104 rows, n = 11 744: 100 9940,
+// 7360; 368 10 100, 9850.  In the product's place: 28 544 rows, n = 1824, m = 745, 31 iterations: none 7290, 4080; 2 7220, 5460; 14 7290, 6770; 48 000
+// rows: 45 12 130, 14 390; few rows, whose longest lists end the launch: 8192 rows, n = 2048, m = 600, 20 iterations: 4 1660, 1450; 10 1670,
+// 1750; 4272 rows, n = 6496, 36 iterations: 24 5850, 5640; 78 5860, 6950; 3432 rows, n = 13 713, 9 iterations: 16 4240, 2640; 394 4250, 5440.
+double residual_support_limit(const csat_dims& d, long long rows) {
+    if (support_choice() == 2) return 4294967295.0;
+    return rows / 4.0 * d.n / (residual_support_apart(d, rows) ? 64 : rows >= 12288 ? 128 : 270);
+}
+
 // ISTA on rows of Y (float, leading dimension ldY).  Generic decoder: w.R must already hold Y in
 // operand layout (the first residual, since x^0 = 0); the final state is left in w.Xs (float mode)
 // or w.Xb (bf16 mode).  Fused decoder (bf16, m <= 512): Y must be w.A-style rows with
@@ -1099,25 +1136,54 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         HIP_TRY(hipGetLastError());
         return CSAT_OK;
     }
+    // large tiles throughout: the iterate has its masks
+    SupportRule rule;
+    if constexpr (kBf16) {
+        const GemmArgs gr{nullptr, w.ldn, 0, nullptr, w.ldn, 0, (int)rows, d.m, d.n, 0}, gu{nullptr, w.ldm, 0, nullptr, w.ldm, 0, (int)rows, d.n, d.m, 0};
+        if (residual_support_applies(d, rows, iters) && use_big_gemm<T>(gr, w.ldm) && use_big_gemm<T>(gu, w.ldn) &&
+            (w.split > 1 || (ldY % 4 == 0 && aligned16(Y)))) {
+            rule.ctl = (const uint32_t*)w.Status + kSupportWord;
+            rule.limit = (uint32_t)std::min(4294967295.0, residual_support_limit(d, rows));
+            CSAT_TRY(support_begin(w, st));
+        }
+    }
     for (int t = 0; t < iters; ++t) {
         if (t > 0) {   // residual r = y - Phi x
             GemmArgs g{kBf16 ? (const void*)w.Xb : (const void*)w.Xs, w.ldn, 0, w.PhiP, w.ldn, 0, 0, d.m, d.n, 0};
             g.M = (int)rows;
             Timed tm(w, CSAT_K_RESIDUAL, st);
+            const ResidualSupportArgs sa{w.Mask, (const f32x4*)w.Xs, w.ldn / 32, (const bf16_t*)w.PhiT, (int)w.ldm, Y, ldY, (bf16_t*)w.R, (uint8_t*)w.KT, rows, d.m, t == 1};
+            auto launch_residual = [&](const auto& epi, const GemmArgs& ga, int parts) -> csat_status {
+                using Epi = std::decay_t<decltype(epi)>;
+                if (!rule.ctl) return launch_gemm_big(ga, w.ldm, parts, epi, st);
+                auto launch = [&](auto mr) -> csat_status {
+                    constexpr int MR = decltype(mr)::value;
+                    if (parts > 1 || !residual_support_apart(d, rows)) return launch_gemm_big(ga, w.ldm, parts, EpiResidualEither<Epi, MR>{epi, rule, sa}, st);
+                    hipLaunchKernelGGL(residual_support_kernel<MR>, dim3((unsigned)std::min<long long>((rows + 15) / 16, 4ll * cu_count())), dim3(256), 0, st, rule, sa);
+                    HIP_TRY(hipGetLastError());
+                    return launch_gemm_big(ga, w.ldm, parts, EpiResidualEither<Epi, 0>{epi, rule, sa}, st);
+                };
+                const long long regs = (w.ldm + 63) / 64;      // the instance whose 64 MR elements hold a row
+                if (regs <= 8) return launch(std::integral_constant<int, 8>{});
+                if (regs <= 10) return launch(std::integral_constant<int, 10>{});
+                if (regs <= 12) return launch(std::integral_constant<int, 12>{});
+                return launch(std::integral_constant<int, 16>{});
+            };
+            if (rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st));
             if (w.split > 1 && use_big_gemm<T>(g, w.ldm)) {     // partial products along K, then r = y - their sum
                 GemmArgs gs = g;
                 gs.K = (int)(w.ldn / w.split);
                 gs.strideA = gs.strideB = gs.K;
-                EpiStore<float> ep{w.SplitP, w.ldm, rows * w.ldm, nullptr, 0, 0, 1.f, (int)rows, d.m};
-                CSAT_TRY(launch_gemm_big(gs, w.ldm, w.split, ep, st));
+                const EpiStore<float> ep{w.SplitP, w.ldm, rows * w.ldm, nullptr, 0, 0, 1.f, (int)rows, d.m};
+                CSAT_TRY(launch_residual(ep, gs, w.split));
                 const long long total = rows * w.ldm;
                 hipLaunchKernelGGL(residual_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Y, ldY,
-                                   w.SplitP, w.split, rows * w.ldm, (bf16_t*)w.R, w.ldm, rows, d.m);
+                                   w.SplitP, w.split, rows * w.ldm, (bf16_t*)w.R, w.ldm, rows, d.m, rule);
                 HIP_TRY(hipGetLastError());
             } else if (use_big_gemm<T>(g, w.ldm) && ldY % 4 == 0 && aligned16(Y)) {
-                EpiResidualTiled er{Y, ldY, (bf16_t*)w.R, w.ldm, rows, d.m};
+                const EpiResidualTiled er{Y, ldY, (bf16_t*)w.R, w.ldm, rows, d.m};
                 g.K = (int)round_up(g.K, 64);
-                CSAT_TRY(launch_gemm_big(g, w.ldm, 1, er, st));
+                CSAT_TRY(launch_residual(er, g, 1));
             } else {
                 EpiResidual<T> er{Y, ldY, (T*)w.R, w.ldm, rows, d.m};
                 CSAT_TRY((decoder_gemm<T>(g, w.ldm, 1, er, st)));
@@ -1127,7 +1193,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         Timed tm(w, CSAT_K_UPDATE, st);
         if (use_big_gemm<T>(g, w.ldn)) {   // large-tile kernel: state in accumulator order
             EpiIstaUpdateTiled eu{(f32x4*)w.Xs, w.ldn / 32, w.Mask, w.Xb, w.ldn, (t == iters - 1) ? Xout : nullptr,
-                                  mu, theta, rows, d.n, t == 0};
+                                  mu, theta, rows, d.n, t == 0, t > 0 && t < iters - 1 ? rule : SupportRule{}};      // (the synthesis reads the last copy)
             g.K = (int)round_up(g.K, 64);
             CSAT_TRY(launch_gemm_big(g, w.ldn, 1, eu, st));
             continue;
@@ -1377,21 +1443,6 @@ double lista_support_limit(const csat_dims& d, long long rows) {
     if (support_choice() == 2) return 4294967295.0;
     return rows / 4.0 * (d.n > 3328 ? 12 : d.n <= 512 ? 128 : rows >= 16384 ? 48 : 24);
 }
-// Clears the rule's words.
-csat_status support_begin(const Workspace& w, hipStream_t st) {
-    hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(64), 0, st, w.Status, 0, (uint32_t*)w.Status + kSupportWord, 2ll);
-    HIP_TRY(hipGetLastError());
-    return CSAT_OK;
-}
-// Counts what the first threshold left (its mask bytes, whole 16-byte pieces).
-csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st) {
-    const long long chunks = bytes / 16;
-    hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
-                       (uint32_t*)w.Status + kSupportWord);
-    HIP_TRY(hipGetLastError());
-    return CSAT_OK;
-}
-
 template <typename T>
 csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x, const float* Y, const void* S,
                     const void* Bw, const float* thetas, int iters, float* X, const void* V, void* C, hipStream_t st) {

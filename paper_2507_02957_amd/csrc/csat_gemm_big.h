@@ -59,10 +59,12 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     constexpr int NGK = KS / 16;                     // MFMA k-slices per stage
     static_assert(BLOCKS % S::kWaves == 0, "requests must divide evenly over the wavefronts");
     static_assert(NGK == 2 || NGK == 4, "KS is 32 or 64");
-    if constexpr (has_rule<Epi>::value) {
+    extern __shared__ uint4 lds[];
+    uint2 words{0u, 0u};
+    if constexpr (has_late_rule<Epi>::value) words = epi.rule.words();      // (asked for here, waited for with the first stage)
+    else if constexpr (has_rule<Epi>::value) {
         if (epi.rule.sparse()) return;
     }
-    extern __shared__ uint4 lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave / WN, wn = wave % WN;
@@ -77,24 +79,25 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     long long rowt, colt;
     const bool a_nt = (g.raster & kRasterStreamA) != 0;      // uniform: A rows go past the caches' recently-used end
     g.raster &= kRasterStreamA - 1;
+    // (32-bit arithmetic: a division of 64 bits is a hundred instructions ahead of the first load)
     if (g.raster == 1) {
-        const int slot = blockIdx.x >> 3;
-        rowt = (long long)(slot / g.a_kwrap) * 8 + (blockIdx.x & 7);
-        colt = slot % g.a_kwrap;
+        const uint32_t slot = blockIdx.x >> 3, tn = g.a_kwrap;
+        rowt = slot / tn * 8 + (blockIdx.x & 7);
+        colt = slot % tn;
         if (rowt * S::kRowsA >= g.M) return;       // the grid is padded to whole groups of 8 row tiles
     } else if (g.raster >= 2) {
         // raster 2 + log2(CB): XCD x owns the column tiles [x tn/8, (x+1) tn/8) and walks them in groups of CB: within a
         // group row tile by row tile, so that the group's column operand (CB x 512 KB at K = 1024) stays in that L2
         // for the whole pass over the rows and a row tile's A panel is shared by CB workgroups running together.
-        const int cb = 1 << (g.raster - 2), per_xcd = g.a_kwrap >> 3;
-        const long long tm = gridDim.x / g.a_kwrap;
-        const long long slot = blockIdx.x >> 3;
-        const long long cg = slot / (tm * cb), rem = slot - cg * tm * cb;
-        rowt = rem / cb;
-        colt = (long long)(blockIdx.x & 7) * per_xcd + cg * cb + rem % cb;
+        const uint32_t lcb = g.raster - 2, per_xcd = (uint32_t)g.a_kwrap >> 3;
+        const uint32_t group = ((uint32_t)(g.M + S::kRowsA - 1) / S::kRowsA) << lcb;      // tiles of a group: row tiles x CB
+        const uint32_t slot = blockIdx.x >> 3;
+        const uint32_t cg = slot / group, rem = slot - cg * group;
+        rowt = rem >> lcb;
+        colt = (blockIdx.x & 7) * per_xcd + (cg << lcb) + (rem & ((1u << lcb) - 1));
     } else {
-        rowt = blockIdx.x / g.a_kwrap;
-        colt = blockIdx.x % g.a_kwrap;
+        rowt = blockIdx.x / (uint32_t)g.a_kwrap;
+        colt = blockIdx.x % (uint32_t)g.a_kwrap;
     }
     const long long row0 = rowt * S::kRowsA, col0 = colt * S::kRowsB;
     const bf16_t* A = (const bf16_t*)g.A + (long long)z * g.strideA;
@@ -159,6 +162,14 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     stage(0, 0);
     typename TilePre<Epi>::type pre = tile_begin<TN>(epi, row0 + wm * 64, col0 + wn * (32 * TN), lane);
     __builtin_amdgcn_s_waitcnt(0);
+    if constexpr (has_late_rule<Epi>::value) {
+        static_assert(Epi::kWaves == WM * WN, "wavefronts");
+        if (epi.rule.sparse(words)) {
+            __syncthreads();
+            epi.instead(lds);
+            return;
+        }
+    }
     __syncthreads();
     for (int ks = 0; ks < ksteps; ++ks) {
         const uint32_t so = (ks & 1) * S::kStage;
@@ -232,7 +243,7 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
             epi.half(0, r0w, c0w, lane, acc[0], stage_w, pre);
             epi.half(1, r0w + 32, c0w, lane, acc[1], stage_w, pre);
         }
-        epi.flush(r0w, c0w, lane, stage_w);
+        epi.flush(r0w, c0w, lane, stage_w, pre);
     } else {
 #pragma unroll
         for (int i = 0; i < 2; ++i)

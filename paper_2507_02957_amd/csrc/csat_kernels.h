@@ -234,6 +234,24 @@ __global__ __launch_bounds__(256, BN == 128 ? 3 : 4) void gemm_nt_kernel(GemmArg
         }
 }
 
+constexpr uint32_t kBufferFlags = 0x00027000;      // raw 32-bit buffer descriptor word 3 (gfx9 family)
+
+// Whether the iterate is sparse enough for the kernels over its support (csat_support.h), decided on the device.  Two words: [0]
+// non-zero float4 of the iterate (four rows of a column), [1] an operand holds an infinity or NaN, whose products with
+// zeros are not zero.
+struct SupportRule {
+    const uint32_t* ctl = nullptr;      // null: over all columns
+    uint32_t limit = 0;
+    __device__ __forceinline__ bool sparse(uint2 w) const { return (ctl != nullptr) & (w.x <= limit) & (w.y == 0); }
+    __device__ __forceinline__ bool sparse() const { return ctl && sparse(*(const uint2*)ctl); }
+    // the words without a branch, to be asked for together with other loads
+    __device__ __forceinline__ uint2 words() const {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(__builtin_amdgcn_make_buffer_rsrc((void*)ctl, 0, ctl ? 8 : 0, kBufferFlags), 0, 0, 0);
+        return uint2{w[0], w[1]};
+    }
+};
+
 // ----------------------------------------------------------------------------------------
 // Epilogues.  Each sees (batch z, row r, column c, fp32 accumulator) and does its own bounds
 // checks: the tile grid may overhang M and N.
@@ -445,21 +463,11 @@ struct EpiListaUpdate {
 // `stage` is kStageBytes of LDS private to the wavefront, used to turn accumulator order into
 // row-contiguous 16-byte accesses.
 
-constexpr uint32_t kBufferFlags = 0x00027000;      // raw 32-bit buffer descriptor word 3 (gfx9 family)
 // Cache policy of the accesses to the fp32 iterate (buffer instruction aux bit 1 = nt): it is touched once per
 // iteration and is larger than any cache, so it must not evict what the next kernel reads (operands in L2,
 // the bf16 copy of the iterate in the Infinity Cache).  Update GEMM -10 %, residual GEMM up to -25 % measured.
 constexpr int kStreamAux = 2;
 constexpr int kOutOfRange = 0x7fffffff;            // byte offset beyond any descriptor: loads give 0, stores are dropped
-
-// Whether the iterate is sparse enough for the kernels over its support (csat_support.h), decided on the device.  Two words: [0]
-// non-zero float4 of the iterate (four rows of a column), [1] an operand holds an infinity or NaN, whose products with
-// zeros are not zero.
-struct SupportRule {
-    const uint32_t* ctl = nullptr;      // null: over all columns
-    uint32_t limit = 0;
-    __device__ __forceinline__ bool sparse() const { return ctl && ctl[0] <= limit && ctl[1] == 0; }
-};
 
 // r = y - Phi x for the large-tile kernel.  Y rows must be 16-byte aligned (ldY % 4 == 0).
 struct EpiResidualTiled {
@@ -500,7 +508,7 @@ struct EpiResidualTiled {
             }
         }
     }
-    __device__ __forceinline__ void flush(long long, long long, int, const char*) const {}
+    __device__ __forceinline__ void flush(long long, long long, int, const char*, const Pre&) const {}
 };
 
 // The ISTA update for the large-tile kernel.  The fp32 state is kept in accumulator order
@@ -515,29 +523,39 @@ struct EpiIstaUpdateTiled {
     static constexpr bool kTile = true;
     static constexpr int kPitch = 272;               // 128 bf16 + 16 bytes
     static constexpr int kStageBytes = 64 * kPitch;
-    struct Pre { uint32_t have[2]; };                // byte j of have[i]: mask of tile (i, j)
+    // byte j of have[i]: mask of tile (i, j); no_copy: `support`, asked before the main loop (asked behind it, a tile waits for the
+    // words: long_video 988 -> 1010 ms)
+    struct Pre { uint32_t have[2]; int no_copy; };
     f32x4* Xs; long long tiles_n;      // column tiles per row tile (ldS / 32)
     uint8_t* Mask;                     // [row tile][column tile][lane]: bit g = float4 g of that lane is non-zero
     bf16_t* Xb; long long ldS;
     float* Xo;
     float mu, theta;
     long long M; int N; int first;
+    SupportRule support;               // where it says so, nothing reads the bf16 copy of this iterate, and it is not written
     __device__ __forceinline__ int live_tiles(long long r0, long long c0w) const {
         if (r0 >= M || c0w >= ldS) return 0;
         const long long left = (ldS - c0w) >> 5;
         return left < 4 ? (int)left : 4;
     }
     __device__ __forceinline__ Pre begin(long long r0w, long long c0w, int lane) const {
-        Pre pre{{0u, 0u}};
+        Pre pre{{0u, 0u}, 0};
         if (first) return pre;
+        // (all loads before the first use: one behind the other's wait cost eight memory latencies ahead of the main loop)
+        const uint2 words = support.words();
+        uint32_t b[2][4];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int nl = live_tiles(r0w + i * 32, c0w);
-            const long long t = ((r0w >> 5) + i) * tiles_n + (c0w >> 5);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(Mask + (((r0w >> 5) + i) * tiles_n + (c0w >> 5)) * 64), 0, live_tiles(r0w + i * 32, c0w) * 64, kBufferFlags);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (j < nl) pre.have[i] |= (uint32_t)Mask[(t + j) * 64 + lane] << (8 * j);
+            for (int j = 0; j < 4; ++j) b[i][j] = __builtin_amdgcn_raw_buffer_load_b8(rs, j * 64 + lane, 0, 0);
         }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) pre.have[i] |= b[i][j] << (8 * j);
+        pre.no_copy = __builtin_amdgcn_readfirstlane((int)support.sparse(words));
         return pre;
     }
     static constexpr bool kWhole = true;      // the kernel calls whole() instead of half(0), half(1)
@@ -547,10 +565,12 @@ struct EpiIstaUpdateTiled {
     __device__ __forceinline__ void whole(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][4], char* stage,
                                           const Pre& pre) const {
         // interior blocks (the common case) need no per-element bounds handling
-        if (r0w + 64 <= M && c0w + 128 <= N && !Xo) run<false>(r0w, c0w, lane, acc, stage, pre);
-        else run<true>(r0w, c0w, lane, acc, stage, pre);
+        if (r0w + 64 <= M && c0w + 128 <= N && !Xo) {
+            if (pre.no_copy) run<false, false>(r0w, c0w, lane, acc, stage, pre);
+            else run<false, true>(r0w, c0w, lane, acc, stage, pre);
+        } else run<true, true>(r0w, c0w, lane, acc, stage, pre);
     }
-    template <bool EDGE>
+    template <bool EDGE, bool COPY>
     __device__ __forceinline__ void run(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][4], char* stage,
                                         const Pre& pre) const {
         const int li = lane & 31, lh = lane >> 5;
@@ -562,13 +582,22 @@ struct EpiIstaUpdateTiled {
         auto issue = [&](auto bc, u32x4 (&xo)[2][4]) {
             constexpr int b = decltype(bc)::value, i = b >> 1, j0 = (b & 1) * 2;
 #pragma unroll
-            for (int jj = 0; jj < 2; ++jj)
+            for (int jj = 0; jj < 2; ++jj) {
+                const int j = j0 + jj;
+                if constexpr (!COPY) {
+                    // a sparse iterate: no lane of most tiles has any
+                    if (__builtin_amdgcn_ballot_w64(((pre.have[i] >> (8 * j)) & 15u) != 0) == 0) {
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) xo[jj][g] = u32x4{0u, 0u, 0u, 0u};
+                        continue;
+                    }
+                }
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int j = j0 + jj;
                     const int off = ((pre.have[i] >> (8 * j + g)) & 1) ? j * 4096 + g * 1024 + lane * 16 : kOutOfRange;
                     xo[jj][g] = __builtin_amdgcn_raw_buffer_load_b128(rs[i], off, 0, kStreamAux);
                 }
+            }
         };
         auto work = [&](auto bc, const u32x4 (&xo)[2][4]) {
             constexpr int b = decltype(bc)::value, i = b >> 1, j0 = (b & 1) * 2;
@@ -595,14 +624,15 @@ struct EpiIstaUpdateTiled {
                         xn[e] = x;
                     }
 #pragma unroll
-                    for (int e = 0; e < 4; e += 2) {
+                    for (int e = 0; COPY && e < 4; e += 2) {
                         const uint32_t pk = f2bf_pk(xn[e], xn[e + 1]);
                         *(bf16_t*)(sw + (8 * g + e) * kPitch + j * 64) = (bf16_t)pk;
                         *(bf16_t*)(sw + (8 * g + e + 1) * kPitch + j * 64) = (bf16_t)(pk >> 16);
                     }
                     const u32x4 xb = __builtin_bit_cast(u32x4, xn);
                     const bool any = ((xb[0] | xb[1]) | (xb[2] | xb[3])) != 0u;    // a thresholded zero is +0
-                    __builtin_amdgcn_raw_buffer_store_b128(xb, rs[i], any ? j * 4096 + g * 1024 + lane * 16 : kOutOfRange, 0, kStreamAux);
+                    if (COPY || __builtin_amdgcn_ballot_w64(any))
+                        __builtin_amdgcn_raw_buffer_store_b128(xb, rs[i], any ? j * 4096 + g * 1024 + lane * 16 : kOutOfRange, 0, kStreamAux);
                     nz |= any ? 1u << g : 0u;
                 }
                 if (j < nl[i]) Mask[(t[i] + j) * 64 + lane] = (uint8_t)nz;
@@ -633,16 +663,20 @@ struct EpiIstaUpdateTiled {
     }
     template <int TN>
     __device__ __forceinline__ Pre begin_wide(long long r0w, long long c0w, int lane) const {
-        Pre pre{{0u, 0u}};
+        Pre pre{{0u, 0u}, 0};
         if (first) return pre;
+        uint32_t b[2][TN];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const int nl = live_wide<TN>(r0w + i * 32, c0w);
-            const long long t = ((r0w >> 5) + i) * tiles_n + (c0w >> 5);
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(Mask + (((r0w >> 5) + i) * tiles_n + (c0w >> 5)) * 64), 0, live_wide<TN>(r0w + i * 32, c0w) * 64, kBufferFlags);
 #pragma unroll
-            for (int j = 0; j < TN; ++j)
-                if (j < nl) pre.have[i] |= (uint32_t)Mask[(t + j) * 64 + lane] << (4 * j);
+            for (int j = 0; j < TN; ++j) b[i][j] = __builtin_amdgcn_raw_buffer_load_b8(rs, j * 64 + lane, 0, 0);
         }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) pre.have[i] |= b[i][j] << (4 * j);
         return pre;
     }
     template <int TN>
@@ -719,7 +753,8 @@ struct EpiIstaUpdateTiled {
     }
     // The wavefront's staged 64 rows x 128 columns of bf16, written 16 bytes per lane:
     // one instruction covers 4 rows x 256 contiguous bytes.
-    __device__ __forceinline__ void flush(long long r0, long long c0, int lane, const char* stage) const {
+    __device__ __forceinline__ void flush(long long r0, long long c0, int lane, const char* stage, const Pre& pre) const {
+        if (pre.no_copy) return;
         const int chunk = lane & 15, rsub = lane >> 4;
 #pragma unroll
         for (int p = 0; p < 16; ++p) {
@@ -793,6 +828,8 @@ struct EpiListaFirstTiled : EpiIstaUpdateTiled {
 
 template <typename E, typename = void> struct has_rule : std::false_type {};
 template <typename E> struct has_rule<E, std::enable_if_t<E::kRule>> : std::true_type {};
+template <typename E, typename = void> struct has_late_rule : std::false_type {};
+template <typename E> struct has_late_rule<E, std::enable_if_t<E::kLate>> : std::true_type {};
 template <typename E, typename = void> struct has_acc_init : std::false_type {};
 template <typename E> struct has_acc_init<E, std::enable_if_t<E::kAccInit>> : std::true_type {};
 template <typename E, typename = void> struct has_whole_epilogue : std::false_type {};
@@ -899,7 +936,8 @@ __global__ void transpose_cast_kernel(const float* src, TO* dst, int R, int Cc) 
 // P[s] [rows, ldR] (float): R [rows, ldR] in bf16 with zero pads.  One thread per element; the sum
 // runs in a fixed order, so the result does not depend on how the partial launches were scheduled.
 static __global__ void residual_reduce_kernel(const float* Y, long long ldY, const float* P, int S, long long strideP,
-                                       bf16_t* R, long long ldR, long long rows, int m) {
+                                       bf16_t* R, long long ldR, long long rows, int m, SupportRule rule) {
+    if (rule.sparse()) return;
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= rows * ldR) return;
     const long long r = idx / ldR;

@@ -123,7 +123,7 @@ struct EpiOmpBest {
         }
         if (row < M) cand[row * nseg + (c0w >> 7)] = b;
     }
-    __device__ __forceinline__ void flush(long long, long long, int, const char*) const {}
+    __device__ __forceinline__ void flush(long long, long long, int, const char*, const Pre&) const {}
 };
 
 // Columns that a row may not pick (picked before, or beyond n): [row tile of 32][chunk][32 words], a bit per row.  Word

@@ -195,4 +195,239 @@ __global__ __launch_bounds__(256, R <= 32 ? 4 : 2) void lista_support_kernel(Lis
     }
 }
 
+// r = y - Phi x over the support of the large-tile decoder's iterate (accumulator order with its masks, EpiIstaUpdateTiled), for
+// the next iteration's operand R.  A wavefront takes four rows, those of one float4 of the iterate (a quad): it collects the columns
+// whose float4 is not zero from the mask bytes, 64 at a time, and adds their multiples of Phi's columns (rows of PhiT, lane l
+// elements 8l to 8l + 7 of every 512 and MR % 8 of a last piece) to the four sums.  Coefficients are rounded to bf16 as in the
+// product over all columns.  The numbers of coefficients differ widely between rows, so the four wavefronts of a workgroup
+// share out the columns of a quad with more than kSupportOwn of them (13 104 rows, n = 11 744, 100 pieces a quad on average: a forward
+// 9.9 ms over all columns, 7.4 so).  A quad without any has r = y: nothing is written where R holds that already.
+//
+// What bounds it: with hardly any coefficient the masks, 16 us for 28 544 rows, n = 1824 (41 with every row of R written again, the
+// product over all columns 118); else the gather, 2 m bytes a column: 38 976 rows, n = 9744, m = 1024, 5 coefficients a row 142 us (790).
+// Wavefronts in flight count: with eight a CU, in the product's place, 19 and 189.
+struct ResidualSupportArgs {
+    const uint8_t* Mask; const f32x4* Xs; long long tiles_n;
+    const bf16_t* PhiT; int ldm;
+    const float* Y; long long ldY;
+    bf16_t* R;
+    uint8_t* Same;      // [quads] 1: R holds the quad's y (read from the second launch on: before it, it holds every row's)
+    long long rows;
+    int m, first;
+};
+constexpr int kSupportOwn = 64, kSupportList = 1024 + 128;
+template <int MR, int WAVES>
+struct ResidualSupportLds {
+    uint16_t lists[WAVES][kSupportList];
+    float part[WAVES][64 * MR];
+    int heavy[3];        // bit w: wavefront w's quad is shared; a word each for three rounds in turn
+};
+
+// Workgroup `block` of `blocks`, of WAVES wavefronts.
+template <int MR, int kSupportWaves>
+__device__ __forceinline__ void residual_support(const ResidualSupportArgs& a, ResidualSupportLds<MR, kSupportWaves>& l, long long block, long long blocks) {
+    constexpr int FULL = MR / 8, TAIL = MR % 8;
+    static_assert(TAIL == 0 || TAIL == 2 || TAIL == 4, "a lane's share of the last piece is one load");
+    auto& lists = l.lists;
+    auto& part = l.part;
+    auto& heavy = l.heavy;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint16_t* list = lists[wave];
+    const long long quads = (a.rows + 3) / 4, step = blocks * kSupportWaves;
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    auto column = [&](int k) { return k < 8 * FULL ? 512 * (k / 8) + 8 * lane + k % 8 : 512 * FULL + TAIL * lane + (k - 8 * FULL); };
+    // bit i: column 32 ct + 16 (lane & 1) + i of the quad, ct = ct0 + lane / 2
+    auto scan = [&](long long quad, long long ct0, long long ct1) {
+        const long long ct = ct0 + (lane >> 1);
+        if (ct >= ct1) return 0u;
+        const uint4 v = *(const uint4*)(a.Mask + ((quad >> 3) * a.tiles_n + ct) * 64 + (quad & 1) * 32 + (lane & 1) * 16);
+        const int g = (int)(quad & 7) >> 1;
+        auto four = [&](uint32_t w) { w = (w >> g) & 0x01010101u; return (w | w >> 7 | w >> 14 | w >> 21) & 15u; };
+        return four(v.x) | four(v.y) << 4 | four(v.z) << 8 | four(v.w) << 12;
+    };
+
+    if (threadIdx.x < 3) heavy[threadIdx.x] = 0;
+    __syncthreads();
+    int round = 0;
+    for (long long quad0 = block * kSupportWaves; quad0 < quads; quad0 += step, round = round == 2 ? 0 : round + 1) {
+        const long long own = quad0 + wave;
+        int pieces = 0;
+        if (own < quads) {
+            for (long long ct0 = 0; ct0 < a.tiles_n; ct0 += 32) pieces += __popc(scan(own, ct0, a.tiles_n));
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) pieces += __shfl_xor(pieces, o, 64);
+            pieces = __builtin_amdgcn_readfirstlane(pieces);
+            if (pieces > kSupportOwn && lane == 0) atomicOr(&heavy[round], 1 << wave);
+        }
+        // (the next round's word: its readers of two rounds ago passed the barrier of the last, and nobody sets it before this one)
+        if (threadIdx.x == 0) heavy[round == 2 ? 0 : round + 1] = 0;
+        __syncthreads();
+        const int shared = __builtin_amdgcn_readfirstlane(heavy[round]);
+
+        // job -1: this wavefront's own quad; then the shared ones, a share of the columns each
+        for (int job = -1; job < kSupportWaves; ++job) {
+            const bool alone = job < 0;
+            if (alone ? own >= quads || pieces > kSupportOwn : !(shared >> job & 1)) continue;
+            const long long quad = alone ? own : quad0 + job;
+            if (alone) {
+                const bool same = a.first || a.Same[quad] != 0;
+                if (lane == 0) a.Same[quad] = pieces == 0;
+                if (pieces == 0 && same) continue;
+            } else if (wave == job && lane == 0) a.Same[quad] = 0;
+            const long long share = (a.tiles_n + kSupportWaves - 1) / kSupportWaves;
+            const long long ct_lo = alone ? 0 : wave * share, ct_hi = alone ? a.tiles_n : ct_lo + share < a.tiles_n ? ct_lo + share : a.tiles_n;
+            const long long tile0 = (quad >> 3) * a.tiles_n;
+            const int g = (int)(quad & 7) >> 1, lh = (int)quad & 1;      // rows 8 g + 4 lh .. + 3 of the 32-row tile
+            float acc[4][MR];
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+#pragma unroll
+                for (int k = 0; k < MR; ++k) acc[r][k] = 0.f;
+
+            auto add = [&](int head, int c) {      // c <= 64 columns of the list
+                int col = 0;
+                u32x2 x = {0u, 0u};      // rows 0 | 1, 2 | 3
+                if (lane < c) {
+                    col = list[head + lane];
+                    const f32x4 v = a.Xs[(tile0 + (col >> 5)) * 256 + g * 64 + lh * 32 + (col & 31)];
+                    x = u32x2{f2bf_pk(v[0], v[1]), f2bf_pk(v[2], v[3])};
+                }
+                struct Col { u32x4 f[FULL]; uint32_t t[2]; };
+                auto load = [&](int e) {
+                    Col q;
+                    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                        (void*)(a.PhiT + (long long)__builtin_amdgcn_readlane(col, e) * a.ldm), 0, a.ldm * 2, kBufferFlags);
+#pragma unroll
+                    for (int k = 0; k < FULL; ++k) q.f[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, k * 1024, 0);
+                    if constexpr (TAIL == 4) {
+                        const u32x2 t = __builtin_amdgcn_raw_buffer_load_b64(rs, lane * 8, FULL * 1024, 0);
+                        q.t[0] = t[0]; q.t[1] = t[1];
+                    }
+                    if constexpr (TAIL == 2) q.t[0] = __builtin_amdgcn_raw_buffer_load_b32(rs, lane * 4, FULL * 1024, 0);
+                    return q;
+                };
+                auto pair = [&](const Col& p, const Col& q, int e) {
+                    uint32_t d[MR];      // element k of both columns
+                    auto two = [&](uint32_t dp, uint32_t dq, uint32_t& lo, uint32_t& hi) {
+                        lo = __builtin_amdgcn_perm(dq, dp, 0x05040100u);
+                        hi = __builtin_amdgcn_perm(dq, dp, 0x07060302u);
+                    };
+#pragma unroll
+                    for (int k = 0; k < FULL; ++k)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) two(p.f[k][i], q.f[k][i], d[8 * k + 2 * i], d[8 * k + 2 * i + 1]);
+#pragma unroll
+                    for (int i = 0; i < TAIL / 2; ++i) two(p.t[i], q.t[i], d[8 * FULL + 2 * i], d[8 * FULL + 2 * i + 1]);
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const uint32_t x0 = __builtin_amdgcn_readlane(x[r >> 1], e), x1 = __builtin_amdgcn_readlane(x[r >> 1], e + 1);
+                        const uint32_t xp = (r & 1) ? (x0 >> 16) | (x1 & 0xffff0000u) : (x0 & 0xffffu) | (x1 << 16);
+                        if ((xp & 0x7fff7fffu) == 0) continue;
+#pragma unroll
+                        for (int k = 0; k < MR; ++k)
+                            acc[r][k] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, d[k]), __builtin_bit_cast(bf16x2, xp), acc[r][k], false);
+                    }
+                };
+                for (int e = 0; e < c; e += 4) {
+                    const Col p = load(e), q = load(e + 1);
+                    if (e + 2 < c) {
+                        const Col p2 = load(e + 2), q2 = load(e + 3);
+                        pair(p, q, e);
+                        pair(p2, q2, e + 2);
+                    } else {
+                        pair(p, q, e);
+                    }
+                }
+            };
+
+            int cnt = 0;
+            for (long long ct0 = ct_lo; ct0 < ct_hi && (!alone || pieces); ct0 += 32) {
+                uint32_t bits = scan(quad, ct0, ct_hi);
+                const int c0 = (int)(ct0 + (lane >> 1)) * 32 + (lane & 1) * 16;
+                for (uint64_t some; (some = __builtin_amdgcn_ballot_w64(bits != 0)) != 0;) {
+                    if (bits) {
+                        list[cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u))] =
+                            (uint16_t)(c0 + __builtin_ctz(bits));
+                        bits &= bits - 1;
+                    }
+                    cnt += __popcll(some);
+                }
+                __builtin_amdgcn_wave_barrier();
+                const bool last = ct0 + 32 >= ct_hi;
+                int head = 0;
+                for (; cnt - head >= 64 || (last && head < cnt); head += 64) add(head, cnt - head < 64 ? cnt - head : 64);
+                if (head && head < cnt) {      // (fewer than 64 are left)
+                    const uint16_t v = list[head + lane];
+                    __builtin_amdgcn_wave_barrier();
+                    list[lane] = v;
+                    __builtin_amdgcn_wave_barrier();
+                }
+                cnt = head < cnt ? cnt - head : 0;
+            }
+
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const long long row = quad * 4 + r < a.rows ? quad * 4 + r : a.rows - 1;
+                const bool live = quad * 4 + r < a.rows;
+                const float* y = a.Y + row * a.ldY;
+                bf16_t* out = a.R + row * a.ldm;
+                if (alone) {
+                    auto store = [&](int k0, auto width) {      // elements k0 .. k0 + width - 1 of this lane
+                        constexpr int N = decltype(width)::value;
+                        const int c = column(k0);
+                        if (c >= a.ldm || !live) return;
+#pragma unroll
+                        for (int i = 0; i < N; i += 2)
+                            *(uint32_t*)(out + c + i) = f2bf_pk(c + i < a.m ? y[c + i] - acc[r][k0 + i] : 0.f, c + i + 1 < a.m ? y[c + i + 1] - acc[r][k0 + i + 1] : 0.f);
+                    };
+#pragma unroll
+                    for (int k = 0; k < FULL; ++k) store(8 * k, std::integral_constant<int, 8>{});
+                    if constexpr (TAIL > 0) store(8 * FULL, std::integral_constant<int, TAIL>{});
+                    continue;
+                }
+                __syncthreads();        // (uniform: every wavefront of the workgroup takes every shared job)
+#pragma unroll
+                for (int k = 0; k < MR; ++k) part[wave][column(k)] = acc[r][k];
+                __syncthreads();
+                for (int c = threadIdx.x * 2; live && c < a.ldm; c += 128 * kSupportWaves) {
+                    float s[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        float sum = part[0][c + e];
+#pragma unroll
+                        for (int v = 1; v < kSupportWaves; ++v) sum += part[v][c + e];
+                        s[e] = c + e < a.m ? y[c + e] - sum : 0.f;
+                    }
+                    *(uint32_t*)(out + c) = f2bf_pk(s[0], s[1]);
+                }
+            }
+        }
+    }
+}
+
+// As a launch of its own, beside the product over all columns.
+template <int MR>
+__global__ __launch_bounds__(256, MR > 12 ? 3 : 4) void residual_support_kernel(SupportRule rule, ResidualSupportArgs a) {
+    if (!rule.sparse()) return;
+    __shared__ ResidualSupportLds<MR, 4> l;
+    residual_support<MR, 4>(a, l, blockIdx.x, gridDim.x);
+}
+
+// The residual product over all columns on large tiles (Epi: EpiResidualTiled, or EpiStore<float> for its parts along K), or in its place the
+// one above (MR = 0: in another launch): a launch that returned at once beside it would cost a small iteration 3 %.  One workgroup per
+// CU either way.
+template <typename Epi, int MR>
+struct EpiResidualEither : Epi {
+    static constexpr bool kLate = true;       // (the rule's words come with the first stage)
+    static constexpr int kWaves = 8;
+    SupportRule rule;
+    ResidualSupportArgs s;
+    __device__ __forceinline__ void instead(void* lds) const {
+        if constexpr (MR > 0) {
+            const long long all = (long long)gridDim.x * gridDim.z, blocks = all < 256 ? all : 256, block = blockIdx.x + (long long)gridDim.x * blockIdx.z;
+            if (block < blocks) residual_support<MR, kWaves>(s, *(ResidualSupportLds<MR, kWaves>*)lds, block, blocks);
+        }
+    }
+};
+
 }  // namespace csat

@@ -991,3 +991,49 @@ def test_unrolled_decoder_over_the_support(heads, n_q, n, m, d, layers, options)
     Xb, Cb = decode(2, y=Yb)
     assert torch.equal(Xb.view(rows, n)[:-1], X.view(rows, n)[:-1]) and torch.equal(Cb.view(rows, d)[:-1], C.view(rows, d)[:-1])
     assert not Xb.view(rows, n)[-1].isfinite().all()
+
+
+# (n_q, n, m, iterations): m around the instances' 512, 640, 768 and 1024 and small ones (asked for); last groups of rows that are not whole;
+# the residual over all columns as one product and split along K; columns that are not whole tiles; more than 1024 columns
+RESIDUAL_SUPPORT_CASES = [(300, 600, 130, 3), (331, 1100, 513, 4), (130, 1500, 640, 3), (257, 1300, 641, 2), (1001, 2048, 768, 3), (90, 2111, 1000, 5),
+                          (258, 1280, 1024, 3)]
+
+
+@pytest.mark.parametrize("n_q,n,m,iters", RESIDUAL_SUPPORT_CASES)
+def test_residual_over_the_support(n_q, n, m, iters, options):
+    """The large-tile decoder with its residual over the non-zero coefficients: against the oracle, and against the product over all columns."""
+    w = _small("residual_support", B=1, H=3, n_q=n_q, n=n, d=64, m=m, dtype="bf16", iters=iters, seed=n)
+    Q, K, V = gen.make_qkv(w)
+    Phi = gen.make_workload_phi(w)
+    mu = _mu(Phi)
+    p = _problem(w, Q, K, V, Phi)
+    A, _ = p.attention(*p.measure())
+    first = np.abs(np.einsum("hqm,mn->hqn", to_np(A), Phi.astype(np.float64)))
+    lam = float(np.quantile(first, 0.985))
+    options("decoder", 1)
+    options("support", 2)
+    p.ws.fill_(0xFF)
+    C, _, X = p.forward(lam, mu, iters)
+    assert csat.csat_profile_decoder_kernel() == -1
+    ref = orc.forward(Q, K, V, Phi, lam, mu, iters)
+    assert 0.001 < float((ref["X"] != 0).mean()) < 0.1
+    assert_close("X", to_np(X), ref["X"], TOL["bf16"])
+    assert_close("C", to_np(C), ref["C"], TOL["bf16"])
+    p.ws.fill_(0xFF)
+    C2, _, X2 = p.forward(lam, mu, iters)
+    assert torch.equal(X, X2) and torch.equal(C, C2)
+    # the stage call has its measurement rows as the caller holds them
+    Xs, Cs = p.recover(A, lam, mu, iters)
+    options("support", 1)
+    C1, _, X1 = p.forward(lam, mu, iters)
+    X1s, C1s = p.recover(A, lam, mu, iters)
+    # the residual is the same up to its float sums, so that one in about 2^8 of its elements is rounded to bf16 the other way: 2^-8 * 2^-4
+    # of the residual, times what the threshold leaves of u (here up to 10)
+    for got, old in ((X, X1), (Xs, X1s), (C.float(), C1.float()), (Cs.float(), C1s.float())):
+        assert float((got - old).norm() / old.norm()) < 5e-3
+    # an infinite measurement reaches its own row only
+    Ab = A.clone()
+    Ab[2, n_q - 1, 1] = float("inf")
+    options("support", 2)
+    Xb, _ = p.recover(Ab, lam, mu, iters)
+    assert torch.equal(Xb.view(-1, n)[:-1], Xs.view(-1, n)[:-1]) and not Xb.view(-1, n)[-1].isfinite().all()

@@ -219,7 +219,8 @@ typedef enum {
     CSAT_OPT_SYNTHESIS = 13,       /* 1: the synthesis C = X V always as a product kernel behind the decoder; 2: that kernel always the GEMM over a transposed copy of V */
     CSAT_OPT_Y_LAYOUT = 14,        /* 1: A~ row-major between the attention kernel and the fused decoder for every shape */
     CSAT_OPT_SUPPORT = 15,         /* products over the support of a sparse iterate: 1 never; 2 wherever a kernel for them exists, whatever the density */
-    CSAT_OPT_COUNT = 16
+    CSAT_OPT_SCREEN = 16,          /* rows whose iterate is zero throughout left out of the decoder: 1 never; 2 wherever it applies, however many rows there are of them */
+    CSAT_OPT_COUNT = 17
 } csat_option;
 csat_status csat_set_option(void* ctx, int key, int value);
 

@@ -14,6 +14,7 @@
 #include "csat_attention_z.h"
 #include "csat_measure.h"
 #include "csat_support.h"
+#include "csat_screen.h"
 #include "csat_launch.h"
 #include "csat_peaks.h"
 
@@ -156,6 +157,11 @@ constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_st
 // The decoders' rule for products over the support of the iterate (csat_support.h), its words in the workspace's status block.
 int support_choice() { return (*tl_opt)[CSAT_OPT_SUPPORT]; }      // 1: never; 2: wherever a kernel exists
 constexpr int kSupportWord = 8;
+int screen_choice() { return (*tl_opt)[CSAT_OPT_SCREEN]; }        // 1: never; 2: wherever it applies
+constexpr int kScreenWord = 16, kScreenSampleWord = 24;
+// Of the sample's rows, the most that may stay: above about half, what is left out is worth less than finding it (and at most half the rows fit
+// packed): 13 104 rows, n = 11 744, m = 1024, 45 % left: 9.8 -> 7.5 ms.
+constexpr double kScreenShare = 0.45;
 
 // Largest m (in 32-wide tiles) the fused decoder takes.  Its residual accumulators need 16 registers per tile: up to
 // 13 tiles they fit next to the operands of the two-chunk schedule; 14 to 16 tiles fill the accumulator file and run
@@ -990,6 +996,18 @@ csat_status launch_ista_resident(const csat_dims& d, const Workspace& w, IstaRes
     return CSAT_ERR_SHAPE;
 }
 
+hipError_t launch_fused_variant(int MT, int variant, const IstaFusedArgs& a, unsigned grid, hipStream_t st) {
+    switch (MT) {
+#define CSAT_FUSED_CASE(N) case N: return ista_fused_launch_mt##N(variant, a, grid, st);
+        CSAT_FUSED_CASE(1) CSAT_FUSED_CASE(2) CSAT_FUSED_CASE(3) CSAT_FUSED_CASE(4)
+        CSAT_FUSED_CASE(5) CSAT_FUSED_CASE(6) CSAT_FUSED_CASE(7) CSAT_FUSED_CASE(8)
+        CSAT_FUSED_CASE(9) CSAT_FUSED_CASE(10) CSAT_FUSED_CASE(11) CSAT_FUSED_CASE(12)
+        CSAT_FUSED_CASE(13) CSAT_FUSED_CASE(14) CSAT_FUSED_CASE(15) CSAT_FUSED_CASE(16)
+#undef CSAT_FUSED_CASE
+    }
+    return hipErrorInvalidValue;
+}
+
 csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipStream_t st) {
     const int cus = cu_count();
     const int variant = fused_variant(MT, rows_pad, a.nct, a.iters);
@@ -1009,6 +1027,11 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     // at most once; see the kernel), unless a segment count is asked for.
     a.tape = 0;
     if (variant >= 3 && variant != 6 && a.groups > cus) a.tape = cus;
+    if (a.packed) {      // (its rows, and so its groups and shares, are the device's)
+        a.segs = 1;
+        HIP_TRY(launch_fused_variant(MT, variant, a, (unsigned)(a.groups < cus ? a.groups : cus), st));
+        return CSAT_OK;
+    }
     if (const int v = (*tl_opt)[CSAT_OPT_FUSED_SEGMENTS]; v >= 1 && v <= a.iters) { a.segs = v; a.tape = 0; }
     else if (v < 0 && variant >= 3) a.tape = -v < a.groups ? -v : a.groups;       // (tests: shares on small launches)
     if ((*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] != 0) a.spin_limit = (*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT] < 0 ? 0 : (*tl_opt)[CSAT_OPT_FUSED_SPIN_LIMIT];
@@ -1017,15 +1040,8 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
     const unsigned grid = (unsigned)(variant == 6 ? a.groups * a.tile_split : units < cus ? units : cus);
     *tl_decoder_kernel = variant;
     if (variant == 6) tl_forms[CSAT_FORM_DECODER_MEMBERS] = a.tile_split;
-    switch (MT) {
-#define CSAT_FUSED_CASE(N) case N: HIP_TRY(ista_fused_launch_mt##N(variant, a, grid, st)); return CSAT_OK;
-        CSAT_FUSED_CASE(1) CSAT_FUSED_CASE(2) CSAT_FUSED_CASE(3) CSAT_FUSED_CASE(4)
-        CSAT_FUSED_CASE(5) CSAT_FUSED_CASE(6) CSAT_FUSED_CASE(7) CSAT_FUSED_CASE(8)
-        CSAT_FUSED_CASE(9) CSAT_FUSED_CASE(10) CSAT_FUSED_CASE(11) CSAT_FUSED_CASE(12)
-        CSAT_FUSED_CASE(13) CSAT_FUSED_CASE(14) CSAT_FUSED_CASE(15) CSAT_FUSED_CASE(16)
-#undef CSAT_FUSED_CASE
-    }
-    return CSAT_ERR_SHAPE;
+    HIP_TRY(launch_fused_variant(MT, variant, a, grid, st));
+    return CSAT_OK;
 }
 
 // Clears the rule's words.
@@ -1035,10 +1051,10 @@ csat_status support_begin(const Workspace& w, hipStream_t st) {
     return CSAT_OK;
 }
 // Counts what the first threshold left (its mask bytes, whole 16-byte pieces).
-csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st) {
+csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st, const uint32_t* screen = nullptr, long long rows = 0) {
     const long long chunks = bytes / 16;
     hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
-                       (uint32_t*)w.Status + kSupportWord);
+                       (uint32_t*)w.Status + kSupportWord, screen, rows);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
@@ -1065,13 +1081,102 @@ double residual_support_limit(const csat_dims& d, long long rows) {
     return rows / 4.0 * d.n / (residual_support_apart(d, rows) ? 64 : rows >= 12288 ? 128 : 270);
 }
 
+// Rows without a coefficient left out of the decoder, the others packed (csat_screen.h).  The packed rows take half of what all rows
+// have, so at most half of them may stay; their y goes into the other half of the iterate's buffer, the lists into K's transposed copy.
+struct ScreenPlan {
+    const uint32_t* words = nullptr;      // null: not for this call
+    const int* Place = nullptr;
+    const float* Y = nullptr; long long ldY = 0;
+};
+// The sample and the launches that return at once take 40 to 60 us: not where the decoder takes less than about 2 ms (its operations at
+// 1 PFLOP/s, 0.12 in float).  X where the caller wants it stays with the decoder over all rows.
+bool screen_applies(const csat_dims& d, const Workspace& w, const void* X, const void* V, const void* C, int iters) {
+    const long long rows = (long long)d.B * d.H * d.n_q, BH = (long long)d.B * d.H;
+    if (screen_choice() == 1 || X || !V || !C || iters < 2 || rows < 1024 || gemm_choice() == 1) return false;
+    if (BH * d.d * w.ldn * (long long)esize(d.dtype) < 10 * rows + 16384) return false;
+    if (d.dtype == CSAT_BF16) {
+        if (!w.fused && (w.ldm < 128 || d.n < 128)) return false;
+        if (w.fused && (decoder_is_resident(w) || !decoder_options_free() || d.n < 128)) return false;
+        const int v = w.fused ? fused_variant(w.MT, w.rows_pad, w.nct, iters) : 3;
+        if (v != 3 && v != 4) return false;
+    } else if (decoder_is_resident_f32(d, w, iters) || (d.m <= 32 && d.n <= 128)) {
+        return false;
+    }
+    return screen_choice() == 2 || 4.0 * iters * rows * d.n * d.m > (d.dtype == CSAT_BF16 ? 2e12 : 2.4e11);
+}
+template <typename T>
+csat_status screen_rows(const Workspace& w, ScreenRowsArgs a, hipStream_t st) {
+    hipLaunchKernelGGL(screen_rows_kernel, dim3((unsigned)std::min<long long>((a.rows + 3) / 4, 8ll * cu_count())), dim3(256), 0, st, a);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+template <typename T>
+csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const float* Y, long long ldY, bool y_tiled, float mu, float theta, ScreenPlan* plan, hipStream_t st) {
+    constexpr bool kBf16 = sizeof(T) == 2;
+    const long long rows = (long long)d.B * d.H * d.n_q, stay_bytes = round_up(rows, 16), blocks = (rows + 1023) / 1024;
+    char* at = w.KT;
+    uint8_t* stay = (uint8_t*)at;
+    int* counts = (int*)(at += round_up(stay_bytes, 256));
+    int* Place = (int*)(at += round_up(blocks * 4, 256));
+    int* List = (int*)(at += round_up(rows * 4, 256));
+    uint32_t *sample_words = (uint32_t*)w.Status + kScreenSampleWord, *words = (uint32_t*)w.Status + kScreenWord;
+    Timed tm(w, CSAT_K_LAYOUT, st);
+    hipLaunchKernelGGL(screen_begin_kernel, dim3((unsigned)std::min<long long>((stay_bytes / 4 + 255) / 256, cu_count())), dim3(256), 0, st, sample_words, (uint32_t*)stay, stay_bytes / 4);
+    HIP_TRY(hipGetLastError());
+    // the fused decoder has neither operand of the product; the others have the first residual
+    if (w.fused) CSAT_TRY(transpose_pack<T>(Phi, (T*)w.PhiT, w.ldm, 1, d.m, d.n, st));
+    const long long stride = std::max<long long>(1, rows / std::max<long long>(512, rows / 16)), sample = rows / stride;
+    ScreenRowsArgs ra{nullptr, nullptr, sample, (int)stride, Y, ldY, y_tiled, nullptr, 0, 0, w.R, w.ldm, kBf16, d.m};
+    if (w.fused) CSAT_TRY(screen_rows<T>(w, ra, st));
+    auto product = [&](long long M, long long lda, const uint32_t* off) -> csat_status {
+        GemmArgs g{w.R, lda, 0, w.PhiT, w.ldm, 0, (int)M, d.n, d.m, 0};
+        const EpiScreen e{stay, mu, theta * kScreenMargin, M, d.n, {off}};
+        if constexpr (kBf16) {
+            g.K = (int)round_up(g.K, 64);
+            return launch_gemm_big(g, d.n, 1, e, st);
+        } else {
+            return launch_gemm_f32(g, d.n, 1, e, st);
+        }
+    };
+    CSAT_TRY(product(sample, w.fused ? w.ldm : w.ldm * stride, nullptr));
+    hipLaunchKernelGGL(screen_decide_kernel, dim3(1), dim3(1024), 0, st, sample_words, (uint32_t*)stay, (int)sample, screen_choice() == 2 ? (int)sample : (int)(sample * kScreenShare));
+    HIP_TRY(hipGetLastError());
+    const SupportRule on{sample_words, 0};
+    if (w.fused) {
+        ra.words = sample_words;
+        ra.rows = rows;
+        ra.stride = 1;
+        CSAT_TRY(screen_rows<T>(w, ra, st));
+    }
+    CSAT_TRY(product(rows, w.ldm, sample_words));
+    hipLaunchKernelGGL(screen_count_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, (const uint32_t*)stay, rows, counts);
+    HIP_TRY(hipGetLastError());
+    hipLaunchKernelGGL(screen_place_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, words, (const uint32_t*)stay, rows, counts, Place, List, (int)(rows / 2 - 256));
+    HIP_TRY(hipGetLastError());
+    float* Yp = w.Xs + w.rows_pad / 2 * w.ldn;
+    CSAT_TRY(screen_rows<T>(w, ScreenRowsArgs{words, List, rows, 1, Y, ldY, y_tiled, Yp, w.ldy, y_tiled, w.fused ? nullptr : w.R, w.fused ? 0 : w.ldm, kBf16, d.m}, st));
+    *plan = ScreenPlan{words, Place, Yp, w.ldy};
+    return CSAT_OK;
+}
+// C of the packed rows, and zeros for the others (behind the synthesis over all rows, which writes C too)
+template <typename T>
+csat_status screen_finish(const csat_dims& d, const Workspace& w, const ScreenPlan& plan, const T* V, T* C, hipStream_t st) {
+    if (!plan.words) return CSAT_OK;
+    const long long rows = (long long)d.B * d.H * d.n_q;
+    Timed tm(w, CSAT_K_SYNTHESIS, st);
+    hipLaunchKernelGGL((screen_finish_kernel<T>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, plan.words, w.Status, plan.Place,
+                       sizeof(T) == 2 ? (const T*)w.Xb : (const T*)w.Xs, w.ldn, V, C, rows, d.n_q, d.n, d.d);
+    HIP_TRY(hipGetLastError());
+    return CSAT_OK;
+}
+
 // ISTA on rows of Y (float, leading dimension ldY).  Generic decoder: w.R must already hold Y in
 // operand layout (the first residual, since x^0 = 0); the final state is left in w.Xs (float mode)
 // or w.Xb (bf16 mode).  Fused decoder (bf16, m <= 512): Y must be w.A-style rows with
 // ldY == w.ldy and zero pads; the final iterate is left in w.Xb.
 template <typename T>
 csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const float* Y, long long ldY, float lambda, float mu,
-                     int iters, float* Xout, hipStream_t st, const T* Vsyn = nullptr, T* Csyn = nullptr, bool y_tiled = false) {
+                     int iters, float* Xout, hipStream_t st, const T* Vsyn = nullptr, T* Csyn = nullptr, bool y_tiled = false, const ScreenPlan& plan = {}) {
     constexpr bool kBf16 = sizeof(T) == 2;
     const long long rows = (long long)d.B * d.H * d.n_q;
     const float theta = mu * lambda;
@@ -1126,6 +1231,14 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         if (!syn && !synthesis_is_direct<T>(d) && w.ldn > (long long)w.nct * 32) CSAT_TRY(fill_zero(w.Xb, (size_t)rows * w.ldn * 2, st));
         {
             Timed tm(w, CSAT_K_UPDATE, st);
+            a.screen = plan.words;
+            if (plan.words) {      // one of the two returns at once
+                IstaFusedArgs p = a;
+                p.packed = 1;
+                p.Y = plan.Y;
+                p.Vf = nullptr; p.C = nullptr; p.Xb = w.Xb;
+                CSAT_TRY(launch_ista_fused(w.MT, p, w.rows_pad, st));
+            }
             CSAT_TRY(launch_ista_fused(w.MT, a, w.rows_pad, st));
         }
         // a decoder that gave up leaves part of the iterate unwritten: make that visible in the outputs
@@ -1137,6 +1250,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         return CSAT_OK;
     }
     // large tiles throughout: the iterate has its masks
+    const size_t support_same = plan.words ? (size_t)(round_up(rows, 256) * 9 + 8192 + rows / 128) / 256 * 256 : 0;      // (behind the lists)
     SupportRule rule;
     if constexpr (kBf16) {
         const GemmArgs gr{nullptr, w.ldn, 0, nullptr, w.ldn, 0, (int)rows, d.m, d.n, 0}, gu{nullptr, w.ldm, 0, nullptr, w.ldm, 0, (int)rows, d.n, d.m, 0};
@@ -1151,8 +1265,9 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         if (t > 0) {   // residual r = y - Phi x
             GemmArgs g{kBf16 ? (const void*)w.Xb : (const void*)w.Xs, w.ldn, 0, w.PhiP, w.ldn, 0, 0, d.m, d.n, 0};
             g.M = (int)rows;
+            g.screen = plan.words;
             Timed tm(w, CSAT_K_RESIDUAL, st);
-            const ResidualSupportArgs sa{w.Mask, (const f32x4*)w.Xs, w.ldn / 32, (const bf16_t*)w.PhiT, (int)w.ldm, Y, ldY, (bf16_t*)w.R, (uint8_t*)w.KT, rows, d.m, t == 1};
+            const ResidualSupportArgs sa{w.Mask, (const f32x4*)w.Xs, w.ldn / 32, (const bf16_t*)w.PhiT, (int)w.ldm, Y, ldY, (bf16_t*)w.R, (uint8_t*)w.KT + support_same, rows, d.m, t == 1, plan.words, plan.Y, plan.ldY};
             auto launch_residual = [&](const auto& epi, const GemmArgs& ga, int parts) -> csat_status {
                 using Epi = std::decay_t<decltype(epi)>;
                 if (!rule.ctl) return launch_gemm_big(ga, w.ldm, parts, epi, st);
@@ -1169,27 +1284,28 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
                 if (regs <= 12) return launch(std::integral_constant<int, 12>{});
                 return launch(std::integral_constant<int, 16>{});
             };
-            if (rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st));
+            if (rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, plan.words, rows));
             if (w.split > 1 && use_big_gemm<T>(g, w.ldm)) {     // partial products along K, then r = y - their sum
                 GemmArgs gs = g;
                 gs.K = (int)(w.ldn / w.split);
                 gs.strideA = gs.strideB = gs.K;
-                const EpiStore<float> ep{w.SplitP, w.ldm, rows * w.ldm, nullptr, 0, 0, 1.f, (int)rows, d.m};
+                const EpiStorePart ep{{w.SplitP, w.ldm, rows * w.ldm, nullptr, 0, 0, 1.f, (int)rows, d.m}};
                 CSAT_TRY(launch_residual(ep, gs, w.split));
                 const long long total = rows * w.ldm;
                 hipLaunchKernelGGL(residual_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Y, ldY,
-                                   w.SplitP, w.split, rows * w.ldm, (bf16_t*)w.R, w.ldm, rows, d.m, rule);
+                                   w.SplitP, w.split, rows * w.ldm, (bf16_t*)w.R, w.ldm, rows, d.m, rule, plan.words, plan.Y, plan.ldY);
                 HIP_TRY(hipGetLastError());
             } else if (use_big_gemm<T>(g, w.ldm) && ldY % 4 == 0 && aligned16(Y)) {
-                const EpiResidualTiled er{Y, ldY, (bf16_t*)w.R, w.ldm, rows, d.m};
+                const EpiResidualTiled er{Y, ldY, (bf16_t*)w.R, w.ldm, rows, d.m, plan.Y, plan.ldY};
                 g.K = (int)round_up(g.K, 64);
                 CSAT_TRY(launch_residual(er, g, 1));
             } else {
-                EpiResidual<T> er{Y, ldY, (T*)w.R, w.ldm, rows, d.m};
+                EpiResidual<T> er{Y, ldY, (T*)w.R, w.ldm, rows, d.m, plan.Y, plan.ldY};
                 CSAT_TRY((decoder_gemm<T>(g, w.ldm, 1, er, st)));
             }
         }
         GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
+        g.screen = plan.words;
         Timed tm(w, CSAT_K_UPDATE, st);
         if (use_big_gemm<T>(g, w.ldn)) {   // large-tile kernel: state in accumulator order
             EpiIstaUpdateTiled eu{(f32x4*)w.Xs, w.ldn / 32, w.Mask, w.Xb, w.ldn, (t == iters - 1) ? Xout : nullptr,
@@ -1282,9 +1398,13 @@ csat_status recover_t(const csat_dims& d, const Workspace& w, const float* Y, co
         else if (!decoder_is_resident_f32(d, w, iters)) CSAT_TRY((pack_rows<float, T>(Y, d.m, (T*)w.R, w.ldm, rows, d.m, st)));
         if (want_c && !synthesis_is_direct<T>(d)) CSAT_TRY(transpose_pack<T>((const T*)V, (T*)w.VT, w.ldn, BH, d.n, d.d, st));
     }
-    CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, w.fused ? w.A : Y, w.fused ? w.ldy : (long long)d.m, lambda, mu, iters, X, st));
-    if (want_c) CSAT_TRY(run_synthesis<T>(d, w, (T*)C, st, (const T*)V));
-    return CSAT_OK;
+    ScreenPlan plan;
+    const float* y = w.fused ? w.A : Y;
+    const long long ld = w.fused ? w.ldy : (long long)d.m;
+    if (want_c && screen_applies(d, w, X, V, C, iters)) CSAT_TRY(screen<T>(d, w, (const T*)Phi, y, ld, false, mu, mu * lambda, &plan, st));
+    CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, y, ld, lambda, mu, iters, X, st, nullptr, nullptr, false, plan));
+    if (want_c) CSAT_TRY(run_synthesis<T>(d, w, (T*)C, st, (const T*)V, SupportRule{plan.words, 0}));
+    return screen_finish<T>(d, w, plan, (const T*)V, (T*)C, st);
 }
 
 template <typename T>
@@ -1329,9 +1449,11 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
         if (Z) HIP_TRY(hipMemcpyAsync(Z, C, (size_t)d.B * d.H * d.n_q * d.d * sizeof(T), hipMemcpyDeviceToDevice, st));
         return CSAT_OK;
     }
-    if (syn) return run_ista<T>(d, w, (const T*)Phi, w.A, w.ldy, lambda, mu, iters, X, st, (const T*)V, (T*)C, y_tiled);
-    CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, w.A, w.ldy, lambda, mu, iters, X, st, nullptr, nullptr, y_tiled));
-    return run_synthesis<T>(d, w, (T*)C, st, (const T*)V);
+    ScreenPlan plan;
+    if (screen_applies(d, w, X, V, C, iters)) CSAT_TRY(screen<T>(d, w, (const T*)Phi, w.A, w.ldy, y_tiled, mu, mu * lambda, &plan, st));
+    CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, w.A, w.ldy, lambda, mu, iters, X, st, syn ? (const T*)V : nullptr, syn ? (T*)C : nullptr, y_tiled, plan));
+    if (!syn) CSAT_TRY(run_synthesis<T>(d, w, (T*)C, st, (const T*)V, SupportRule{plan.words, 0}));
+    return screen_finish<T>(d, w, plan, (const T*)V, (T*)C, st);
 }
 
 // Column-wise decode (n_q == n): the decoder's problems are the d feature columns of Z per head.

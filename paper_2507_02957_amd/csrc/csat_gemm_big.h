@@ -60,6 +60,9 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     static_assert(BLOCKS % S::kWaves == 0, "requests must divide evenly over the wavefronts");
     static_assert(NGK == 2 || NGK == 4, "KS is 32 or 64");
     extern __shared__ uint4 lds[];
+    u32x4 packed{1u, 0u, 0u, 0u};
+    if constexpr (has_screen<Epi>::value)
+        packed = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void*)g.screen, 0, g.screen ? 16 : 0, kBufferFlags), 0, 0, 0);
     uint2 words{0u, 0u};
     if constexpr (has_late_rule<Epi>::value) words = epi.rule.words();      // (asked for here, waited for with the first stage)
     else if constexpr (has_rule<Epi>::value) {
@@ -159,6 +162,18 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
     if constexpr (has_acc_init<Epi>::value) epi.template init<TN>(row0 + wm * 64, col0 + wn * (32 * TN), lane, acc);
 
+    // (asked for at the top: here the words have come while the addresses were formed)
+    if constexpr (has_screen<Epi>::value) {
+        if (g.screen && __builtin_amdgcn_readfirstlane(packed[0]) == 0) {
+            if (row0 >= (long long)(uint32_t)__builtin_amdgcn_readfirstlane(packed[2])) {
+                if constexpr (has_late_rule<Epi>::value) {      // (the kernel in its place shares out the rows in its own way)
+                    if (epi.rule.sparse(words)) epi.instead(lds);
+                }
+                return;
+            }
+            epi.packed();
+        }
+    }
     stage(0, 0);
     typename TilePre<Epi>::type pre = tile_begin<TN>(epi, row0 + wm * 64, col0 + wn * (32 * TN), lane);
     __builtin_amdgcn_s_waitcnt(0);

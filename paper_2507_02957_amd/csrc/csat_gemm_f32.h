@@ -63,6 +63,12 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
     const int slot = blockIdx.x >> 3;
     const long long row0 = ((long long)(slot / g.raster) * 8 + (blockIdx.x & 7)) * BM, col0 = (long long)(slot % g.raster) * BN;
     if (row0 >= g.M) return;
+    if constexpr (has_rule<Epi>::value) {
+        if (epi.rule.sparse()) return;
+    }
+    u32x4 packed{1u, 0u, 0u, 0u};
+    if constexpr (has_screen<Epi>::value)
+        packed = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void*)g.screen, 0, g.screen ? 16 : 0, kBufferFlags), 0, 0, 0);
     const float* A = (const float*)g.A + (long long)z * g.strideA;
     const float* Bt = (const float*)g.Bt + (long long)z * g.strideB;
     const int kchunks = (g.K + 3) / 4, ksteps = (kchunks + 7) / 8;
@@ -108,6 +114,12 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
     };
     clear();
     load_global(0);
+    if constexpr (has_screen<Epi>::value) {
+        if (g.screen && __builtin_amdgcn_readfirstlane(packed[0]) == 0) {
+            if (row0 >= (long long)(uint32_t)__builtin_amdgcn_readfirstlane(packed[2])) return;
+            epi.packed();
+        }
+    }
     for (int ks = 0; ks < ksteps; ++ks) {
 #pragma unroll
         for (int i = 0; i < RA; ++i) store_row(ra[i], sA, PLANE_A, lrow + 32 * i);

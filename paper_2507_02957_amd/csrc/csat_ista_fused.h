@@ -68,6 +68,10 @@ struct IstaFusedArgs {
     // residual, [tile][member][iteration parity][MT][4][64] float4.  sync: [2 + 2 per workgroup] then, the parts' flags.
     int tile_split;
     f32x4* xchg;
+    // Two-chunk kernel only: rows packed on the device (csat_screen.h).  The launch runs where words[0] == 0 if `packed`, with words[2]
+    // rows, and where it does not if not.
+    const uint32_t* screen;
+    int packed;
     int state_stream;      // one-chunk schedule: the iterate's loads and stores carry the non-temporal hint
 };
 

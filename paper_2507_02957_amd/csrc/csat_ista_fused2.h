@@ -76,6 +76,14 @@ constexpr int fused2_ahead_loads(int q, int LA, int G, int NF, int NG, int NP) {
 template <int MT, bool SPARSE>
 __global__ __launch_bounds__(256, 1) void ista_fused2_kernel(IstaFusedArgs a) {
     extern __shared__ uint4 lds[];
+    if (a.screen) {
+        if ((a.screen[0] == 0) != (a.packed != 0)) return;
+        if (a.packed) {
+            a.rows = (long long)__builtin_amdgcn_readfirstlane((int)a.screen[2]);
+            a.groups = (int)((a.rows + 127) / 128);
+            a.tape = a.groups > (int)gridDim.x ? (int)gridDim.x : 0;
+        }
+    }
     constexpr int SETF = ista_fused_set_frags(MT), FW = SETF / 4;   // fragments per chunk, per wavefront
     constexpr int HALF = ista_fused2_chunk_bytes(MT);   // bytes of one packed chunk in LDS
     constexpr int SHIFT = CSAT_FUSED2_SLAB_SHIFT;

@@ -77,6 +77,7 @@ struct GemmArgs {
     int a_kwrap;   // > 0: A has only this many 16-byte chunks of K per row and is re-read cyclically
                    // (A' = [A | A | ...]); used to contract Q against a [hi | lo] split operand
     int raster = 0;   // large-tile kernel only: how the 1-D grid walks the tiles (see csat_gemm_big.h)
+    const uint32_t* screen = nullptr;   // rows packed on the device (csat_screen.h), for epilogues with kScreen: words, or null
 };
 constexpr int kRasterStreamA = 64;   // flag in GemmArgs::raster: the A rows are loaded with the non-temporal hint
 
@@ -332,6 +333,9 @@ struct EpiResidual {
     const float* Y; long long ldY;
     TO* R; long long ldR;
     long long M; int N;
+    const float* Yp = nullptr; long long ldYp = 0;      // y where the rows are packed
+    static constexpr bool kScreen = true;
+    __device__ __forceinline__ void packed() { Y = Yp; ldY = ldYp; }
     __device__ __forceinline__ void operator()(int, long long r, long long c, float v) const {
         if (r >= M || c >= ldR) return;
         float out = (c < N) ? Y[r * ldY + c] - v : 0.f;
@@ -364,6 +368,8 @@ struct EpiIstaUpdate {
     float* Xo;
     float mu, theta;
     long long M; int N; int first;
+    static constexpr bool kScreen = true;
+    __device__ __forceinline__ void packed() {}
     __device__ __forceinline__ void operator()(int, long long r, long long c, float v) const {
         if (r >= M || c >= ldS) return;
         float x = 0.f;
@@ -478,6 +484,9 @@ struct EpiResidualTiled {
     const float* Y; long long ldY;
     bf16_t* R; long long ldR;
     long long M; int N;
+    const float* Yp = nullptr; long long ldYp = 0;      // y where the rows are packed
+    static constexpr bool kScreen = true;
+    __device__ __forceinline__ void packed() { Y = Yp; ldY = ldYp; }
     __device__ __forceinline__ Pre begin(long long, long long, int) const { return {}; }
     __device__ __forceinline__ void half(int, long long r0, long long c0w, int lane, const f32x16 (&acc)[4], char* stage,
                                          const Pre&) const {
@@ -532,6 +541,8 @@ struct EpiIstaUpdateTiled {
     float* Xo;
     float mu, theta;
     long long M; int N; int first;
+    static constexpr bool kScreen = true;
+    __device__ __forceinline__ void packed() {}
     SupportRule support;               // where it says so, nothing reads the bf16 copy of this iterate, and it is not written
     __device__ __forceinline__ int live_tiles(long long r0, long long c0w) const {
         if (r0 >= M || c0w >= ldS) return 0;
@@ -770,7 +781,7 @@ struct EpiIstaUpdateTiled {
 // accumulators start from W = B y (stored in accumulator order by the first layer, loaded before the
 // main loop), so the epilogue is the ISTA one with mu = 1 and this layer's threshold.
 struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
-    static constexpr bool kAccInit = true, kRule = true;
+    static constexpr bool kAccInit = true, kRule = true, kScreen = false;
     const f32x4* W;
     SupportRule rule;
     template <int TN>
@@ -797,6 +808,7 @@ struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
 // in accumulator order: tile (row tile, column tile) of 32 x 32 is 256 float4, [g][lane] = rows 8g + 4*lh .. +3 of column li, as
 // the sparse iterate.
 struct EpiListaFirstTiled : EpiIstaUpdateTiled {
+    static constexpr bool kScreen = false;
     f32x4* W;
     template <int TN>
     __device__ __forceinline__ void keep(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN]) const {
@@ -828,6 +840,8 @@ struct EpiListaFirstTiled : EpiIstaUpdateTiled {
 
 template <typename E, typename = void> struct has_rule : std::false_type {};
 template <typename E> struct has_rule<E, std::enable_if_t<E::kRule>> : std::true_type {};
+template <typename E, typename = void> struct has_screen : std::false_type {};
+template <typename E> struct has_screen<E, std::enable_if_t<E::kScreen>> : std::true_type {};
 template <typename E, typename = void> struct has_late_rule : std::false_type {};
 template <typename E> struct has_late_rule<E, std::enable_if_t<E::kLate>> : std::true_type {};
 template <typename E, typename = void> struct has_acc_init : std::false_type {};
@@ -936,8 +950,14 @@ __global__ void transpose_cast_kernel(const float* src, TO* dst, int R, int Cc) 
 // P[s] [rows, ldR] (float): R [rows, ldR] in bf16 with zero pads.  One thread per element; the sum
 // runs in a fixed order, so the result does not depend on how the partial launches were scheduled.
 static __global__ void residual_reduce_kernel(const float* Y, long long ldY, const float* P, int S, long long strideP,
-                                       bf16_t* R, long long ldR, long long rows, int m, SupportRule rule) {
+                                       bf16_t* R, long long ldR, long long rows, int m, SupportRule rule, const uint32_t* screen,
+                                       const float* Yp, long long ldYp) {
     if (rule.sparse()) return;
+    if (screen && screen[0] == 0) {      // packed rows
+        rows = screen[2];
+        Y = Yp;
+        ldY = ldYp;
+    }
     const long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= rows * ldR) return;
     const long long r = idx / ldR;

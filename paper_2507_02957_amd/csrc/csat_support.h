@@ -11,8 +11,15 @@
 namespace csat {
 
 // Adds the non-zero float4 that the mask bytes name to ctl[0].
-static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* mask, long long chunks, uint32_t* ctl) {
+// (packed rows, csat_screen.h: of their 32-row tiles, the number scaled to all rows, which the limit is for)
+static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* mask, long long chunks, uint32_t* ctl, const uint32_t* screen, long long rows) {
     uint32_t n = 0;
+    float scale = 1.f;
+    if (screen && screen[0] == 0) {
+        const long long left = screen[2];
+        chunks = chunks / ((rows + 31) / 32) * ((left + 31) / 32);
+        scale = left > 0 ? (float)rows / left : 0.f;
+    }
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < chunks; i += (long long)gridDim.x * 256) {
         const uint4 v = mask[i];
         n += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
@@ -22,7 +29,7 @@ static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* 
     __shared__ uint32_t part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(ctl, part[0] + part[1] + part[2] + part[3]);
+    if (threadIdx.x == 0) atomicAdd(ctl, (uint32_t)((part[0] + part[1] + part[2] + part[3]) * scale));
 }
 
 // DT[j][i] = D[i][j], both [n, ld] with zero pads, 64 x 64 tiles through LDS.
@@ -214,6 +221,7 @@ struct ResidualSupportArgs {
     uint8_t* Same;      // [quads] 1: R holds the quad's y (read from the second launch on: before it, it holds every row's)
     long long rows;
     int m, first;
+    const uint32_t* screen = nullptr; const float* Yp = nullptr; long long ldYp = 0;      // packed rows (csat_screen.h) and their y
 };
 constexpr int kSupportOwn = 64, kSupportList = 1024 + 128;
 template <int MR, int WAVES>
@@ -225,12 +233,17 @@ struct ResidualSupportLds {
 
 // Workgroup `block` of `blocks`, of WAVES wavefronts.
 template <int MR, int kSupportWaves>
-__device__ __forceinline__ void residual_support(const ResidualSupportArgs& a, ResidualSupportLds<MR, kSupportWaves>& l, long long block, long long blocks) {
+__device__ __forceinline__ void residual_support(ResidualSupportArgs a, ResidualSupportLds<MR, kSupportWaves>& l, long long block, long long blocks) {
     constexpr int FULL = MR / 8, TAIL = MR % 8;
     static_assert(TAIL == 0 || TAIL == 2 || TAIL == 4, "a lane's share of the last piece is one load");
     auto& lists = l.lists;
     auto& part = l.part;
     auto& heavy = l.heavy;
+    if (a.screen && a.screen[0] == 0) {
+        a.rows = a.screen[2];
+        a.Y = a.Yp;
+        a.ldY = a.ldYp;
+    }
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     uint16_t* list = lists[wave];
     const long long quads = (a.rows + 3) / 4, step = blocks * kSupportWaves;
@@ -413,9 +426,13 @@ __global__ __launch_bounds__(256, MR > 12 ? 3 : 4) void residual_support_kernel(
     residual_support<MR, 4>(a, l, blockIdx.x, gridDim.x);
 }
 
-// The residual product over all columns on large tiles (Epi: EpiResidualTiled, or EpiStore<float> for its parts along K), or in its place the
+// The residual product over all columns on large tiles (Epi: EpiResidualTiled, or EpiStorePart for its parts along K), or in its place the
 // one above (MR = 0: in another launch): a launch that returned at once beside it would cost a small iteration 3 %.  One workgroup per
 // CU either way.
+struct EpiStorePart : EpiStore<float> {
+    static constexpr bool kScreen = true;
+    __device__ __forceinline__ void packed() {}
+};
 template <typename Epi, int MR>
 struct EpiResidualEither : Epi {
     static constexpr bool kLate = true;       // (the rule's words come with the first stage)

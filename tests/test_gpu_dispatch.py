@@ -1037,3 +1037,61 @@ def test_residual_over_the_support(n_q, n, m, iters, options):
     options("support", 2)
     Xb, _ = p.recover(Ab, lam, mu, iters)
     assert torch.equal(Xb.view(-1, n)[:-1], Xs.view(-1, n)[:-1]) and not Xb.view(-1, n)[-1].isfinite().all()
+
+
+# (dtype, n_q, n, m, d, iterations, columns of Phi the rows lean on): rows for 128-row groups on the two-chunk decoder with the synthesis inside it and
+# outside, the large-tile decoder with and without its product split along K, float; counts that are not whole tiles, and none at all
+SCREEN_CASES = [("bf16", 2816, 1600, 392, 64, 4, 0.2), ("bf16", 2800, 700, 200, 128, 5, 0.4), ("bf16", 2816, 330, 100, 64, 3, 0.3), ("bf16", 700, 900, 500, 64, 4, 0.3),
+                ("bf16", 5000, 800, 450, 80, 3, 0.1), ("bf16", 2816, 1600, 392, 64, 4, 0.0), ("f32", 900, 700, 150, 64, 4, 0.3), ("f32", 1100, 333, 75, 72, 3, 0.4),
+                ("bf16", 2816, 1600, 392, 64, 4, 0.9)]
+
+
+@pytest.mark.parametrize("dtype,n_q,n,m,d,iters,share", SCREEN_CASES)
+def test_rows_without_coefficients_left_out(dtype, n_q, n, m, d, iters, share, options):
+    """Rows with |Phi^T y| <= lambda have x = 0 throughout and are left out of the decoder: C is zero there and the decoder's elsewhere."""
+    heads = 3
+    g = torch.Generator(device=DEV).manual_seed(n + m)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).to(t)
+    rows = heads * n_q
+    Y = 0.002 * torch.randn(rows, m, generator=g, device=DEV)
+    lean = torch.rand(rows, generator=g, device=DEV) < share
+    cols = torch.randint(0, n, (rows, 3), generator=g, device=DEV)
+    Y[lean] += 0.4 * Phi.float().t()[cols[lean]].sum(1)
+    mu, lam = 0.25 * m / n, 0.1
+    V = torch.randn(heads, n, d, generator=g, device=DEV).to(t)
+    dims = csat.make_dims(1, heads, n_q, n, d, m, dtype)
+
+    def decode(choice, y=Y):
+        options("screen", choice)
+        ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(heads, n_q, d, dtype=t, device=DEV).fill_(7.0)
+        csat.csat_recover(dims, y.view(heads, n_q, m).clone(), Phi, lam, mu, iters, None, V, C, ws)
+        assert csat.csat_decoder_status(ws) == 0
+        return C.view(rows, d)
+
+    C, C1 = decode(2), decode(1)
+    x = torch.zeros(rows, n, dtype=torch.float64, device=DEV)
+    P = Phi.double()
+    for _ in range(iters):
+        u = x + mu * torch.matmul(Y.double() - torch.matmul(x, P.t().contiguous()), P)
+        x = u.sign() * (u.abs() - mu * lam).clamp_min(0.0)
+    want = torch.matmul(x.view(heads, n_q, n), V.double()).view(rows, d)
+    zero = (x == 0).all(1)
+    assert bool((C[zero] == 0).all()) and (share == 0.0) == bool(zero.all())
+    assert torch.equal(decode(2), C)
+    if share > 0:
+        assert float((C.double() - want).norm() / want.norm()) < (2e-2 if dtype == "bf16" else 1e-5)
+        # the same roundings; sums of the synthesis in another order
+        assert float((C.float() - C1.float()).norm() / C1.float().norm()) < (4e-3 if dtype == "bf16" else 2e-6)
+    # NaN and infinities stay with their rows
+    Yb = Y.clone()
+    i, j = int(zero.nonzero()[0]), int(zero.nonzero()[-1])
+    Yb[i, 0], Yb[j, m - 1] = float("nan"), float("inf")
+    Cb = decode(2, Yb)
+    same = torch.ones(rows, dtype=torch.bool, device=DEV)
+    same[i] = same[j] = False
+    # (float: a tile of rows with such a one is computed on the float MFMA, in other sums: 2^-24 of u each, |u| up to 10 |x|)
+    assert torch.equal(Cb[same], C[same]) if dtype == "bf16" else float((Cb[same] - C[same]).norm()) <= 2e-6 * float(C[same].norm())
+    old = decode(1, Yb)
+    assert torch.equal(Cb.isnan(), old.isnan()) and torch.equal(Cb.isinf(), old.isinf())

@@ -1060,12 +1060,12 @@ csat_status support_count(const Workspace& w, const uint8_t* mask, long long byt
 }
 
 // Whether the large-tile decoder's residual may go over the support of the iterate, which the device decides: not where the
-// product over all columns takes less than about 20 us (its operations at 1.2 PFLOP/s).
+// product over all columns takes less than about 40 us (its operations at 1.2 PFLOP/s).
 // (A byte for every four rows lies in K's transposed copy, which the decoder does not read.)
 bool residual_support_applies(const csat_dims& d, long long rows, int iters) {
     if (support_choice() == 1 || iters < 2 || d.m > 1024 || d.n > 65536) return false;
-    if (rows / 4 >= (long long)d.B * d.H * d.d * d.n * 2) return false;
-    return support_choice() == 2 || (double)rows * d.n * d.m > 1.2e10;
+    if (rows / 4 >= (long long)d.B * d.H * d.d * d.n * 2 || rows / 4 * d.n >= (1ll << 32)) return false;
+    return support_choice() == 2 || (double)rows * d.n * d.m > 2.4e10;
 }
 // ... in a launch of its own, with more wavefronts than in the product's place, where a launch that returns at once is below 1 % of an
 // iteration (the product over all columns about 200 us).
@@ -1081,6 +1081,20 @@ double residual_support_limit(const csat_dims& d, long long rows) {
     return rows / 4.0 * d.n / (residual_support_apart(d, rows) ? 64 : rows >= 12288 ? 128 : 270);
 }
 
+// ... and the float decoder's, in the product's place (rows that take a few microseconds each, however short Phi's columns are: not below m = 256, where
+// the product is as quick), and up to which share of the iterate.  Forward over all columns against over the support, us: 19 200 rows,
+// n = 1600, m = 392, 20 iterations: 0.023 3010, 2460; 0.025 3220, 2950; 0.029 3710, 3720; 0.036 7060, 7110; few rows, whose longest lists end the launch:
+// 4000 rows, n = 3000, m = 400: 0.012 3840, 4070; 7536 rows, n = 1120, m = 300, 41 iterations: 0.0015 4510, 4340; 0.006 4510, 4730; 16 384 rows,
+// n = 2048, m = 178, 29 iterations: 0.006 6050, 7460.
+bool residual_support_f32_applies(const csat_dims& d, long long rows, int iters) {
+    if (support_choice() == 1 || iters < 2 || d.m > 1024 || gemm_choice() == 1 || (d.m <= 32 && d.n <= 128) || d.n <= 32 || rows * d.n >= (1ll << 32)) return false;
+    return support_choice() == 2 || (d.m >= 256 && (double)rows * d.n * d.m > 2e9 && (iters - 1.0) * rows * d.n * d.m > 6.5e10);      // (a millisecond of products: 20 us)
+}
+double residual_support_f32_limit(const csat_dims& d, long long rows) {
+    if (support_choice() == 2) return 4294967295.0;
+    return (double)rows * d.n * (rows >= 12288 ? 0.025 : 0.002);
+}
+
 // Rows without a coefficient left out of the decoder, the others packed (csat_screen.h).  The packed rows take half of what all rows
 // have, so at most half of them may stay; their y goes into the other half of the iterate's buffer, the lists into K's transposed copy.
 struct ScreenPlan {
@@ -1088,7 +1102,7 @@ struct ScreenPlan {
     const int* Place = nullptr;
     const float* Y = nullptr; long long ldY = 0;
 };
-// The sample and the launches that return at once take 40 to 60 us: not where the decoder takes less than about 2 ms (its operations at
+// The sample and the launches that return at once take 40 to 60 us: not where the decoder takes less than about 2.5 ms (its operations at
 // 1 PFLOP/s, 0.12 in float).  X where the caller wants it stays with the decoder over all rows.
 bool screen_applies(const csat_dims& d, const Workspace& w, const void* X, const void* V, const void* C, int iters) {
     const long long rows = (long long)d.B * d.H * d.n_q, BH = (long long)d.B * d.H;
@@ -1102,7 +1116,7 @@ bool screen_applies(const csat_dims& d, const Workspace& w, const void* X, const
     } else if (decoder_is_resident_f32(d, w, iters) || (d.m <= 32 && d.n <= 128)) {
         return false;
     }
-    return screen_choice() == 2 || 4.0 * iters * rows * d.n * d.m > (d.dtype == CSAT_BF16 ? 2e12 : 2.4e11);
+    return screen_choice() == 2 || 4.0 * iters * rows * d.n * d.m > (d.dtype == CSAT_BF16 ? 2.5e12 : 3e11);
 }
 template <typename T>
 csat_status screen_rows(const Workspace& w, ScreenRowsArgs a, hipStream_t st) {
@@ -1125,7 +1139,7 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const f
     HIP_TRY(hipGetLastError());
     // the fused decoder has neither operand of the product; the others have the first residual
     if (w.fused) CSAT_TRY(transpose_pack<T>(Phi, (T*)w.PhiT, w.ldm, 1, d.m, d.n, st));
-    const long long stride = std::max<long long>(1, rows / std::max<long long>(512, rows / 16)), sample = rows / stride;
+    const long long stride = std::max<long long>(1, rows / std::max<long long>(512, rows / 64)), sample = rows / stride;
     ScreenRowsArgs ra{nullptr, nullptr, sample, (int)stride, Y, ldY, y_tiled, nullptr, 0, 0, w.R, w.ldm, kBf16, d.m};
     if (w.fused) CSAT_TRY(screen_rows<T>(w, ra, st));
     auto product = [&](long long M, long long lda, const uint32_t* off) -> csat_status {
@@ -1164,7 +1178,7 @@ csat_status screen_finish(const csat_dims& d, const Workspace& w, const ScreenPl
     if (!plan.words) return CSAT_OK;
     const long long rows = (long long)d.B * d.H * d.n_q;
     Timed tm(w, CSAT_K_SYNTHESIS, st);
-    hipLaunchKernelGGL((screen_finish_kernel<T>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, plan.words, w.Status, plan.Place,
+    hipLaunchKernelGGL((screen_finish_kernel<T>), dim3((unsigned)std::min<long long>((rows + 3) / 4, 16ll * cu_count())), dim3(256), 0, st, plan.words, w.Status, plan.Place,
                        sizeof(T) == 2 ? (const T*)w.Xb : (const T*)w.Xs, w.ldn, V, C, rows, d.n_q, d.n, d.d);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
@@ -1261,12 +1275,38 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
             CSAT_TRY(support_begin(w, st));
         }
     }
+    if constexpr (!kBf16) {
+        if (residual_support_f32_applies(d, rows, iters) && (plan.words || support_choice() == 2)) {      // (packed rows, above all: few tiles of a long contraction)
+            rule.ctl = (const uint32_t*)w.Status + kSupportWord;
+            rule.limit = (uint32_t)std::min(4294967295.0, residual_support_f32_limit(d, rows));
+            CSAT_TRY(support_begin(w, st));
+        }
+    }
     for (int t = 0; t < iters; ++t) {
         if (t > 0) {   // residual r = y - Phi x
             GemmArgs g{kBf16 ? (const void*)w.Xb : (const void*)w.Xs, w.ldn, 0, w.PhiP, w.ldn, 0, 0, d.m, d.n, 0};
             g.M = (int)rows;
             g.screen = plan.words;
             Timed tm(w, CSAT_K_RESIDUAL, st);
+            if constexpr (!kBf16) {
+                if (rule.ctl) {
+                    if (t == 1) {
+                        hipLaunchKernelGGL(support_count_f32_kernel, dim3((unsigned)std::min<long long>((rows + 7) / 8, cu_count())), dim3(256), 0, st, w.Xs, w.ldn, rows, d.n, 8,
+                                           (uint32_t*)w.Status + kSupportWord, plan.words, (const float*)w.PhiT, d.n * w.ldm);
+                        HIP_TRY(hipGetLastError());
+                    }
+                    const EpiResidual<float> er{Y, ldY, (float*)w.R, w.ldm, rows, d.m, plan.Y, plan.ldY};
+                    const ResidualSupportF32Args sf{w.Xs, w.ldn, (const float*)w.PhiT, (int)w.ldm, Y, ldY, (float*)w.R, rows, d.n, d.m, plan.words, plan.Y, plan.ldY};
+                    auto launch = [&](auto mr) {
+                        constexpr int MR = decltype(mr)::value;
+                        if (!plan.words) return launch_gemm_f32(g, w.ldm, 1, EpiResidualEitherF32<EpiResidual<float>, MR>{er, rule, sf}, st);
+                        return launch_gemm_f32(g, w.ldm, 1, EpiResidualEitherF32<EpiScreened<EpiResidual<float>>, MR>{{er}, rule, sf}, st);
+                    };
+                    if (w.ldm <= 256) CSAT_TRY(launch(std::integral_constant<int, 1>{}));
+                    else if (w.ldm <= 512) CSAT_TRY(launch(std::integral_constant<int, 2>{}));
+                    else CSAT_TRY(launch(std::integral_constant<int, 4>{}));
+                }
+            }
             const ResidualSupportArgs sa{w.Mask, (const f32x4*)w.Xs, w.ldn / 32, (const bf16_t*)w.PhiT, (int)w.ldm, Y, ldY, (bf16_t*)w.R, (uint8_t*)w.KT + support_same, rows, d.m, t == 1, plan.words, plan.Y, plan.ldY};
             auto launch_residual = [&](const auto& epi, const GemmArgs& ga, int parts) -> csat_status {
                 using Epi = std::decay_t<decltype(epi)>;
@@ -1284,13 +1324,16 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
                 if (regs <= 12) return launch(std::integral_constant<int, 12>{});
                 return launch(std::integral_constant<int, 16>{});
             };
-            if (rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, plan.words, rows));
-            if (w.split > 1 && use_big_gemm<T>(g, w.ldm)) {     // partial products along K, then r = y - their sum
+            if (kBf16 && rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, plan.words, rows));
+            if (!kBf16 && rule.ctl) {
+                // (launched above)
+            } else if (w.split > 1 && use_big_gemm<T>(g, w.ldm)) {     // partial products along K, then r = y - their sum
                 GemmArgs gs = g;
                 gs.K = (int)(w.ldn / w.split);
                 gs.strideA = gs.strideB = gs.K;
                 const EpiStorePart ep{{w.SplitP, w.ldm, rows * w.ldm, nullptr, 0, 0, 1.f, (int)rows, d.m}};
-                CSAT_TRY(launch_residual(ep, gs, w.split));
+                if (plan.words) CSAT_TRY(launch_residual(EpiScreened<EpiStorePart>{ep}, gs, w.split));
+                else CSAT_TRY(launch_residual(ep, gs, w.split));
                 const long long total = rows * w.ldm;
                 hipLaunchKernelGGL(residual_reduce_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, Y, ldY,
                                    w.SplitP, w.split, rows * w.ldm, (bf16_t*)w.R, w.ldm, rows, d.m, rule, plan.words, plan.Y, plan.ldY);
@@ -1298,10 +1341,12 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
             } else if (use_big_gemm<T>(g, w.ldm) && ldY % 4 == 0 && aligned16(Y)) {
                 const EpiResidualTiled er{Y, ldY, (bf16_t*)w.R, w.ldm, rows, d.m, plan.Y, plan.ldY};
                 g.K = (int)round_up(g.K, 64);
-                CSAT_TRY(launch_residual(er, g, 1));
+                if (plan.words) CSAT_TRY(launch_residual(EpiScreened<EpiResidualTiled>{er}, g, 1));
+                else CSAT_TRY(launch_residual(er, g, 1));
             } else {
                 EpiResidual<T> er{Y, ldY, (T*)w.R, w.ldm, rows, d.m, plan.Y, plan.ldY};
-                CSAT_TRY((decoder_gemm<T>(g, w.ldm, 1, er, st)));
+                if (plan.words) CSAT_TRY((decoder_gemm<T>(g, w.ldm, 1, EpiScreened<EpiResidual<T>>{er}, st)));
+                else CSAT_TRY((decoder_gemm<T>(g, w.ldm, 1, er, st)));
             }
         }
         GemmArgs g{w.R, w.ldm, 0, w.PhiT, w.ldm, 0, (int)rows, d.n, d.m, 0};
@@ -1311,12 +1356,14 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
             EpiIstaUpdateTiled eu{(f32x4*)w.Xs, w.ldn / 32, w.Mask, w.Xb, w.ldn, (t == iters - 1) ? Xout : nullptr,
                                   mu, theta, rows, d.n, t == 0, t > 0 && t < iters - 1 ? rule : SupportRule{}};      // (the synthesis reads the last copy)
             g.K = (int)round_up(g.K, 64);
-            CSAT_TRY(launch_gemm_big(g, w.ldn, 1, eu, st));
+            if (plan.words) CSAT_TRY(launch_gemm_big(g, w.ldn, 1, EpiScreened<EpiIstaUpdateTiled>{eu}, st));
+            else CSAT_TRY(launch_gemm_big(g, w.ldn, 1, eu, st));
             continue;
         }
         EpiIstaUpdate eu{w.Xs, kBf16 ? w.Xb : nullptr, w.ldn, (t == iters - 1) ? Xout : nullptr,
                          mu, theta, rows, d.n, t == 0};
-        CSAT_TRY((decoder_gemm<T>(g, w.ldn, 1, eu, st)));
+        if (plan.words) CSAT_TRY((decoder_gemm<T>(g, w.ldn, 1, EpiScreened<EpiIstaUpdate>{eu}, st)));
+        else CSAT_TRY((decoder_gemm<T>(g, w.ldn, 1, eu, st)));
     }
     return CSAT_OK;
 }
@@ -1552,7 +1599,7 @@ ListaExtra carve_lista(const csat_dims& d, const Workspace& w, char* base) {
 // take less than about 400 us in all (20 us a layer and its operations at 0.9 PFLOP/s), 2 to 3 % of which the counting and the launches
 // that return at once would take.  S - I transposed takes the place of the second operand buffer.
 bool lista_support_applies(const csat_dims& d, long long rows, int iters) {
-    if (support_choice() == 1 || iters < 2 || iters > kSupportMaxLayers || d.n > kListaSupportMaxN || rows < d.n) return false;
+    if (support_choice() == 1 || iters < 2 || iters > kSupportMaxLayers || d.n > kListaSupportMaxN || rows < d.n || rows / 4 * d.n >= (1ll << 32)) return false;
     return support_choice() == 2 || (iters - 1) * (20.0 + (double)rows * d.n * d.n / 4.5e8) > 400.0;
 }
 // ... and up to which density: non-zero float4 (four rows of a column) that the first layer may leave to every four rows.  Over

@@ -62,10 +62,12 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
     // into one L2.  g.raster: column tiles; the grid is padded to whole groups of eight row tiles.
     const int slot = blockIdx.x >> 3;
     const long long row0 = ((long long)(slot / g.raster) * 8 + (blockIdx.x & 7)) * BM, col0 = (long long)(slot % g.raster) * BN;
-    if (row0 >= g.M) return;
+    if (!has_late_rule<Epi>::value && row0 >= g.M) return;      // (what may run in the product's place shares out the rows itself)
     if constexpr (has_rule<Epi>::value) {
         if (epi.rule.sparse()) return;
     }
+    uint2 words{0u, 0u};
+    if constexpr (has_late_rule<Epi>::value) words = epi.rule.words();
     u32x4 packed{1u, 0u, 0u, 0u};
     if constexpr (has_screen<Epi>::value)
         packed = __builtin_amdgcn_raw_buffer_load_b128(__builtin_amdgcn_make_buffer_rsrc((void*)g.screen, 0, g.screen ? 16 : 0, kBufferFlags), 0, 0, 0);
@@ -114,6 +116,14 @@ __global__ __launch_bounds__(256, 3) void gemm_nt_f32_split_kernel(GemmArgs g, E
     };
     clear();
     load_global(0);
+    if constexpr (has_late_rule<Epi>::value) {
+        static_assert(Epi::kLds <= sizeof(lds), "LDS");
+        if (epi.rule.sparse(words)) {
+            epi.instead(lds);
+            return;
+        }
+        if (row0 >= g.M) return;
+    }
     if constexpr (has_screen<Epi>::value) {
         if (g.screen && __builtin_amdgcn_readfirstlane(packed[0]) == 0) {
             if (row0 >= (long long)(uint32_t)__builtin_amdgcn_readfirstlane(packed[2])) return;

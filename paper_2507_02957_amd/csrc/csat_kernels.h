@@ -333,8 +333,7 @@ struct EpiResidual {
     const float* Y; long long ldY;
     TO* R; long long ldR;
     long long M; int N;
-    const float* Yp = nullptr; long long ldYp = 0;      // y where the rows are packed
-    static constexpr bool kScreen = true;
+    const float* Yp = nullptr; long long ldYp = 0;      // y where the rows are packed (EpiScreened)
     __device__ __forceinline__ void packed() { Y = Yp; ldY = ldYp; }
     __device__ __forceinline__ void operator()(int, long long r, long long c, float v) const {
         if (r >= M || c >= ldR) return;
@@ -368,7 +367,6 @@ struct EpiIstaUpdate {
     float* Xo;
     float mu, theta;
     long long M; int N; int first;
-    static constexpr bool kScreen = true;
     __device__ __forceinline__ void packed() {}
     __device__ __forceinline__ void operator()(int, long long r, long long c, float v) const {
         if (r >= M || c >= ldS) return;
@@ -459,6 +457,12 @@ struct EpiListaUpdate {
     }
 };
 
+// ... of a launch whose rows the device may have packed (csat_screen.h; asked for in every launch, the words cost float products 2 %, small bf16 ones 1 %).
+template <typename Epi>
+struct EpiScreened : Epi {
+    static constexpr bool kScreen = true;
+};
+
 // Tile-level epilogues of the large-tile kernel.  A wavefront owns 64 rows x 128 columns as 2 x 4
 // MFMA tiles (lane (li, lh), accumulator register v <-> row 8*(v/4) + 4*lh + (v%4), column li) and
 // calls, in this order:
@@ -484,8 +488,7 @@ struct EpiResidualTiled {
     const float* Y; long long ldY;
     bf16_t* R; long long ldR;
     long long M; int N;
-    const float* Yp = nullptr; long long ldYp = 0;      // y where the rows are packed
-    static constexpr bool kScreen = true;
+    const float* Yp = nullptr; long long ldYp = 0;      // y where the rows are packed (EpiScreened)
     __device__ __forceinline__ void packed() { Y = Yp; ldY = ldYp; }
     __device__ __forceinline__ Pre begin(long long, long long, int) const { return {}; }
     __device__ __forceinline__ void half(int, long long r0, long long c0w, int lane, const f32x16 (&acc)[4], char* stage,
@@ -541,7 +544,6 @@ struct EpiIstaUpdateTiled {
     float* Xo;
     float mu, theta;
     long long M; int N; int first;
-    static constexpr bool kScreen = true;
     __device__ __forceinline__ void packed() {}
     SupportRule support;               // where it says so, nothing reads the bf16 copy of this iterate, and it is not written
     __device__ __forceinline__ int live_tiles(long long r0, long long c0w) const {
@@ -781,7 +783,7 @@ struct EpiIstaUpdateTiled {
 // accumulators start from W = B y (stored in accumulator order by the first layer, loaded before the
 // main loop), so the epilogue is the ISTA one with mu = 1 and this layer's threshold.
 struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
-    static constexpr bool kAccInit = true, kRule = true, kScreen = false;
+    static constexpr bool kAccInit = true, kRule = true;
     const f32x4* W;
     SupportRule rule;
     template <int TN>
@@ -808,7 +810,6 @@ struct EpiListaUpdateTiled : EpiIstaUpdateTiled {
 // in accumulator order: tile (row tile, column tile) of 32 x 32 is 256 float4, [g][lane] = rows 8g + 4*lh .. +3 of column li, as
 // the sparse iterate.
 struct EpiListaFirstTiled : EpiIstaUpdateTiled {
-    static constexpr bool kScreen = false;
     f32x4* W;
     template <int TN>
     __device__ __forceinline__ void keep(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN]) const {

@@ -160,12 +160,21 @@ static __global__ __launch_bounds__(256) void screen_rows_kernel(ScreenRowsArgs 
     for (long long i = (long long)blockIdx.x * 4 + (threadIdx.x >> 6); i < rows; i += (long long)gridDim.x * 4) {
         const long long k = i < have ? i : have - 1, r = a.List ? a.List[k] : k * a.stride;
         const long long width = a.Yp && a.ldYp > a.ldR ? a.ldYp : a.R ? a.ldR : a.ldYp;
-        for (int c = lane; c < width; c += 64) {
-            const float y = c < a.m ? a.Y[a.y_tiled ? tiled_at(r, a.ldY, c) : r * a.ldY + c] : 0.f;
-            if (a.Yp && c < a.ldYp) a.Yp[a.yp_tiled ? tiled_at(i, a.ldYp, c) : i * a.ldYp + c] = y;
-            if (a.R && c < a.ldR) {
-                if (a.r_bf16) ((bf16_t*)a.R)[i * a.ldR + c] = f2bf(y);
-                else ((float*)a.R)[i * a.ldR + c] = y;
+        for (int c0 = 0; c0 < width; c0 += 512) {
+            float y[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int c = c0 + 64 * e + lane;
+                y[e] = c < a.m ? a.Y[a.y_tiled ? tiled_at(r, a.ldY, c) : r * a.ldY + c] : 0.f;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int c = c0 + 64 * e + lane;
+                if (a.Yp && c < a.ldYp) a.Yp[a.yp_tiled ? tiled_at(i, a.ldYp, c) : i * a.ldYp + c] = y[e];
+                if (a.R && c < a.ldR) {
+                    if (a.r_bf16) ((bf16_t*)a.R)[i * a.ldR + c] = f2bf(y[e]);
+                    else ((float*)a.R)[i * a.ldR + c] = y[e];
+                }
             }
         }
     }
@@ -181,17 +190,20 @@ __global__ __launch_bounds__(256) void screen_finish_kernel(const uint32_t* word
     constexpr int W = 16 / sizeof(T), kList = 64 * W;      // coefficients per lane and trip
     __shared__ uint32_t cols[4][kList];
     __shared__ float vals[4][kList];
+    struct alignas(16) Piece { T v[W]; };
+    struct alignas(4 * sizeof(T)) Four { T v[4]; };
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (const long long r = (long long)blockIdx.x * 4 + wave; r < rows) {
+    for (long long r = (long long)blockIdx.x * 4 + wave; r < rows; r += (long long)gridDim.x * 4) {
         const int place = __builtin_amdgcn_readfirstlane(Place[r]);
-        for (int d0 = 0; d0 < d; d0 += 256) {      // four of d per lane
+        for (int d0 = 0; d0 < d; d0 += 256) {
+            // four elements of a row of V per lane, as many rows side by side as the wavefront holds
+            const int lanes = (d - d0 < 256 ? d - d0 : 256) / 4, side = 64 / lanes, mine = lane / lanes, c4 = d0 + 4 * (lane % lanes);
             float acc[4] = {0.f, 0.f, 0.f, 0.f};
             if (*err) acc[0] = acc[1] = acc[2] = acc[3] = __uint_as_float(0x7fc00000u);
             else if (place >= 0) {
                 const T* x = X + place * ldx;
-                const T* v = V + r / n_q * n * (long long)d + d0;
-                struct alignas(16) Piece { T v[W]; };
-                for (int c0 = 0; c0 < n; c0 += kList) {      // (rows of X are padded to whole pieces with zeros or unused)
+                const T* v = V + r / n_q * n * (long long)d + c4;
+                for (int c0 = 0; c0 < n; c0 += kList) {      // (rows of X are padded to whole pieces)
                     const int c = c0 + W * lane;
                     Piece p{};
                     if (c < ldx) p = *(const Piece*)(x + c);
@@ -209,29 +221,38 @@ __global__ __launch_bounds__(256) void screen_finish_kernel(const uint32_t* word
                         cnt += __popcll(some);
                     }
                     __builtin_amdgcn_wave_barrier();
-                    for (int q = 0; q < cnt; q += 8) {
-                        float xq[8], vq[8][4];
+                    for (int q = 0; q < cnt; q += 8 * side) {
+                        Four f[8];
 #pragma unroll
                         for (int i = 0; i < 8; ++i) {
-                            const int at = q + i < cnt ? q + i : q;
-                            xq[i] = q + i < cnt ? vals[wave][at] : 0.f;
-                            const T* vr = v + (long long)cols[wave][at] * d + lane;
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) vq[i][k] = d0 + 64 * k + lane < d ? Elem<T>::load(vr + 64 * k) : 0.f;
+                            const int at = q + i * side + mine;
+                            f[i] = *(const Four*)(v + (long long)cols[wave][at < cnt ? at : q] * d);
                         }
 #pragma unroll
                         for (int i = 0; i < 8; ++i) {
-                            if (q + i >= cnt) break;
+                            const int at = q + i * side + mine;
+                            if (mine >= side || at >= cnt) continue;
+                            const float xq = vals[wave][at];
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) acc[k] = fmaf(xq[i], vq[i][k], acc[k]);
+                            for (int k = 0; k < 4; ++k) acc[k] = fmaf(xq, Elem<T>::load(&f[i].v[k]), acc[k]);
                         }
                     }
                     __builtin_amdgcn_wave_barrier();
                 }
-            }
+                // the sums that lie side by side
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (d0 + 64 * k + lane < d) Elem<T>::store(C + r * d + d0 + 64 * k + lane, acc[k]);
+                for (int k = 0; k < 4; ++k) {
+                    float sum = acc[k];
+                    for (int g = 1; g < side; ++g) sum += __shfl(acc[k], (lane % lanes) + g * lanes, 64);
+                    acc[k] = sum;
+                }
+            }
+            if (lane < lanes) {
+                Four o;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) Elem<T>::store(&o.v[k], acc[k]);
+                *(Four*)(C + r * d + c4) = o;
+            }
         }
     }
 }

@@ -430,7 +430,6 @@ __global__ __launch_bounds__(256, MR > 12 ? 3 : 4) void residual_support_kernel(
 // one above (MR = 0: in another launch): a launch that returned at once beside it would cost a small iteration 3 %.  One workgroup per
 // CU either way.
 struct EpiStorePart : EpiStore<float> {
-    static constexpr bool kScreen = true;
     __device__ __forceinline__ void packed() {}
 };
 template <typename Epi, int MR>
@@ -444,6 +443,164 @@ struct EpiResidualEither : Epi {
             const long long all = (long long)gridDim.x * gridDim.z, blocks = all < 256 ? all : 256, block = blockIdx.x + (long long)gridDim.x * blockIdx.z;
             if (block < blocks) residual_support<MR, kWaves>(s, *(ResidualSupportLds<MR, kWaves>*)lds, block, blocks);
         }
+    }
+};
+
+// Non-zero elements of every `stride`-th row of a float iterate [rows, ld], times stride, to ctl[0] (packed rows as support_count_kernel);
+// ctl[1] where the operand holds an infinity or NaN: its coefficient may be zero here (float's threshold gives zero for NaN), and
+// zero times it is not.
+static __global__ __launch_bounds__(256) void support_count_f32_kernel(const float* X, long long ld, long long rows, int n, int stride, uint32_t* ctl, const uint32_t* screen,
+                                                                       const float* operand, long long elements) {
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < elements; i += (long long)gridDim.x * 256)
+        if (!(fabsf(operand[i]) < INFINITY)) ctl[1] = 1u;
+    const long long all = rows;
+    if (screen && screen[0] == 0) rows = screen[2];
+    uint32_t c = 0;
+    for (long long r = (long long)blockIdx.x * stride; r < rows; r += (long long)gridDim.x * stride)
+        for (int i = threadIdx.x; i < n; i += 256) c += X[r * ld + i] != 0.f;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) c += __shfl_xor(c, o, 64);
+    __shared__ uint32_t part[4];
+    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(ctl, (uint32_t)((part[0] + part[1] + part[2] + part[3]) * (float)stride * ((float)all / (rows > 0 ? rows : 1))));
+}
+
+// r = y - Phi x over the support of a float iterate, in float: a wavefront per row, which collects the row's non-zero coefficients as it reads
+// it and adds their multiples of Phi's columns (rows of PhiT, lane l elements 4l to 4l + 3 of every 256); the four wavefronts of a workgroup share
+// out the columns of a row with more than kSupportOwn coefficients.  Exact products, one rounding a term: fewer terms than the
+// product over all columns sums, none of them split.  4300 packed rows of 37 coefficients, n = 1600, m = 392: 77 us over all columns (238 tiles
+// of a long contraction), 50 so, most of it the latency of reading a row and then its columns.
+struct ResidualSupportF32Args {
+    const float* X; long long ldx;
+    const float* PhiT; int ldm;
+    const float* Y; long long ldY;
+    float* R;
+    long long rows;
+    int n, m;
+    const uint32_t* screen; const float* Yp; long long ldYp;
+};
+template <int MR>
+struct ResidualSupportF32Lds {
+    uint32_t cols[4][512];
+    float vals[4][512];
+    float part[4][256 * MR];
+    int heavy[3];        // as ResidualSupportLds
+};
+template <int MR>
+__device__ __forceinline__ void residual_support_f32(ResidualSupportF32Args a, ResidualSupportF32Lds<MR>& l, long long block, long long blocks) {
+    if (a.screen && a.screen[0] == 0) {
+        a.rows = a.screen[2];
+        a.Y = a.Yp;
+        a.ldY = a.ldYp;
+    }
+    constexpr int UN = MR <= 2 ? 8 : 4;      // columns on the way
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (threadIdx.x < 3) l.heavy[threadIdx.x] = 0;
+    __syncthreads();
+    int round = 0;
+    const int share = ((a.n + 3) / 4 + 255) / 256 * 256;      // columns of a wavefront's part of a shared row
+    for (long long row0 = block * 4; row0 < a.rows; row0 += blocks * 4, round = round == 2 ? 0 : round + 1) {
+        const long long own = row0 + wave;
+        int count = 0;
+        if (own < a.rows) {
+            const float* x = a.X + own * a.ldx;
+            for (int c = 4 * lane; c < a.n; c += 256) {      // (rows are padded to whole float4 with zeros)
+                const f32x4 v = *(const f32x4*)(x + c);
+                count += (v[0] != 0.f) + (v[1] != 0.f) + (v[2] != 0.f) + (v[3] != 0.f);
+            }
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o, 64);
+            count = __builtin_amdgcn_readfirstlane(count);
+            if (count > kSupportOwn && lane == 0) atomicOr(&l.heavy[round], 1 << wave);
+        }
+        if (threadIdx.x == 0) l.heavy[round == 2 ? 0 : round + 1] = 0;
+        __syncthreads();
+        const int shared = __builtin_amdgcn_readfirstlane(l.heavy[round]);
+        for (int job = -1; job < 4; ++job) {
+            const bool alone = job < 0;
+            if (alone ? own >= a.rows || count > kSupportOwn : !(shared >> job & 1)) continue;
+            const long long row = alone ? own : row0 + job;
+            const float* x = a.X + row * a.ldx;
+            const int lo = alone ? 0 : wave * share, hi = alone ? a.n : lo + share < a.n ? lo + share : a.n;
+            f32x4 acc[MR];
+#pragma unroll
+            for (int k = 0; k < MR; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            for (int c0 = lo; c0 < hi && (!alone || count); c0 += 512) {
+                int cnt = 0;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int c = c0 + 256 * h + 4 * lane;
+                    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+                    if (c < hi) v = *(const f32x4*)(x + c);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const uint64_t some = __builtin_amdgcn_ballot_w64(v[e] != 0.f);
+                        if (!some) continue;
+                        const int at = cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(some >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)some, 0u));
+                        if (v[e] != 0.f) {
+                            l.cols[wave][at] = c + e;
+                            l.vals[wave][at] = v[e];
+                        }
+                        cnt += __popcll(some);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+                for (int q = 0; q < cnt; q += UN) {
+                    f32x4 p[UN][MR];
+                    float xq[UN];
+#pragma unroll
+                    for (int i = 0; i < UN; ++i) {
+                        const int at = q + i < cnt ? q + i : q;
+                        xq[i] = q + i < cnt ? l.vals[wave][at] : 0.f;
+                        const int col = __builtin_amdgcn_readfirstlane((int)l.cols[wave][at]);
+                        __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc((void*)(a.PhiT + (long long)col * a.ldm), 0, a.ldm * 4, kBufferFlags);
+#pragma unroll
+                        for (int k = 0; k < MR; ++k) p[i][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, lane * 16, k * 1024, 0));
+                    }
+#pragma unroll
+                    for (int i = 0; i < UN; ++i) {
+                        if (q + i >= cnt) break;
+#pragma unroll
+                        for (int k = 0; k < MR; ++k)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[k][e] = fmaf(xq[i], p[i][k][e], acc[k][e]);
+                    }
+                }
+                __builtin_amdgcn_wave_barrier();
+            }
+            const float* y = a.Y + row * a.ldY;
+            float* out = a.R + row * a.ldm;
+            if (alone) {
+#pragma unroll
+                for (int k = 0; k < MR; ++k) {
+                    const int c = 256 * k + 4 * lane;
+                    if (c >= a.ldm) continue;
+                    f32x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = c + e < a.m ? y[c + e] - acc[k][e] : 0.f;
+                    *(f32x4*)(out + c) = o;
+                }
+                continue;
+            }
+            __syncthreads();        // (uniform: every wavefront of the workgroup takes every shared row)
+#pragma unroll
+            for (int k = 0; k < MR; ++k) *(f32x4*)(l.part[wave] + 256 * k + 4 * lane) = acc[k];
+            __syncthreads();
+            for (int c = threadIdx.x; c < a.ldm; c += 256)
+                out[c] = c < a.m ? y[c] - ((l.part[0][c] + l.part[1][c]) + (l.part[2][c] + l.part[3][c])) : 0.f;
+        }
+    }
+}
+// The float residual over all columns, or in its place the one above.
+template <typename Epi, int MR>
+struct EpiResidualEitherF32 : Epi {
+    static constexpr bool kLate = true;
+    SupportRule rule;
+    ResidualSupportF32Args s;
+    static constexpr size_t kLds = sizeof(ResidualSupportF32Lds<MR>);
+    __device__ __forceinline__ void instead(void* lds) const {
+        residual_support_f32<MR>(s, *(ResidualSupportF32Lds<MR>*)lds, blockIdx.x, gridDim.x);
     }
 };
 

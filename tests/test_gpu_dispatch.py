@@ -1095,3 +1095,50 @@ def test_rows_without_coefficients_left_out(dtype, n_q, n, m, d, iters, share, o
     assert torch.equal(Cb[same], C[same]) if dtype == "bf16" else float((Cb[same] - C[same]).norm()) <= 2e-6 * float(C[same].norm())
     old = decode(1, Yb)
     assert torch.equal(Cb.isnan(), old.isnan()) and torch.equal(Cb.isinf(), old.isinf())
+
+
+# (n_q, n, m, iterations): m on both sides of the instances' 256 and 512, rows of a few and of many coefficients, groups of rows and pieces of
+# columns that are not whole
+@pytest.mark.parametrize("n_q,n,m,iters", [(90, 300, 75, 3), (333, 1100, 256, 4), (101, 2049, 257, 3), (259, 1300, 512, 3), (130, 1601, 513, 2), (67, 1300, 1000, 3)])
+def test_float_residual_over_the_support(n_q, n, m, iters, options):
+    """The float decoder with its residual over the non-zero coefficients: no further from float64 than with the product over all columns."""
+    heads = 2
+    g = torch.Generator(device=DEV).manual_seed(n + m)
+    rows = heads * n_q
+    Phi = torch.randn(m, n, generator=g, device=DEV) / m ** 0.5
+    Y = 0.02 * torch.randn(rows, m, generator=g, device=DEV) * torch.rand(rows, 1, generator=g, device=DEV) ** 3
+    cols = torch.randint(0, n, (rows, 4), generator=g, device=DEV)
+    Y += 0.3 * Phi.t()[cols].sum(1)
+    lam, mu = 0.05, float(1.0 / torch.linalg.matrix_norm(Phi.double(), 2) ** 2)
+    V = torch.randn(heads, n, 64, generator=g, device=DEV)
+    dims = csat.make_dims(1, heads, n_q, n, 64, m, "f32")
+
+    def decode(choice, y=Y, phi=Phi):
+        options("support", choice)
+        ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        X, C = torch.empty(heads, n_q, n, device=DEV), torch.empty(heads, n_q, 64, device=DEV)
+        csat.csat_recover(dims, y.view(heads, n_q, m).clone(), phi, lam, mu, iters, X, V, C, ws)
+        torch.cuda.synchronize()
+        return X.view(rows, n), C
+
+    X, C = decode(2)
+    X1, C1 = decode(1)
+    x = torch.zeros(rows, n, dtype=torch.float64, device=DEV)
+    P, mu64, theta = Phi.double(), float(np.float32(mu)), float(np.float32(mu) * np.float32(lam))
+    for _ in range(iters):
+        u = x + mu64 * torch.matmul(Y.double() - torch.matmul(x, P.t().contiguous()), P)
+        x = u.sign() * (u.abs() - theta).clamp_min(0.0)
+    assert 0.0005 < float((x != 0).double().mean()) < 0.5
+    err, err1 = (float((v.double() - x).norm() / x.norm()) for v in (X, X1))
+    assert err <= 1.1 * err1 and err < 1e-5       # (a tenth: the update's sums, equal on both sides but for their operands' last bits)
+    again = decode(2)
+    assert torch.equal(again[0], X) and torch.equal(again[1], C)
+    # a matrix with an infinity stays on the product over all columns, NaN and infinities in a row with that row
+    bad = Phi.clone()
+    bad[m // 2, n - 1] = float("inf")
+    got, old = decode(2, phi=bad), decode(1, phi=bad)
+    assert all(torch.equal(p.isnan(), q.isnan()) and torch.equal(p.isinf(), q.isinf()) for p, q in zip(got, old))
+    Yb = Y.clone()
+    Yb[3, 0], Yb[rows - 1, m - 1] = float("nan"), float("inf")
+    got, old = decode(2, y=Yb), decode(1, y=Yb)
+    assert all(torch.equal(p.isnan(), q.isnan()) and torch.equal(p.isinf(), q.isinf()) for p, q in zip(got, old))

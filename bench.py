@@ -303,6 +303,8 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
         Zt = torch.empty(w.B, w.H, w.n_q, w.d, dtype=tQ.dtype, device=dev)
         Pk = torch.empty(w.B, w.H, w.n_q, args.picks, dtype=torch.int32, device=dev)
 
+    ws[:256].fill_(0xFF)      # (the status block, for the rows decoded below)
+
     def step():
         if args.mode == "columns_hadamard":
             csat.csat_forward_rd_hadamard(dims, tQ, tK, tV, t_rows, t_signs, w.lam, mu, w.iters, C, None, ws)
@@ -361,6 +363,11 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     stage_ms = {k: v[0] / prof_steps for k, v in prof.items()}
 
     rows = w.B * w.H * (w.d if args.mode in ("columns", "columns_hadamard") else w.n_q)      # decoder problems
+    # rows that the decoder ran: where the library left out those without any coefficient (words 16 and 18 of the workspace's
+    # status block, which starts as -1 here), the others; the decoder's figures below are of these, `value` of the method as defined
+    words = ws.view(torch.int32)[16:19].tolist()
+    decoded = words[2] if args.mode == "rows" and words[0] == 0 else rows
+    all_rows, rows = rows, decoded
     T = w.iters
     fused = prof["residual"][1] == 0 and args.mode in ("rows", "columns")          # one launch runs every ISTA iteration
     hadamard = args.mode in ("hadamard", "columns_hadamard")
@@ -417,7 +424,7 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     traffic, traffic_src = None, None
     try:
         rec = json.load(open(os.path.join(ROOT, "profiles", "hbm_traffic.json"))).get(w.name)
-        if rec and rec["kernel"] == kname and args.mode == "rows":
+        if rec and rec["kernel"] == kname and args.mode == "rows" and decoded == all_rows:
             traffic, traffic_src = rec["fetch_bytes"] + rec["write_bytes"], rec["summary"]
     except (OSError, ValueError, KeyError):
         pass
@@ -447,7 +454,7 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     roof["launches_per_step"] = n_dom / prof_steps
     roof["arithmetic_intensity_flop_per_byte"] = ai
     roof["arithmetic_intensity_measured_traffic"] = ai_roof if traffic else None
-    # Flops the dominant kernel executes per launch, padding included (nothing is skipped: the decoder is dense);
+    # Flops the dominant kernel executes per launch, padding included (of the rows it ran nothing is skipped: the decoder is dense);
     # `achieved` counts only the algorithmic ones.  One-launch decoders: every 32-row tile (in groups of four on the 128-row
     # kernels) runs 2*MT MFMAs (32x32x16; six of them as one float product) per chunk and product, the decoder in LDS over
     # its instance's chunks in bf16; large-tile GEMM: whole 256x256 tiles over K padded to 64.
@@ -476,6 +483,9 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
             roof["mfma_frac_of_achievable"] = roof["mfma_tflops"] / pk["mfma_loop_TFLOPps"]
         roof["hbm_algorithmic_frac_of_achievable"] = roof["hbm_algorithmic_gbs"] / pk["stream_copy_GBps"]
 
+    if args.mode == "lista" and roof["mfma_frac"] > 1.0:      # the layers ran over the support of a sparse iterate
+        roof.update(kernel="lista_support_kernel", bound="l2", achieved=None, frac=None, executed_flops=None, executed_over_algorithmic=None)
+    roof["rows_decoded"], roof["rows"] = decoded, all_rows
     flops = nominal_flops(w, args.mode, args.picks)
     out = {
         "metric": {"rows": "csat_forward_tflops", "columns": "csat_forward_columnwise_tflops",

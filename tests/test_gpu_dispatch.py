@@ -1142,3 +1142,43 @@ def test_float_residual_over_the_support(n_q, n, m, iters, options):
     Yb[3, 0], Yb[rows - 1, m - 1] = float("nan"), float("inf")
     got, old = decode(2, y=Yb), decode(1, y=Yb)
     assert all(torch.equal(p.isnan(), q.isnan()) and torch.equal(p.isinf(), q.isinf()) for p, q in zip(got, old))
+
+
+@pytest.mark.parametrize("dtype,n_q,n,m", [("bf16", 2816, 700, 200), ("bf16", 1100, 900, 500), ("f32", 900, 700, 300)])
+def test_packed_rows_and_support_in_a_graph(dtype, n_q, n, m, options):
+    """What the device decides, it decides in every replay anew: replays over changed measurements against the eager call."""
+    heads, iters, d = 3, 4, 64
+    g = torch.Generator(device=DEV).manual_seed(n)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).to(t)
+    V = torch.randn(heads, n, d, generator=g, device=DEV).to(t)
+    rows = heads * n_q
+    dims = csat.make_dims(1, heads, n_q, n, d, m, dtype)
+    options("screen", 2)
+    options("support", 2)
+
+    def measurements(share):
+        Y = 0.002 * torch.randn(rows, m, generator=g, device=DEV)
+        lean = torch.rand(rows, generator=g, device=DEV) < share
+        Y[lean] += 0.4 * Phi.float().t()[torch.randint(0, n, (rows,), generator=g, device=DEV)[lean]]
+        return Y.view(heads, n_q, m)
+
+    Y = measurements(0.2)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    C = torch.empty(heads, n_q, d, dtype=t, device=DEV)
+    call = lambda: csat.csat_recover(dims, Y, Phi, 0.1, 0.25 * m / n, iters, None, V, C, ws)      # noqa: E731
+    call()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        call()
+    for share in (0.3, 0.0, 0.9, 0.1):      # (0.9: too many rows to pack)
+        Y.copy_(measurements(share))
+        call()
+        torch.cuda.synchronize()
+        want = C.clone()
+        C.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(C, want) and (share == 0.0) == (not bool(C.any()))

@@ -400,13 +400,16 @@ csat_status launch_gemm_big(const GemmArgs& g, long long n_cover, int batch, con
 // their width, and a twelfth for the wider tile's loop.  A forward of 20 layers over 76 800 rows, n = 1600 (six rounds of 320 against nine of
 // 256): 8.63 ms against 9.60; not where the rounds are as wide: 8 layers over 16 000 rows, n = 2000 (two, two) 1.51 against 1.43,
 // 6 over 8000, n = 3500 (two, two) 1.32 against 1.17.
-template <typename Epi>
-csat_status launch_gemm_big_lista(const GemmArgs& g, long long n_cover, const Epi& epi, hipStream_t st) {
+bool wide_tiles_pay(const GemmArgs& g, long long n_cover) {
     auto cost = [&](int width) {
         const long long tiles = (g.M + 255ll) / 256 * ((n_cover + width - 1) / width);
         return (tiles + cu_count() - 1) / cu_count() * width;
     };
-    const bool wide = cost(320) * 13 < cost(256) * 12;
+    return cost(320) * 13 < cost(256) * 12;
+}
+template <typename Epi>
+csat_status launch_gemm_big_lista(const GemmArgs& g, long long n_cover, const Epi& epi, hipStream_t st) {
+    const bool wide = wide_tiles_pay(g, n_cover);
     tl_forms[CSAT_FORM_LISTA_TILE] = wide ? 320 : 256;
     if (wide) return launch_gemm_big_shape<Epi, 4, 2, 64, 5>(g, n_cover, 1, epi, st);
     return launch_gemm_big<Epi>(g, n_cover, 1, epi, st);
@@ -1147,6 +1150,7 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const f
         const EpiScreen e{stay, mu, theta * kScreenMargin, M, d.n, {off}};
         if constexpr (kBf16) {
             g.K = (int)round_up(g.K, 64);
+            if (wide_tiles_pay(g, d.n)) return launch_gemm_big_shape<EpiScreen, 4, 2, 64, 5>(g, d.n, 1, e, st);
             return launch_gemm_big(g, d.n, 1, e, st);
         } else {
             return launch_gemm_f32(g, d.n, 1, e, st);
@@ -1402,6 +1406,7 @@ csat_status run_synthesis(const csat_dims& d, const Workspace& w, T* C, hipStrea
                w.VT, w.ldn, (long long)d.d * w.ldn, d.n_q, d.d, d.n, 0};
     EpiStore<T> ec{C, d.d, (long long)d.n_q * d.d, nullptr, 0, 0, 1.f, d.n_q, d.d};
     Timed tm(w, CSAT_K_SYNTHESIS, st);
+    if (rule.ctl) return decoder_gemm<T>(g, d.d, BH, EpiRuled<EpiStore<T>>{ec, rule}, st);
     return decoder_gemm<T>(g, d.d, BH, ec, st);
 }
 

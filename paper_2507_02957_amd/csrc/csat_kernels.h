@@ -273,6 +273,13 @@ struct EpiStore {
     }
 };
 
+// A product that is not needed where the rule says so (the large-tile and float kernels then return at once).
+template <typename Epi>
+struct EpiRuled : Epi {
+    static constexpr bool kRule = true;
+    SupportRule rule;
+};
+
 // Batches below z2 end in `a`, the others in `b`: two products of one launch.
 template <typename EA, typename EB>
 struct EpiPair {

@@ -3,9 +3,10 @@
 // with many such rows (short_video: four of five) find them with the first iteration's product, and the decoder runs the rows that are left,
 // packed together.  The device decides: a sample of the rows first (every few rows; 1 to 2 % of such a call where all rows stay), then all.
 //
-// What it takes (short_video, 76 800 rows, of which 17 000 stay): the sample 40 us, bf16 operands of all rows 48, their product 157 (its short contraction:
-// seven steps a tile), the lists 12, packing 48, C 140; the decoder runs 133 groups of rows instead of 600, 1.35 ms instead of 3.2. A forward
-// 3.58 -> 1.95 ms; float, 19 200 rows 7.25 -> 2.90; 205 824 rows, n = 1608, m = 752, one of a hundred left 9.7 -> 2.5.
+// What it takes (short_video, 76 800 rows, of which 15 000 to 17 000 stay): the sample and the launches around it 45 us, bf16 operands of all rows 48, their product
+// 122 (on 256 x 320 tiles; 156 on 256 x 256: its contraction is seven steps a tile), the lists 12, packing 39, C 47; the decoder runs 120 to 133 groups of
+// rows instead of 600, 1.35 ms (a chain of 20 iterations) instead of 3.2. A forward 3.49 -> 1.75 ms; float, 19 200 rows 6.91 -> 2.31 (with the
+// residual over the support); 205 824 rows, n = 1608, m = 752, one of a hundred left 9.7 -> 2.5.
 //
 // A row stays unless |mu Phi^T y| <= (1 - 2^-8) theta everywhere, so that the decoder's own sums, in whatever order, would have
 // given zero too; NaN and infinities stay.
@@ -22,7 +23,7 @@ constexpr int kScreenWords = 4;
 // The product's epilogue: Stay[r] = 1 where a row has an element above the bound.
 struct EpiScreen {
     static constexpr bool kTile = true;
-    static constexpr int kStageBytes = 0;
+    static constexpr int kStageBytes = 0, kWideStageBytes = 0;
     static constexpr bool kRule = true, kRows = true;
     struct Pre {};
     struct Rule {
@@ -46,6 +47,20 @@ struct EpiScreen {
             for (int j = 0; j < 4; ++j) above |= c0w + 32 * j + (lane & 31) < N && !(fabsf(mu * acc[j][v]) <= bound);
             mark(above, r0 + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, lane);
         }
+    }
+    template <int TN>
+    __device__ __forceinline__ Pre begin_wide(long long, long long, int) const { return {}; }
+    template <int TN>
+    __device__ __forceinline__ void whole_wide(long long r0w, long long c0w, int lane, const f32x16 (&acc)[2][TN], char*, const Pre&) const {
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                bool above = false;
+#pragma unroll
+                for (int j = 0; j < TN; ++j) above |= c0w + 32 * j + (lane & 31) < N && !(fabsf(mu * acc[i][j][v]) <= bound);
+                mark(above, r0w + 32 * i + 8 * (v / 4) + 4 * (lane >> 5) + v % 4, lane);
+            }
     }
     __device__ __forceinline__ void flush(long long, long long, int, const char*, const Pre&) const {}
     __device__ __forceinline__ void rows(long long r0, long long c, const f32x16& acc) const {

@@ -1314,10 +1314,11 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
             const ResidualSupportArgs sa{w.Mask, (const f32x4*)w.Xs, w.ldn / 32, (const bf16_t*)w.PhiT, (int)w.ldm, Y, ldY, (bf16_t*)w.R, (uint8_t*)w.KT + support_same, rows, d.m, t == 1, plan.words, plan.Y, plan.ldY};
             auto launch_residual = [&](const auto& epi, const GemmArgs& ga, int parts) -> csat_status {
                 using Epi = std::decay_t<decltype(epi)>;
+                tl_forms[CSAT_FORM_RESIDUAL] = parts + (rule.ctl && parts == 1 && residual_support_apart(d, rows) ? 16 : 0);
                 if (!rule.ctl) return launch_gemm_big(ga, w.ldm, parts, epi, st);
                 auto launch = [&](auto mr) -> csat_status {
                     constexpr int MR = decltype(mr)::value;
-                    if (parts > 1 || !residual_support_apart(d, rows)) return launch_gemm_big(ga, w.ldm, parts, EpiResidualEither<Epi, MR>{epi, rule, sa}, st);
+                    if (tl_forms[CSAT_FORM_RESIDUAL] < 16) return launch_gemm_big(ga, w.ldm, parts, EpiResidualEither<Epi, MR>{epi, rule, sa}, st);
                     hipLaunchKernelGGL(residual_support_kernel<MR>, dim3((unsigned)std::min<long long>((rows + 15) / 16, 4ll * cu_count())), dim3(256), 0, st, rule, sa);
                     HIP_TRY(hipGetLastError());
                     return launch_gemm_big(ga, w.ldm, parts, EpiResidualEither<Epi, 0>{epi, rule, sa}, st);

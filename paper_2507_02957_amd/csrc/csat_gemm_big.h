@@ -80,6 +80,7 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     // round-robin over the XCDs: the A rows are fetched into one L2 instead of one per column tile, and
     // the workgroups of an XCD walk K of the column operand together.  Right for few column tiles.
     long long rowt, colt;
+    bool beyond = false;      // late rule only: no tile for this workgroup
     const bool a_nt = (g.raster & kRasterStreamA) != 0;      // uniform: A rows go past the caches' recently-used end
     g.raster &= kRasterStreamA - 1;
     // (32-bit arithmetic: a division of 64 bits is a hundred instructions ahead of the first load)
@@ -87,7 +88,11 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
         const uint32_t slot = blockIdx.x >> 3, tn = g.a_kwrap;
         rowt = slot / tn * 8 + (blockIdx.x & 7);
         colt = slot % tn;
-        if (rowt * S::kRowsA >= g.M) return;       // the grid is padded to whole groups of 8 row tiles
+        // the grid is padded to whole groups of 8 row tiles (what may run in the product's place shares out the rows over all of it)
+        if (rowt * S::kRowsA >= g.M) {
+            if constexpr (!has_late_rule<Epi>::value) return;
+            beyond = true;
+        }
     } else if (g.raster >= 2) {
         // raster 2 + log2(CB): XCD x owns the column tiles [x tn/8, (x+1) tn/8) and walks them in groups of CB: within a
         // group row tile by row tile, so that the group's column operand (CB x 512 KB at K = 1024) stays in that L2
@@ -166,15 +171,13 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
     if constexpr (has_screen<Epi>::value) {
         if (g.screen && __builtin_amdgcn_readfirstlane(packed[0]) == 0) {
             if (row0 >= (long long)(uint32_t)__builtin_amdgcn_readfirstlane(packed[2])) {
-                if constexpr (has_late_rule<Epi>::value) {      // (the kernel in its place shares out the rows in its own way)
-                    if (epi.rule.sparse(words)) epi.instead(lds);
-                }
-                return;
+                if constexpr (!has_late_rule<Epi>::value) return;
+                beyond = true;
             }
             epi.packed();
         }
     }
-    stage(0, 0);
+    if (!beyond) stage(0, 0);
     typename TilePre<Epi>::type pre = tile_begin<TN>(epi, row0 + wm * 64, col0 + wn * (32 * TN), lane);
     __builtin_amdgcn_s_waitcnt(0);
     if constexpr (has_late_rule<Epi>::value) {
@@ -184,6 +187,7 @@ __global__ __launch_bounds__(64 * WM * WN, 8 / (WM * WN)) void gemm_nt_bf16_big_
             epi.instead(lds);
             return;
         }
+        if (beyond) return;
     }
     __syncthreads();
     for (int ks = 0; ks < ksteps; ++ks) {

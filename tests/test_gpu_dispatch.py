@@ -1182,3 +1182,57 @@ def test_packed_rows_and_support_in_a_graph(dtype, n_q, n, m, options):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(C, want) and (share == 0.0) == (not bool(C.any()))
+
+
+# (dtype, heads, n_q, n, m, iterations, share of rows with coefficients, packed, parts, apart): residual products that are not split along K, of row
+# tiles that are no multiple of eight (their grid is padded), for all rows and for packed ones; the kernel over the support as a launch of its
+# own (more than 1.2e11 products a residual); split along K with packed rows; float with packed rows
+RESIDUAL_EITHER_CASES = [("bf16", 3, 258, 832, 600, 4, 1.0, False, 1, False), ("bf16", 3, 1001, 1216, 1024, 3, 0.5, False, 1, False),
+                         ("bf16", 3, 938, 832, 600, 4, 0.38, True, 1, False), ("bf16", 1, 2305, 1216, 1000, 3, 0.3, True, 1, False),
+                         ("bf16", 3, 700, 960, 600, 4, 0.3, True, 5, False),
+                         ("bf16", 3, 20011, 3100, 660, 3, 0.5, False, 1, True), ("bf16", 3, 20011, 2050, 1000, 3, 0.5, False, 1, True),
+                         ("bf16", 3, 20011, 3100, 660, 3, 0.3, True, 1, True), ("f32", 3, 1700, 900, 392, 4, 0.3, True, 0, False),
+                         ("f32", 2, 1300, 1600, 600, 3, 0.3, True, 0, False)]
+
+
+@pytest.mark.parametrize("dtype,heads,n_q,n,m,iters,share,packed,parts,apart", RESIDUAL_EITHER_CASES)
+def test_residual_over_the_support_without_x(dtype, heads, n_q, n, m, iters, share, packed, parts, apart, options):
+    """C of the products' decoder with its residual over the support, every row against float64 and against the product over all columns."""
+    g = torch.Generator(device=DEV).manual_seed(n + m)
+    t, bf16 = (torch.bfloat16, True) if dtype == "bf16" else (torch.float32, False)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).to(t)
+    rows, d = heads * n_q, 64
+    Y = 0.002 * torch.randn(rows, m, generator=g, device=DEV)
+    lean = torch.rand(rows, generator=g, device=DEV) < share
+    cols = torch.randint(0, n, (rows, 3), generator=g, device=DEV)
+    Y[lean] += 0.4 * Phi.float().t()[cols[lean]].sum(1)
+    mu, lam = 0.25 * m / n, 0.13
+    V = torch.randn(heads, n, d, generator=g, device=DEV).to(t)
+    dims = csat.make_dims(1, heads, n_q, n, d, m, dtype)
+    options("screen", 2 if packed else 1)
+
+    def decode(choice):
+        options("support", choice)
+        ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(heads, n_q, d, dtype=t, device=DEV).fill_(7.0)
+        csat.csat_recover(dims, Y.view(heads, n_q, m), Phi, lam, mu, iters, None, V, C, ws)
+        assert csat.csat_profile_launch_form("residual") == (parts + (16 if apart and choice == 2 else 0))
+        return C, ws[:256].view(torch.int32).tolist()
+
+    C, words = decode(2)
+    C1, _ = decode(1)
+    x = torch.zeros(rows, n, dtype=torch.float64, device=DEV)
+    P = Phi.double()
+    for _ in range(iters):
+        u = x + mu * torch.matmul(Y.double() - torch.matmul(x, P.t().contiguous()), P)
+        x = u.sign() * (u.abs() - mu * lam).clamp_min(0.0)
+    stay = int((x != 0).any(1).sum())
+    # the device's words: non-zero pieces counted and none that forbids; the rows that it packed, none of them with coefficients left out
+    assert words[8] > 0 and words[9] == 0
+    assert words[16] == 0 and stay <= words[18] <= rows // 2 - 256 if packed else words[16] == -1
+    want = torch.matmul(x.view(heads, n_q, n), V.double()).view(rows, d)
+    assert float((C.double().view(rows, d) - want).norm() / want.norm()) < (2e-2 if bf16 else 1e-5)
+    # the same roundings but for the residual's sums (bf16: as test_residual_over_the_support), row by row on the scale of the largest
+    diff, size = (C.float() - C1.float()).view(rows, d).norm(dim=1), C1.float().view(rows, d).norm(dim=1)
+    assert float(diff.max()) < (3e-2 if bf16 else 1e-5) * float(size.max()) and float(diff.norm() / size.norm()) < (5e-3 if bf16 else 2e-6)
+    assert torch.equal(decode(2)[0], C)

@@ -1053,11 +1053,12 @@ csat_status support_begin(const Workspace& w, hipStream_t st) {
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
-// Counts what the first threshold left (its mask bytes, whole 16-byte pieces).
-csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st, const uint32_t* screen = nullptr, long long rows = 0) {
+// Counts what the first threshold left (its mask bytes, whole 16-byte pieces), and looks V over (in bf16, of v_bytes) where given.
+csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st, const uint32_t* screen = nullptr, long long rows = 0, const void* V = nullptr,
+                          long long v_bytes = 0) {
     const long long chunks = bytes / 16;
     hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
-                       (uint32_t*)w.Status + kSupportWord, screen, rows);
+                       (uint32_t*)w.Status + kSupportWord, screen, rows, (const uint4*)V, v_bytes / 16);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
@@ -1128,7 +1129,7 @@ csat_status screen_rows(const Workspace& w, ScreenRowsArgs a, hipStream_t st) {
     return CSAT_OK;
 }
 template <typename T>
-csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const float* Y, long long ldY, bool y_tiled, float mu, float theta, ScreenPlan* plan, hipStream_t st) {
+csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T* V, const float* Y, long long ldY, bool y_tiled, float mu, float theta, ScreenPlan* plan, hipStream_t st) {
     constexpr bool kBf16 = sizeof(T) == 2;
     const long long rows = (long long)d.B * d.H * d.n_q, stay_bytes = round_up(rows, 16), blocks = (rows + 1023) / 1024;
     char* at = w.KT;
@@ -1167,7 +1168,9 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const f
         CSAT_TRY(screen_rows<T>(w, ra, st));
     }
     CSAT_TRY(product(rows, w.ldm, sample_words));
-    hipLaunchKernelGGL(screen_count_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, (const uint32_t*)stay, rows, counts);
+    const long long v_pieces = (long long)d.B * d.H * d.n * d.d * (long long)sizeof(T) / 16;
+    hipLaunchKernelGGL((screen_count_kernel<T>), dim3((unsigned)(blocks + std::min<long long>((v_pieces + 1023) / 1024, 4ll * cu_count()))), dim3(256), 0, st, on, (const uint32_t*)stay,
+                       rows, counts, (int)blocks, (const uint4*)V, v_pieces);
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(screen_place_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, words, (const uint32_t*)stay, rows, counts, Place, List, (int)(rows / 2 - 256));
     HIP_TRY(hipGetLastError());
@@ -1454,7 +1457,7 @@ csat_status recover_t(const csat_dims& d, const Workspace& w, const float* Y, co
     ScreenPlan plan;
     const float* y = w.fused ? w.A : Y;
     const long long ld = w.fused ? w.ldy : (long long)d.m;
-    if (want_c && screen_applies(d, w, X, V, C, iters)) CSAT_TRY(screen<T>(d, w, (const T*)Phi, y, ld, false, mu, mu * lambda, &plan, st));
+    if (want_c && screen_applies(d, w, X, V, C, iters)) CSAT_TRY(screen<T>(d, w, (const T*)Phi, (const T*)V, y, ld, false, mu, mu * lambda, &plan, st));
     CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, y, ld, lambda, mu, iters, X, st, nullptr, nullptr, false, plan));
     if (want_c) CSAT_TRY(run_synthesis<T>(d, w, (T*)C, st, (const T*)V, SupportRule{plan.words, 0}));
     return screen_finish<T>(d, w, plan, (const T*)V, (T*)C, st);
@@ -1503,7 +1506,7 @@ csat_status forward_t(const csat_dims& d, const Workspace& w, const void* Q, con
         return CSAT_OK;
     }
     ScreenPlan plan;
-    if (screen_applies(d, w, X, V, C, iters)) CSAT_TRY(screen<T>(d, w, (const T*)Phi, w.A, w.ldy, y_tiled, mu, mu * lambda, &plan, st));
+    if (screen_applies(d, w, X, V, C, iters)) CSAT_TRY(screen<T>(d, w, (const T*)Phi, (const T*)V, w.A, w.ldy, y_tiled, mu, mu * lambda, &plan, st));
     CSAT_TRY(run_ista<T>(d, w, (const T*)Phi, w.A, w.ldy, lambda, mu, iters, X, st, syn ? (const T*)V : nullptr, syn ? (T*)C : nullptr, y_tiled, plan));
     if (!syn) CSAT_TRY(run_synthesis<T>(d, w, (T*)C, st, (const T*)V, SupportRule{plan.words, 0}));
     return screen_finish<T>(d, w, plan, (const T*)V, (T*)C, st);
@@ -1669,7 +1672,7 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
     if constexpr (kBf16) {
         if (rule.ctl) {
             Timed tm(w, CSAT_K_LAYOUT, st);
-            CSAT_TRY(support_count(w, x.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st));
+            CSAT_TRY(support_count(w, x.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, nullptr, 0, want_c ? V : nullptr, want_c ? (long long)BH * d.n * d.d * 2 : 0));
             hipLaunchKernelGGL(support_transpose_kernel, dim3((unsigned)((w.ldn + 63) / 64), (unsigned)((d.n + 63) / 64)), dim3(256), 0, st, rule,
                                (const bf16_t*)x.D, (bf16_t*)x.Op[0], d.n, (int)w.ldn);
             HIP_TRY(hipGetLastError());

@@ -253,6 +253,24 @@ struct SupportRule {
     }
 };
 
+// Whether one of the 16-byte pieces id, id + all, ... below `pieces` holds an infinity or NaN of T.
+template <typename T>
+__device__ __forceinline__ bool holds_unbounded(const uint4* p, long long pieces, long long id, long long all) {
+    bool some = false;
+    auto word = [&](uint32_t w) {
+        some |= (w & 0x7f800000u) == 0x7f800000u;
+        if constexpr (sizeof(T) == 2) some |= (w & 0x7f80u) == 0x7f80u;
+    };
+    for (long long i = id; i < pieces; i += 4 * all) {
+        uint4 v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = i + k * all < pieces ? p[i + k * all] : uint4{0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) { word(v[k].x); word(v[k].y); word(v[k].z); word(v[k].w); }
+    }
+    return some;
+}
+
 // ----------------------------------------------------------------------------------------
 // Epilogues.  Each sees (batch z, row r, column c, fp32 accumulator) and does its own bounds
 // checks: the tile grid may overhang M and N.

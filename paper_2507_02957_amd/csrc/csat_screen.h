@@ -90,9 +90,15 @@ static __global__ __launch_bounds__(1024) void screen_decide_kernel(uint32_t* wo
 }
 
 // Rows that stay, in order: counts of 1024 rows each, then their places (Place[r], -1 where r does not stay; List[place] = r).
-// More than `most` rows: packing off after all.
-static __global__ __launch_bounds__(256) void screen_count_kernel(SupportRule on, const uint32_t* stay, long long rows, int* counts) {
+// More than `most` rows: packing off after all.  And where V holds an infinity or NaN, whose products with the coefficients that are
+// zero are NaN: its `pieces` are looked over by the workgroups behind the `blocks` that count, which then set `on`'s second word.
+template <typename T>
+__global__ __launch_bounds__(256) void screen_count_kernel(SupportRule on, const uint32_t* stay, long long rows, int* counts, int blocks, const uint4* V, long long pieces) {
     if (!on.sparse()) return;
+    if ((int)blockIdx.x >= blocks) {
+        if (holds_unbounded<T>(V, pieces, (long long)(blockIdx.x - blocks) * 256 + threadIdx.x, (long long)(gridDim.x - blocks) * 256)) ((uint32_t*)on.ctl)[1] = 1u;
+        return;
+    }
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;      // four rows
     int n = i * 4 < rows ? __popc(stay[i]) : 0;
 #pragma unroll

@@ -12,7 +12,10 @@ namespace csat {
 
 // Adds the non-zero float4 that the mask bytes name to ctl[0].
 // (packed rows, csat_screen.h: of their 32-row tiles, the number scaled to all rows, which the limit is for)
-static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* mask, long long chunks, uint32_t* ctl, const uint32_t* screen, long long rows) {
+// v (optional): ctl[1] is set where one of its pieces (bf16) holds an infinity or NaN.
+static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* mask, long long chunks, uint32_t* ctl, const uint32_t* screen, long long rows, const uint4* v,
+                                                                   long long v_pieces) {
+    if (holds_unbounded<bf16_t>(v, v_pieces, (long long)blockIdx.x * 256 + threadIdx.x, (long long)gridDim.x * 256)) ctl[1] = 1u;
     uint32_t n = 0;
     float scale = 1.f;
     if (screen && screen[0] == 0) {

@@ -1236,3 +1236,41 @@ def test_residual_over_the_support_without_x(dtype, heads, n_q, n, m, iters, sha
     diff, size = (C.float() - C1.float()).view(rows, d).norm(dim=1), C1.float().view(rows, d).norm(dim=1)
     assert float(diff.max()) < (3e-2 if bf16 else 1e-5) * float(size.max()) and float(diff.norm() / size.norm()) < (5e-3 if bf16 else 2e-6)
     assert torch.equal(decode(2)[0], C)
+
+
+# (what runs, dtype, heads, n_q, n, m, d): rows left out, on the two-chunk decoder, the large-tile pair and in float; the unrolled decoder over its support,
+# with both kernels of its synthesis
+@pytest.mark.parametrize("op,dtype,heads,n_q,n,m,d", [("screen", "bf16", 3, 2816, 700, 200, 64), ("screen", "bf16", 3, 700, 900, 500, 72), ("screen", "f32", 3, 900, 700, 150, 64),
+                                                      ("lista", "bf16", 3, 391, 770, 160, 128), ("lista", "bf16", 3, 391, 770, 160, 72)])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_infinities_and_nan_of_v(op, dtype, heads, n_q, n, m, d, bad, options):
+    """Zero times an infinity or NaN is NaN: C is what the product over all coefficients gives, in the last element of V as in the first."""
+    g = torch.Generator(device=DEV).manual_seed(n + d)
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).to(t)
+    Y = 0.002 * torch.randn(heads, n_q, m, generator=g, device=DEV)
+    lean = torch.rand(heads, n_q, generator=g, device=DEV) < 0.3
+    Y[lean] += 0.4 * Phi.float().t()[torch.randint(0, n, (int(lean.sum()),), generator=g, device=DEV)]
+    mu, lam, iters = 0.25 * m / n, 0.13, 3
+    S, B = (torch.eye(n, device=DEV) - mu * torch.matmul(Phi.float().t().contiguous(), Phi.float())).to(t), (mu * Phi.float().t()).to(t).contiguous()
+    dims = csat.make_dims(1, heads, n_q, n, d, m, dtype)
+    V = torch.randn(heads, n, d, generator=g, device=DEV).to(t)
+
+    def decode(v, choice):
+        options("screen" if op == "screen" else "support", choice)
+        ws = torch.empty(max(csat.csat_workspace_bytes(dims, iters), csat.csat_lista_workspace_bytes(dims, iters)), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(heads, n_q, d, dtype=t, device=DEV).fill_(7.0)
+        if op == "screen":
+            csat.csat_recover(dims, Y, Phi, lam, mu, iters, None, v, C, ws)
+        else:
+            csat.csat_recover_lista(dims, Y, S, B, [mu * lam] * iters, None, v, C, ws)
+        return C, ws[:256].view(torch.int32).tolist()
+
+    C, words = decode(V, 2)
+    assert C.isfinite().all() and (words[16] == 0 if op == "screen" else words[9] == 0)
+    for h, j, k in ((0, 0, 0), (heads - 1, n - 1, d - 1), (1, n // 2, 5)):
+        Vb = V.clone()
+        Vb[h, j, k] = bad
+        got, want = decode(Vb, 2)[0], decode(Vb, 1)[0]
+        assert want[h, :, k].isnan().sum() > n_q // 2 and want.isfinite().sum() == want.numel() - n_q
+        assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.nan_to_num(), want.nan_to_num())

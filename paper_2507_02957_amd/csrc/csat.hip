@@ -1168,13 +1168,15 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T
         CSAT_TRY(screen_rows<T>(w, ra, st));
     }
     CSAT_TRY(product(rows, w.ldm, sample_words));
+    // whole 256 rows of packed y behind the first half of the iterate, whose rows may be shorter than y's (m close to n, in float: 8 and 32 the multiples)
+    float* Yp = w.Xs + w.rows_pad / 2 * w.ldn;
+    const long long most = std::min(rows / 2, w.rows_pad / 2 * w.ldn / w.ldy) - 256;
     const long long v_pieces = (long long)d.B * d.H * d.n * d.d * (long long)sizeof(T) / 16;
     hipLaunchKernelGGL((screen_count_kernel<T>), dim3((unsigned)(blocks + std::min<long long>((v_pieces + 1023) / 1024, 4ll * cu_count()))), dim3(256), 0, st, on, (const uint32_t*)stay,
                        rows, counts, (int)blocks, (const uint4*)V, v_pieces);
     HIP_TRY(hipGetLastError());
-    hipLaunchKernelGGL(screen_place_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, words, (const uint32_t*)stay, rows, counts, Place, List, (int)(rows / 2 - 256));
+    hipLaunchKernelGGL(screen_place_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, words, (const uint32_t*)stay, rows, counts, Place, List, (int)most);
     HIP_TRY(hipGetLastError());
-    float* Yp = w.Xs + w.rows_pad / 2 * w.ldn;
     CSAT_TRY(screen_rows<T>(w, ScreenRowsArgs{words, List, rows, 1, Y, ldY, y_tiled, Yp, w.ldy, y_tiled, w.fused ? nullptr : w.R, w.fused ? 0 : w.ldm, kBf16, d.m}, st));
     *plan = ScreenPlan{words, Place, Yp, w.ldy};
     return CSAT_OK;

@@ -1274,3 +1274,31 @@ def test_infinities_and_nan_of_v(op, dtype, heads, n_q, n, m, d, bad, options):
         got, want = decode(Vb, 2)[0], decode(Vb, 1)[0]
         assert want[h, :, k].isnan().sum() > n_q // 2 and want.isfinite().sum() == want.numel() - n_q
         assert torch.equal(got.isnan(), want.isnan()) and torch.equal(got.nan_to_num(), want.nan_to_num())
+
+
+@pytest.mark.parametrize("n", [161, 330, 1000])
+def test_packed_rows_of_a_square_matrix(n, options):
+    """m = n in float: a row of y is longer in the workspace than one of the iterate, so fewer than half of the rows fit packed.  The oracle is the decoder
+    over all rows; nothing is written behind the workspace."""
+    heads, n_q, d, iters, m = 3, 2816, 64, 3, n
+    g = torch.Generator(device=DEV).manual_seed(n)
+    Phi = torch.randn(m, n, generator=g, device=DEV) / m ** 0.5
+    V = torch.randn(heads, n, d, generator=g, device=DEV)
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "f32")
+    rows, wb = heads * n_q, csat.csat_workspace_bytes(dims, iters)
+    fit = min(rows // 2, rows // 2 * ((n + 7) // 8 * 8) // ((m + 31) // 32 * 32)) - 256      # (rows: a multiple of 256)
+    for stay in (fit // 2, fit - 3, fit, fit + 1, rows // 2 - 256, rows // 2):
+        Y = torch.zeros(rows, m, device=DEV)
+        lean = torch.randperm(rows, generator=g, device=DEV)[:stay]
+        Y[lean] = 0.4 * Phi.t()[torch.randint(0, n, (stay,), generator=g, device=DEV)]
+        out = []
+        for choice in (2, 1):
+            options("screen", choice)
+            ws = torch.full((wb + 4096,), 0xA5, dtype=torch.uint8, device=DEV)
+            C = torch.empty(heads, n_q, d, device=DEV).fill_(7.0)
+            csat.csat_recover(dims, Y.view(heads, n_q, m), Phi, 0.1, 0.1, iters, None, V, C, ws[:wb])
+            assert bool((ws[wb:] == 0xA5).all())
+            out.append((C, ws[:256].view(torch.int32).tolist()))
+        (C, words), (C1, _) = out
+        assert words[18] == stay and (words[16] == 0) == (stay <= fit)
+        assert float((C - C1).norm() / C1.norm()) < 2e-6      # (sums of the synthesis in another order)

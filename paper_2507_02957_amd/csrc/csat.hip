@@ -1623,6 +1623,17 @@ double lista_support_limit(const csat_dims& d, long long rows) {
     if (support_choice() == 2) return 4294967295.0;
     return rows / 4.0 * (d.n > 3328 ? 12 : d.n <= 512 ? 128 : rows >= 16384 ? 48 : 24);
 }
+// ... and not where thresholds fall far below the first layer's: its count then says nothing of the coefficients that the later layers leave.  Over
+// all columns against over the support, us (first layer's float4 a quad; the lowest threshold, of the first): 76 800 rows, n = 1600, 20 layers:
+// (9, 0.6) 8670, 2880; (0.4, 0.25) 8750, 4130; (25, 0.4) 9300, 8340; (25, 0.2) 10 300, 20 650; (9, 0.016) 11 080, 87 490; 44 800 rows, n = 700: (24, 0.6)
+// 2220, 1150; (56, 0.4) 2630, 2800; (56, 0.2) 2800, 5370.  (An S that makes the iterate grow is not looked for: with a random matrix of norm 2 added
+// to short_video's, 8600 and 10 080; reports of the rows on the way, by which the launch could give up, cost 2 % of every other call.)
+constexpr float kListaSupportFall = 0.25f;
+bool lista_thresholds_fall(const float* thetas, int iters) {
+    for (int t = 1; t < iters; ++t)
+        if (!(std::fabs(thetas[t]) >= kListaSupportFall * std::fabs(thetas[0]))) return true;
+    return false;
+}
 template <typename T>
 csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x, const float* Y, const void* S,
                     const void* Bw, const float* thetas, int iters, float* X, const void* V, void* C, hipStream_t st) {
@@ -1640,7 +1651,7 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
                        use_big_gemm<T>(GemmArgs{nullptr, w.ldm, 0, nullptr, w.ldm, 0, (int)rows, d.n, d.m, 0}, w.ldn) &&
                        lista_choice() != 1;
     SupportRule rule;
-    if (tiled && lista_support_applies(d, rows, iters)) {
+    if (tiled && lista_support_applies(d, rows, iters) && (support_choice() == 2 || !lista_thresholds_fall(thetas, iters))) {
         rule.ctl = (const uint32_t*)w.Status + kSupportWord;
         rule.limit = (uint32_t)std::min(4294967295.0, lista_support_limit(d, rows));
         CSAT_TRY(support_begin(w, st));

@@ -1302,3 +1302,35 @@ def test_packed_rows_of_a_square_matrix(n, options):
         (C, words), (C1, _) = out
         assert words[18] == stay and (words[16] == 0) == (stay <= fit)
         assert float((C - C1).norm() / C1.norm()) < 2e-6      # (sums of the synthesis in another order)
+
+
+# thresholds of lambda from .. to, the lowest in the middle or at the end; whether the device is asked at all
+@pytest.mark.parametrize("first,low,last,asked", [(1.25, 0.9, 0.75, True), (1.25, 0.75, 0.32, True), (1.25, 0.75, 0.3, False), (1.25, 0.3, 1.0, False), (0.0, 0.5, 1.0, True)])
+def test_unrolled_decoder_whose_thresholds_fall(first, low, last, asked, options):
+    """Thresholds that fall far below the first layer's leave an iterate that its count says nothing of: such a call stays on the layers over all columns."""
+    heads, n_q, n, m, d, layers = 8, 701, 700, 200, 64, 21
+    g = torch.Generator(device=DEV).manual_seed(d)
+    Phi = torch.randn(m, n, generator=g, device=DEV) / m ** 0.5
+    mu = float(1.0 / torch.linalg.matrix_norm(Phi, 2) ** 2)
+    S, B = (torch.eye(n, device=DEV) - mu * torch.matmul(Phi.t().contiguous(), Phi)).bfloat16(), (mu * Phi.t()).bfloat16().contiguous()
+    Y = 0.02 * torch.randn(heads, n_q, m, generator=g, device=DEV)
+    Y += 0.4 * Phi.t()[torch.randint(0, n, (heads, n_q), generator=g, device=DEV)]
+    V = torch.randn(heads, n, d, generator=g, device=DEV).bfloat16()
+    half = layers // 2
+    thetas = [mu * 0.1 * (first + (low - first) * t / half if t < half else low + (last - low) * (t - half) / half) for t in range(layers)]
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "bf16")
+
+    def decode(choice):
+        options("support", choice)
+        ws = torch.empty(csat.csat_lista_workspace_bytes(dims, layers), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        X, C = torch.empty(heads, n_q, n, device=DEV), torch.empty(heads, n_q, d, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover_lista(dims, Y, S, B, thetas, X, V, C, ws)
+        return X, C, ws[:256].view(torch.int32).tolist()
+
+    X, C, words = decode(0)
+    X1, C1, _ = decode(1)
+    assert words[9] == (0 if asked else -1)
+    if not asked or words[8] > heads * n_q / 4 * 24:
+        assert torch.equal(X, X1) and torch.equal(C, C1)
+    else:      # as test_unrolled_decoder_over_the_support
+        assert float((X1 - X).norm() / X.norm()) < 1e-3 and float((C1.float() - C.float()).norm() / C.float().norm()) < 4e-3

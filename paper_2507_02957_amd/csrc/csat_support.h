@@ -10,6 +10,11 @@
 
 namespace csat {
 
+// n more in ctl[0]; a sum that a word does not hold sets ctl[1] (a dense iterate, whose sum would read as next to nothing).
+__device__ __forceinline__ void support_add(uint32_t* ctl, float n) {
+    const uint32_t more = n < 4294967040.f ? (uint32_t)n : 0xffffffffu, before = atomicAdd(ctl, more);
+    if (before + more < before) ctl[1] = 1u;
+}
 // Adds the non-zero float4 that the mask bytes name to ctl[0].
 // (packed rows, csat_screen.h: of their 32-row tiles, the number scaled to all rows, which the limit is for)
 // v (optional): ctl[1] is set where one of its pieces (bf16) holds an infinity or NaN.
@@ -32,7 +37,7 @@ static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* 
     __shared__ uint32_t part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(ctl, (uint32_t)((part[0] + part[1] + part[2] + part[3]) * scale));
+    if (threadIdx.x == 0) support_add(ctl, (part[0] + part[1] + part[2] + part[3]) * scale);
 }
 
 // DT[j][i] = D[i][j], both [n, ld] with zero pads, 64 x 64 tiles through LDS.
@@ -466,7 +471,7 @@ static __global__ __launch_bounds__(256) void support_count_f32_kernel(const flo
     __shared__ uint32_t part[4];
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = c;
     __syncthreads();
-    if (threadIdx.x == 0) atomicAdd(ctl, (uint32_t)((part[0] + part[1] + part[2] + part[3]) * (float)stride * ((float)all / (rows > 0 ? rows : 1))));
+    if (threadIdx.x == 0) support_add(ctl, (part[0] + part[1] + part[2] + part[3]) * (float)stride * ((float)all / (rows > 0 ? rows : 1)));
 }
 
 // r = y - Phi x over the support of a float iterate, in float: a wavefront per row, which collects the row's non-zero coefficients as it reads

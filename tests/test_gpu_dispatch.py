@@ -1334,3 +1334,29 @@ def test_unrolled_decoder_whose_thresholds_fall(first, low, last, asked, options
         assert torch.equal(X, X1) and torch.equal(C, C1)
     else:      # as test_unrolled_decoder_over_the_support
         assert float((X1 - X).norm() / X.norm()) < 1e-3 and float((C1.float() - C.float()).norm() / C.float().norm()) < 4e-3
+
+
+def test_count_of_a_dense_iterate_does_not_wrap(options):
+    """Just below 2^32 elements of a float iterate, all of them non-zero: every eighth row, counted eight times, is more than a word holds."""
+    heads, n_q, n, m, d, iters = 5, 42949, 20000, 256, 64, 2
+    rows = heads * n_q
+    assert rows * n < 2 ** 32 < (rows + 7) // 8 * 8 * n
+    g = torch.Generator(device=DEV).manual_seed(n)
+    Phi = torch.randn(m, n, generator=g, device=DEV) / m ** 0.5
+    Y = torch.randn(heads, n_q, m, generator=g, device=DEV)
+    V = torch.randn(heads, n, d, generator=g, device=DEV)
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "f32")
+    ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV)
+    ws[:256].fill_(0xFF)
+    C = torch.empty(heads, n_q, d, device=DEV)
+    csat.csat_recover(dims, Y, Phi, 0.0, 0.25 * m / n, iters, None, V, C, ws)
+    count, not_sparse = ws[:256].view(torch.int32).tolist()[8:10]
+    assert not_sparse != 0 or count % 2 ** 32 > 0.025 * rows * n
+    # x after two iterations from zero, of some rows
+    P, mu = Phi.double(), 0.25 * m / n
+    y = Y.view(rows, m)[[0, rows // 2, rows - 1]].double()
+    x = mu * torch.matmul(y, P)
+    x = x + mu * torch.matmul(y - torch.matmul(x, P.t().contiguous()), P)
+    want = torch.stack([torch.matmul(x[i], V[h].double()) for i, h in enumerate((0, rows // 2 // n_q, heads - 1))])
+    got = C.view(rows, d)[[0, rows // 2, rows - 1]].double()
+    assert float((got - want).norm() / want.norm()) < 1e-5

@@ -24,6 +24,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <numeric>
 #include <thread>
 #include <vector>
 
@@ -1143,7 +1144,10 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T
     HIP_TRY(hipGetLastError());
     // the fused decoder has neither operand of the product; the others have the first residual
     if (w.fused) CSAT_TRY(transpose_pack<T>(Phi, (T*)w.PhiT, w.ldm, 1, d.m, d.n, st));
-    const long long stride = std::max<long long>(1, rows / std::max<long long>(512, rows / 64)), sample = rows / stride;
+    // every so many rows, and no divisor of a head's: rows of one place in their heads are often alike
+    long long stride = std::max<long long>(1, rows / std::max<long long>(512, rows / 64));
+    while (std::gcd(stride, (long long)d.n_q) != 1) ++stride;
+    const long long sample = rows / stride;
     ScreenRowsArgs ra{nullptr, nullptr, sample, (int)stride, Y, ldY, y_tiled, nullptr, 0, 0, w.R, w.ldm, kBf16, d.m};
     if (w.fused) CSAT_TRY(screen_rows<T>(w, ra, st));
     auto product = [&](long long M, long long lda, const uint32_t* off) -> csat_status {

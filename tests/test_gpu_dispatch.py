@@ -1360,3 +1360,25 @@ def test_count_of_a_dense_iterate_does_not_wrap(options):
     want = torch.stack([torch.matmul(x[i], V[h].double()) for i, h in enumerate((0, rows // 2 // n_q, heads - 1))])
     got = C.view(rows, d)[[0, rows // 2, rows - 1]].double()
     assert float((got - want).norm() / want.norm()) < 1e-5
+
+
+@pytest.mark.parametrize("every,packs", [(64, True), (1, False)])
+def test_sample_of_rows_meets_every_place_in_a_head(every, packs, options):
+    """Heads of a multiple of 64 rows whose every 64th has coefficients: the sample that decides on packing is not of those alone."""
+    heads, n_q, n, m, d, iters = 48, 2048, 700, 200, 64, 50
+    g = torch.Generator(device=DEV).manual_seed(every)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).bfloat16()
+    Y = torch.zeros(heads, n_q, m, device=DEV)
+    Y[:, ::every] = 0.4 * Phi.float().t()[torch.randint(0, n, (heads, n_q // every), generator=g, device=DEV)]
+    V = torch.randn(heads, n, d, generator=g, device=DEV).bfloat16()
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "bf16")
+    out = []
+    for choice in (0, 1):
+        options("screen", choice)
+        ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(heads, n_q, d, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover(dims, Y, Phi, 0.1, 0.25 * m / n, iters, None, V, C, ws)
+        out.append((C.float(), ws[:256].view(torch.int32).tolist()))
+    (C, words), (C1, _) = out
+    assert (words[16] == 0) == packs and (not packs or words[18] == heads * n_q // every)
+    assert float((C - C1).norm() / C1.norm()) < 4e-3      # as test_rows_without_coefficients_left_out

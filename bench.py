@@ -365,8 +365,9 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
     rows = w.B * w.H * (w.d if args.mode in ("columns", "columns_hadamard") else w.n_q)      # decoder problems
     # rows that the decoder ran: where the library left out those without any coefficient (words 16 and 18 of the workspace's
     # status block, which starts as -1 here), the others; the decoder's figures below are of these, `value` of the method as defined
-    words = ws.view(torch.int32)[16:19].tolist()
-    decoded = words[2] if args.mode == "rows" and words[0] == 0 else rows
+    words = ws.view(torch.int32)[:32].tolist()
+    decoded = words[18] if args.mode == "rows" and words[16] == 0 else rows
+    over_support = args.mode == "lista" and words[10] == 1      # the unrolled decoder's layers ran over the support of their iterate
     all_rows, rows = rows, decoded
     T = w.iters
     fused = prof["residual"][1] == 0 and args.mode in ("rows", "columns")          # one launch runs every ISTA iteration
@@ -483,8 +484,11 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
             roof["mfma_frac_of_achievable"] = roof["mfma_tflops"] / pk["mfma_loop_TFLOPps"]
         roof["hbm_algorithmic_frac_of_achievable"] = roof["hbm_algorithmic_gbs"] / pk["stream_copy_GBps"]
 
-    if args.mode == "lista" and roof["mfma_frac"] > 1.0:      # the layers ran over the support of a sparse iterate
-        roof.update(kernel="lista_support_kernel", bound="l2", achieved=None, frac=None, executed_flops=None, executed_over_algorithmic=None)
+    if over_support:      # (the figures above are of products that did not run)
+        roof.update({k: None for k in ("achieved", "frac", "algorithmic_bytes", "arithmetic_intensity_flop_per_byte", "executed_flops", "executed_over_algorithmic",
+                                       "mfma_tflops", "mfma_frac", "mfma_frac_of_achievable", "hbm_algorithmic_gbs", "hbm_algorithmic_frac",
+                                       "hbm_algorithmic_frac_of_achievable") if k in roof}, kernel="lista_support_kernel", bound="l2",
+                    avg_launch_us=ms_dom / prof_steps * 1e3, launches_per_step=1.0)
     roof["rows_decoded"], roof["rows"] = decoded, all_rows
     flops = nominal_flops(w, args.mode, args.picks)
     out = {
@@ -500,7 +504,7 @@ def measure(args, workload, steps, warmup, with_peaks, with_cpu):
                    "iters": w.iters, "lambda": w.lam, "phi": w.phi_kind, "decode": args.mode,
                    "launch": "hip graph replay" if args.graph else "eager",
                    **({"picks": args.picks} if args.mode == "omp" else {})},
-        "nominal_flops": flops,
+        "nominal_flops": flops,      # of every row and coefficient: `value` counts what a sparse call leaves out too (roofline.rows_decoded)
         "stage_ms": stage_ms,
         "roofline": roof,
     }

@@ -155,7 +155,8 @@ bool sparse_state(size_t dense_state_bytes) {
 
 constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_static's workspace
 
-// The decoders' rule for products over the support of the iterate (csat_support.h), its words in the workspace's status block.
+// The decoders' rule for products over the support of the iterate (csat_support.h), its words in the workspace's status block (a third: 1 where the unrolled
+// decoder's layers ran over theirs).
 int support_choice() { return (*tl_opt)[CSAT_OPT_SUPPORT]; }      // 1: never; 2: wherever a kernel exists
 constexpr int kSupportWord = 8;
 int screen_choice() { return (*tl_opt)[CSAT_OPT_SCREEN]; }        // 1: never; 2: wherever it applies
@@ -1050,7 +1051,7 @@ csat_status launch_ista_fused(int MT, IstaFusedArgs a, long long rows_pad, hipSt
 
 // Clears the rule's words.
 csat_status support_begin(const Workspace& w, hipStream_t st) {
-    hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(64), 0, st, w.Status, 0, (uint32_t*)w.Status + kSupportWord, 2ll);
+    hipLaunchKernelGGL(set_word_kernel, dim3(1), dim3(64), 0, st, w.Status, 0, (uint32_t*)w.Status + kSupportWord, 3ll);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }

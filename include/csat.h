@@ -277,7 +277,8 @@ typedef enum {
     CSAT_FORM_OMP_PICK = 5,          /* matching pursuit's pick: 1 a search over stored correlations, 2 while Phi's columns pass, 3 in the large-tile product */
     CSAT_FORM_OMP_REFIT = 6,         /* matching pursuit's orthonormal vectors: 1 held in registers, 2 stored */
     CSAT_FORM_RESIDUAL = 7,          /* large-tile decoder's residual: parts of the product along K, 16 more where its kernel over the support is a launch of its own */
-    CSAT_FORM_COUNT = 8
+    CSAT_FORM_SCREEN_TILE = 8,       /* rows left out, bf16: columns of a tile of the product that finds them (256 or 320), 0 where none was looked for */
+    CSAT_FORM_COUNT = 9
 } csat_launch_form;
 csat_status csat_profile_launch_form(void* ctx, int form, int* value);
 

@@ -30,7 +30,7 @@ OPTIONS = {"decoder": 0, "gemm": 1, "raster": 2, "state": 3, "fused_segments": 4
            "measure": 12, "synthesis": 13, "y_layout": 14, "support": 15, "screen": 16}
 # forms of csat_profile_launch_form (include/csat.h, csat_launch_form)
 LAUNCH_FORMS = {"decoder_members": 0, "small_tiles": 1, "attention_waves": 2, "lista_tile": 3, "omp_shares": 4, "omp_pick": 5, "omp_refit": 6,
-                "residual": 7}
+                "residual": 7, "screen_tile": 8}
 CSAT_ERR_TIMEOUT = -8
 KERNEL_IDS = {"layout": 0, "measure": 1, "scores": 2, "softmax": 3, "output": 4, "residual": 5, "update": 6,
               "synthesis": 7}

@@ -1156,7 +1156,9 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T
         const EpiScreen e{stay, mu, theta * kScreenMargin, M, d.n, {off}};
         if constexpr (kBf16) {
             g.K = (int)round_up(g.K, 64);
-            if (wide_tiles_pay(g, d.n)) return launch_gemm_big_shape<EpiScreen, 4, 2, 64, 5>(g, d.n, 1, e, st);
+            const bool wide = wide_tiles_pay(g, d.n);
+            tl_forms[CSAT_FORM_SCREEN_TILE] = wide ? 320 : 256;      // (of all rows: the sample's comes first)
+            if (wide) return launch_gemm_big_shape<EpiScreen, 4, 2, 64, 5>(g, d.n, 1, e, st);
             return launch_gemm_big(g, d.n, 1, e, st);
         } else {
             return launch_gemm_f32(g, d.n, 1, e, st);

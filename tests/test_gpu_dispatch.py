@@ -1383,3 +1383,39 @@ def test_sample_of_rows_meets_every_place_in_a_head(every, packs, options):
     (C, words), (C1, _) = out
     assert (words[16] == 0) == packs and (not packs or words[18] == heads * n_q // every)
     assert float((C - C1).norm() / C1.norm()) < 4e-3      # as test_rows_without_coefficients_left_out
+
+
+# (n_q, n, m, iterations): three heads of rows that take fewer rounds on the wider tile, last tiles of rows and of columns that are not whole; the
+# two-chunk decoder and the large-tile pair
+@pytest.mark.parametrize("n_q,n,m,iters", [(4099, 1571, 392, 3), (4096, 1600, 264, 3), (4100, 1300, 640, 3)])
+def test_rows_left_out_are_found_on_wide_tiles(n_q, n, m, iters, options):
+    """Every row that leans on one column of Phi stays, whichever element of a tile that is, and no other; C against float64."""
+    heads, d = 3, 64
+    g = torch.Generator(device=DEV).manual_seed(n + m)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).bfloat16()
+    rows = heads * n_q
+    lean = torch.rand(rows, generator=g, device=DEV) < 0.3
+    cols = torch.randint(0, n, (rows,), generator=g, device=DEV)
+    Y = 0.002 * torch.randn(rows, m, generator=g, device=DEV)
+    Y[lean] += 0.3 * Phi.float().t()[cols[lean]]
+    # 0.3 |phi|^2 on that column, at most 0.3 |phi_i phi_j| on the others: the rest is noise of 0.002
+    mu, lam = 0.25 * m / n, 0.18
+    peak = torch.matmul(Y.double(), Phi.double()).abs().amax(1)
+    assert bool(((peak > 1.02 * lam) == lean).all()) and not bool(((peak - lam).abs() < 0.02 * lam).any())
+    V = torch.randn(heads, n, d, generator=g, device=DEV).bfloat16()
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "bf16")
+    options("screen", 2)
+    ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+    C = torch.empty(heads, n_q, d, dtype=torch.bfloat16, device=DEV).fill_(7.0)
+    csat.csat_recover(dims, Y.view(heads, n_q, m), Phi, lam, mu, iters, None, V, C, ws)
+    assert csat.csat_profile_launch_form("screen_tile") == 320
+    words = ws[:256].view(torch.int32).tolist()
+    assert words[16] == 0 and words[18] == int(lean.sum())
+    x = torch.zeros(rows, n, dtype=torch.float64, device=DEV)
+    P = Phi.double()
+    for _ in range(iters):
+        u = x + mu * torch.matmul(Y.double() - torch.matmul(x, P.t().contiguous()), P)
+        x = u.sign() * (u.abs() - mu * lam).clamp_min(0.0)
+    want = torch.matmul(x.view(heads, n_q, n), V.double()).view(rows, d)
+    C = C.view(rows, d)
+    assert bool((C[~lean] == 0).all()) and float((C.double() - want).norm() / want.norm()) < 2e-2

@@ -155,8 +155,7 @@ bool sparse_state(size_t dense_state_bytes) {
 
 constexpr size_t kStaticScratchBytes = (size_t)48 << 20;      // csat_forward_static's workspace
 
-// The decoders' rule for products over the support of the iterate (csat_support.h), its words in the workspace's status block (a third: 1 where the unrolled
-// decoder's layers ran over theirs).
+// The decoders' rule for products over the support of the iterate (csat_support.h), its words in the workspace's status block.
 int support_choice() { return (*tl_opt)[CSAT_OPT_SUPPORT]; }      // 1: never; 2: wherever a kernel exists
 constexpr int kSupportWord = 8;
 int screen_choice() { return (*tl_opt)[CSAT_OPT_SCREEN]; }        // 1: never; 2: wherever it applies
@@ -1079,12 +1078,19 @@ bool residual_support_apart(const csat_dims& d, long long rows) { return (double
 // ... and up to which density: non-zero float4 (four rows of a column) that the first iteration may leave to every four rows.  Forward over
 // all columns against over the support, us.  Apart: 205 824 rows, n = 1608, m = 752, 11 iterations: 2 a quad 14 910, 9750; 18 14 990, 12 490;
 // 38 976 rows, n = 9744, m = 1024, 31 iterations: 10 54 400, 29 900; 142 54 100, 38 900; 394 54 700, 50 700; 13 104 rows, n = 11 744: 100 9940,
-// 7360; 368 10 100, 9850.  In the product's place: 28 544 rows, n = 1824, m = 745, 31 iterations: none 7290, 4080; 2 7220, 5460; 14 7290, 6770; 48 000
+// 7360; 368 10 100, 9850.  In the product's place: 28 544 rows, n = 1824, m = 745, 31 iterations: none 7160, 3820; 5 7170, 5960; 22 7210, 7780; 48 000
 // rows: 45 12 130, 14 390; few rows, whose longest lists end the launch: 8192 rows, n = 2048, m = 600, 20 iterations: 4 1660, 1450; 10 1670,
-// 1750; 4272 rows, n = 6496, 36 iterations: 24 5850, 5640; 78 5860, 6950; 3432 rows, n = 13 713, 9 iterations: 16 4240, 2640; 394 4250, 5440.
-double residual_support_limit(const csat_dims& d, long long rows) {
+// 1750; 4272 rows, n = 6496, 36 iterations: 24 5850, 5640; 78 5860, 6950; 3432 rows, n = 13 713, 9 iterations: 50 3890, 2590; 392 3900, 4880; 9000 rows,
+// n = 5000, m = 1024, 20 iterations: 37 4960, 4710; 142 5000, 6650.  A product that ends after few steps of few rounds of tiles leaves less to
+// win: where both are as quick goes with the square of `steps`, its columns times its rounds (45 shapes): 12 800 rows, n = 2000, m = 1000 (one
+// round): 2 2940, 2600; 14 2940, 3550; 15 168 rows, n = 3008, m = 1024: 6 4290, 3880; 25 4330, 4650; 30 624 rows, n = 1425, m = 953 (two),
+// 16 iterations: 3 3430, 3190; 10 3460, 3820.
+double residual_support_limit(const csat_dims& d, const Workspace& w, long long rows) {
     if (support_choice() == 2) return 4294967295.0;
-    return rows / 4.0 * d.n / (residual_support_apart(d, rows) ? 64 : rows >= 12288 ? 128 : 270);
+    const double quads = rows / 4.0 * d.n;
+    if (residual_support_apart(d, rows)) return quads / 64;
+    const double share = rows >= 12288 ? 128 : 270, rounds = (double)(((rows + 255) / 256 * ((w.ldm + 255) / 256) + cu_count() - 1) / cu_count()), steps = d.n * rounds;
+    return quads / (w.split > 1 ? share : std::max(share, 2.5e9 / (steps * steps)));
 }
 
 // ... and the float decoder's, in the product's place (rows that take a few microseconds each, however short Phi's columns are: not below m = 256, where
@@ -1287,7 +1293,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         if (residual_support_applies(d, rows, iters) && use_big_gemm<T>(gr, w.ldm) && use_big_gemm<T>(gu, w.ldn) &&
             (w.split > 1 || (ldY % 4 == 0 && aligned16(Y)))) {
             rule.ctl = (const uint32_t*)w.Status + kSupportWord;
-            rule.limit = (uint32_t)std::min(4294967295.0, residual_support_limit(d, rows));
+            rule.limit = (uint32_t)std::min(4294967295.0, residual_support_limit(d, w, rows));
             CSAT_TRY(support_begin(w, st));
         }
     }

@@ -237,14 +237,17 @@ __global__ __launch_bounds__(256, BN == 128 ? 3 : 4) void gemm_nt_kernel(GemmArg
 
 constexpr uint32_t kBufferFlags = 0x00027000;      // raw 32-bit buffer descriptor word 3 (gfx9 family)
 
-// Whether the iterate is sparse enough for the kernels over its support (csat_support.h), decided on the device.  Two words: [0]
+// Whether the iterate is sparse enough for the kernels over its support (csat_support.h), decided on the device.  Three words: [0]
 // non-zero float4 of the iterate (four rows of a column), [1] an operand holds an infinity or NaN, whose products with
-// zeros are not zero.
+// zeros are not zero, [2] 1 where the bf16 ones ran, which they note.
 struct SupportRule {
     const uint32_t* ctl = nullptr;      // null: over all columns
     uint32_t limit = 0;
     __device__ __forceinline__ bool sparse(uint2 w) const { return (ctl != nullptr) & (w.x <= limit) & (w.y == 0); }
     __device__ __forceinline__ bool sparse() const { return ctl && sparse(*(const uint2*)ctl); }
+    __device__ __forceinline__ void note() const {
+        if (blockIdx.x + blockIdx.y + blockIdx.z + threadIdx.x == 0) ((uint32_t*)ctl)[2] = 1u;
+    }
     // the words without a branch, to be asked for together with other loads
     __device__ __forceinline__ uint2 words() const {
         typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));

@@ -40,10 +40,10 @@ static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* 
     if (threadIdx.x == 0) support_add(ctl, (part[0] + part[1] + part[2] + part[3]) * scale);
 }
 
-// DT[j][i] = D[i][j], both [n, ld] with zero pads, 64 x 64 tiles through LDS.  Notes in the rule's third word that the layers run over the support.
+// DT[j][i] = D[i][j], both [n, ld] with zero pads, 64 x 64 tiles through LDS.
 static __global__ __launch_bounds__(256) void support_transpose_kernel(SupportRule rule, const bf16_t* D, bf16_t* DT, int n, int ld) {
     if (!rule.sparse()) return;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) ((uint32_t*)rule.ctl)[2] = 1u;
+    rule.note();
     __shared__ bf16_t tile[64][66];
     const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64, tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
     for (int i = ty; i < 64; i += 4) tile[i][tx] = r0 + i < n && c0 + tx < n ? D[(long long)(r0 + i) * ld + c0 + tx] : (bf16_t)0;
@@ -431,6 +431,7 @@ __device__ __forceinline__ void residual_support(ResidualSupportArgs a, Residual
 template <int MR>
 __global__ __launch_bounds__(256, MR > 12 ? 3 : 4) void residual_support_kernel(SupportRule rule, ResidualSupportArgs a) {
     if (!rule.sparse()) return;
+    if (a.first) rule.note();
     __shared__ ResidualSupportLds<MR, 4> l;
     residual_support<MR, 4>(a, l, blockIdx.x, gridDim.x);
 }
@@ -450,6 +451,7 @@ struct EpiResidualEither : Epi {
     __device__ __forceinline__ void instead(void* lds) const {
         if constexpr (MR > 0) {
             const long long all = (long long)gridDim.x * gridDim.z, blocks = all < 256 ? all : 256, block = blockIdx.x + (long long)gridDim.x * blockIdx.z;
+            if (s.first) rule.note();
             if (block < blocks) residual_support<MR, kWaves>(s, *(ResidualSupportLds<MR, kWaves>*)lds, block, blocks);
         }
     }

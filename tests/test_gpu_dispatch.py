@@ -1419,3 +1419,34 @@ def test_rows_left_out_are_found_on_wide_tiles(n_q, n, m, iters, options):
     want = torch.matmul(x.view(heads, n_q, n), V.double()).view(rows, d)
     C = C.view(rows, d)
     assert bool((C[~lean] == 0).all()) and float((C.double() - want).norm() / want.norm()) < 2e-2
+
+
+# (rows, n, m, columns that a row leans on, whether the residual runs over the support): products of one and of two rounds of tiles, whose few steps leave
+# little to win, and few rows of long columns
+@pytest.mark.parametrize("rows,n,m,lean,sparse", [(12800, 2000, 1000, 3, False), (12800, 2000, 1000, 0.5, True), (28544, 1824, 744, 2, True), (28544, 1824, 744, 3, False),
+                                                  (3432, 13713, 1024, 8, True), (3432, 13713, 1024, 16, False)])
+def test_residual_over_the_support_where_it_is_quicker(rows, n, m, lean, sparse, options):
+    """The density up to which the residual's kernel over the support takes the product's place, as the device notes."""
+    d, iters = 64, 3
+    g = torch.Generator(device=DEV).manual_seed(n)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).bfloat16()
+    Y = 0.002 * torch.randn(rows, m, generator=g, device=DEV)
+    for _ in range(max(1, int(lean))):
+        some = torch.rand(rows, 1, generator=g, device=DEV) < lean
+        Y += some * 0.4 * Phi.float().t()[torch.randint(0, n, (rows,), generator=g, device=DEV)]
+    V = torch.randn(8, n, d, generator=g, device=DEV).bfloat16()
+    dims = csat.make_dims(1, 8, rows // 8, n, d, m, "bf16")
+    options("screen", 1)
+    out = []
+    for choice in (0, 1, 2):
+        options("support", choice)
+        ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(8, rows // 8, d, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover(dims, Y.view(8, rows // 8, m), Phi, 0.25, 0.25 * m / n, iters, None, V, C, ws)
+        assert csat.csat_profile_launch_form("residual") == 1
+        out.append((C, ws[:256].view(torch.int32).tolist()))
+    (C, words), (C1, words1), (C2, words2) = out
+    # pieces of four rows that the first iteration leaves, almost all of a column each
+    assert 0.9 * lean * rows < words[8] < 1.1 * lean * rows and words[9] == 0
+    assert words[10] == int(sparse) and words1[10] == -1 and words2[10] == 1
+    assert torch.equal(C, C2 if sparse else C1)

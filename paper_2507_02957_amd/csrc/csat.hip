@@ -1130,8 +1130,7 @@ bool screen_applies(const csat_dims& d, const Workspace& w, const void* X, const
     }
     return screen_choice() == 2 || 4.0 * iters * rows * d.n * d.m > (d.dtype == CSAT_BF16 ? 2.5e12 : 3e11);
 }
-template <typename T>
-csat_status screen_rows(const Workspace& w, ScreenRowsArgs a, hipStream_t st) {
+csat_status screen_rows(const ScreenRowsArgs& a, hipStream_t st) {
     hipLaunchKernelGGL(screen_rows_kernel, dim3((unsigned)std::min<long long>((a.rows + 3) / 4, 8ll * cu_count())), dim3(256), 0, st, a);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
@@ -1156,7 +1155,7 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T
     while (std::gcd(stride, (long long)d.n_q) != 1) ++stride;
     const long long sample = rows / stride;
     ScreenRowsArgs ra{nullptr, nullptr, sample, (int)stride, Y, ldY, y_tiled, nullptr, 0, 0, w.R, w.ldm, kBf16, d.m};
-    if (w.fused) CSAT_TRY(screen_rows<T>(w, ra, st));
+    if (w.fused) CSAT_TRY(screen_rows(ra, st));
     auto product = [&](long long M, long long lda, const uint32_t* off) -> csat_status {
         GemmArgs g{w.R, lda, 0, w.PhiT, w.ldm, 0, (int)M, d.n, d.m, 0};
         const EpiScreen e{stay, mu, theta * kScreenMargin, M, d.n, {off}};
@@ -1178,7 +1177,7 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T
         ra.words = sample_words;
         ra.rows = rows;
         ra.stride = 1;
-        CSAT_TRY(screen_rows<T>(w, ra, st));
+        CSAT_TRY(screen_rows(ra, st));
     }
     CSAT_TRY(product(rows, w.ldm, sample_words));
     // whole 256 rows of packed y behind the first half of the iterate, whose rows may be shorter than y's (m close to n, in float: 8 and 32 the multiples)
@@ -1190,7 +1189,7 @@ csat_status screen(const csat_dims& d, const Workspace& w, const T* Phi, const T
     HIP_TRY(hipGetLastError());
     hipLaunchKernelGGL(screen_place_kernel, dim3((unsigned)blocks), dim3(256), 0, st, on, words, (const uint32_t*)stay, rows, counts, Place, List, (int)most);
     HIP_TRY(hipGetLastError());
-    CSAT_TRY(screen_rows<T>(w, ScreenRowsArgs{words, List, rows, 1, Y, ldY, y_tiled, Yp, w.ldy, y_tiled, w.fused ? nullptr : w.R, w.fused ? 0 : w.ldm, kBf16, d.m}, st));
+    CSAT_TRY(screen_rows(ScreenRowsArgs{words, List, rows, 1, Y, ldY, y_tiled, Yp, w.ldy, y_tiled, w.fused ? nullptr : w.R, w.fused ? 0 : w.ldm, kBf16, d.m}, st));
     *plan = ScreenPlan{words, Place, Yp, w.ldy};
     return CSAT_OK;
 }
@@ -1310,8 +1309,8 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
             g.M = (int)rows;
             g.screen = plan.words;
             Timed tm(w, CSAT_K_RESIDUAL, st);
-            if constexpr (!kBf16) {
-                if (rule.ctl) {
+            auto residual_f32 = [&]() -> csat_status {
+                if constexpr (!kBf16) {
                     if (t == 1) {
                         hipLaunchKernelGGL(support_count_f32_kernel, dim3((unsigned)std::min<long long>((rows + 7) / 8, cu_count())), dim3(256), 0, st, w.Xs, w.ldn, rows, d.n, 8,
                                            (uint32_t*)w.Status + kSupportWord, plan.words, (const float*)w.PhiT, d.n * w.ldm);
@@ -1324,11 +1323,12 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
                         if (!plan.words) return launch_gemm_f32(g, w.ldm, 1, EpiResidualEitherF32<EpiResidual<float>, MR>{er, rule, sf}, st);
                         return launch_gemm_f32(g, w.ldm, 1, EpiResidualEitherF32<EpiScreened<EpiResidual<float>>, MR>{{er}, rule, sf}, st);
                     };
-                    if (w.ldm <= 256) CSAT_TRY(launch(std::integral_constant<int, 1>{}));
-                    else if (w.ldm <= 512) CSAT_TRY(launch(std::integral_constant<int, 2>{}));
-                    else CSAT_TRY(launch(std::integral_constant<int, 4>{}));
+                    if (w.ldm <= 256) return launch(std::integral_constant<int, 1>{});
+                    if (w.ldm <= 512) return launch(std::integral_constant<int, 2>{});
+                    return launch(std::integral_constant<int, 4>{});
                 }
-            }
+                return CSAT_OK;
+            };
             const ResidualSupportArgs sa{w.Mask, (const f32x4*)w.Xs, w.ldn / 32, (const bf16_t*)w.PhiT, (int)w.ldm, Y, ldY, (bf16_t*)w.R, (uint8_t*)w.KT + support_same, rows, d.m, t == 1, plan.words, plan.Y, plan.ldY};
             auto launch_residual = [&](const auto& epi, const GemmArgs& ga, int parts) -> csat_status {
                 using Epi = std::decay_t<decltype(epi)>;
@@ -1349,7 +1349,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
             };
             if (kBf16 && rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, plan.words, rows));
             if (!kBf16 && rule.ctl) {
-                // (launched above)
+                CSAT_TRY(residual_f32());
             } else if (w.split > 1 && use_big_gemm<T>(g, w.ldm)) {     // partial products along K, then r = y - their sum
                 GemmArgs gs = g;
                 gs.K = (int)(w.ldn / w.split);
@@ -1644,7 +1644,7 @@ double lista_support_limit(const csat_dims& d, long long rows) {
 constexpr float kListaSupportFall = 0.25f;
 bool lista_thresholds_fall(const float* thetas, int iters) {
     for (int t = 1; t < iters; ++t)
-        if (!(std::fabs(thetas[t]) >= kListaSupportFall * std::fabs(thetas[0]))) return true;
+        if (thetas[t] < kListaSupportFall * thetas[0]) return true;
     return false;
 }
 template <typename T>

@@ -8,8 +8,9 @@
 // rows instead of 600, 1.35 ms (a chain of 20 iterations) instead of 3.2. A forward 3.49 -> 1.75 ms; float, 19 200 rows 6.91 -> 2.31 (with the
 // residual over the support); 205 824 rows, n = 1608, m = 752, one of a hundred left 9.7 -> 2.5.
 //
-// A row stays unless |mu Phi^T y| <= (1 - 2^-8) theta everywhere, so that the decoder's own sums, in whatever order, would have
-// given zero too; NaN and infinities stay.
+// A row stays unless |mu Phi^T y| <= (1 - 2^-8) theta everywhere; NaN and infinities stay.  The decoder's own sums, in another order, then give zero
+// too, as long as they differ by less than lambda / 256 (a few roundings of 2^-24 of sum |phi y|).  Below such a lambda (1e-4 of sum |phi y|) a coefficient that is
+// the rounding of these sums may be left out; zero is as near to the exact value.
 #pragma once
 #include "csat_kernels.h"
 

@@ -448,9 +448,9 @@ struct EpiResidualEither : Epi {
     static constexpr int kWaves = 8;
     SupportRule rule;
     ResidualSupportArgs s;
-    __device__ __forceinline__ void instead(void* lds) const {
+    __device__ __forceinline__ void instead(void* lds, uint32_t block, uint32_t all) const {
         if constexpr (MR > 0) {
-            const long long all = (long long)gridDim.x * gridDim.z, blocks = all < 256 ? all : 256, block = blockIdx.x + (long long)gridDim.x * blockIdx.z;
+            const uint32_t blocks = all < 256 ? all : 256;
             if (s.first) rule.note();
             if (block < blocks) residual_support<MR, kWaves>(s, *(ResidualSupportLds<MR, kWaves>*)lds, block, blocks);
         }

@@ -1055,11 +1055,11 @@ csat_status support_begin(const Workspace& w, hipStream_t st) {
     return CSAT_OK;
 }
 // Counts what the first threshold left (its mask bytes, whole 16-byte pieces), and looks V over (in bf16, of v_bytes) where given.
-csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st, const uint32_t* screen = nullptr, long long rows = 0, const void* V = nullptr,
-                          long long v_bytes = 0) {
+csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st, const uint32_t* screen = nullptr, float scale = 0.f, long long rows = 0,
+                          const void* V = nullptr, long long v_bytes = 0) {
     const long long chunks = bytes / 16;
     hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
-                       (uint32_t*)w.Status + kSupportWord, screen, rows, (const uint4*)V, v_bytes / 16);
+                       (uint32_t*)w.Status + kSupportWord, screen, scale, rows, (const uint4*)V, v_bytes / 16);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;
 }
@@ -1081,16 +1081,21 @@ bool residual_support_apart(const csat_dims& d, long long rows) { return (double
 // 7360; 368 10 100, 9850.  In the product's place: 28 544 rows, n = 1824, m = 745, 31 iterations: none 7160, 3820; 5 7170, 5960; 22 7210, 7780; 48 000
 // rows: 45 12 130, 14 390; few rows, whose longest lists end the launch: 8192 rows, n = 2048, m = 600, 20 iterations: 4 1660, 1450; 10 1670,
 // 1750; 4272 rows, n = 6496, 36 iterations: 24 5850, 5640; 78 5860, 6950; 3432 rows, n = 13 713, 9 iterations: 50 3890, 2590; 392 3900, 4880; 9000 rows,
-// n = 5000, m = 1024, 20 iterations: 37 4960, 4710; 142 5000, 6650.  A product that ends after few steps of few rounds of tiles leaves less to
-// win: where both are as quick goes with the square of `steps`, its columns times its rounds (45 shapes): 12 800 rows, n = 2000, m = 1000 (one
-// round): 2 2940, 2600; 14 2940, 3550; 15 168 rows, n = 3008, m = 1024: 6 4290, 3880; 25 4330, 4650; 30 624 rows, n = 1425, m = 953 (two),
-// 16 iterations: 3 3430, 3190; 10 3460, 3820.
-double residual_support_limit(const csat_dims& d, const Workspace& w, long long rows) {
+// n = 5000, m = 1024, 20 iterations: 37 4960, 4710; 142 5000, 6650.  A short product leaves less to win: of its steps (columns times rounds of tiles) the masks
+// and rows take about 1650 in any case, and below 1500 columns, of many rows, the density where both are as quick goes with the square of the steps (70 shapes, of which
+// some turn at half or at four times that density, as their coefficients lie in few rows or in all): 12 800 rows, n = 2000, m = 1000: 2 2940, 2600; 14 2940, 3550; 15 600 rows, n = 2400,
+// m = 800: 6.5 3425, 3140; 15 168 rows, n = 3008, m = 1024: 6 4290, 3880; 25 4330, 4650; 22 232 rows, n = 1582, m = 766, 16 iterations: 7 3180, 2710; 27
+// 3190, 3520; 30 624 rows, n = 1425, m = 953: 3 3430, 3190; 10 3460, 3820.  Not where rows are packed: 29 112 rows, n = 1961, m = 840, 14 of them
+// packed: 20 1710, 1240.
+double residual_support_limit(const csat_dims& d, const Workspace& w, long long rows, bool packed) {
     if (support_choice() == 2) return 4294967295.0;
     const double quads = rows / 4.0 * d.n;
     if (residual_support_apart(d, rows)) return quads / 64;
-    const double share = rows >= 12288 ? 128 : 270, rounds = (double)(((rows + 255) / 256 * ((w.ldm + 255) / 256) + cu_count() - 1) / cu_count()), steps = d.n * rounds;
-    return quads / (w.split > 1 ? share : std::max(share, 2.5e9 / (steps * steps)));
+    const double share = rows >= 12288 ? 128 : 270;
+    if (packed || w.split > 1) return quads / share;
+    const double steps = d.n * (double)(((rows + 255) / 256 * ((w.ldm + 255) / 256) + cu_count() - 1) / cu_count());
+    const double least = d.n >= 1500 ? (double)rows * d.n * d.m / (1.75e5 * std::max(steps - 1650, 50.0)) : std::pow(50000 / steps, 2);
+    return quads / std::max(share, least);
 }
 
 // ... and the float decoder's, in the product's place (rows that take a few microseconds each, however short Phi's columns are: not below m = 256, where
@@ -1292,7 +1297,7 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
         if (residual_support_applies(d, rows, iters) && use_big_gemm<T>(gr, w.ldm) && use_big_gemm<T>(gu, w.ldn) &&
             (w.split > 1 || (ldY % 4 == 0 && aligned16(Y)))) {
             rule.ctl = (const uint32_t*)w.Status + kSupportWord;
-            rule.limit = (uint32_t)std::min(4294967295.0, residual_support_limit(d, w, rows));
+            rule.limit = (uint32_t)std::min(4294967295.0, residual_support_limit(d, w, rows, false));
             CSAT_TRY(support_begin(w, st));
         }
     }
@@ -1347,7 +1352,9 @@ csat_status run_ista(const csat_dims& d, const Workspace& w, const T* Phi, const
                 if (regs <= 12) return launch(std::integral_constant<int, 12>{});
                 return launch(std::integral_constant<int, 16>{});
             };
-            if (kBf16 && rule.ctl && t == 1) CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, plan.words, rows));
+            if (kBf16 && rule.ctl && t == 1)
+                CSAT_TRY(support_count(w, w.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, plan.words,
+                                       (float)(residual_support_limit(d, w, rows, false) / residual_support_limit(d, w, rows, true)), rows));
             if (!kBf16 && rule.ctl) {
                 CSAT_TRY(residual_f32());
             } else if (w.split > 1 && use_big_gemm<T>(g, w.ldm)) {     // partial products along K, then r = y - their sum
@@ -1698,7 +1705,7 @@ csat_status lista_t(const csat_dims& d, const Workspace& w, const ListaExtra& x,
     if constexpr (kBf16) {
         if (rule.ctl) {
             Timed tm(w, CSAT_K_LAYOUT, st);
-            CSAT_TRY(support_count(w, x.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, nullptr, 0, want_c ? V : nullptr, want_c ? (long long)BH * d.n * d.d * 2 : 0));
+            CSAT_TRY(support_count(w, x.Mask, (rows + 31) / 32 * (w.ldn / 32) * 64, st, nullptr, 0.f, 0, want_c ? V : nullptr, want_c ? (long long)BH * d.n * d.d * 2 : 0));
             hipLaunchKernelGGL(support_transpose_kernel, dim3((unsigned)((w.ldn + 63) / 64), (unsigned)((d.n + 63) / 64)), dim3(256), 0, st, rule,
                                (const bf16_t*)x.D, (bf16_t*)x.Op[0], d.n, (int)w.ldn);
             HIP_TRY(hipGetLastError());

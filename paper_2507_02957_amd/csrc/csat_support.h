@@ -16,9 +16,9 @@ __device__ __forceinline__ void support_add(uint32_t* ctl, float n) {
     if (before + more < before) ctl[1] = 1u;
 }
 // Adds the non-zero float4 that the mask bytes name to ctl[0].
-// (packed rows, csat_screen.h: of their 32-row tiles, the number scaled to all rows, which the limit is for)
+// (packed rows, csat_screen.h: of their 32-row tiles, the number scaled to all rows, which the limit is for, and by `packed`, the limit's ratio to theirs)
 // v (optional): ctl[1] is set where one of its pieces (bf16) holds an infinity or NaN.
-static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* mask, long long chunks, uint32_t* ctl, const uint32_t* screen, long long rows, const uint4* v,
+static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* mask, long long chunks, uint32_t* ctl, const uint32_t* screen, float packed, long long rows, const uint4* v,
                                                                    long long v_pieces) {
     if (holds_unbounded<bf16_t>(v, v_pieces, (long long)blockIdx.x * 256 + threadIdx.x, (long long)gridDim.x * 256)) ctl[1] = 1u;
     uint32_t n = 0;
@@ -26,7 +26,7 @@ static __global__ __launch_bounds__(256) void support_count_kernel(const uint4* 
     if (screen && screen[0] == 0) {
         const long long left = screen[2];
         chunks = chunks / ((rows + 31) / 32) * ((left + 31) / 32);
-        scale = left > 0 ? (float)rows / left : 0.f;
+        scale = left > 0 ? packed * rows / left : 0.f;
     }
     for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < chunks; i += (long long)gridDim.x * 256) {
         const uint4 v = mask[i];

@@ -1421,22 +1421,24 @@ def test_rows_left_out_are_found_on_wide_tiles(n_q, n, m, iters, options):
     assert bool((C[~lean] == 0).all()) and float((C.double() - want).norm() / want.norm()) < 2e-2
 
 
-# (rows, n, m, columns that a row leans on, whether the residual runs over the support): products of one and of two rounds of tiles, whose few steps leave
-# little to win, and few rows of long columns
-@pytest.mark.parametrize("rows,n,m,lean,sparse", [(12800, 2000, 1000, 3, False), (12800, 2000, 1000, 0.5, True), (28544, 1824, 744, 2, True), (28544, 1824, 744, 3, False),
-                                                  (3432, 13713, 1024, 8, True), (3432, 13713, 1024, 16, False)])
-def test_residual_over_the_support_where_it_is_quicker(rows, n, m, lean, sparse, options):
+# (rows, n, m, columns that a row leans on, whether the residual runs over the support, share of the rows, the others left out): products of one and of
+# two rounds of tiles, whose few steps leave little to win, few rows of long columns, and packed rows
+@pytest.mark.parametrize("rows,n,m,lean,sparse,share", [(12800, 2000, 1000, 3, False, 1.0), (12800, 2000, 1000, 0.5, True, 1.0), (28544, 1824, 744, 2, True, 1.0), (28544, 1824, 744, 5, False, 1.0),
+                                                        (3432, 13713, 1024, 8, True, 1.0), (3432, 13713, 1024, 16, False, 1.0),
+                                                        (28544, 1824, 744, 3, True, 0.2), (28544, 1824, 744, 5, False, 0.2), (12800, 2000, 1000, 3, True, 0.1)])
+def test_residual_over_the_support_where_it_is_quicker(rows, n, m, lean, sparse, share, options):
     """The density up to which the residual's kernel over the support takes the product's place, as the device notes."""
     d, iters = 64, 3
     g = torch.Generator(device=DEV).manual_seed(n)
     Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).bfloat16()
     Y = 0.002 * torch.randn(rows, m, generator=g, device=DEV)
+    stay = torch.rand(rows, 1, generator=g, device=DEV) < share
     for _ in range(max(1, int(lean))):
-        some = torch.rand(rows, 1, generator=g, device=DEV) < lean
+        some = stay & (torch.rand(rows, 1, generator=g, device=DEV) < lean)
         Y += some * 0.4 * Phi.float().t()[torch.randint(0, n, (rows,), generator=g, device=DEV)]
     V = torch.randn(8, n, d, generator=g, device=DEV).bfloat16()
     dims = csat.make_dims(1, 8, rows // 8, n, d, m, "bf16")
-    options("screen", 1)
+    options("screen", 1 if share == 1.0 else 2)
     out = []
     for choice in (0, 1, 2):
         options("support", choice)
@@ -1446,7 +1448,8 @@ def test_residual_over_the_support_where_it_is_quicker(rows, n, m, lean, sparse,
         assert csat.csat_profile_launch_form("residual") == 1
         out.append((C, ws[:256].view(torch.int32).tolist()))
     (C, words), (C1, words1), (C2, words2) = out
-    # pieces of four rows that the first iteration leaves, almost all of a column each
-    assert 0.9 * lean * rows < words[8] < 1.1 * lean * rows and words[9] == 0
+    # pieces of four rows that the first iteration leaves, almost all of a column each; of packed rows as many as of all rows so dense
+    assert 0.9 * lean * rows < words2[8] < 1.1 * lean * rows and words[9] == 0
+    assert words2[18] == (-1 if share == 1.0 else int(stay.sum()))
     assert words[10] == int(sparse) and words1[10] == -1 and words2[10] == 1
     assert torch.equal(C, C2 if sparse else C1)

@@ -1058,7 +1058,8 @@ csat_status support_begin(const Workspace& w, hipStream_t st) {
 csat_status support_count(const Workspace& w, const uint8_t* mask, long long bytes, hipStream_t st, const uint32_t* screen = nullptr, float scale = 0.f, long long rows = 0,
                           const void* V = nullptr, long long v_bytes = 0) {
     const long long chunks = bytes / 16;
-    hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((chunks + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
+    // (V may be longer than the masks: 18 432 rows, n = 96, d = 96, its 3.5 MB by the masks' nine workgroups 30 us of a call of 780)
+    hipLaunchKernelGGL(support_count_kernel, dim3((unsigned)std::min<long long>((std::max(chunks, v_bytes / 16) + 1023) / 1024, cu_count())), dim3(256), 0, st, (const uint4*)mask, chunks,
                        (uint32_t*)w.Status + kSupportWord, screen, scale, rows, (const uint4*)V, v_bytes / 16);
     HIP_TRY(hipGetLastError());
     return CSAT_OK;

@@ -1453,3 +1453,27 @@ def test_residual_over_the_support_where_it_is_quicker(rows, n, m, lean, sparse,
     assert words2[18] == (-1 if share == 1.0 else int(stay.sum()))
     assert words[10] == int(sparse) and words1[10] == -1 and words2[10] == 1
     assert torch.equal(C, C2 if sparse else C1)
+
+
+@pytest.mark.parametrize("left,packs", [(46, True), (50, False), (51, False)])
+def test_sample_near_half_of_the_rows(left, packs, options):
+    """Rows left of every 101, in heads and sample alike: below half of them they are packed, however near the sample comes to it."""
+    heads, n_q, n, m, d, iters = 48, 2048, 700, 200, 64, 50
+    rows = heads * n_q
+    g = torch.Generator(device=DEV).manual_seed(left)
+    Phi = (torch.randn(m, n, generator=g, device=DEV) / m ** 0.5).bfloat16()
+    lean = torch.arange(rows, device=DEV) * 37 % 101 < left
+    Y = torch.zeros(rows, m, device=DEV)
+    Y[lean] = 0.4 * Phi.float().t()[torch.randint(0, n, (int(lean.sum()),), generator=g, device=DEV)]
+    V = torch.randn(heads, n, d, generator=g, device=DEV).bfloat16()
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "bf16")
+    out = []
+    for choice in (0, 1):
+        options("screen", choice)
+        ws = torch.empty(csat.csat_workspace_bytes(dims, iters), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(heads, n_q, d, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover(dims, Y.view(heads, n_q, m), Phi, 0.1, 0.25 * m / n, iters, None, V, C, ws)
+        out.append((C.float(), ws[:256].view(torch.int32).tolist()))
+    (C, words), (C1, _) = out
+    assert (words[16] == 0) == packs and (not packs or words[18] == int(lean.sum()))
+    assert float((C - C1).norm() / C1.norm()) < 4e-3      # as test_rows_without_coefficients_left_out

@@ -1640,10 +1640,15 @@ bool lista_support_applies(const csat_dims& d, long long rows, int iters) {
 // n = 2500, 20 000 rows, 10 layers: 39 2985, 2070; 80 3040, 3260; n = 700, 44 800 rows, 20 layers: 24 2270, 1120; 56 2450, 1720; 139
 // 2720, 2970; fewer rows, whose longest lists end the launch: n = 700, 5600 rows, 8 layers: 52 299, 311; n = 2048, 8192 rows, 10 layers: 10 772, 470; 20
 // 750, 630; 43 740, 880; n = 4096 (its matrix far beyond an L2), 16 384 rows, 10 layers: 23 4590, 4960; 57 4600, 7570; short rows, whose layers take as long
-// as their launches: n = 416, 6656 rows, 16 layers: 271 a quad 488, 468; 402 493, 772.
+// as their launches: n = 416, 6656 rows, 16 layers: 271 a quad 488, 468; 402 493, 772; n = 278, 34 656 rows, 38 layers: 118 1720, 1600; 218 1780, 2550; of those
+// shorter than 128 float4 a quad are no limit, but a share of their columns, all of few rows' and two in five where rows are many: n = 116, 4704 rows, 24 layers: 101 510,
+// 300; n = 94, 16 416 rows, 27 layers: 78 606, 565; n = 146, 22 912 rows, 35 layers: 63 910, 670; 116 930, 1100; n = 96, 18 432 rows, 25 layers:
+// 95 572, 810; n = 108, 95 056 rows, 27 layers: 37 1340, 1170; 60 1350, 1620; 94 1360, 2680; few long rows: n = 3052, 12 712 rows, 11 layers:
+// 1.5 2480, 1805; 13 2520, 3510; n = 2163, 2192 rows, 39 layers: 6 2600, 2380; 17 2600, 3390.
 double lista_support_limit(const csat_dims& d, long long rows) {
     if (support_choice() == 2) return 4294967295.0;
-    return rows / 4.0 * (d.n > 3328 ? 12 : d.n <= 512 ? 128 : rows >= 16384 ? 48 : 24);
+    if (d.n <= 512) return rows / 4.0 * std::min(128.0, std::max(0.4, std::min(1.0, 15000.0 / rows)) * d.n);
+    return rows / 4.0 * (d.n > 3328 || (d.n > 2048 && rows < 16384) ? 12 : rows >= 16384 ? 48 : 24);
 }
 // ... and not where thresholds fall far below the first layer's: its count then says nothing of the coefficients that the later layers leave.  Over
 // all columns against over the support, us (first layer's float4 a quad; the lowest threshold, of the first): 76 800 rows, n = 1600, 20 layers:

@@ -1,6 +1,8 @@
 """Parity of single kernels and of the branches of their dispatch, at the sizes where they can go wrong: edges of
 tiles, remainders, the smallest and the largest of their ranges.  Workspaces start as NaN patterns, so a kernel that
 reads what no kernel of its own call wrote shows."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -1477,3 +1479,31 @@ def test_sample_near_half_of_the_rows(left, packs, options):
     (C, words), (C1, _) = out
     assert (words[16] == 0) == packs and (not packs or words[18] == int(lean.sum()))
     assert float((C - C1).norm() / C1.norm()) < 4e-3      # as test_rows_without_coefficients_left_out
+
+
+# (heads, n_q, n, m, layers, threshold in standard deviations of the first layer's u, over the support): short rows, all but dense or not, and long rows
+@pytest.mark.parametrize("heads,n_q,n,m,layers,sigmas,sparse", [(192, 96, 96, 65, 25, 0.01, False), (192, 96, 96, 65, 25, 1.5, True), (48, 1000, 108, 65, 25, 0.3, False),
+                                                                (48, 1000, 108, 65, 25, 2.0, True), (4, 3178, 3052, 400, 11, 3.0, False), (4, 3178, 3052, 400, 11, 3.6, True)])
+def test_unrolled_decoder_over_the_support_where_it_is_quicker(heads, n_q, n, m, layers, sigmas, sparse, options):
+    """The density up to which the layers run over the support: in short rows a share of their columns."""
+    g = torch.Generator(device=DEV).manual_seed(n + int(sigmas * 10))
+    rows, d = heads * n_q, 64
+    Y, B = torch.randn(rows, m, generator=g, device=DEV), (0.05 * torch.randn(n, m, generator=g, device=DEV)).bfloat16()
+    S = (0.9 * torch.eye(n, device=DEV)).bfloat16()
+    V = torch.randn(heads, n, d, generator=g, device=DEV).bfloat16()
+    theta = sigmas * 0.05 * m ** 0.5
+    dims = csat.make_dims(1, heads, n_q, n, d, m, "bf16")
+    out = []
+    for choice in (0, 1, 2):
+        options("support", choice)
+        ws = torch.empty(csat.csat_lista_workspace_bytes(dims, layers), dtype=torch.uint8, device=DEV).fill_(0xFF)
+        C = torch.empty(heads, n_q, d, dtype=torch.bfloat16, device=DEV)
+        csat.csat_recover_lista(dims, Y.view(heads, n_q, m), S, B, [theta] * layers, None, V, C, ws)
+        out.append((C, ws[:256].view(torch.int32).tolist()))
+    (C, words), (C1, words1), (C2, words2) = out
+    # the first layer leaves a float4 where one of its four is above (columns of B differ in length by a few per cent)
+    above = math.erfc(sigmas / 2 ** 0.5)
+    assert abs(words[8] / (rows / 4 * n * (1 - (1 - above) ** 4)) - 1) < 0.25 and words[9] == 0
+    assert words[10] == int(sparse) and words1[10] == -1 and words2[10] == 1
+    assert torch.equal(C, C2 if sparse else C1)
+    assert float((C1.float() - C2.float()).norm() / C1.float().norm()) < 4e-3      # as test_unrolled_decoder_over_the_support
